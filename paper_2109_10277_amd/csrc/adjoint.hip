@@ -7,8 +7,8 @@
 //   * deposit (shape S)             -> gather of the adjoint planes with S and
 //                                      grad S;
 //   * pusher right-hand side        -> its Jacobian, transposed;
-//   * Adams-Bashforth step          -> adjoint history ring (slot s holds the
-//                                      adjoint of the f stored in slot s);
+//   * Adams-Bashforth step          -> ring of the step adjoints of the last
+//                                      four slices (slot j mod 4);
 //   * (lap - s)^-1, centred d/dx    -> the same solves, D^T = -D.
 // Positions are the displacements xi (cell units) of the forward kernels, so
 // the position adjoints are per cell.  Particles the step absorbs, dead
@@ -88,21 +88,52 @@ __device__ inline void interp(const T* __restrict__ F, const Axis<O, R>& X, cons
   }
 }
 
-template <typename T>
-__device__ inline bool inside_c(int c0, T t, int n) {
-  const T fl = floor(t);
-  const int c = c0 + static_cast<int>(fl);
-  return c >= 0 && (c < n || (c == n && t == fl));
-}
-
 }  // namespace
+
+// Deposit transpose of the trial currents: from the gathered adjoints of
+// Jx~ (= +lsb_y / 2dz) and Jy~ (= -lsb_x / 2dz) at the trial position, the
+// adjoints of the trial state (offsets, u, Psi).
+template <typename T, int O>
+__device__ __forceinline__ void trial_deposit_adjoint(const AdjPushArgs<T>& a, int ci0, int cj0,
+                                                      T fx0, T fy0, T xn, T en, T tux, T tuy,
+                                                      T psin, T w, int nx, int ny, T (&v)[5]) {
+  const Axis<O, T> TX = locate_axis<O>(ci0, fx0 + xn, nx);
+  const Axis<O, T> TY = locate_axis<O>(cj0, fy0 + en, ny);
+  T gjx, gjx_x, gjx_y, gjy, gjy_x, gjy_y;
+  interp(a.lsb_y, TX, TY, nx, gjx, gjx_x, gjx_y);
+  interp(a.lsb_x, TX, TY, nx, gjy, gjy_x, gjy_y);
+  const T s2 = static_cast<T>(a.inv2dz);
+  gjx *= s2; gjx_x *= s2; gjx_y *= s2;
+  gjy *= -s2; gjy_x *= -s2; gjy_y *= -s2;
+  const T floor_d = static_cast<T>(a.psi_floor);
+  const T tdraw = T(1) + psin;
+  const bool tun = !(tdraw < floor_d);
+  const T tid = T(1) / (tun ? tdraw : floor_d);
+  const T qn = -w;
+  const T vjx = qn * tux * tid, vjy = qn * tuy * tid;
+  v[0] = vjx * gjx_x + vjy * gjy_x;
+  v[1] = vjx * gjx_y + vjy * gjy_y;
+  v[2] = qn * tid * gjx;
+  v[3] = qn * tid * gjy;
+  v[4] = tun ? (-qn * tux * tid * tid * gjx - qn * tuy * tid * tid * gjy) : T(0);
+}
 
 // Transpose of one real (MODE 0) or trial (MODE 1) push from the taped
 // state of slice k.  Real: lam_y holds the adjoint of the pushed state on
-// entry and that of the slice-k state (push part) on exit; the ring slot of
-// f_k is consumed.  Trial: the adjoint of the trial state comes from the
-// trial-current adjoints (Jx~ = +lsb_y/2dz, Jy~ = -lsb_x/2dz) gathered at the
-// trial position and is added to lam_y.
+// entry and that of the slice-k state (push part) on exit.  Trial: the
+// adjoint of the trial state comes from the trial-current adjoints gathered
+// at the recorded trial position and is added to lam_y.
+//
+// The Adams-Bashforth history is transposed through a ring of the last four
+// slices' step adjoints: slot j mod 4 holds the adjoint Lambda_j of the
+// states pushed from slice j (real push and trials), and the adjoint that
+// f_k collects from the later steps is -dz sum_m b_m Lambda_{k+m}.  So the
+// real push reads the ring (20 values) and stores its own slot (5), the
+// trial adds to that slot, and neither needs the forward history: whether
+// the particle stayed in the box, and its trial state, come from the trial
+// record.  Bound by HBM: with the history read and every slot of the ring
+// read, modified and written in both pushes (76 and 83 values a particle
+// instead of 43 and 39) they took 364 and 431 us at 1024^2, 4 ppc, FP32.
 template <typename T, int MODE, int O, typename Scatter>
 __device__ __forceinline__ void adj_push_one(const Geom& g, const Lattice& L,
                                              const AdjPushArgs<T>& a, int I, int J,
@@ -110,7 +141,42 @@ __device__ __forceinline__ void adj_push_one(const Geom& g, const Lattice& L,
   const int64_t np = L.np;
   const int64_t p = static_cast<int64_t>(J) * L.nX + I;
   const T w = a.p.w[p];
-  if (w == T(0)) return;
+  const T fac = a.rec[4 * np + p];   // 0: absorbed by the step
+  T y[5] = {a.p.xi_x[p], a.p.xi_y[p], a.p.ux[p], a.p.uy[p], a.p.psi[p]};
+  const T dz = static_cast<T>(a.dzeta);
+  const T b[5] = {T(kAB5[0]), T(kAB5[1]), T(kAB5[2]), T(kAB5[3]), T(kAB5[4])};
+  T* ly = a.lam_y;
+  T* own = a.lam_ring + static_cast<size_t>(a.k & 3) * 5 * np;   // Lambda_k (and _{k+4} before)
+  const bool moved = fac != T(0);
+  T lnew[5] = {0, 0, 0, 0, 0};
+  T lf[5] = {0, 0, 0, 0, 0};
+  T lf_own[2] = {0, 0};   // trial: lf[2], lf[3] of this iteration's deposit alone
+  if (MODE == 0) {
+    T lam4[5][5];   // Lambda_{k+m}, m = 1..4
+#pragma unroll
+    for (int c = 0; c < 5; ++c) lnew[c] = ly[c * np + p];
+#pragma unroll
+    for (int m = 1; m <= 4; ++m)
+#pragma unroll
+      for (int c = 0; c < 5; ++c)
+        lam4[m][c] = a.lam_ring[(static_cast<size_t>((a.k + m) & 3) * 5 + c) * np + p];
+    if (w == T(0)) return;
+#pragma unroll
+    for (int c = 0; c < 5; ++c) {
+      if (!moved) lnew[c] = T(0);
+      const T sum = b[0] * lnew[c] + (b[1] * lam4[1][c] + b[2] * lam4[2][c] + b[3] * lam4[3][c] +
+                                      b[4] * lam4[4][c]);
+      lf[c] = moved ? -dz * sum : T(0);
+      own[c * np + p] = lnew[c];
+    }
+    if (!moved) {
+#pragma unroll
+      for (int c = 0; c < 5; ++c) ly[c * np + p] = T(0);
+      return;
+    }
+  } else {
+    if (w == T(0) || !moved) return;   // nothing deposited by any iteration
+  }
   const int nx = g.nx, ny = g.ny;
   const int lpx = 31 - __clz(L.ppc_x), lpy = 31 - __clz(L.ppc_y);
   const int ci0 = I >> lpx, cj0 = J >> lpy;
@@ -118,18 +184,6 @@ __device__ __forceinline__ void adj_push_one(const Geom& g, const Lattice& L,
   const T fy0 = (T(2 * (J & (L.ppc_y - 1)) + 1)) / T(2 * L.ppc_y);
   const T inv_hx = static_cast<T>(1.0 / a.hx), inv_hy = static_cast<T>(1.0 / a.hy);
   const T floor_d = static_cast<T>(a.psi_floor);
-  const T dz = static_cast<T>(a.dzeta);
-  const T b[5] = {T(kAB5[0]), T(kAB5[1]), T(kAB5[2]), T(kAB5[3]), T(kAB5[4])};
-  const int k = a.k;
-  int slot[5];
-  slot[0] = k & 3;                    // f_k (new) ; also f_{k-4}
-  for (int m = 1; m <= 4; ++m) slot[m] = (k - m + 8) & 3;   // f_{k-m}
-  T y[5] = {a.p.xi_x[p], a.p.xi_y[p], a.p.ux[p], a.p.uy[p], a.p.psi[p]};
-  T h[5][5];   // h[m][c] = f_{k-m}[c], m = 1..4
-#pragma unroll
-  for (int m = 1; m <= 4; ++m)
-#pragma unroll
-    for (int c = 0; c < 5; ++c) h[m][c] = a.p.hist[(static_cast<size_t>(slot[m]) * 5 + c) * np + p];
   // gather with gradients at the current position
   const Axis<O, T> X = locate_axis<O>(ci0, fx0 + y[0], nx);
   const Axis<O, T> Y = locate_axis<O>(cj0, fy0 + y[1], ny);
@@ -137,7 +191,7 @@ __device__ __forceinline__ void adj_push_one(const Geom& g, const Lattice& L,
   const T* F[6] = {a.f.exmby, a.f.eypbx, a.f.ez, a.f.bx, a.f.by, a.f.bz};
 #pragma unroll
   for (int c = 0; c < 6; ++c) interp(F[c], X, Y, nx, v[c], gx[c], gy[c]);
-  const T e1 = v[0], e2 = v[1], ez = v[2], bx = v[3], by = v[4], bz = v[5];
+  const T e1 = v[0], e2 = v[1], bx = v[3], by = v[4], bz = v[5];
   const T ux = y[2], uy = y[3];
   const T draw = T(1) + y[4];
   const bool unclamped = !(draw < floor_d);
@@ -146,56 +200,11 @@ __device__ __forceinline__ void adj_push_one(const Geom& g, const Lattice& L,
   const T u2 = T(1) + ux * ux + uy * uy;
   const T gam = (T(1) + ux * ux + uy * uy + d * d) * T(0.5) * id;
   const T G = gam * id;                              // gamma / D
-  T f[5];
-  f[0] = -ux * id * inv_hx;
-  f[1] = -uy * id * inv_hy;
-  f[2] = gam * id * e1 + by + bz * uy * id;
-  f[3] = gam * id * e2 - bx - bz * ux * id;
-  f[4] = (ux * e1 + uy * e2) * id - ez;
-  T yn[5];
-#pragma unroll
-  for (int c = 0; c < 5; ++c)
-    yn[c] = y[c] - dz * (b[0] * f[c] + b[1] * h[1][c] + b[2] * h[2][c] + b[3] * h[3][c] + b[4] * h[4][c]);
-  const bool moved = inside_c(ci0, fx0 + yn[0], nx) && inside_c(cj0, fy0 + yn[1], ny);
-  T* ly = a.lam_y;
-  T* lr = a.lam_ring;
-  T lnew[5] = {0, 0, 0, 0, 0};
-  T lf[5];
-  T lf_own[2] = {0, 0};   // trial: lf[2], lf[3] of this iteration's deposit alone
-  if (MODE == 0) {
-    // adjoint of the pushed state and of the history slot holding f_k
-#pragma unroll
-    for (int c = 0; c < 5; ++c) {
-      const T lyk = ly[c * np + p];
-      const T lslot = lr[(static_cast<size_t>(slot[0]) * 5 + c) * np + p];
-      lnew[c] = moved ? lyk : T(0);
-      lf[c] = moved ? (-dz * b[0] * lnew[c] + lslot) : T(0);
-      lr[(static_cast<size_t>(slot[0]) * 5 + c) * np + p] = T(0);
-    }
-  } else {
-    if (moved) {
-      // deposit transpose of Jx~, Jy~ at the trial state
-      const Axis<O, T> TX = locate_axis<O>(ci0, fx0 + yn[0], nx);
-      const Axis<O, T> TY = locate_axis<O>(cj0, fy0 + yn[1], ny);
-      T gjx, gjx_x, gjx_y, gjy, gjy_x, gjy_y;
-      interp(a.lsb_y, TX, TY, nx, gjx, gjx_x, gjx_y);
-      interp(a.lsb_x, TX, TY, nx, gjy, gjy_x, gjy_y);
-      const T s2 = static_cast<T>(a.inv2dz);
-      gjx *= s2; gjx_x *= s2; gjx_y *= s2;
-      gjy *= -s2; gjy_x *= -s2; gjy_y *= -s2;
-      const T tux = yn[2], tuy = yn[3];
-      const T tdraw = T(1) + yn[4];
-      const bool tun = !(tdraw < floor_d);
-      const T td = tun ? tdraw : floor_d;
-      const T tid = T(1) / td;
-      const T qn = -w;
-      const T vjx = qn * tux * tid, vjy = qn * tuy * tid;
-      lnew[0] = vjx * gjx_x + vjy * gjy_x;
-      lnew[1] = vjx * gjx_y + vjy * gjy_y;
-      lnew[2] = qn * tid * gjx;
-      lnew[3] = qn * tid * gjy;
-      lnew[4] = tun ? (-qn * tux * tid * tid * gjx - qn * tuy * tid * tid * gjy) : T(0);
-    }
+  if (MODE == 1) {
+    const T kick = dz * b[0];
+    trial_deposit_adjoint<T, O>(a, ci0, cj0, fx0, fy0, a.rec[p], a.rec[np + p],
+                                a.rec[2 * np + p] - kick * by, a.rec[3 * np + p] + kick * bx,
+                                a.rec[5 * np + p], w, nx, ny, lnew);
     // this iteration's own Bx, By terms use its own deposit adjoint only;
     // the later iterations' sums join everything they share with it
 #pragma unroll
@@ -204,14 +213,12 @@ __device__ __forceinline__ void adj_push_one(const Geom& g, const Lattice& L,
 #pragma unroll
       for (int c = 0; c < 5; ++c) lnew[c] += a.acc[c * np + p];
 #pragma unroll
-    for (int c = 0; c < 5; ++c) lf[c] = -dz * b[0] * lnew[c];
+    for (int c = 0; c < 5; ++c) {
+      lf[c] = -dz * b[0] * lnew[c];
+      own[c * np + p] += lnew[c];
+    }
   }
-  // history adjoints and the identity part of the step
-#pragma unroll
-  for (int m = 1; m <= 4; ++m)
-#pragma unroll
-    for (int c = 0; c < 5; ++c)
-      if (lnew[c] != T(0)) lr[(static_cast<size_t>(slot[m]) * 5 + c) * np + p] += -dz * b[m] * lnew[c];
+  // the identity part of the step
   T lam[5];
 #pragma unroll
   for (int c = 0; c < 5; ++c) lam[c] = lnew[c];
@@ -331,7 +338,6 @@ __device__ __forceinline__ void adj_trial_later_one(const Geom& g, const Lattice
   const int ci0 = I >> lpx, cj0 = J >> lpy;
   const T fx0 = (T(2 * (I & (L.ppc_x - 1)) + 1)) / T(2 * L.ppc_x);
   const T fy0 = (T(2 * (J & (L.ppc_y - 1)) + 1)) / T(2 * L.ppc_y);
-  const T floor_d = static_cast<T>(a.psi_floor);
   const T dz = static_cast<T>(a.dzeta);
   const T b0 = T(kAB5[0]);
   // this iteration's Bx, By at the slice-k position, with gradients
@@ -341,27 +347,14 @@ __device__ __forceinline__ void adj_trial_later_one(const Geom& g, const Lattice
   interp(a.f.bx, X, Y, nx, bx, bx_x, bx_y);
   interp(a.f.by, X, Y, nx, by, by_x, by_y);
   const T kick = dz * b0;
-  const T tux = cx - kick * by, tuy = cy + kick * bx;
-  const T tdraw = T(1) + psin;
-  const bool tun = !(tdraw < floor_d);
-  const T tid = T(1) / (tun ? tdraw : floor_d);
-  const T qn = -w;
-  // deposit transpose of Jx~, Jy~ at the trial position
-  const Axis<O, T> TX = locate_axis<O>(ci0, fx0 + xn, nx);
-  const Axis<O, T> TY = locate_axis<O>(cj0, fy0 + en, ny);
-  T gjx, gjx_x, gjx_y, gjy, gjy_x, gjy_y;
-  interp(a.lsb_y, TX, TY, nx, gjx, gjx_x, gjx_y);
-  interp(a.lsb_x, TX, TY, nx, gjy, gjy_x, gjy_y);
-  const T s2 = static_cast<T>(a.inv2dz);
-  gjx *= s2; gjx_x *= s2; gjx_y *= s2;
-  gjy *= -s2; gjy_x *= -s2; gjy_y *= -s2;
-  const T vjx = qn * tux * tid, vjy = qn * tuy * tid;
   T v[7];
-  v[0] = vjx * gjx_x + vjy * gjy_x;
-  v[1] = vjx * gjx_y + vjy * gjy_y;
-  v[2] = qn * tid * gjx;
-  v[3] = qn * tid * gjy;
-  v[4] = tun ? (-qn * tux * tid * tid * gjx - qn * tuy * tid * tid * gjy) : T(0);
+  {
+    T d5[5];
+    trial_deposit_adjoint<T, O>(a, ci0, cj0, fx0, fy0, xn, en, cx - kick * by, cy + kick * bx, psin,
+                                w, nx, ny, d5);
+#pragma unroll
+    for (int c = 0; c < 5; ++c) v[c] = d5[c];
+  }
   // f_x carries +By, f_y -Bx, each times -dz b0 in the step
   const T lgbx = dz * b0 * v[3], lgby = -dz * b0 * v[2];
   scat(0, X, Y, static_cast<double>(lgbx));

@@ -207,8 +207,8 @@ struct PushArgs {
   // Psi at k+1.  The first trial push of a slice writes it (if non-null),
   // later ones read it.
   T* rec;
-  // kPushTrialTape: copy of the slice-k particle state the push reads, 26
-  // planes of np in the order xi_x, xi_y, ux, uy, psi, w, hist[4][5]
+  // kPushTrialTape: copy of the slice-k particle state the push reads, 6
+  // planes of np in the order xi_x, xi_y, ux, uy, psi, w
   T* tape;
   BeamRide beam;            // kPushReal only
 };
@@ -353,14 +353,15 @@ struct AdjPushArgs {
   Particles<T> p;           // taped state of slice k
   SliceFields<T> f;         // fields of the push being transposed
   T* lam_y;                 // [5][np]
-  T* lam_ring;              // [4][5][np], slot s = adjoint of history slot s
+  T* lam_ring;              // [4][5][np], slot j mod 4 = step adjoint Lambda_j of slice j
   const T* lsb_x;           // trial: solved adjoint sources of the corrector
   const T* lsb_y;
   double* lam_F[6];         // scatter targets: Ex-By, Ey+Bx, Ez, Bx, By, Bz
   int k;
   double dzeta, hx, hy, psi_floor, inv2dz;
   int tile_rows, tile_halo;   // lattice tiles of the forward push
-  // later predictor-corrector iterations: the slice's trial record and the
+  // the slice's trial record (every push's transpose reads it) and, for the
+  // later predictor-corrector iterations, the
   // per-particle sums [7][np] of their adjoints that the first iteration's
   // transpose takes up (adjoints of the new x, y offsets, u_x, u_y, Psi and
   // of the slice-k offsets through their own Bx, By); acc_mode 1 stores, 2

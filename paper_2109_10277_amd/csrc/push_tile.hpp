@@ -389,7 +389,7 @@ __device__ __forceinline__ void push_tile(const Geom& g, const Lattice& L, const
   const size_t np = static_cast<size_t>(L.np);
   T* hist = a.p.hist;
   const int s_new = a.k & 3;
-  const int s1 = (a.k + 3) & 3, s2 = (a.k + 2) & 3, s3 = (a.k + 1) & 3, s4 = s_new;
+  const int s1 = (a.k + 3) & 3, s2 = (a.k + 2) & 3, s3 = (a.k + 1) & 3;
   unsigned int nclamp = 0, nabs = 0, nglob = 0;
 
   if constexpr (MODE == kTrialLater)
@@ -409,18 +409,17 @@ __device__ __forceinline__ void push_tile(const Geom& g, const Lattice& L, const
     if (MODE != kDepositOnly) {
       // the history part P_k of the step (written by the previous real push)
       // and, for the real push, f_{k-1}, f_{k-2}, f_{k-3} (which form P_{k+1}
-      // with f_k); a taped push reads every slot for the tape
+      // with f_k)
       T pk[5];
-      T h[4][5];
+      T h[3][5];
 #pragma unroll
       for (int c = 0; c < 5; ++c) {
         pk[c] = a.p.pab[c * np + p];
-        if constexpr (MODE == kPushReal || TAPE) {
+        if constexpr (MODE == kPushReal) {
           h[0][c] = hist[(s1 * 5 + c) * np + p];
           h[1][c] = hist[(s2 * 5 + c) * np + p];
           h[2][c] = hist[(s3 * 5 + c) * np + p];
         }
-        if constexpr (TAPE) h[3][c] = hist[(s4 * 5 + c) * np + p];
       }
       if constexpr (MODE == kPushTrial && TAPE) {
         // the state the reverse pass of this slice starts from
@@ -431,14 +430,6 @@ __device__ __forceinline__ void push_tile(const Geom& g, const Lattice& L, const
         t[3 * np + p] = uy;
         t[4 * np + p] = psi;
         t[5 * np + p] = w;
-        T* th = t + 6 * np;
-#pragma unroll
-        for (int c = 0; c < 5; ++c) {
-          th[(s1 * 5 + c) * np + p] = h[0][c];
-          th[(s2 * 5 + c) * np + p] = h[1][c];
-          th[(s3 * 5 + c) * np + p] = h[2][c];
-          th[(s4 * 5 + c) * np + p] = h[3][c];
-        }
       }
       T e1, e2, ez, bx, by, bz;
       if constexpr (O == 1) {

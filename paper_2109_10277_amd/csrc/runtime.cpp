@@ -861,7 +861,7 @@ class Box final : public BoxBase {
     const int64_t slots = std::min(K, n_slices);
     const int64_t part = 26 * np * ts;
     const int64_t ck = part + 2 * pl * 8 + 4 * pl * ts;
-    const int64_t slot = part + 6 * np * ts + 5 * pl * ts + 2 * (cfg_.pc_max_iter + 1) * pl * ts;
+    const int64_t slot = 12 * np * ts + 5 * pl * ts + 2 * (cfg_.pc_max_iter + 1) * pl * ts;
     const int64_t work = 32 * np * ts + 18 * pl * 8 + 4 * static_cast<int64_t>(cfg_.nzeta) + 1024;
     return nck * ck + slots * slot + work + 256 * (8 * (nck + slots) + 32);
   }
@@ -978,17 +978,20 @@ class Box final : public BoxBase {
     rec_valid_ = false;
   }
 
-  Particles<T> alloc_particles() {
+  // a saved copy of the particle state as one block of planes, with the
+  // Adams-Bashforth history (a checkpoint) or without (a tape slot: the
+  // reverse pass needs none)
+  Particles<T> alloc_particles(bool history) {
     const size_t np = static_cast<size_t>(lat_.np);
     Particles<T> q{};
-    T* base = adj_alloc<T>(26 * np);
+    T* base = adj_alloc<T>((history ? 26 : 6) * np);
     q.xi_x = base;
     q.xi_y = base + np;
     q.ux = base + 2 * np;
     q.uy = base + 3 * np;
     q.psi = base + 4 * np;
     q.w = base + 5 * np;
-    q.hist = base + 6 * np;
+    q.hist = history ? base + 6 * np : nullptr;
     return q;
   }
 
@@ -1004,7 +1007,7 @@ class Box final : public BoxBase {
       const size_t pl = plane(), np = static_cast<size_t>(lat_.np);
       for (int c = 0; c < nck; ++c) {
         Checkpoint<T> ck{};
-        ck.p = alloc_particles();
+        ck.p = alloc_particles(true);
         double* j = adj_alloc<double>(2 * pl);
         ck.j[0] = j;
         ck.j[1] = j + pl;
@@ -1014,7 +1017,7 @@ class Box final : public BoxBase {
       }
       for (int s = 0; s < slots; ++s) {
         TapeSlot<T> ts{};
-        ts.p = alloc_particles();
+        ts.p = alloc_particles(false);
         T* f = adj_alloc<T>(5 * pl);
         for (int q = 0; q < 5; ++q) ts.f[q] = f + q * pl;
         ts.b = adj_alloc<T>(2 * static_cast<size_t>(cfg_.pc_max_iter + 1) * pl);
@@ -1193,6 +1196,7 @@ class Box final : public BoxBase {
     pa.inv2dz = 0.5 / cfg_.dzeta;
     pa.tile_rows = tile_rows_;
     pa.tile_halo = tile_halo_;
+    pa.rec = t.rec;
     // real push k -> k+1 (none after the last recorded slice)
     if (!last) {
       pa.f = {t.f[1], t.f[2], t.f[3], bxM, byM, t.f[4]};
@@ -1204,7 +1208,6 @@ class Box final : public BoxBase {
     // particle and taken up by the first iteration's transpose)
     const double* lbx = lam_f_[3];
     const double* lby = lam_f_[4];
-    pa.rec = t.rec;
     for (int m = M - 1; m >= 0; --m) {
       AdjSrcArgs<T> s{};
       s.count = 2;
@@ -1621,7 +1624,7 @@ class Box final : public BoxBase {
         PushArgs<T> a = push_args(fields(bxk, byk), trial_, k, 2, trial_sh_);
         // taped slices keep their record for the reverse pass
         a.rec = tape_slot_ ? tape_slot_->rec : trial_rec_;
-        // a slot's particle arrays are one block of 26 planes (alloc_particles)
+        // a slot's particle arrays are one block of 6 planes (alloc_particles)
         if (tape_slot_) a.tape = tape_slot_->p.xi_x;
         const PushMode first_trial = tape_slot_ ? kPushTrialTape : kPushTrial;
         a.pc_partial = partial_;
