@@ -14,21 +14,19 @@
 // the position adjoints are per cell.  Particles the step absorbs, dead
 // particles and floored 1+Psi are locally constant.
 #include "common.hpp"
+#include "dst_impl.hpp"
 #include "kernels.hpp"
+#include "partials.hpp"
 #include "push_tile.hpp"
 #include "shape.hpp"
 
 namespace qsp {
 
+using namespace dst_detail;
+
 namespace {
 
 __device__ inline void gadd(double* p, double v) { unsafeAtomicAdd(p, v); }
-
-// node value with the Dirichlet nodes (index 0 and n) read as zero
-template <typename T>
-__device__ inline T inner(const T* __restrict__ F, int i, int j, int nx, int ny) {
-  return (i >= 1 && j >= 1 && i < nx && j < ny) ? F[static_cast<size_t>(j) * nx + i] : T(0);
-}
 
 // One axis of a particle's stencil: lowest node b, fraction d, clamped node
 // indices, and the shape weights and their slopes (per cell) in precision R,
@@ -413,6 +411,17 @@ __global__ void __launch_bounds__(kBlock) k_adj_trial_later(Geom g, Lattice L, A
 // rho-Jz, Jx, Jy, Jz (FP64 planes) with S and grad S.
 template <typename T, int O>
 __global__ void __launch_bounds__(kBlock) k_adj_deposit(Geom g, Lattice L, AdjDepArgs<T> a) {
+  if (blockIdx.x == 0) {
+    // the beam-parameter gradient of the slice from the grid kernel's partial
+    // records (3 x 4096 atomics to three addresses took 90 of its 107 us)
+    double t[3];
+    partials::sum<3>(a.part, a.part_n, t);
+    if (threadIdx.x == 0) {
+      a.grad_amp[a.k] = -t[0];
+      a.grad_sigma[0] += -a.amp * t[1];
+      a.grad_sigma[1] += -a.amp * t[2];
+    }
+  }
   const int64_t np = L.np;
   const int64_t p = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x;
   if (p >= np) return;
@@ -458,168 +467,32 @@ __global__ void __launch_bounds__(kBlock) k_adj_deposit(Geom g, Lattice L, AdjDe
 // ------------------------------------------------------------------ grid side
 
 // out[c] = cotangent of field c at slice k (node layout, T; boundary nodes
-// dropped) + extra[c] (FP64 stored layout); both may be null.  Also clears
-// the planes zero[0..2] (the per-slice accumulators).
+// dropped) + extra[c] (FP64 stored layout); both may be null.  With `loss`
+// set it also adds sum_c <cot[c], field[c]> to *loss (one atomic per
+// workgroup of a grid held to kLossBlocks).
+constexpr unsigned kLossBlocks = 1024;
+
 template <typename T>
-__global__ void k_adj_seed(Geom g, AdjSeedArgs<T> a) {
-  const size_t n = static_cast<size_t>(g.nx) * g.ny;
-  const size_t stride = static_cast<size_t>(gridDim.x) * blockDim.x;
-  for (size_t e = blockIdx.x * static_cast<size_t>(blockDim.x) + threadIdx.x; e < n; e += stride) {
-    const int i = static_cast<int>(e % g.nx), j = static_cast<int>(e / g.nx);
+__global__ void __launch_bounds__(kBlock) k_adj_seed(Geom g, AdjSeedArgs<T> a) {
+  const int n = g.nx * g.ny;
+  const int stride = static_cast<int>(gridDim.x) * kBlock;
+  double s = 0.0;
+  for (int e = static_cast<int>(blockIdx.x) * kBlock + static_cast<int>(threadIdx.x); e < n; e += stride) {
+    const int i = e & (g.nx - 1), j = e >> g.lx;
     const bool interior = i > 0 && j > 0;
-    const size_t nodes = static_cast<size_t>(j) * (g.nx + 1) + i;
+    const int nodes = j * (g.nx + 1) + i;
 #pragma unroll
     for (int c = 0; c < 7; ++c) {
       double v = 0.0;
-      if (interior && a.cot[c]) v = static_cast<double>(a.cot[c][nodes]);
+      if (interior && a.cot[c]) {
+        v = static_cast<double>(a.cot[c][nodes]);
+        if (a.loss) s += v * static_cast<double>(a.field[c][e]);
+      }
       if (a.extra[c]) v += a.extra[c][e];
       a.out[c][e] = v;
     }
-#pragma unroll
-    for (int c = 0; c < 3; ++c)
-      if (a.zero[c]) a.zero[c][e] = 0.0;
   }
-}
-
-// predictor-corrector step m, grid part: from the solved adjoint sources
-// lsb = (lap - s)^-1 lam_B^{m+1}:  lam_Jz += d_y lsb_x - d_x lsb_y,
-// lam_Jprev += (-lsb_y, lsb_x) / 2dz, lam_B^m = -s lsb (the trial kernel then
-// adds its gather transpose).
-template <typename T>
-__global__ void k_adj_pc_grid(Geom g, AdjPCGridArgs<T> a) {
-  const int nx = g.nx, ny = g.ny;
-  const size_t n = static_cast<size_t>(nx) * ny;
-  const double ihx = 0.5 / g.hx, ihy = 0.5 / g.hy;
-  const size_t stride = static_cast<size_t>(gridDim.x) * blockDim.x;
-  for (size_t e = blockIdx.x * static_cast<size_t>(blockDim.x) + threadIdx.x; e < n; e += stride) {
-    const int i = static_cast<int>(e % nx), j = static_cast<int>(e / nx);
-    const double sx = a.lsb_x[e], sy = a.lsb_y[e];
-    double djz = 0.0;
-    if (i > 0 && j > 0) {
-      const double sx_n = inner(a.lsb_x, i, j + 1, nx, ny), sx_s = inner(a.lsb_x, i, j - 1, nx, ny);
-      const double sy_e = inner(a.lsb_y, i + 1, j, nx, ny), sy_w = inner(a.lsb_y, i - 1, j, nx, ny);
-      djz = (sx_n - sx_s) * ihy - (sy_e - sy_w) * ihx;
-    }
-    a.lam_jz[e] += djz;
-    a.jp_x[e] += -sy * a.inv2dz;
-    a.jp_y[e] += sx * a.inv2dz;
-    a.lam_bx[e] = -a.shift * sx;
-    a.lam_by[e] = -a.shift * sy;
-  }
-}
-
-// initial guess B^0 = 2 B_{k-1} - B_{k-2}, transposed; the adjoint of B_{k-1}
-// also collects what slice k+1 handed to B_{k-1} (its B_{k-2})
-__global__ void k_adj_guess(size_t n, const double* lam_b0x, const double* lam_b0y,
-                            const double* carry_b2x, const double* carry_b2y, double* b1x,
-                            double* b1y, double* b2x, double* b2y) {
-  const size_t stride = static_cast<size_t>(gridDim.x) * blockDim.x;
-  for (size_t e = blockIdx.x * static_cast<size_t>(blockDim.x) + threadIdx.x; e < n; e += stride) {
-    b1x[e] = carry_b2x[e] + 2.0 * lam_b0x[e];
-    b1y[e] = carry_b2y[e] + 2.0 * lam_b0y[e];
-    b2x[e] = -lam_b0x[e];
-    b2y[e] = -lam_b0y[e];
-  }
-}
-
-// adjoints of the deposit channels of slice k from the solved adjoint
-// sources, and the beam-parameter gradient of slice k:
-//   lam_R = -lpsi,  lam_Jx = carry_jx - d_x lez - d_y lbz,
-//   lam_Jy = carry_jy - d_y lez + d_x lbz,  lam_Jz as accumulated;
-//   dL/da_k = -<lam_Jz, G>,  dL/dsigma += -a_k <lam_Jz, dG/dsigma>.
-template <typename T>
-__global__ void __launch_bounds__(kBlock) k_adj_dep_grid(Geom g, AdjDepGridArgs<T> a) {
-  const int nx = g.nx, ny = g.ny;
-  const size_t n = static_cast<size_t>(nx) * ny;
-  const double ihx = 0.5 / g.hx, ihy = 0.5 / g.hy;
-  double s_amp = 0.0, s_sx = 0.0, s_sy = 0.0;
-  const size_t stride = static_cast<size_t>(gridDim.x) * blockDim.x;
-  for (size_t e = blockIdx.x * static_cast<size_t>(blockDim.x) + threadIdx.x; e < n; e += stride) {
-    const int i = static_cast<int>(e % nx), j = static_cast<int>(e / nx);
-    double r = 0.0, jx = a.carry_jx[e], jy = a.carry_jy[e];
-    if (i > 0 && j > 0) {
-      r = -static_cast<double>(a.lpsi[e]);
-      const double ez_e = inner(a.lez, i + 1, j, nx, ny), ez_w = inner(a.lez, i - 1, j, nx, ny);
-      const double ez_n = inner(a.lez, i, j + 1, nx, ny), ez_s = inner(a.lez, i, j - 1, nx, ny);
-      const double bz_e = inner(a.lbz, i + 1, j, nx, ny), bz_w = inner(a.lbz, i - 1, j, nx, ny);
-      const double bz_n = inner(a.lbz, i, j + 1, nx, ny), bz_s = inner(a.lbz, i, j - 1, nx, ny);
-      jx += -(ez_e - ez_w) * ihx - (bz_n - bz_s) * ihy;
-      jy += -(ez_n - ez_s) * ihy + (bz_e - bz_w) * ihx;
-      const double lz = a.lam_jz[e];
-      s_amp += lz * a.bgx[i] * a.bgy[j];
-      s_sx += lz * a.dbgx[i] * a.bgy[j];
-      s_sy += lz * a.bgx[i] * a.dbgy[j];
-    } else {
-      jx = jy = 0.0;
-    }
-    a.lam_r[e] = r;
-    a.lam_jx[e] = jx;
-    a.lam_jy[e] = jy;
-  }
-  __shared__ double red[3][kBlock / 64];
-  for (int off = 32; off > 0; off >>= 1) {
-    s_amp += __shfl_down(s_amp, off, 64);
-    s_sx += __shfl_down(s_sx, off, 64);
-    s_sy += __shfl_down(s_sy, off, 64);
-  }
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  if (lane == 0) {
-    red[0][wave] = s_amp;
-    red[1][wave] = s_sx;
-    red[2][wave] = s_sy;
-  }
-  __syncthreads();
-  if (threadIdx.x == 0 && a.grad_amp) {
-    double t0 = 0, t1 = 0, t2 = 0;
-    for (int w = 0; w < kBlock / 64; ++w) {
-      t0 += red[0][w];
-      t1 += red[1][w];
-      t2 += red[2][w];
-    }
-    gadd(a.grad_amp + a.k, -t0);
-    gadd(a.grad_sigma, -a.amp * t1);
-    gadd(a.grad_sigma + 1, -a.amp * t2);
-  }
-}
-
-// sources of up to three adjoint solves:
-//   out[q] = c0[q] * P0[q] + c1[q] * d_x P1[q] + c2[q] * d_y P2[q]
-// (FP64 stored planes, any may be null; zero on the Dirichlet nodes), cast to T
-template <typename T>
-__global__ void k_adj_source(Geom g, AdjSrcArgs<T> a) {
-  const int nx = g.nx, ny = g.ny;
-  const size_t n = static_cast<size_t>(nx) * ny;
-  const double ihx = 0.5 / g.hx, ihy = 0.5 / g.hy;
-  const size_t stride = static_cast<size_t>(gridDim.x) * blockDim.x;
-  for (size_t e = blockIdx.x * static_cast<size_t>(blockDim.x) + threadIdx.x; e < n; e += stride) {
-    const int i = static_cast<int>(e % nx), j = static_cast<int>(e / nx);
-    for (int q = 0; q < a.count; ++q) {
-      double s = 0.0;
-      if (i > 0 && j > 0) {
-        if (a.p0[q]) s += a.c0[q] * a.p0[q][e];
-        if (a.p1[q]) s += a.c1[q] * (inner(a.p1[q], i + 1, j, nx, ny) - inner(a.p1[q], i - 1, j, nx, ny)) * ihx;
-        if (a.p2[q]) s += a.c2[q] * (inner(a.p2[q], i, j + 1, nx, ny) - inner(a.p2[q], i, j - 1, nx, ny)) * ihy;
-      }
-      a.out[q][e] = static_cast<T>(s);
-    }
-  }
-}
-
-// sum_F <W_F(k), F_k> over the given fields into *loss (FP64)
-template <typename T>
-__global__ void __launch_bounds__(kBlock) k_loss(Geom g, LossArgs<T> a) {
-  const size_t n = static_cast<size_t>(g.nx) * g.ny;
-  double s = 0.0;
-  const size_t stride = static_cast<size_t>(gridDim.x) * blockDim.x;
-  for (size_t e = blockIdx.x * static_cast<size_t>(blockDim.x) + threadIdx.x; e < n; e += stride) {
-    const int i = static_cast<int>(e % g.nx), j = static_cast<int>(e / g.nx);
-    if (i == 0 || j == 0) continue;
-    const size_t nodes = static_cast<size_t>(j) * (g.nx + 1) + i;
-#pragma unroll
-    for (int c = 0; c < 7; ++c)
-      if (a.cot[c] && a.field[c])
-        s += static_cast<double>(a.cot[c][nodes]) * static_cast<double>(a.field[c][e]);
-  }
+  if (!a.loss) return;
   __shared__ double red[kBlock / 64];
   for (int off = 32; off > 0; off >>= 1) s += __shfl_down(s, off, 64);
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
@@ -629,6 +502,121 @@ __global__ void __launch_bounds__(kBlock) k_loss(Geom g, LossArgs<T> a) {
     for (int w = 0; w < kBlock / 64; ++w) t += red[w];
     gadd(a.loss, t);
   }
+}
+
+// Source assembly of an adjoint solve + forward transform along x, field by
+// field (blockIdx.y):  s = p0 + d_x p1 + d_y p2 (FP64 planes, p1 and p2 may
+// be null), and for an earlier predictor-corrector iteration, whose p0 holds
+// only what the trial push scattered, s = p0 - shift lsb with the solved
+// source lsb of the iteration after it; p0 is then cleared for the next
+// scatter and lsb joins `sum` (stored or added), from which the slice's
+// Jz and J_perp adjoints are formed once.  Zero on the Dirichlet nodes.
+template <typename T, int LOGN, int RC>
+__global__ void __launch_bounds__(kBlock, dst_blocks_per_cu(LOGN, sizeof(T)))
+k_adj_src(Geom g, AdjSrcArgs<T> a, AxisTables<T> tx) {
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  T* buf = reinterpret_cast<T*>(smem_raw);
+  constexpr int n = 1 << LOGN;   // = nx
+  const int R = RC > 0 ? RC : g.rr;
+  const int ppitch = pair_pitch<T>(n);
+  const Cplx<T>* tw;
+  const T* pre;
+  stage_tables<T, LOGN>(tx, smem_raw + static_cast<size_t>(R / 2) * ppitch * sizeof(T), tw, pre);
+  const int j0 = xcd_strip(blockIdx.x, gridDim.x) * R;
+  const int fld = blockIdx.y;
+  const double ihx = 0.5 / g.hx, ihy = 0.5 / g.hy;
+  double* __restrict__ p0 = a.p0[fld];
+  const double* __restrict__ p1 = a.p1[fld];
+  const double* __restrict__ p2 = a.p2[fld];
+  const T* __restrict__ lsb = a.lsb[fld];
+  double* __restrict__ sum = a.sum[fld];
+  for_row_elems<RC, LOGN>(R, [&](int e) {
+    const int r = e >> LOGN, i = e & (n - 1);
+    const int j = j0 + r;
+    const int o = j * n + i;
+    const bool in = i > 0 && j > 0;
+    double s = p0[o];
+    if (p1) {
+      const double pe = p1[i + 1 < n ? o + 1 : o], pw = p1[i > 0 ? o - 1 : o];
+      const double pn = p2[j + 1 < g.ny ? o + n : o], ps = p2[j > 0 ? o - n : o];
+      s += ((i + 1 < n ? pe : 0.0) - (i > 1 ? pw : 0.0)) * ihx +
+           ((j + 1 < g.ny ? pn : 0.0) - (j > 1 ? ps : 0.0)) * ihy;
+    }
+    if (lsb) {
+      const double l = static_cast<double>(lsb[o]);
+      s -= a.shift * l;
+      p0[o] = 0.0;
+      sum[o] = a.sum_add ? sum[o] + l : l;
+    }
+    buf[RowLay<T, LOGN>::rpos(n, ppitch, r, i)] = static_cast<T>(in ? s : 0.0);
+  });
+  __syncthreads();
+  block_dst<T, LOGN>(buf, g.lx, R, ppitch, tw, pre);
+  rows_to_plane<T, RC, LOGN>(g, R, j0, buf, ppitch, a.out + static_cast<size_t>(fld) * g.nx * g.ny);
+}
+
+// End of a slice on the grid.  With S the sum over the iterations of the
+// solved corrector sources lsb (the first iteration's still in lsb0, the
+// others in `sum`) and the solved psi, Ez, Bz adjoint sources:
+//   lam_Jz = d_y S_x - d_x S_y,   lam_R = -lpsi,
+//   lam_Jx = carry_jx - d_x lez - d_y lbz,  lam_Jy = carry_jy - d_y lez + d_x lbz,
+//   carry to slice k-1: J_perp (-S_y, S_x) / 2dz;
+//   initial guess B^0 = 2 B_{k-1} - B_{k-2} transposed: with
+//   L0 = lam_b - shift lsb0,  b1 = b2 + 2 L0 (with what slice k+1 handed to
+//   B_{k-1}) and b2 = -L0;  lam_b cleared for the next slice's scatter;
+//   dL/da_k = -<lam_Jz, G>, dL/dsigma = -a_k <lam_Jz, dG/dsigma> as partial
+//   records.
+template <typename T>
+__global__ void __launch_bounds__(kBlock) k_adj_dep_grid(Geom g, AdjDepGridArgs<T> a) {
+  const int nx = g.nx, ny = g.ny;
+  const int n = nx * ny;
+  const double ihx = 0.5 / g.hx, ihy = 0.5 / g.hy;
+  double acc[3] = {0.0, 0.0, 0.0};
+  const int stride = static_cast<int>(gridDim.x) * kBlock;
+  for (int e = static_cast<int>(blockIdx.x) * kBlock + static_cast<int>(threadIdx.x); e < n; e += stride) {
+    const int i = e & (nx - 1), j = e >> g.lx;
+    const bool in = i > 0 && j > 0;
+    // neighbours with clamped indices; values on the Dirichlet nodes are zero
+    const int oe = i + 1 < nx ? e + 1 : e, ow = i > 0 ? e - 1 : e;
+    const int on = j + 1 < ny ? e + nx : e, os = j > 0 ? e - nx : e;
+    const bool he = i + 1 < nx, hw = i > 1, hn = j + 1 < ny, hs = j > 1;
+    auto val = [&](const T* l, const double* s, int o) {
+      const double v = static_cast<double>(l[o]);
+      return s ? v + s[o] : v;
+    };
+    const double l0x = static_cast<double>(a.lsb_x[e]), l0y = static_cast<double>(a.lsb_y[e]);
+    const double sx = a.sum_x ? l0x + a.sum_x[e] : l0x, sy = a.sum_y ? l0y + a.sum_y[e] : l0y;
+    const double sx_n = val(a.lsb_x, a.sum_x, on), sx_s = val(a.lsb_x, a.sum_x, os);
+    const double sy_e = val(a.lsb_y, a.sum_y, oe), sy_w = val(a.lsb_y, a.sum_y, ow);
+    const double ez_e = a.lez[oe], ez_w = a.lez[ow], ez_n = a.lez[on], ez_s = a.lez[os];
+    const double bz_e = a.lbz[oe], bz_w = a.lbz[ow], bz_n = a.lbz[on], bz_s = a.lbz[os];
+    const double r = a.lpsi[e];
+    const double cjx = a.carry_jx[e], cjy = a.carry_jy[e];
+    const double l0bx = a.lam_bx[e] - a.shift * l0x, l0by = a.lam_by[e] - a.shift * l0y;
+    const double b2x = a.b2x[e], b2y = a.b2y[e];
+    auto diff = [](double p, bool hp, double m, bool hm) { return (hp ? p : 0.0) - (hm ? m : 0.0); };
+    const double lz = diff(sx_n, hn, sx_s, hs) * ihy - diff(sy_e, he, sy_w, hw) * ihx;
+    const double jx = cjx - diff(ez_e, he, ez_w, hw) * ihx - diff(bz_n, hn, bz_s, hs) * ihy;
+    const double jy = cjy - diff(ez_n, hn, ez_s, hs) * ihy + diff(bz_e, he, bz_w, hw) * ihx;
+    if (in) {
+      acc[0] += lz * a.bgx[i] * a.bgy[j];
+      acc[1] += lz * a.dbgx[i] * a.bgy[j];
+      acc[2] += lz * a.bgx[i] * a.dbgy[j];
+    }
+    a.lam_r[e] = in ? -r : 0.0;
+    a.lam_jx[e] = in ? jx : 0.0;
+    a.lam_jy[e] = in ? jy : 0.0;
+    a.lam_jz[e] = in ? lz : 0.0;
+    a.jp_x[e] = -sy * a.inv2dz;
+    a.jp_y[e] = sx * a.inv2dz;
+    a.b1x[e] = b2x + 2.0 * l0bx;
+    a.b1y[e] = b2y + 2.0 * l0by;
+    a.b2x[e] = -l0bx;
+    a.b2y[e] = -l0by;
+    a.lam_bx[e] = 0.0;
+    a.lam_by[e] = 0.0;
+  }
+  partials::store<3>(acc, a.part, static_cast<int>(blockIdx.x));
 }
 
 template <typename T>
@@ -741,42 +729,43 @@ void launch_adj_deposit(const Geom& g, const Lattice& L, const AdjDepArgs<T>& a,
 
 template <typename T>
 void launch_adj_seed(const Geom& g, const AdjSeedArgs<T>& a, hipStream_t st) {
-  hipLaunchKernelGGL(k_adj_seed<T>, g1(static_cast<size_t>(g.nx) * g.ny), dim3(kBlock), 0, st, g, a);
+  dim3 grid = g1(static_cast<size_t>(g.nx) * g.ny);
+  if (a.loss && grid.x > kLossBlocks) grid.x = kLossBlocks;
+  hipLaunchKernelGGL(k_adj_seed<T>, grid, dim3(kBlock), 0, st, g, a);
   QSP_LAUNCH_CHECK();
 }
 
 template <typename T>
-void launch_adj_pc_grid(const Geom& g, const AdjPCGridArgs<T>& a, hipStream_t st) {
-  hipLaunchKernelGGL(k_adj_pc_grid<T>, g1(static_cast<size_t>(g.nx) * g.ny), dim3(kBlock), 0, st, g,
-                     a);
+void launch_adj_src(const Geom& g, const AdjSrcArgs<T>& a, const AxisTables<T>& tx, hipStream_t st) {
+  if (a.count < 1 || a.count > 3) throw std::invalid_argument("adjoint source: 1..3 planes");
+  for (int q = 0; q < a.count; ++q)
+    if (!a.p0[q] || (a.p1[q] != nullptr) != (a.p2[q] != nullptr) || (a.lsb[q] && !a.sum[q]))
+      throw std::invalid_argument("adjoint source: missing planes");
+  const int R = g.rr;
+  if (g.strip && R != 4) throw std::invalid_argument("adjoint source: strip-ordered planes need blocks of 4 rows");
+  const size_t lds = static_cast<size_t>(R / 2) * pair_pitch<T>(g.nx) * sizeof(T) + table_bytes<T>(g.nx);
+  with_logn(g.nx, [&](auto e) {
+    constexpr int E = decltype(e)::value;
+    with_rows<T, E>(R, [&](auto rc) {
+      constexpr int RC = decltype(rc)::value;
+      if (lds > 65536)
+        QSP_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&k_adj_src<T, E, RC>),
+                                    hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds)));
+      hipLaunchKernelGGL((k_adj_src<T, E, RC>), dim3(g.ny / R, a.count), dim3(kBlock), lds, st, g, a,
+                         tx);
+    });
+  });
   QSP_LAUNCH_CHECK();
 }
 
-void launch_adj_guess(size_t n, const double* lam_b0x, const double* lam_b0y, const double* c2x,
-                      const double* c2y, double* b1x, double* b1y, double* b2x, double* b2y,
-                      hipStream_t st) {
-  hipLaunchKernelGGL(k_adj_guess, g1(n), dim3(kBlock), 0, st, n, lam_b0x, lam_b0y, c2x, c2y, b1x, b1y,
-                     b2x, b2y);
-  QSP_LAUNCH_CHECK();
+int adj_part_count(const Geom& g) {
+  const int b = (g.nx * g.ny + kBlock - 1) / kBlock;
+  return b < 2048 ? b : 2048;
 }
 
 template <typename T>
 void launch_adj_dep_grid(const Geom& g, const AdjDepGridArgs<T>& a, hipStream_t st) {
-  hipLaunchKernelGGL(k_adj_dep_grid<T>, g1(static_cast<size_t>(g.nx) * g.ny), dim3(kBlock), 0, st, g,
-                     a);
-  QSP_LAUNCH_CHECK();
-}
-
-template <typename T>
-void launch_adj_source(const Geom& g, const AdjSrcArgs<T>& a, hipStream_t st) {
-  if (a.count < 1 || a.count > 3) throw std::invalid_argument("adjoint source: 1..3 planes");
-  hipLaunchKernelGGL(k_adj_source<T>, g1(static_cast<size_t>(g.nx) * g.ny), dim3(kBlock), 0, st, g, a);
-  QSP_LAUNCH_CHECK();
-}
-
-template <typename T>
-void launch_loss(const Geom& g, const LossArgs<T>& a, hipStream_t st) {
-  hipLaunchKernelGGL(k_loss<T>, g1(static_cast<size_t>(g.nx) * g.ny), dim3(kBlock), 0, st, g, a);
+  hipLaunchKernelGGL(k_adj_dep_grid<T>, dim3(adj_part_count(g)), dim3(kBlock), 0, st, g, a);
   QSP_LAUNCH_CHECK();
 }
 
@@ -803,10 +792,9 @@ void launch_copy_planes(size_t n, int count, const CopyPlanes<T, U>& c, hipStrea
   template void launch_adj_deposit<T>(const Geom&, const Lattice&, const AdjDepArgs<T>&,        \
                                       hipStream_t);                                            \
   template void launch_adj_seed<T>(const Geom&, const AdjSeedArgs<T>&, hipStream_t);            \
-  template void launch_adj_pc_grid<T>(const Geom&, const AdjPCGridArgs<T>&, hipStream_t);       \
   template void launch_adj_dep_grid<T>(const Geom&, const AdjDepGridArgs<T>&, hipStream_t);     \
-  template void launch_adj_source<T>(const Geom&, const AdjSrcArgs<T>&, hipStream_t);           \
-  template void launch_loss<T>(const Geom&, const LossArgs<T>&, hipStream_t);                   \
+  template void launch_adj_src<T>(const Geom&, const AdjSrcArgs<T>&, const AxisTables<T>&,      \
+                                  hipStream_t);                                                \
   template void launch_copy_particles<T>(const Lattice&, const Particles<T>&,                   \
                                          const Particles<T>&, int, double, hipStream_t);        \
   template void launch_copy_planes<T, T>(size_t, int, const CopyPlanes<T, T>&, hipStream_t);

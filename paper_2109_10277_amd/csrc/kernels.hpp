@@ -377,6 +377,13 @@ struct AdjDepArgs {
   const double* lam_dep[4]; // rho-Jz, Jx, Jy, Jz
   T* lam_y;
   double psi_floor;
+  // beam gradient of the slice, from the grid kernel's partial records
+  const double* part;
+  int part_n;
+  double* grad_amp;         // [nzeta], entry k stored
+  double* grad_sigma;       // [2], added to
+  double amp;
+  int k;
 };
 
 template <typename T>
@@ -384,57 +391,52 @@ struct AdjSeedArgs {
   const T* cot[7];          // node layout cotangents (QSP_PSI .. QSP_BZ), may be null
   const double* extra[7];   // stored-layout additions, may be null
   double* out[7];
-  double* zero[3];          // planes cleared alongside, may be null
-};
-
-template <typename T>
-struct AdjPCGridArgs {
-  const T* lsb_x;
-  const T* lsb_y;
-  double* lam_jz;
-  double* jp_x;
-  double* jp_y;
-  double* lam_bx;
-  double* lam_by;
-  double shift, inv2dz;
+  const T* field[7];        // fields of the slice (read with loss set)
+  double* loss;             // may be null
 };
 
 template <typename T>
 struct AdjDepGridArgs {
-  const T* lpsi;
+  const T* lpsi;            // solved adjoint sources of psi, Ez, Bz
   const T* lez;
   const T* lbz;
-  const double* lam_jz;
-  const double* carry_jx;
+  const T* lsb_x;           // of the first corrector iteration
+  const T* lsb_y;
+  const double* sum_x;      // sums of the later iterations' (null: one iteration)
+  const double* sum_y;
+  const double* carry_jx;   // J_perp adjoint handed down by slice k+1
   const double* carry_jy;
-  double* lam_r;
+  double* lam_r;            // adjoints of rho - Jz, Jx, Jy, Jz
   double* lam_jx;
   double* lam_jy;
+  double* lam_jz;
+  double* jp_x;             // J_perp adjoint for slice k-1
+  double* jp_y;
+  double* lam_bx;           // scattered adjoint of B^0, cleared
+  double* lam_by;
+  double* b1x;              // adjoint of B_{k-1}
+  double* b1y;
+  double* b2x;              // adjoint of B_{k-2}, in and out
+  double* b2y;
   const double* bgx;
   const double* bgy;
   const double* dbgx;
   const double* dbgy;
-  double* grad_amp;
-  double* grad_sigma;
-  double amp;
-  int k;
+  double* part;             // [adj_part_count][3]
+  double shift, inv2dz;
 };
 
 template <typename T>
 struct AdjSrcArgs {
-  const double* p0[3];
-  const double* p1[3];
+  double* p0[3];            // scattered adjoints (cleared where lsb is set)
+  const double* p1[3];      // + d_x p1 + d_y p2 (both or none)
   const double* p2[3];
-  double c0[3], c1[3], c2[3];
-  T* out[3];
+  const T* lsb[3];          // - shift lsb; lsb joins sum (may be null)
+  double* sum[3];
+  int sum_add;              // 0: store, 1: add
+  double shift;
+  T* out;                   // count planes, transformed along x
   int count;
-};
-
-template <typename T>
-struct LossArgs {
-  const T* cot[7];
-  const T* field[7];
-  double* loss;
 };
 
 template <typename T, typename U>
@@ -452,16 +454,11 @@ void launch_adj_deposit(const Geom&, const Lattice&, const AdjDepArgs<T>&, hipSt
 template <typename T>
 void launch_adj_seed(const Geom&, const AdjSeedArgs<T>&, hipStream_t);
 template <typename T>
-void launch_adj_pc_grid(const Geom&, const AdjPCGridArgs<T>&, hipStream_t);
-void launch_adj_guess(size_t n, const double* lam_b0x, const double* lam_b0y, const double* c2x,
-                      const double* c2y, double* b1x, double* b1y, double* b2x, double* b2y,
-                      hipStream_t);
+void launch_adj_src(const Geom&, const AdjSrcArgs<T>&, const AxisTables<T>&, hipStream_t);
 template <typename T>
 void launch_adj_dep_grid(const Geom&, const AdjDepGridArgs<T>&, hipStream_t);
-template <typename T>
-void launch_adj_source(const Geom&, const AdjSrcArgs<T>&, hipStream_t);
-template <typename T>
-void launch_loss(const Geom&, const LossArgs<T>&, hipStream_t);
+// partial records of launch_adj_dep_grid
+int adj_part_count(const Geom&);
 template <typename T>
 // copies state and history; where dst keeps the history part P (pab), it
 // is formed from the copied state of slice k (step dzeta)

@@ -862,7 +862,7 @@ class Box final : public BoxBase {
     const int64_t part = 26 * np * ts;
     const int64_t ck = part + 2 * pl * 8 + 4 * pl * ts;
     const int64_t slot = 12 * np * ts + 5 * pl * ts + 2 * (cfg_.pc_max_iter + 1) * pl * ts;
-    const int64_t work = 32 * np * ts + 18 * pl * 8 + 4 * static_cast<int64_t>(cfg_.nzeta) + 1024;
+    const int64_t work = 32 * np * ts + 20 * pl * 8 + 24 * adj_part_count(geom_) + 4 * static_cast<int64_t>(cfg_.nzeta) + 1024;
     return nck * ck + slots * slot + work + 256 * (8 * (nck + slots) + 32);
   }
 
@@ -876,9 +876,8 @@ class Box final : public BoxBase {
     while (cursor_ < n_slices) {
       const int k = cursor_;
       if (k % K == 0 && k < last0) save_checkpoint(k / K);
-      OutCopy oc = box_outputs(out, k);
       TapeSlot<T>* slot = k >= last0 ? &tape_[k - last0] : nullptr;
-      taped_step(oc, slot, out && out->pc_resid ? out->pc_resid + k : nullptr);
+      taped_step(out, slot, out && out->pc_resid ? out->pc_resid + k : nullptr);
     }
     if (out && out->pc_iters)
       QSP_HIP(hipMemcpyAsync(out->pc_iters, iters_dev_, n_slices * sizeof(int32_t),
@@ -906,7 +905,8 @@ class Box final : public BoxBase {
     if (loss) launch_zero(loss, 1, st_);
     launch_zero_t<T>(lam_y_, 5 * np, st_);
     launch_zero_t<T>(lam_ring_, 20 * np, st_);
-    for (double* q : {carry_j_[0], carry_j_[1], carry_b1_[0], carry_b1_[1], carry_b2_[0], carry_b2_[1]})
+    for (double* q : {carry_j_[0], carry_j_[1], carry_b1_[0], carry_b1_[1], carry_b2_[0], carry_b2_[1],
+                      lam_b_[0], lam_b_[1]})
       launch_zero(q, pl, st_);
     for (int c = nchunks - 1; c >= 0; --c) {
       const int k0 = c * K, k1 = std::min(k0 + K, n_slices);
@@ -914,8 +914,7 @@ class Box final : public BoxBase {
         // recompute the chunk from its checkpoint, taping every slice
         restore_checkpoint(c);
         while (cursor_ < k1) {
-          OutCopy oc{};
-          taped_step(oc, &tape_[cursor_ - k0], nullptr);
+          taped_step(nullptr, &tape_[cursor_ - k0], nullptr);
         }
         read_iterations(k0, k1);
       }
@@ -1027,7 +1026,7 @@ class Box final : public BoxBase {
       lam_y_ = adj_alloc<T>(5 * np);
       lam_ring_ = adj_alloc<T>(20 * np);
       lam_acc_ = adj_alloc<T>(7 * np);
-      double* w = adj_alloc<double>(18 * pl);
+      double* w = adj_alloc<double>(20 * pl);
       for (int q = 0; q < 6; ++q) lam_f_[q] = w + q * pl;
       lam_psi_ = w + 6 * pl;
       lam_jz_ = w + 7 * pl;
@@ -1041,6 +1040,9 @@ class Box final : public BoxBase {
       carry_b2_[1] = w + 15 * pl;
       lam_b_[0] = w + 16 * pl;
       lam_b_[1] = w + 17 * pl;
+      lam_sum_[0] = w + 18 * pl;
+      lam_sum_[1] = w + 19 * pl;
+      adj_part_ = adj_alloc<double>(3 * static_cast<size_t>(adj_part_count(geom_)));
       iters_dev_ = adj_alloc<int32_t>(cfg_.nzeta);
       iters_host_.assign(cfg_.nzeta, 0);
     } catch (...) {
@@ -1094,23 +1096,29 @@ class Box final : public BoxBase {
 
   // one forward slice; with a tape slot, also records what the reverse pass
   // of this slice reads
-  void taped_step(OutCopy& oc, TapeSlot<T>* slot, double* resid_out) {
+  void taped_step(const qsp_box_out* out, TapeSlot<T>* slot, double* resid_out) {
     const int k = cursor_;
+    OutCopy oc{};
     // the slice's first trial push copies the particle state into the slot,
     // so a tape needs the predictor-corrector
     if (slot && explicit_) throw std::logic_error("a taped slice needs the predictor-corrector");
     tape_slot_ = slot;
-    step(oc, iters_dev_ + k, resid_out);
-    tape_slot_ = nullptr;
-    if (slot) {
-      CopyPlanes<T, T> f{};
-      const T* src[5] = {psi_, exmby_, eypbx_, ez_, bz_};
-      for (int q = 0; q < 5; ++q) {
-        f.src[q] = src[q];
-        f.dst[q] = slot->f[q];
-      }
-      launch_copy_planes<T, T>(plane(), 5, f, st_);
+    // a taped slice's fields are solved straight into its slot
+    T* const own[5] = {psi_, exmby_, eypbx_, ez_, bz_};
+    auto point = [this](T* const* f) {
+      psi_ = f[0], exmby_ = f[1], eypbx_ = f[2], ez_ = f[3], bz_ = f[4];
+    };
+    if (slot) point(slot->f);
+    try {
+      if (out) oc = box_outputs(out, k);
+      step(oc, iters_dev_ + k, resid_out);
+    } catch (...) {
+      point(own);
+      tape_slot_ = nullptr;
+      throw;
     }
+    point(own);
+    tape_slot_ = nullptr;
   }
 
   void read_iterations(int k0, int k1) {
@@ -1123,25 +1131,23 @@ class Box final : public BoxBase {
     return t.b + (2 * static_cast<size_t>(m) + c) * plane();
   }
 
-  // (lap - shift)^-1 of nb planes staged in t2_; the solutions land in t1_
-  void adj_solve(int nb, double shift) {
+  // column pass (in place) and inverse row pass of nb planes of t2_
+  // transformed along x; the solutions land in out[]
+  void adj_solve(int nb, double shift, T* const* out) {
     const size_t pl = plane();
-    RowInvArgs<T> r{};
-    for (int b = 0; b < nb; ++b) {
-      r.in[b] = t2_ + b * pl;
-      r.out[b] = t1_ + b * pl;
-    }
-    r.out_strip = geom_.strip;
-    launch_row_inv<T>(geom_, r, nb, tx(), st_);
     ColArgs<T> c{};
-    c.in = t1_;
+    c.in = t2_;
     c.out = t2_;
     for (int b = 0; b < 4; ++b) c.shift[b] = shift;
     c.honor_done = 0;
     c.w = col_width<T>(geom_, nb);
     launch_col_solve<T>(geom_, c, nb, ty(), lamx_, ctr_, st_);
+    RowInvArgs<T> r{};
+    for (int b = 0; b < nb; ++b) {
+      r.in[b] = t2_ + b * pl;
+      r.out[b] = out[b];
+    }
     r.in_strip = geom_.strip;
-    r.out_strip = 0;
     launch_row_inv<T>(geom_, r, nb, tx(), st_);
   }
 
@@ -1169,20 +1175,12 @@ class Box final : public BoxBase {
       a.extra[QSP_BY] = carry_b1_[1];
       a.out[QSP_PSI] = lam_psi_;
       for (int c = 1; c < 7; ++c) a.out[c] = lam_f_[c - 1];
-      a.zero[0] = lam_jz_;
-      a.zero[1] = jp_[0];
-      a.zero[2] = jp_[1];
-      launch_adj_seed<T>(geom_, a, st_);
       if (has_cot && loss) {
-        LossArgs<T> l{};
         const T* fld[7] = {t.f[0], t.f[1], t.f[2], t.f[3], bxM, byM, t.f[4]};
-        for (int c = 0; c < 7; ++c) {
-          l.cot[c] = a.cot[c];
-          l.field[c] = fld[c];
-        }
-        l.loss = loss;
-        launch_loss<T>(geom_, l, st_);
+        for (int c = 0; c < 7; ++c) a.field[c] = fld[c];
+        a.loss = loss;
       }
+      launch_adj_seed<T>(geom_, a, st_);
     }
     AdjPushArgs<T> pa{};
     pa.p = t.p;
@@ -1206,32 +1204,27 @@ class Box final : public BoxBase {
     // predictor-corrector iterations in reverse; those after the first
     // transpose only what their own Bx, By change (the rest is summed per
     // particle and taken up by the first iteration's transpose)
-    const double* lbx = lam_f_[3];
-    const double* lby = lam_f_[4];
+    T* const lsb[2] = {t1_, t1_ + pl};   // kept until the end of the slice
     for (int m = M - 1; m >= 0; --m) {
+      // the adjoint of B^{m+1}: from the seed and the real push, then from
+      // the trial push of the iteration after it
       AdjSrcArgs<T> s{};
       s.count = 2;
-      s.p0[0] = lbx;
-      s.p0[1] = lby;
-      s.c0[0] = s.c0[1] = 1.0;
-      s.out[0] = t2_;
-      s.out[1] = t2_ + pl;
-      launch_adj_source<T>(geom_, s, st_);
-      adj_solve(2, shift_);
-      AdjPCGridArgs<T> g{};
-      g.lsb_x = t1_;
-      g.lsb_y = t1_ + pl;
-      g.lam_jz = lam_jz_;
-      g.jp_x = jp_[0];
-      g.jp_y = jp_[1];
-      g.lam_bx = lam_b_[0];
-      g.lam_by = lam_b_[1];
-      g.shift = shift_;
-      g.inv2dz = 0.5 / cfg_.dzeta;
-      launch_adj_pc_grid<T>(geom_, g, st_);
+      s.out = t2_;
+      s.shift = shift_;
+      s.sum_add = m < M - 2;
+      for (int c = 0; c < 2; ++c) {
+        s.p0[c] = m == M - 1 ? lam_f_[3 + c] : lam_b_[c];
+        if (m < M - 1) {
+          s.lsb[c] = lsb[c];
+          s.sum[c] = lam_sum_[c];
+        }
+      }
+      launch_adj_src<T>(geom_, s, tx(), st_);
+      adj_solve(2, shift_, lsb);
       pa.f = {t.f[1], t.f[2], t.f[3], tape_b(t, m, 0), tape_b(t, m, 1), t.f[4]};
-      pa.lsb_x = t1_;
-      pa.lsb_y = t1_ + pl;
+      pa.lsb_x = lsb[0];
+      pa.lsb_y = lsb[1];
       pa.lam_F[0] = lam_f_[0];
       pa.lam_F[1] = lam_f_[1];
       pa.lam_F[2] = lam_f_[2];
@@ -1246,48 +1239,53 @@ class Box final : public BoxBase {
         pa.acc_mode = 0;
         launch_adj_push<T>(geom_, lat_, pa, true, st_);
       }
-      lbx = lam_b_[0];
-      lby = lam_b_[1];
     }
-    // initial guess B^0 = 2 B_{k-1} - B_{k-2}
-    launch_adj_guess(pl, lbx, lby, carry_b2_[0], carry_b2_[1], carry_b1_[0], carry_b1_[1],
-                     carry_b2_[0], carry_b2_[1], st_);
     // psi (with Ex-By = -d_x psi, Ey+Bx = -d_y psi), Ez and Bz solves
+    T* const lpez[3] = {t1_ + 2 * pl, t1_ + 3 * pl, t2_ + 3 * pl};
     {
       AdjSrcArgs<T> s{};
       s.count = 3;
+      s.out = t2_;
       s.p0[0] = lam_psi_;
       s.p1[0] = lam_f_[0];
       s.p2[0] = lam_f_[1];
-      s.c0[0] = s.c1[0] = s.c2[0] = 1.0;
       s.p0[1] = lam_f_[2];
-      s.c0[1] = 1.0;
       s.p0[2] = lam_f_[5];
-      s.c0[2] = 1.0;
-      for (int q = 0; q < 3; ++q) s.out[q] = t2_ + q * pl;
-      launch_adj_source<T>(geom_, s, st_);
-      adj_solve(3, 0.0);
+      launch_adj_src<T>(geom_, s, tx(), st_);
+      adj_solve(3, 0.0, lpez);
     }
-    // adjoints of the deposit channels of slice k and the beam gradient
+    // adjoints of the deposit channels of slice k, of its predecessors'
+    // J_perp and B, and the beam gradient
     {
       AdjDepGridArgs<T> d{};
-      d.lpsi = t1_;
-      d.lez = t1_ + pl;
-      d.lbz = t1_ + 2 * pl;
-      d.lam_jz = lam_jz_;
+      d.lpsi = lpez[0];
+      d.lez = lpez[1];
+      d.lbz = lpez[2];
+      d.lsb_x = lsb[0];
+      d.lsb_y = lsb[1];
+      d.sum_x = M > 1 ? lam_sum_[0] : nullptr;
+      d.sum_y = M > 1 ? lam_sum_[1] : nullptr;
       d.carry_jx = carry_j_[0];
       d.carry_jy = carry_j_[1];
       d.lam_r = lam_psi_;
       d.lam_jx = carry_j_[0];
       d.lam_jy = carry_j_[1];
+      d.lam_jz = lam_jz_;
+      d.jp_x = jp_[0];
+      d.jp_y = jp_[1];
+      d.lam_bx = lam_b_[0];
+      d.lam_by = lam_b_[1];
+      d.b1x = carry_b1_[0];
+      d.b1y = carry_b1_[1];
+      d.b2x = carry_b2_[0];
+      d.b2y = carry_b2_[1];
       d.bgx = bgx_;
       d.bgy = bgy_;
       d.dbgx = dbgx_;
       d.dbgy = dbgy_;
-      d.grad_amp = grad_amp;
-      d.grad_sigma = grad_sigma;
-      d.amp = has_gauss_ ? amp_[k] : 0.0;
-      d.k = k;
+      d.part = adj_part_;
+      d.shift = shift_;
+      d.inv2dz = 0.5 / cfg_.dzeta;
       launch_adj_dep_grid<T>(geom_, d, st_);
     }
     {
@@ -1299,6 +1297,12 @@ class Box final : public BoxBase {
       a.lam_dep[3] = lam_jz_;
       a.lam_y = lam_y_;
       a.psi_floor = cfg_.psi_floor;
+      a.part = adj_part_;
+      a.part_n = adj_part_count(geom_);
+      a.grad_amp = grad_amp;
+      a.grad_sigma = grad_sigma;
+      a.amp = has_gauss_ ? amp_[k] : 0.0;
+      a.k = k;
       launch_adj_deposit<T>(geom_, lat_, a, st_);
     }
     // the adjoint of J_perp_{k-1} collected here is slice k-1's carry
@@ -1898,6 +1902,8 @@ class Box final : public BoxBase {
   double* carry_b1_[2] = {};
   double* carry_b2_[2] = {};
   double* lam_b_[2] = {};
+  double* lam_sum_[2] = {};   // solved corrector sources of a slice's later iterations, summed
+  double* adj_part_ = nullptr;
   DevCounters* ctr_ = nullptr;
   double* partial_ = nullptr;
   std::vector<double> amp_;
