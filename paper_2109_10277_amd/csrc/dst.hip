@@ -126,6 +126,56 @@ k_row_inv(Geom g, RowInvArgs<T> a, AxisTables<T> tx) {
   });
 }
 
+// First and last pass of a batched solve on the caller's node arrays
+// ([ny+1][nx+1], row j at j (nx + 1)): OUT = false reads the sources straight
+// into the rows (boundary nodes taken as zero) and writes an intermediate
+// plane, OUT = true reads one and writes the solution with its zero boundary.
+// Both ends are bound by latency and launches: as separate layout copies they
+// took 4.6 us a plane, 27 of the 66 us of a batch of three at 1024^2 in FP32.
+template <typename T, int LOGN, int RC, bool OUT>
+__global__ void __launch_bounds__(kBlock, dst_blocks_per_cu(LOGN, sizeof(T)))
+k_row_nodes(Geom g, NodeRowArgs<T> a, AxisTables<T> tx) {
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  T* buf = reinterpret_cast<T*>(smem_raw);
+  constexpr int n = 1 << LOGN;   // = nx
+  const int R = RC > 0 ? RC : g.rr;
+  const int ppitch = pair_pitch<T>(n);
+  const Cplx<T>* tw;
+  const T* pre;
+  stage_tables<T, LOGN>(tx, smem_raw + static_cast<size_t>(R / 2) * ppitch * sizeof(T), tw, pre);
+  const int j0 = xcd_strip(blockIdx.x, gridDim.x) * R;
+  const int b = blockIdx.y;
+  const size_t plane = static_cast<size_t>(n) * g.ny;
+  const size_t nodes = static_cast<size_t>(n + 1) * (g.ny + 1);
+  if constexpr (!OUT) {
+    const T* __restrict__ src = a.nodes_in + b * nodes;
+    for_row_elems<RC, LOGN, 16>(R, [&](int e) {
+      const int r = e >> LOGN, i = e & (n - 1);
+      const int j = j0 + r;
+      const T v = src[j * (n + 1) + i];
+      buf[RowLay<T, LOGN>::rpos(n, ppitch, r, i)] = i > 0 && j > 0 ? v : T(0);
+    });
+  } else {
+    plane_to_rows<T, RC, LOGN>(g, R, j0, a.plane + b * plane, buf, ppitch);
+  }
+  __syncthreads();
+  block_dst<T, LOGN>(buf, g.lx, R, ppitch, tw, pre);
+  if constexpr (!OUT) {
+    rows_to_plane<T, RC, LOGN>(g, R, j0, buf, ppitch, a.plane + b * plane);
+  } else {
+    T* __restrict__ dst = a.nodes_out + b * nodes;
+    for_row_elems<RC, LOGN, 16>(R, [&](int e) {
+      const int r = e >> LOGN, i = e & (n - 1);
+      const int j = j0 + r;
+      const T v = buf[RowLay<T, LOGN>::rpos(n, ppitch, r, i)];
+      dst[j * (n + 1) + i] = j > 0 ? v : T(0);
+    });
+    if (static_cast<int>(threadIdx.x) < R) dst[(j0 + static_cast<int>(threadIdx.x)) * (n + 1) + n] = T(0);
+    if (j0 + R == g.ny)
+      for (int i = threadIdx.x; i <= n; i += kBlock) dst[g.ny * (n + 1) + i] = T(0);
+  }
+}
+
 template <typename T, int LOGN, int RC>
 __global__ void __launch_bounds__(kBlock, dst_blocks_per_cu(LOGN, sizeof(T)))
 k_row_inv_pc(Geom g, PCArgs<T> a, AxisTables<T> tx, DevCounters* ctr) {
@@ -241,6 +291,32 @@ void launch_row_inv(const Geom& g, const RowInvArgs<T>& a, int nfield, const Axi
 }
 
 template <typename T>
+void launch_row_nodes(const Geom& g, const NodeRowArgs<T>& a, bool out, int nbatch,
+                      const AxisTables<T>& tx, hipStream_t st) {
+  const int R = g.rr;
+  if (nbatch < 1 || nbatch > 4 || !a.plane || (out ? !a.nodes_out : !a.nodes_in))
+    throw std::invalid_argument("node row pass: bad planes or batch");
+  check_rows<T>(g.nx, R);
+  check_strip(g, R);
+  const size_t lds = static_cast<size_t>(R / 2) * pair_pitch<T>(g.nx) * sizeof(T) + table_bytes<T>(g.nx);
+  with_logn(g.nx, [&](auto e) {
+    constexpr int E = decltype(e)::value;
+    with_rows<T, E>(R, [&](auto rc) {
+      constexpr int RC = decltype(rc)::value;
+      const dim3 grid(g.ny / R, nbatch);
+      if (out) {
+        allow_lds(reinterpret_cast<const void*>(&k_row_nodes<T, E, RC, true>), lds);
+        hipLaunchKernelGGL((k_row_nodes<T, E, RC, true>), grid, dim3(kBlock), lds, st, g, a, tx);
+      } else {
+        allow_lds(reinterpret_cast<const void*>(&k_row_nodes<T, E, RC, false>), lds);
+        hipLaunchKernelGGL((k_row_nodes<T, E, RC, false>), grid, dim3(kBlock), lds, st, g, a, tx);
+      }
+    });
+  });
+  QSP_LAUNCH_CHECK();
+}
+
+template <typename T>
 void launch_row_inv_pc(const Geom& g, const PCArgs<T>& a, const AxisTables<T>& tx,
                        DevCounters* ctr, hipStream_t st) {
   const int R = g.rr;
@@ -281,6 +357,8 @@ template int row_rows<double>(int, int);
                                     const DevCounters*, hipStream_t);                      \
   template void launch_row_inv<T>(const Geom&, const RowInvArgs<T>&, int,                  \
                                   const AxisTables<T>&, hipStream_t);                      \
+  template void launch_row_nodes<T>(const Geom&, const NodeRowArgs<T>&, bool, int,         \
+                                    const AxisTables<T>&, hipStream_t);                    \
   template void launch_row_inv_pc<T>(const Geom&, const PCArgs<T>&, const AxisTables<T>&,  \
                                      DevCounters*, hipStream_t);
 QSP_INST(float)

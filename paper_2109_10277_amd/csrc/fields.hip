@@ -128,24 +128,7 @@ __global__ void k_to_nodes(Geom g, const T* src, double* dst) {
   }
 }
 
-template <typename T>
-__global__ void k_to_nodes_t(Geom g, const T* src, T* dst) {
-  const size_t n = static_cast<size_t>(g.nx + 1) * (g.ny + 1);
-  for (size_t e = blockIdx.x * static_cast<size_t>(blockDim.x) + threadIdx.x; e < n;
-       e += static_cast<size_t>(gridDim.x) * blockDim.x) {
-    const int i = static_cast<int>(e % (g.nx + 1)), j = static_cast<int>(e / (g.nx + 1));
-    dst[e] = (i < g.nx && j < g.ny) ? src[static_cast<size_t>(j) * g.nx + i] : T(0);
-  }
-}
-
 }  // namespace
-
-template <typename T>
-void launch_to_nodes_t(const Geom& g, const T* src, T* dst, hipStream_t st) {
-  hipLaunchKernelGGL(k_to_nodes_t<T>, grid_for(static_cast<size_t>(g.nx + 1) * (g.ny + 1)),
-                     dim3(kBlock), 0, st, g, src, dst);
-  QSP_LAUNCH_CHECK();
-}
 
 void launch_zero_int(int* p, size_t n, hipStream_t st) {
   hipLaunchKernelGGL(k_zero<int>, grid_for(n), dim3(kBlock), 0, st, p, n);
@@ -214,11 +197,9 @@ void launch_to_nodes(const Geom& g, const T* src, double* dst, hipStream_t st) {
   template void launch_guess<T>(const Geom&, T*, T*, const T*, const T*, const T*,        \
                                 const T*, DevCounters*, hipStream_t);                     \
   template void launch_from_nodes<double, T>(const Geom&, const double*, T*, hipStream_t); \
-  template void launch_to_nodes<T>(const Geom&, const T*, double*, hipStream_t);        \
-  template void launch_to_nodes_t<T>(const Geom&, const T*, T*, hipStream_t);
+  template void launch_to_nodes<T>(const Geom&, const T*, double*, hipStream_t);
 QSP_INST(float)
 QSP_INST(double)
 #undef QSP_INST
-template void launch_from_nodes<float, float>(const Geom&, const float*, float*, hipStream_t);
 
 }  // namespace qsp

@@ -81,6 +81,14 @@ struct RowInvArgs {
   int in_strip, out_strip;  // in / out planes in the strip order of Geom::strip
 };
 
+// The ends of a batched solve on node arrays [nbatch][ny+1][nx+1].
+template <typename T>
+struct NodeRowArgs {
+  const T* nodes_in;        // sources (first pass)
+  T* nodes_out;             // solutions (last pass)
+  T* plane;                 // nbatch intermediate planes, written / read
+};
+
 template <typename T>
 struct PCArgs {
   const T* in;              // 2 planes from the column pass
@@ -103,6 +111,9 @@ void launch_col_solve(const Geom&, const ColArgs<T>&, int nfield, const AxisTabl
 template <typename T>
 void launch_row_inv(const Geom&, const RowInvArgs<T>&, int nfield, const AxisTables<T>&,
                     hipStream_t);
+template <typename T>
+void launch_row_nodes(const Geom&, const NodeRowArgs<T>&, bool out, int nbatch, const AxisTables<T>&,
+                      hipStream_t);
 template <typename T>
 void launch_row_inv_pc(const Geom&, const PCArgs<T>&, const AxisTables<T>&, DevCounters*,
                        hipStream_t);
@@ -312,8 +323,6 @@ template <typename S, typename T>
 void launch_from_nodes(const Geom&, const S* src, T* dst, hipStream_t);  // [ny+1][nx+1] -> stored
 template <typename T>
 void launch_to_nodes(const Geom&, const T* src, double* dst, hipStream_t);    // stored -> [ny+1][nx+1]
-template <typename T>
-void launch_to_nodes_t(const Geom&, const T* src, T* dst, hipStream_t);
 
 // ---------------------------------------------------------------- beams
 struct BeamScratch {

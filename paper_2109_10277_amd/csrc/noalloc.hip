@@ -39,10 +39,26 @@ unsigned char* scratch_on(int device) {
   return g_ptr[device];
 }
 
-// The transform tables of one axis (layout as the context's, see
-// AxisTables), computed on the device, one thread per entry.
+// The transform tables of the two axes (layout as the context's, see
+// AxisTables), computed on the device, one thread per entry and one grid row
+// per axis.
 template <typename T>
-__global__ void k_axis_tables(int n, double h, qsp::Cplx<T>* tw, T* pre, double* lam) {
+struct AxisJob {
+  int n;
+  double h;
+  qsp::Cplx<T>* tw;
+  T* pre;
+  double* lam;
+};
+
+template <typename T>
+__global__ void k_axis_tables(AxisJob<T> x, AxisJob<T> y) {
+  const AxisJob<T> q = blockIdx.y == 0 ? x : y;
+  const int n = q.n;
+  qsp::Cplx<T>* tw = q.tw;
+  T* pre = q.pre;
+  double* lam = q.lam;
+  const double h = q.h;
   const int m = blockIdx.x * blockDim.x + threadIdx.x;
   if (m >= 2 * n) return;
   double s, c;
@@ -64,8 +80,8 @@ __global__ void k_axis_tables(int n, double h, qsp::Cplx<T>* tw, T* pre, double*
     pre[m] = static_cast<T>(sinpi(static_cast<double>(m) / n));
   }
   if (m < n) {
-    const double q = sinpi(0.5 * m / n);
-    lam[m] = -4.0 / (h * h) * q * q;
+    const double sm = sinpi(0.5 * m / n);
+    lam[m] = -4.0 / (h * h) * sm * sm;
   }
 }
 
@@ -99,38 +115,29 @@ void solve(const qsp_config& c, unsigned char* ptr, int nb, const T* src, T* dst
   g.rr = row_rows<T>(c.nx, c.ny);
   g.order = 1;
   g.strip = 0;   // the passes run in place: the planes stay row-major
-  const size_t pl = static_cast<size_t>(c.nx) * c.ny;
-  const size_t nn = static_cast<size_t>(c.nx + 1) * (c.ny + 1);
   T* planes = reinterpret_cast<T*>(ptr);
   unsigned char* tab = ptr + kPlaneBytes;
   // tables are 8-byte aligned pieces: x axis first, then y
   const AxisTables<T> tx = axis_at<T>(tab, c.nx);
   const AxisTables<T> ty = axis_at<T>(tab + axis_table_bytes<T>(c.nx), c.ny);
-  hipLaunchKernelGGL(k_axis_tables<T>, dim3((2 * c.nx + 255) / 256), dim3(256), 0, st, c.nx, g.hx,
-                     const_cast<Cplx<T>*>(tx.tw), const_cast<T*>(tx.pre),
-                     const_cast<double*>(tx.lam));
+  const AxisJob<T> jx{c.nx, g.hx, const_cast<Cplx<T>*>(tx.tw), const_cast<T*>(tx.pre),
+                      const_cast<double*>(tx.lam)};
+  const AxisJob<T> jy{c.ny, g.hy, const_cast<Cplx<T>*>(ty.tw), const_cast<T*>(ty.pre),
+                      const_cast<double*>(ty.lam)};
+  const int nmax = c.nx > c.ny ? c.nx : c.ny;
+  hipLaunchKernelGGL(k_axis_tables<T>, dim3((2 * nmax + 255) / 256, 2), dim3(256), 0, st, jx, jy);
   QSP_LAUNCH_CHECK();
-  hipLaunchKernelGGL(k_axis_tables<T>, dim3((2 * c.ny + 255) / 256), dim3(256), 0, st, c.ny, g.hy,
-                     const_cast<Cplx<T>*>(ty.tw), const_cast<T*>(ty.pre),
-                     const_cast<double*>(ty.lam));
-  QSP_LAUNCH_CHECK();
-  for (int b = 0; b < nb; ++b) launch_from_nodes<T, T>(g, src + b * nn, planes + b * pl, st);
   // each pass reads its rows or column strips into LDS before writing them
-  // back, so all three run in place
-  RowInvArgs<T> r{};
-  for (int b = 0; b < nb; ++b) {
-    r.in[b] = planes + b * pl;
-    r.out[b] = planes + b * pl;
-  }
-  launch_row_inv<T>(g, r, nb, tx, st);
+  // back, so all three work on the same planes
+  NodeRowArgs<T> r{src, dst, planes};
+  launch_row_nodes<T>(g, r, false, nb, tx, st);
   ColArgs<T> col{};
   col.in = planes;
   col.out = planes;
   for (int b = 0; b < 4; ++b) col.shift[b] = shift;
   col.w = col_width<T>(g, nb);
   launch_col_solve<T>(g, col, nb, ty, tx.lam, nullptr, st);
-  launch_row_inv<T>(g, r, nb, tx, st);
-  for (int b = 0; b < nb; ++b) launch_to_nodes_t<T>(g, planes + b * pl, dst + b * nn, st);
+  launch_row_nodes<T>(g, r, true, nb, tx, st);
 }
 
 bool pow2_in(int v, int lo, int hi) { return v >= lo && v <= hi && (v & (v - 1)) == 0; }

@@ -535,31 +535,16 @@ class Box final : public BoxBase {
 
   void solve_poisson(int nb, const void* src, void* dst, double shift) override {
     QSP_HIP(hipSetDevice(device_));
-    const size_t pl = plane(), nn = nodes();
-    const T* s = static_cast<const T*>(src);
-    T* d = static_cast<T*>(dst);
-    for (int b = 0; b < nb; ++b) launch_from_nodes<T, T>(geom_, s + b * nn, t2_ + b * pl, st_);
-    RowInvArgs<T> r{};
-    for (int b = 0; b < nb; ++b) {
-      r.in[b] = t2_ + b * pl;
-      r.out[b] = t1_ + b * pl;
-    }
-    r.out_strip = geom_.strip;
-    launch_row_inv<T>(geom_, r, nb, tx(), st_);
+    // rows of the sources, columns, rows of the solutions: all in t2_
+    NodeRowArgs<T> r{static_cast<const T*>(src), static_cast<T*>(dst), t2_};
+    launch_row_nodes<T>(geom_, r, false, nb, tx(), st_);
     ColArgs<T> c{};
-    c.in = t1_;
+    c.in = t2_;
     c.out = t2_;
     for (int b = 0; b < 4; ++b) c.shift[b] = shift;
     c.w = col_width<T>(geom_, nb);
     launch_col_solve<T>(geom_, c, nb, ty(), lamx_, ctr_, st_);
-    for (int b = 0; b < nb; ++b) {
-      r.in[b] = t2_ + b * pl;
-      r.out[b] = t1_ + b * pl;
-    }
-    r.in_strip = geom_.strip;
-    r.out_strip = 0;
-    launch_row_inv<T>(geom_, r, nb, tx(), st_);
-    for (int b = 0; b < nb; ++b) launch_to_nodes_t<T>(geom_, t1_ + b * pl, d + b * nn, st_);
+    launch_row_nodes<T>(geom_, r, true, nb, tx(), st_);
   }
 
   // ---------------------------------------------------------------- loop
