@@ -519,9 +519,7 @@ k_adj_src(Geom g, AdjSrcArgs<T> a, AxisTables<T> tx) {
   constexpr int n = 1 << LOGN;   // = nx
   const int R = RC > 0 ? RC : g.rr;
   const int ppitch = pair_pitch<T>(n);
-  const Cplx<T>* tw;
-  const T* pre;
-  stage_tables<T, LOGN>(tx, smem_raw + static_cast<size_t>(R / 2) * ppitch * sizeof(T), tw, pre);
+  const auto xf = stage_tables<T, LOGN, row_pairs<T, LOGN>()>(tx, smem_raw + static_cast<size_t>(R / 2) * ppitch * sizeof(T), R / 2);
   const int j0 = xcd_strip(blockIdx.x, gridDim.x) * R;
   const int fld = blockIdx.y;
   const double ihx = 0.5 / g.hx, ihy = 0.5 / g.hy;
@@ -530,28 +528,53 @@ k_adj_src(Geom g, AdjSrcArgs<T> a, AxisTables<T> tx) {
   const double* __restrict__ p2 = a.p2[fld];
   const T* __restrict__ lsb = a.lsb[fld];
   double* __restrict__ sum = a.sum[fld];
-  for_row_elems<RC, LOGN>(R, [&](int e) {
-    const int r = e >> LOGN, i = e & (n - 1);
-    const int j = j0 + r;
-    const int o = j * n + i;
-    const bool in = i > 0 && j > 0;
-    double s = p0[o];
-    if (p1) {
-      const double pe = p1[i + 1 < n ? o + 1 : o], pw = p1[i > 0 ? o - 1 : o];
-      const double pn = p2[j + 1 < g.ny ? o + n : o], ps = p2[j > 0 ? o - n : o];
-      s += ((i + 1 < n ? pe : 0.0) - (i > 1 ? pw : 0.0)) * ihx +
-           ((j + 1 < g.ny ? pn : 0.0) - (j > 1 ? ps : 0.0)) * ihy;
+  struct In {
+    double c, e, w, n, s;
+    T l;
+    __device__ void pin() {
+      dst_detail::pin(c);
+      dst_detail::pin(e);
+      dst_detail::pin(w);
+      dst_detail::pin(n);
+      dst_detail::pin(s);
+      dst_detail::pin(l);
     }
-    if (lsb) {
-      const double l = static_cast<double>(lsb[o]);
-      s -= a.shift * l;
-      p0[o] = 0.0;
-      sum[o] = a.sum_add ? sum[o] + l : l;
-    }
-    buf[RowLay<T, LOGN>::rpos(n, ppitch, r, i)] = static_cast<T>(in ? s : 0.0);
-  });
+  };
+  for_row_batches<RC, LOGN, src_batch<T, LOGN>(), In>(
+      R,
+      [&](int e, In& v) {
+        const int i = e & (n - 1), j = j0 + (e >> LOGN);
+        const int o = j * n + i;
+        v = In{load_at<double>(p0, o), 0.0, 0.0, 0.0, 0.0, T(0)};
+        if (p1) {
+          v.e = load_at(p1, i + 1 < n ? o + 1 : o);
+          v.w = load_at(p1, i > 0 ? o - 1 : o);
+          v.n = load_at(p2, j + 1 < g.ny ? o + n : o);
+          v.s = load_at(p2, j > 0 ? o - n : o);
+        }
+        if (lsb) {
+          v.l = load_at(lsb, o);
+          if (a.sum_add) v.e = load_at<double>(sum, o);   // an iteration's source has no derivative part
+        }
+      },
+      [&](int, int e, const In& v) {
+        const int r = e >> LOGN, i = e & (n - 1), j = j0 + r;
+        const int o = j * n + i;
+        double s = v.c;
+        if (p1)
+          s += ((i + 1 < n ? v.e : 0.0) - (i > 1 ? v.w : 0.0)) * ihx +
+               ((j + 1 < g.ny ? v.n : 0.0) - (j > 1 ? v.s : 0.0)) * ihy;
+        if (lsb) {
+          const double l = static_cast<double>(v.l);
+          s -= a.shift * l;
+          p0[o] = 0.0;
+          sum[o] = a.sum_add ? v.e + l : l;
+        }
+        buf[RowLay<T, LOGN>::rpos(n, ppitch, r, i)] = static_cast<T>((i > 0 && j > 0) ? s : 0.0);
+      });
+  xf.commit();
   __syncthreads();
-  block_dst<T, LOGN>(buf, g.lx, R, ppitch, tw, pre);
+  block_dst<T, LOGN>(buf, R, ppitch, xf);
   rows_to_plane<T, RC, LOGN>(g, R, j0, buf, ppitch, a.out + static_cast<size_t>(fld) * g.nx * g.ny);
 }
 
@@ -739,10 +762,9 @@ template <typename T>
 void launch_adj_src(const Geom& g, const AdjSrcArgs<T>& a, const AxisTables<T>& tx, hipStream_t st) {
   if (a.count < 1 || a.count > 3) throw std::invalid_argument("adjoint source: 1..3 planes");
   for (int q = 0; q < a.count; ++q)
-    if (!a.p0[q] || (a.p1[q] != nullptr) != (a.p2[q] != nullptr) || (a.lsb[q] && !a.sum[q]))
+    if (!a.p0[q] || (a.p1[q] != nullptr) != (a.p2[q] != nullptr) || (a.lsb[q] && (!a.sum[q] || a.p1[q])))
       throw std::invalid_argument("adjoint source: missing planes");
   const int R = g.rr;
-  if (g.strip && R != 4) throw std::invalid_argument("adjoint source: strip-ordered planes need blocks of 4 rows");
   const size_t lds = static_cast<size_t>(R / 2) * pair_pitch<T>(g.nx) * sizeof(T) + table_bytes<T>(g.nx);
   with_logn(g.nx, [&](auto e) {
     constexpr int E = decltype(e)::value;

@@ -72,6 +72,19 @@ struct Geom {
   int strip;
 };
 
+// base[i] with the byte offset formed in 32 bits (the caller guarantees
+// i * sizeof(T) < 2^32), so that a uniform base loads or stores through one
+// VGPR of offset instead of a 64-bit address per lane
+template <typename T>
+__device__ __forceinline__ T load_at(const T* base, unsigned int i) {
+  return *reinterpret_cast<const T*>(reinterpret_cast<const char*>(base) +
+                                     i * static_cast<unsigned int>(sizeof(T)));
+}
+template <typename T>
+__device__ __forceinline__ void store_at(T* base, unsigned int i, T v) {
+  *reinterpret_cast<T*>(reinterpret_cast<char*>(base) + i * static_cast<unsigned int>(sizeof(T))) = v;
+}
+
 // Offset of element (j, i) of a strip-ordered intermediate plane.
 __host__ __device__ inline size_t strip_at(int j, int i, int ny) {
   return (static_cast<size_t>(i >> 2) * ny + j) * 4 + (i & 3);
@@ -83,31 +96,57 @@ struct Lattice {
   int64_t np;
 };
 
-// Sine transforms of FP32 rows of 256-1024 points use the recurrence-free
-// core (an FFT of the odd extension, twice the length); the others the
-// half-length transform with a prefix sum for the odd outputs.
-__host__ __device__ constexpr bool fast_core(int elem_size, int n) {
-  return elem_size == 4 && n >= 256 && n <= 1024;
+// Which transform rows of n points use, by element size (see dst_impl.hpp):
+//   symmetric core   128 points, FP64 from 128, FP32 from 1024 up: the FFT of
+//                    the odd extension with its redundant half left out;
+//   wave core        FP32 of 256 and 512 points: the whole odd extension,
+//                    one wave per row pair.  These sizes are bound by the
+//                    length of a lane's chain, which the symmetric core does
+//                    not shorten;
+//   half-length      16-64 points: with a prefix sum for the odd outputs.
+__host__ __device__ constexpr bool sym_core(int elem_size, int n) {
+  return n >= 1024 || n == 128 || (elem_size == 8 && n >= 128);
+}
+__host__ __device__ constexpr bool wave_core(int elem_size, int n) {
+  return elem_size == 4 && (n == 256 || n == 512);
 }
 
-// Lanes that transform one row pair with the FP32 core: two waves (128) at
-// 1024 points, one wave (64) at 256 and 512 (two waves measured slower
-// there: 512^2 column pass 10.3 against 8.3 us).
-__host__ __device__ constexpr int core_lanes(int elem_size, int n) {
-  return fast_core(elem_size, n) && n >= 1024 ? 128 : 64;
-}
+// Rows (columns) a workgroup of the symmetric core transforms in the row
+// (column) passes.
+__host__ __device__ constexpr int sym_rows(int n) { return n >= 2048 ? 2 : 4; }
+__host__ __device__ constexpr int sym_cols(int n) { return n >= 2048 ? 2 : 4; }
 
 // Per-axis transform tables (device pointers): for the half-length
 // transform tw[m] = e^{-2 pi i m / n} and pre[j] = sin(pi j / n); for the
-// FP32 core with NL = core_lanes lanes per pair tw[k1 * NL + l] =
-// e^{-2 pi i l k1 / 2n} (2n entries) and pre holds the complex table
-// W_NL^{la c1} at [la * 9 + c1] (la < NL / 8, c1 < 8, entry 8 of a row 0).
+// wave core tw[k1 * 64 + l] = e^{-2 pi i l k1 / 2n} (2n entries) and pre holds
+// the complex table W_64^{la c1} at [la * 9 + c1] (la < 8, c1 < 8, entry 8 of
+// a row 0); for the symmetric core tw as in sym_table_* and pre unused.
 template <typename T>
 struct AxisTables {
   const Cplx<T>* tw;
   const T* pre;
   const double* lam;     // Laplacian eigenvalue of sine mode p, p = 0..n-1 (0 unused)
 };
+
+// Table of the symmetric core in AxisTables::tw, H = n / 16, G = max(1, H / 8):
+// entries m < 9 H: W_2n^{l k} at m = k H + l; then 16 G entries W_2H^{g c} at
+// m = 9 H + 16 g + c; then 9 x 8 values sin(pi (2 j + 1) k / 16) as the real
+// parts at m = 9 H + 16 G + 8 k + j.  sym_table_angle gives entry m's angle
+// in units of pi (e^{-i pi angle}, or sin(pi angle) for the last part).
+__host__ __device__ constexpr int sym_g(int n) { return n / 16 >= 8 ? n / 128 : 1; }
+__host__ __device__ constexpr int sym_table_w(int n) { return 9 * (n / 16); }
+__host__ __device__ constexpr int sym_table_s(int n) { return sym_table_w(n) + 16 * sym_g(n); }
+__host__ __device__ constexpr int sym_table_size(int n) { return sym_table_s(n) + 72; }
+__host__ __device__ inline double sym_table_angle(int n, int m) {
+  const int H = n / 16;
+  if (m < sym_table_w(n)) return static_cast<double>((m % H) * (m / H)) / n;
+  if (m < sym_table_s(n)) {
+    const int q = m - sym_table_w(n);
+    return static_cast<double>((q / 16) * (q % 16)) / H;
+  }
+  const int q = m - sym_table_s(n);
+  return static_cast<double>(((2 * (q % 8) + 1) * (q / 8)) % 32) / 16.0;
+}
 
 // Device-side scalars of the predictor-corrector and counters.
 struct DevCounters {

@@ -20,36 +20,60 @@ k_src_fwd_pez(Geom g, SrcPEZ<T> a, AxisTables<T> tx) {
   constexpr int n = 1 << LOGN;   // = nx
   const int R = RC > 0 ? RC : g.rr;
   const int ppitch = pair_pitch<T>(n);
-  const Cplx<T>* tw;
-  const T* pre;
-  stage_tables<T, LOGN>(tx, smem_raw + static_cast<size_t>(R / 2) * ppitch * sizeof(T), tw, pre);
+  const auto xf = stage_tables<T, LOGN, row_pairs<T, LOGN>()>(tx, smem_raw + static_cast<size_t>(R / 2) * ppitch * sizeof(T), R / 2);
   // neighbouring row blocks share the 128-byte lines of strip-ordered
   // planes: keep them on one XCD (one L2)
   const int j0 = xcd_strip(blockIdx.x, gridDim.x) * R;
   const int fld = blockIdx.y;   // 0 psi, 1 Ez, 2 Bz
-  const double ihx = 0.5 / g.hx, ihy = 0.5 / g.hy;
-  // neighbour indices are clamped so that every load is in bounds; values
-  // outside the interior are replaced by selects
-  for_row_elems<RC, LOGN>(R, [&](int e) {
-    const int r = e >> LOGN, i = e & (n - 1);
-    const int j = j0 + r;
-    const int o = j * n + i;
-    double s;
-    if (fld == 0) {
-      s = -(a.rho_mjz[o] + (a.ionx ? a.n0 * a.ionx[i] * a.iony[j] : a.n0));
-    } else {
-      const int ow = i > 0 ? o - 1 : o, oe = i + 1 < n ? o + 1 : o;
-      const int os = j > 0 ? o - n : o, on = j + 1 < g.ny ? o + n : o;
-      const double xe = a.jx[oe], xw = a.jx[ow], xn = a.jx[on], xs = a.jx[os];
-      const double ye = a.jy[oe], yw = a.jy[ow], yn = a.jy[on], ys = a.jy[os];
-      const double jx_e = i + 1 < n ? xe : 0.0, jy_e = i + 1 < n ? ye : 0.0;
-      const double jx_n = j + 1 < g.ny ? xn : 0.0, jy_n = j + 1 < g.ny ? yn : 0.0;
-      s = fld == 1 ? (jx_e - xw) * ihx + (jy_n - ys) * ihy : (jx_n - xs) * ihy - (jy_e - yw) * ihx;
+  // psi: -(rho - Jz + ions); Ez: d_x Jx + d_y Jy; Bz: d_y Jx - d_x Jy
+  const double ihx = fld == 1 ? 0.5 / g.hx : -0.5 / g.hx, ihy = 0.5 / g.hy;
+  const double* __restrict__ ax = fld == 0 ? a.rho_mjz : (fld == 1 ? a.jx : a.jy);
+  const double* __restrict__ ay = fld == 1 ? a.jy : a.jx;
+  struct In {
+    double e, w, n, s;
+    __device__ void pin() {
+      dst_detail::pin(e);
+      dst_detail::pin(w);
+      dst_detail::pin(n);
+      dst_detail::pin(s);
     }
-    buf[RowLay<T, LOGN>::rpos(n, ppitch, r, i)] = static_cast<T>((i > 0 && j > 0) ? s : 0.0);
-  });
+  };
+  auto put = [&](int e, double s) {
+    const int r = e >> LOGN, i = e & (n - 1);
+    buf[RowLay<T, LOGN>::rpos(n, ppitch, r, i)] = static_cast<T>((i > 0 && j0 + r > 0) ? s : 0.0);
+  };
+  if (fld == 0) {
+    struct Rho {
+      double r;
+      __device__ void pin() { dst_detail::pin(r); }
+    };
+    const bool ions = a.ionx != nullptr;
+    for_row_batches<RC, LOGN, 2 * src_batch<T, LOGN>(), Rho>(
+        R, [&](int e, Rho& v) { v.r = load_at(ax, j0 * n + e); },
+        [&](int, int e, const Rho& v) {
+          put(e, -(v.r + (ions ? a.n0 * a.ionx[e & (n - 1)] * a.iony[j0 + (e >> LOGN)] : a.n0)));
+        });
+  } else {
+    // neighbour indices are clamped so that every load is in bounds; values
+    // outside the interior are replaced by selects
+    for_row_batches<RC, LOGN, src_batch<T, LOGN>(), In>(
+        R,
+        [&](int e, In& v) {
+          const int i = e & (n - 1), j = j0 + (e >> LOGN);
+          const int o = j * n + i;
+          v.e = load_at(ax, i + 1 < n ? o + 1 : o);
+          v.w = load_at(ax, i > 0 ? o - 1 : o);
+          v.n = load_at(ay, j + 1 < g.ny ? o + n : o);
+          v.s = load_at(ay, j > 0 ? o - n : o);
+        },
+        [&](int, int e, const In& v) {
+          const int i = e & (n - 1), j = j0 + (e >> LOGN);
+          put(e, ((i + 1 < n ? v.e : 0.0) - v.w) * ihx + ((j + 1 < g.ny ? v.n : 0.0) - v.s) * ihy);
+        });
+  }
+  xf.commit();
   __syncthreads();
-  block_dst<T, LOGN>(buf, g.lx, R, ppitch, tw, pre);
+  block_dst<T, LOGN>(buf, R, ppitch, xf);
   rows_to_plane<T, RC, LOGN>(g, R, j0, buf, ppitch, a.out + static_cast<size_t>(fld) * g.nx * g.ny);
 }
 
@@ -72,9 +96,9 @@ k_col_solve(Geom g, ColArgs<T> a, AxisTables<T> ty, const double* __restrict__ l
   extern __shared__ __align__(16) unsigned char smem_raw[];
   col_block<T, LOGN>(g, a, ty, lamx, xcd_strip(blockIdx.x, gridDim.x), blockIdx.y, smem_raw);
   // the side job's stores come last (the memory counter the strip load waits
-  // on also counts stores); the two-wave core's pass issues them itself,
+  // on also counts stores); the symmetric core's pass issues them itself,
   // before its transforms
-  if constexpr (core_lanes(sizeof(T), 1 << LOGN) != 128)
+  if constexpr (!sym_core(sizeof(T), 1 << LOGN))
     zero_job(a.zero, static_cast<size_t>(blockIdx.y) * gridDim.x + blockIdx.x,
              static_cast<size_t>(gridDim.x) * gridDim.y);
 }
@@ -90,19 +114,40 @@ k_row_inv(Geom g, RowInvArgs<T> a, AxisTables<T> tx) {
   constexpr int n = 1 << LOGN;   // = nx
   const int R = RC > 0 ? RC : g.rr;
   const int ppitch = pair_pitch<T>(n);
-  const Cplx<T>* tw;
-  const T* pre;
-  stage_tables<T, LOGN>(tx, smem_raw + static_cast<size_t>(R / 2) * ppitch * sizeof(T), tw, pre);
+  const auto xf = stage_tables<T, LOGN, row_pairs<T, LOGN>()>(tx, smem_raw + static_cast<size_t>(R / 2) * ppitch * sizeof(T), R / 2);
   const int j0 = xcd_strip(blockIdx.x, gridDim.x) * R;   // neighbours on one XCD
   const int fld = blockIdx.y;
-  {
-    Geom gi = g;
-    gi.strip = a.in_strip;
+  Geom gi = g;
+  gi.strip = a.in_strip;
+  const size_t plane = static_cast<size_t>(g.nx) * g.ny;
+  const size_t gstride = static_cast<size_t>(gridDim.x) * gridDim.y * kBlock;
+  const size_t gi0 = (static_cast<size_t>(blockIdx.y) * gridDim.x + blockIdx.x) * kBlock + threadIdx.x;
+  GuessRegs<T> gr;
+  if constexpr (RC > 0) {
+    RowFetch<T, RC, LOGN> rows;
+    rows.load(gi, j0, a.in[fld]);
+    if (a.guess.ctr) guess_load(a.guess, plane, gi0, gstride, gr);
+    __builtin_amdgcn_sched_barrier(0);
+    rows.put(gi, buf, ppitch);
+  } else {
     plane_to_rows<T, RC, LOGN>(gi, R, j0, a.in[fld], buf, ppitch);
+    if (a.guess.ctr) guess_load(a.guess, plane, gi0, gstride, gr);
+  }
+  xf.commit();
+  if (a.guess.ctr) {   // its stores drain under the transform
+    if (gi0 == 0) {
+      a.guess.ctr->pc_done = 0u;
+      a.guess.ctr->pc_iters = 0u;
+      a.guess.ctr->pc_resid = 0.0;
+    }
+    guess_store(a.guess, plane, gi0, gstride, gr);
+    for (size_t i0 = gi0 + kGuess * gstride; i0 < plane; i0 += kGuess * gstride) {
+      guess_load(a.guess, plane, i0, gstride, gr);
+      guess_store(a.guess, plane, i0, gstride, gr);
+    }
   }
   __syncthreads();
-  block_dst<T, LOGN>(buf, g.lx, R, ppitch, tw, pre);
-  guess_job(a.guess, static_cast<size_t>(g.nx) * g.ny);
+  block_dst<T, LOGN>(buf, R, ppitch, xf);
   T* out = a.out[fld];
   T* out_dx = a.out_dx[fld];
   if (a.out_strip) {   // an intermediate plane (no -d_x)
@@ -112,18 +157,24 @@ k_row_inv(Geom g, RowInvArgs<T> a, AxisTables<T> tx) {
     return;
   }
   const T mihx = static_cast<T>(-0.5 / g.hx);
-  for_row_elems<RC, LOGN>(R, [&](int e) {
-    const int r = e >> LOGN, i = e & (n - 1);
-    const int j = j0 + r;
-    const T* row = buf + RowLay<T, LOGN>::rpos(n, ppitch, r, 0);
-    const T u = row[RowLay<T, LOGN>::ridx(i)];
-    out[j * n + i] = j > 0 ? u : T(0);
-    if (out_dx) {
-      const T ue = row[RowLay<T, LOGN>::ridx(i + 1 < n ? i + 1 : i)], uw = row[RowLay<T, LOGN>::ridx(i > 0 ? i - 1 : 0)];
-      const T d = mihx * ((i + 1 < n ? ue : T(0)) - uw);
-      out_dx[j * n + i] = (i > 0 && j > 0) ? d : T(0);
-    }
-  });
+  auto put = [&](auto with_dx) {   // tested once: per element the loop stays rolled
+    for_row_elems<RC, LOGN>(R, [&](int e) {
+      const int r = e >> LOGN, i = e & (n - 1);
+      const int j = j0 + r;
+      const T* row = buf + RowLay<T, LOGN>::rpos(n, ppitch, r, 0);
+      const T u = row[RowLay<T, LOGN>::ridx(i)];
+      store_at(out, j * n + i, j > 0 ? u : T(0));
+      if constexpr (decltype(with_dx)::value) {
+        const T ue = row[RowLay<T, LOGN>::ridx(i + 1 < n ? i + 1 : i)], uw = row[RowLay<T, LOGN>::ridx(i > 0 ? i - 1 : 0)];
+        const T d = mihx * ((i + 1 < n ? ue : T(0)) - uw);
+        store_at(out_dx, j * n + i, (i > 0 && j > 0) ? d : T(0));
+      }
+    });
+  };
+  if (out_dx)
+    put(std::true_type{});
+  else
+    put(std::false_type{});
 }
 
 // First and last pass of a batched solve on the caller's node arrays
@@ -140,9 +191,7 @@ k_row_nodes(Geom g, NodeRowArgs<T> a, AxisTables<T> tx) {
   constexpr int n = 1 << LOGN;   // = nx
   const int R = RC > 0 ? RC : g.rr;
   const int ppitch = pair_pitch<T>(n);
-  const Cplx<T>* tw;
-  const T* pre;
-  stage_tables<T, LOGN>(tx, smem_raw + static_cast<size_t>(R / 2) * ppitch * sizeof(T), tw, pre);
+  const auto xf = stage_tables<T, LOGN, row_pairs<T, LOGN>()>(tx, smem_raw + static_cast<size_t>(R / 2) * ppitch * sizeof(T), R / 2);
   const int j0 = xcd_strip(blockIdx.x, gridDim.x) * R;
   const int b = blockIdx.y;
   const size_t plane = static_cast<size_t>(n) * g.ny;
@@ -152,14 +201,15 @@ k_row_nodes(Geom g, NodeRowArgs<T> a, AxisTables<T> tx) {
     for_row_elems<RC, LOGN, 16>(R, [&](int e) {
       const int r = e >> LOGN, i = e & (n - 1);
       const int j = j0 + r;
-      const T v = src[j * (n + 1) + i];
+      const T v = load_at(src, j * (n + 1) + i);
       buf[RowLay<T, LOGN>::rpos(n, ppitch, r, i)] = i > 0 && j > 0 ? v : T(0);
     });
   } else {
     plane_to_rows<T, RC, LOGN>(g, R, j0, a.plane + b * plane, buf, ppitch);
   }
+  xf.commit();
   __syncthreads();
-  block_dst<T, LOGN>(buf, g.lx, R, ppitch, tw, pre);
+  block_dst<T, LOGN>(buf, R, ppitch, xf);
   if constexpr (!OUT) {
     rows_to_plane<T, RC, LOGN>(g, R, j0, buf, ppitch, a.plane + b * plane);
   } else {
@@ -168,7 +218,7 @@ k_row_nodes(Geom g, NodeRowArgs<T> a, AxisTables<T> tx) {
       const int r = e >> LOGN, i = e & (n - 1);
       const int j = j0 + r;
       const T v = buf[RowLay<T, LOGN>::rpos(n, ppitch, r, i)];
-      dst[j * (n + 1) + i] = j > 0 ? v : T(0);
+      store_at(dst, j * (n + 1) + i, j > 0 ? v : T(0));
     });
     if (static_cast<int>(threadIdx.x) < R) dst[(j0 + static_cast<int>(threadIdx.x)) * (n + 1) + n] = T(0);
     if (j0 + R == g.ny)
@@ -195,23 +245,16 @@ static void allow_lds(const void* fn, size_t lds) {
                                 static_cast<int>(lds)));
 }
 
-// Each wave transforms one group of row pairs (one pair for the FP32 core,
-// max(1, 512/n) otherwise; two waves per pair at 1024 with the FP32 core,
-// exactly two pairs): a pass must not give a workgroup more rows.
-// The strip order of the intermediate planes moves 4 rows x 4 columns at a
-// time: it needs 4-row row blocks and 4-column column strips.
-static void check_strip(const Geom& g, int rows_or_cols) {
-  if (g.strip && rows_or_cols != 4)
-    throw std::invalid_argument("transform pass: strip-ordered planes need blocks of 4 rows or columns");
-}
-
+// A pass must not give a workgroup other rows than its transform takes:
+// sym_rows for the symmetric core, at most one group of row pairs (one pair
+// for the wave core, max(1, 512/n) otherwise) per wave for the others.
 template <typename T>
 static void check_rows(int n, int rows) {
-  if (core_lanes(sizeof(T), n) == 128) {   // the two-wave core needs all four waves busy
-    if (rows != 4) throw std::invalid_argument("transform pass: the two-wave core takes 4 rows");
+  if (sym_core(sizeof(T), n)) {
+    if (rows != sym_rows(n)) throw std::invalid_argument("transform pass: wrong rows for the symmetric core");
     return;
   }
-  const int per = fast_core(sizeof(T), n) || n >= 512 ? 1 : 512 / n;
+  const int per = wave_core(sizeof(T), n) || n >= 512 ? 1 : 512 / n;
   if (rows > 2 * per * (kBlock / 64))
     throw std::invalid_argument("transform pass: more row pairs than its waves take");
 }
@@ -221,7 +264,6 @@ void launch_src_fwd_pez(const Geom& g, const SrcPEZ<T>& a, const AxisTables<T>& 
                         hipStream_t st) {
   const int R = g.rr;
   check_rows<T>(g.nx, R);
-  check_strip(g, R);
   const size_t lds = static_cast<size_t>(R / 2) * pair_pitch<T>(g.nx) * sizeof(T) + table_bytes<T>(g.nx);
   with_logn(g.nx, [&](auto e) {
     constexpr int E = decltype(e)::value;
@@ -239,7 +281,6 @@ void launch_src_fwd_bxby(const Geom& g, const SrcBxBy<T>& a, const AxisTables<T>
                          const DevCounters* ctr, hipStream_t st) {
   const int R = g.rr;
   check_rows<T>(g.nx, R);
-  check_strip(g, R);
   const size_t lds = static_cast<size_t>(R / 2) * pair_pitch<T>(g.nx) * sizeof(T) + table_bytes<T>(g.nx);
   with_logn(g.nx, [&](auto e) {
     constexpr int E = decltype(e)::value;
@@ -259,8 +300,11 @@ void launch_col_solve(const Geom& g, const ColArgs<T>& a, int nfield, const Axis
   const int W = a.w;
   if (W < 2 || (W & (W - 1)) || g.nx % W || nfield < 1 || nfield > 4)
     throw std::invalid_argument("column pass: bad strip width or field count");
-  check_rows<T>(g.ny, W);
-  check_strip(g, W);
+  if (sym_core(sizeof(T), g.ny) ? W != sym_cols(g.ny) : false)
+    throw std::invalid_argument("column pass: wrong columns for the symmetric core");
+  if (!sym_core(sizeof(T), g.ny)) check_rows<T>(g.ny, W);
+  if (g.strip && W != 4)   // a strip of the intermediate planes is 4 columns
+    throw std::invalid_argument("column pass: strip-ordered planes need strips of 4 columns");
   const size_t lds = static_cast<size_t>(W / 2) * pair_pitch<T>(g.ny) * sizeof(T) + table_bytes<T>(g.ny) +
                      lam_bytes<T>(g.ny, W);
   with_logn(g.ny, [&](auto e) {
@@ -277,7 +321,6 @@ void launch_row_inv(const Geom& g, const RowInvArgs<T>& a, int nfield, const Axi
                     hipStream_t st) {
   const int R = g.rr;
   check_rows<T>(g.nx, R);
-  check_strip(g, R);
   const size_t lds = static_cast<size_t>(R / 2) * pair_pitch<T>(g.nx) * sizeof(T) + table_bytes<T>(g.nx);
   with_logn(g.nx, [&](auto e) {
     constexpr int E = decltype(e)::value;
@@ -297,7 +340,6 @@ void launch_row_nodes(const Geom& g, const NodeRowArgs<T>& a, bool out, int nbat
   if (nbatch < 1 || nbatch > 4 || !a.plane || (out ? !a.nodes_out : !a.nodes_in))
     throw std::invalid_argument("node row pass: bad planes or batch");
   check_rows<T>(g.nx, R);
-  check_strip(g, R);
   const size_t lds = static_cast<size_t>(R / 2) * pair_pitch<T>(g.nx) * sizeof(T) + table_bytes<T>(g.nx);
   with_logn(g.nx, [&](auto e) {
     constexpr int E = decltype(e)::value;
@@ -321,7 +363,6 @@ void launch_row_inv_pc(const Geom& g, const PCArgs<T>& a, const AxisTables<T>& t
                        DevCounters* ctr, hipStream_t st) {
   const int R = g.rr;
   check_rows<T>(g.nx, R);
-  check_strip(g, R);
   const size_t lds = static_cast<size_t>(R / 2) * pair_pitch<T>(g.nx) * sizeof(T) + table_bytes<T>(g.nx);
   with_logn(g.nx, [&](auto e) {
     constexpr int E = decltype(e)::value;

@@ -74,6 +74,14 @@ __device__ inline void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+// Keeps a loaded value in its register from here on: without it the compiler
+// moves a load whose value only feeds a select into a branch beside the
+// select, and so turns a batch of loads into one memory round trip each
+// (source assembly of a 1024^2 corrector pass, FP32: 31.2k of the kernel's
+// 41k cycles in three dependent round trips per element).
+__device__ __forceinline__ void pin(float& x) { asm volatile("" : "+v"(x)); }
+__device__ __forceinline__ void pin(double& x) { asm volatile("" : "+v"(x)); }
+
 template <typename T>
 __device__ inline Cplx<T> cadd(Cplx<T> a, Cplx<T> b) { return {a.re + b.re, a.im + b.im}; }
 template <typename T>
@@ -319,7 +327,7 @@ __device__ __forceinline__ void wave_dst(T* g, int npg, int ppitch, const Cplx<T
 
 
 // ---------------------------------------------------------------------------
-// FP32 core for n = 256, 512, 1024 without a recurrence.  The odd outputs of
+// FP32 core for n = 256 and 512 without a recurrence.  The odd outputs of
 // the half-length transform above come from a prefix sum, whose FP32
 // round-off grows like sqrt(n) and, through the centred differences taken of
 // the solved fields, reaches ~1e-4 of Ey+Bx at 512^2-1024^2.  Here the two
@@ -328,7 +336,7 @@ __device__ __forceinline__ void wave_dst(T* g, int npg, int ppitch, const Cplx<T
 // length N: with X = DFT_N(z), S^a_p = -Im X_p / 2 and S^b_p = Re X_p / 2.
 // Every output carries plain FFT round-off.
 //
-// One wave per pair, N = 64 P (P = 8, 16, 32 points per lane), as a 4-step
+// One wave per pair, N = 64 P (P = 8, 16 points per lane), as a 4-step
 // FFT with the index j = l + 64 m (lane l, register m) and k = k1 + P k2:
 //   A   each lane: DFT_P over m in registers, times W_N^{l k1};
 //   B1  DFT_64 over l split as 8 x 8 (l = la + 8 lb, k2 = c1 + 8 c2):
@@ -340,18 +348,19 @@ __device__ __forceinline__ void wave_dst(T* g, int npg, int ppitch, const Cplx<T
 // ---------------------------------------------------------------------------
 constexpr int kCorePitch = 72;   // complex entries per k1 row of the transposes
 
-// Row layout in LDS around the FP32 core (gfx950 serves LDS as 32 banks of 4
-// bytes, half a wave at a time): 4 padding words after every 32, row b of a
-// pair at an offset = 4 (mod 32), pairs 8 (mod 32) apart (at 1024 points: 8
-// and 16).  Then the core's last-stage writes (k = kb + P c1 + const over
-// the lanes kb < 4, c1 < 8 of a half-wave) land on 32 distinct banks, and
-// so do the column pass's strip accesses (8 columns = 4 pairs x 2 rows, 4
-// consecutive rows each; at 1024 points 4 columns, 8 rows each); runs of 32
-// consecutive entries (row passes, the core's first stage) stay contiguous.
+// Row layout in LDS around the two FFT cores (gfx950 serves LDS as 32 banks
+// of 4 bytes, half a wave of 4-byte or a quarter of 8-byte accesses at a
+// time): 4 padding words after every 32.  Row b of a pair lies at an offset
+// = 4 (mod 32) words (8 from 1024 points up), pairs 8 (mod 32) apart with the
+// wave core, 16 with the symmetric core.  Then the cores' last-stage writes
+// (k = k1 + 16 c1 or kb + P c1 + const over the lanes) land on distinct banks,
+// and so do the column pass's strip accesses; runs of 32 consecutive words
+// (row passes, the first stage) stay contiguous.
+template <typename T>
 struct CoreLay {
-  __host__ __device__ static constexpr int ridx(int i) { return i + 4 * (i >> 5); }
-  // offset of row b in the pair (named as in Pad): = 4 (mod 32), or = 8 at
-  // 1024 points, whose column strips are 4 columns (2 pairs) wide
+  static constexpr int S = sizeof(T) == 4 ? 5 : 4;   // log2 of the run
+  static constexpr int Q = sizeof(T) == 4 ? 4 : 2;   // padding after it
+  __host__ __device__ static constexpr int ridx(int i) { return i + Q * (i >> S); }
   __host__ __device__ static constexpr int rlen(int n) {
     return ((ridx(n) + 31) & ~31) + (n >= 1024 ? 8 : 4);
   }
@@ -362,7 +371,8 @@ struct CoreLay {
 
 // W_32^k = e^{-2 pi i k / 32} for k >= 0 (from cos(2 pi k / 32), k = 0..8;
 // W_32^{k+16} = -W_32^k).  Called with compile-time k only.
-__device__ __forceinline__ Cplx<float> w32(int k) {
+template <typename T>
+__device__ __forceinline__ Cplx<T> w32(int k) {
   constexpr double c32[9] = {1.0,
                              0.98078528040323044913,
                              0.92387953251128675613,
@@ -376,7 +386,7 @@ __device__ __forceinline__ Cplx<float> w32(int k) {
   k &= 15;
   const double c = k <= 8 ? c32[k] : -c32[16 - k];
   const double s = k <= 8 ? c32[8 - k] : c32[k - 8];
-  return {static_cast<float>(sg * c), static_cast<float>(-sg * s)};
+  return {static_cast<T>(sg * c), static_cast<T>(-sg * s)};
 }
 
 // In-register forward DFT of length P = R1 * 8 (R1 = 1, 2, 4), in place with
@@ -387,13 +397,13 @@ __host__ __device__ constexpr int dft_pos(int k) {
   return 8 * (k % (P / 8)) + k / (P / 8);
 }
 
-template <int P>
-__device__ __forceinline__ void dft_reg(Cplx<float>* v) {
+template <int P, typename T>
+__device__ __forceinline__ void dft_reg(Cplx<T>* v) {
   constexpr int R1 = P / 8;
   if constexpr (R1 == 2) {
 #pragma unroll
     for (int j0 = 0; j0 < 8; ++j0) {
-      const Cplx<float> a = v[j0], b = v[j0 + 8];
+      const Cplx<T> a = v[j0], b = v[j0 + 8];
       v[j0] = cadd(a, b);
       v[j0 + 8] = csub(a, b);
     }
@@ -405,60 +415,63 @@ __device__ __forceinline__ void dft_reg(Cplx<float>* v) {
 #pragma unroll
     for (int k0 = 1; k0 < R1; ++k0)
 #pragma unroll
-      for (int j0 = 1; j0 < 8; ++j0) v[8 * k0 + j0] = cmul(v[8 * k0 + j0], w32(j0 * k0 * (32 / P)));
+      for (int j0 = 1; j0 < 8; ++j0) v[8 * k0 + j0] = cmul(v[8 * k0 + j0], w32<T>(j0 * k0 * (32 / P)));
   }
 #pragma unroll
   for (int k0 = 0; k0 < R1; ++k0) dft8(v + 8 * k0);
 }
 
 // DST-I of one pair (rows a at g, b at g + rlen(n), entry 0 = 0) by one
-// wave, in place; twa[k1 * 64 + l] = W_N^{l k1} (global memory), w64[la * 9
+// wave, in place; twa[k1 - 1] = W_N^{l k1} (the lane's registers), w64[la * 9
 // + c1] = W_64^{la c1} (LDS).  The pair's region holds P rows of kCorePitch
 // complex.
 // Output scaling of the core: none (plain transform).  The cores call
 // epi(q, oa, ob) for their q-th output slot of the lane.
 struct NoScale {
-  __device__ void operator()(int, float&, float&) const {}
+  template <typename T>
+  __device__ void operator()(int, T&, T&) const {}
 };
+
+// 1 / d: the hardware estimate in FP32 (1 ulp), refined by two Newton steps
+// in FP64
+__device__ __forceinline__ float recip(float d) { return __builtin_amdgcn_rcpf(d); }
+__device__ __forceinline__ double recip(double d) {
+  double y = __builtin_amdgcn_rcp(d);
+  y = fma(fma(-d, y, 1.0), y, y);
+  return fma(fma(-d, y, 1.0), y, y);
+}
 
 // Output scaling of the core in the column pass: S_k of the pair's columns
 // p_a, p_b divided by (lambda_x(p) + lambda_y(k) - shift) nx ny / 4, the
 // eigenvalue of the shifted Laplacian times the two transforms'
 // normalisation; column p = 0 (a boundary node line) is zero.  ry holds
 // (lambda_y(k) - shift) nx ny / 4 for the lane's NK output slots k (see
-// core_out_k), xa / xb lambda_x(p) nx ny / 4.
-template <int NK>
+// core_out_k, sym_out_k), xa / xb lambda_x(p) nx ny / 4.
+template <typename T, int NK>
 struct EigenScale {
-  float ry[NK];
-  float xa, xb;
+  T ry[NK];
+  T xa, xb;
   bool za;
-  __device__ void operator()(int q, float& oa, float& ob) const {
-    const float ra = __builtin_amdgcn_rcpf(xa + ry[q]);
-    const float rb = __builtin_amdgcn_rcpf(xb + ry[q]);
-    oa = za ? 0.f : oa * ra;
+  __device__ void operator()(int q, T& oa, T& ob) const {
+    const T ra = recip(xa + ry[q]);
+    const T rb = recip(xb + ry[q]);
+    oa = za ? T(0) : oa * ra;
     ob *= rb;
   }
 };
 
-// Output slots of a lane: the one-wave core (P points per lane, lane l)
-// writes k = (l >> 3) + 8 t + P (l & 7) + 8 P c2 in slot q = 4 t + c2; the
-// two-wave core (P points per lane, lane L of 128) k = k1 + P c1 + 8 P q with
-// k1 = (L >> 6) P / 2 + ((L & 63) >> 3), c1 = L & 7 (lanes whose k1 falls
-// outside their wave's rows write nothing; their k is wrapped into [0, n)).
+// Output slots of a lane of the wave core (P points per lane, lane l):
+// k = (l >> 3) + 8 t + P (l & 7) + 8 P c2 in slot q = 4 t + c2.
 template <int P>
 __device__ __forceinline__ int core_out_k(int l, int q) {
   return (l >> 3) + 8 * (q >> 2) + P * (l & 7) + 8 * P * (q & 3);
 }
-template <int P>
-__device__ __forceinline__ int core2_out_k(int L, int q) {
-  return ((L >> 6) * (P / 2) + ((L & 63) >> 3) + P * (L & 7) + 8 * P * q) & (64 * P - 1);
-}
 
 template <int P, typename Epi = NoScale>
-__device__ __forceinline__ void wave_dst_core(float* g, const Cplx<float>* __restrict__ twa,
-                                              const Cplx<float>* __restrict__ w64,
+__device__ __forceinline__ void wave_dst_core(float* g, const Cplx<float> (&twa)[P - 1],
+                                              const Cplx<float>* w64,
                                               const Epi& epi = Epi{}) {
-  using Pd = CoreLay;
+  using Pd = CoreLay<float>;
   constexpr int n = 32 * P;
   constexpr int NB = P / 8;
   const int l = threadIdx.x & 63;
@@ -484,7 +497,7 @@ __device__ __forceinline__ void wave_dst_core(float* g, const Cplx<float>* __res
 #pragma unroll
   for (int k1 = 0; k1 < P; ++k1) {
     const Cplx<float> y = v[dft_pos<P>(k1)];
-    s[k1 * kCorePitch + l] = k1 ? cmul(y, twa[k1 * 64 + l]) : y;
+    s[k1 * kCorePitch + l] = k1 ? cmul(y, twa[k1 > 0 ? k1 - 1 : 0]) : y;
   }
   wave_sync();
   // B1: combos (k1, la) = (l >> 3 + 8 t, l & 7)
@@ -537,148 +550,316 @@ __device__ __forceinline__ void wave_dst_core(float* g, const Cplx<float>* __res
 }
 
 // ---------------------------------------------------------------------------
-// Two-wave FP32 core for rows of n = 64 P points (used with P = 16, n = 1024):
-// the pair's 128 lanes share the N = 128 P-point FFT, P points per lane, so
-// that twice as many waves (two per SIMD on a full grid) hide each other's
-// latencies:
-//   A   lane L: DFT_P over m of z_{L + 128 m}, times W_N^{L k1} (k = k1 +
-//       P k2), into row k1 of the transpose region; one workgroup barrier;
-//   B1  DFT_128 over L split as 16 x 8 (L = la + 16 lb, k2 = c1 + 8 c2):
-//       DFT_8 over lb, times W_128^{la c1}; wave w of the pair owns rows
-//       k1 = w P/2 .. (w + 1) P/2 - 1 from here on (no more barriers);
-//   B2  DFT_16 over la (4 P of a wave's 64 lanes), outputs k = k1 + P c1 +
-//       8 P c2 for c2 < 8.
-// The transposes use a region of their own after the rows (rows of 152
-// complex: the strided reads and writes of B1 and B2 meet every bank once
-// per 16 lanes), so the first stage reads its rows without a barrier before
-// its writes.  Every thread of the workgroup must call it (its barrier);
-// the caller synchronises the workgroup before the rows are read again.
+// Symmetric core (n = 128 .. 2048, FP32 and FP64): the FFT of the odd
+// extension z (length N = 2n, rows a + i b) without its redundant half.  With
+// H = n / 16, l = 0 .. 2H - 1, j = l + 2H m, k = k1 + 16 k2 the four-step FFT is
+//   A_k1(l) = DFT_16 over m of z_{l + 2H m},  y_k1(l) = W_N^{l k1} A_k1(l),
+//   X_{k1 + 16 k2} = DFT_2H over l of y_k1.
+// z_{N-j} = -z_j gives y_k1(2H - l) = -conj(W_N^{l k1}) A_{16-k1}(l), so lanes
+// l < H supply both ends of every row, and X_{N-k} = -X_k lets the rows
+// k1 = 0 .. 8 give every output (k >= n as -X at N - k).  A wave of 64 lanes
+// transforms a pair at n = 1024 where the full extension takes two, and the
+// LDS exchanges, which bound the 1024^2 passes (13.6k of the 21.5k cycles of a
+// column pass were LDS issue), move 9/16 of the data.
+//   A    main lane l (H per pair): DFT_16, 9 rows x 2 ends;
+//        l = H, its own mirror image: y_k1(H) = -2i sum_{m<8} z_{H + 2H m}
+//        sin(pi (2m + 1) k1 / 16), by lanes of the next wave;
+//   --   workgroup barrier;
+//   B    row k1 by G = H / 8 lanes of 16 points (rows 0-7: the main lanes, row
+//        8: the next wave): DFT_16 over l = g + G lb, W_2H^{g c1}, exchange
+//        inside the row, DFT_G; k2 = c1 + 16 c2.  At n = 128 a lane holds a
+//        whole row.
+// The rows of the exchange region are RP = 16 (G + 1) + G complex apart and
+// the exchange entries G + 1: every access pattern (consecutive l; g + G lb
+// over rows; c1 (G + 1) + g) meets each bank once per service group.
+// The twiddles of stage A stay in the lane's registers, those of stage B (16 G,
+// rows of 17) in LDS, so a transform issues no global load.  (All of them and
+// the column pass's eigenvalues by global loads of every lane moved 80 KB a
+// workgroup through the vector cache, five times its strip.)
 // ---------------------------------------------------------------------------
-constexpr int kCore2Pitch = 152;   // complex entries per k1 row of the transposes
+template <int LOGN, int NP = 1>
+struct Sym {
+  static constexpr int n = 1 << LOGN;
+  static constexpr int H = n / 16, NL = 2 * H;
+  static constexpr int G = sym_g(n);
+  static constexpr int GP = G + 1;
+  static constexpr int RP = G == 1 ? NL + 1 : 16 * GP + (G < 16 ? G : 0);
+  static constexpr int pairs = NP;                         // per workgroup
+  static constexpr int nmain = pairs * H;                  // main lanes
+  static constexpr int xtra = (nmain + 63) / 64 * 64;      // first lane of the next wave
+  static_assert(H >= 8 && xtra + 64 <= kBlock && 16 * pairs <= 64, "workgroup shape");
+  // T units in front of the exchange region, and of a whole pair
+  template <typename T>
+  __host__ __device__ static constexpr int soff() {
+    return (CoreLay<T>::rlen(n) + CoreLay<T>::ridx(n) + 31) & ~31;
+  }
+  template <typename T>
+  __host__ __device__ static constexpr int pitch() {
+    return ((soff<T>() + 2 * 9 * RP + 31) & ~31) + 16;
+  }
+};
 
-__host__ __device__ constexpr int core2_soff(int n) {   // floats before the transposes
-  return (CoreLay::rlen(n) + CoreLay::ridx(n) + 31) & ~31;
+// A lane's tasks: stage A of row l (main) or the l = H entry k1 (next wave),
+// stage B of row k1 with position g in it.
+template <int LOGN, int NP>
+struct SymLane {
+  using Y = Sym<LOGN, NP>;
+  bool main, mid, row;   // has a main stage A, a middle entry, a row of stage B
+  int pair_a, l;         // stage A (l = entry k1 for a middle lane)
+  int pair_b, k1, g;     // stage B
+  __device__ SymLane() {
+    const int L = static_cast<int>(threadIdx.x), x = L - Y::xtra;
+    main = L < Y::nmain;
+    mid = x >= 0 && x < 16 * Y::pairs && (x & 15) < 9;
+    row = main || (x >= 0 && x < Y::G * Y::pairs);
+    pair_a = main ? L / Y::H : (mid ? x >> 4 : 0);
+    l = main ? L % Y::H : (mid ? x & 15 : 0);
+    pair_b = main ? L / Y::H : (row ? x / Y::G : 0);
+    k1 = main ? (L % Y::H) / Y::G : 8;
+    g = main ? L % Y::G : (row ? x % Y::G : 0);
+  }
+};
+
+template <typename T, int LOGN>
+struct SymTw {
+  Cplx<T> a[8];        // W_N^{l k}, k = 1..8; middle lane: sines in re
+  Cplx<T> b;           // the thread's entry of the stage-B table
+};
+template <int LOGN>
+__host__ __device__ constexpr int sym_b_entries() {   // complex, in LDS
+  return Sym<LOGN>::G > 1 ? 17 * Sym<LOGN>::G : 0;
 }
 
-template <int P, typename Epi = NoScale>
-__device__ __forceinline__ void pair2_dst_core(float* g, int L, const Cplx<float>* __restrict__ twa,
-                                               const Cplx<float>* __restrict__ w128,
-                                               const Epi& epi = Epi{}) {
-  using Pd = CoreLay;
-  constexpr int n = 64 * P;
-  constexpr int HR = P / 2;   // transpose rows per wave
-  float* ra = g;
-  float* rb = g + Pd::rlen(n);
-  Cplx<float>* s = reinterpret_cast<Cplx<float>*>(g + core2_soff(n));
-  // A: z_{L + 128 m}; m >= P/2 from the mirror 2n - j = 128 (P - m) - L
-  Cplx<float> v[P];
+template <typename T, int LOGN, int NP>
+__device__ __forceinline__ SymTw<T, LOGN> sym_load(const Cplx<T>* __restrict__ tw) {
+  using Y = Sym<LOGN, NP>;
+  const SymLane<LOGN, NP> q;
+  SymTw<T, LOGN> w;
+  // table entries of the lane: row strides H (main) or 1 (a middle entry's sines)
+  const Cplx<T>* pa = q.main ? tw + Y::H + q.l : tw + sym_table_s(Y::n) + 8 * q.l;
+  const int st = q.main ? Y::H : 1;
 #pragma unroll
-  for (int m = 0; m < P / 2; ++m) {
-    const int j = Pd::ridx(L + 128 * m);
-    v[m] = {ra[j], rb[j]};
-  }
+  for (int k = 0; k < 8; ++k) w.a[k] = pa[k * st];
+  const int tid = static_cast<int>(threadIdx.x);
+  w.b = tw[sym_table_w(Y::n) + (tid < 16 * Y::G ? tid : 0)];
+  return w;
+}
+
+// Output k of slot q of a lane's row, and whether the slot's value is stored
+// (rows 0 and 8 hold every value twice).
+template <int LOGN, int NP>
+__device__ __forceinline__ int sym_out_k(const SymLane<LOGN, NP>& t, int q, bool& stored) {
+  using Y = Sym<LOGN, NP>;
+  const int c1 = Y::G > 1 ? t.g + Y::G * (q / Y::G) : q;
+  const int k2 = Y::G > 1 ? c1 + 16 * (q % Y::G) : q;
+  const bool direct = k2 < Y::H;
+  stored = direct || (t.k1 & 7) != 0;
+  return direct ? t.k1 + 16 * k2 : 16 * (Y::NL - k2) - t.k1;
+}
+
+// Transform of the workgroup's pairs in place (entry 0 of every row = 0 on
+// entry; S_k on exit, entry 0 = 0).  Every thread of the workgroup calls it;
+// the caller synchronises before the rows are read again.  epi(q, oa, ob)
+// sees the values of slot q.
+template <typename T, int LOGN, int NP, typename Epi = NoScale>
+__device__ __forceinline__ void sym_dst(T* buf, const SymTw<T, LOGN>& w, const Cplx<T>* tb,
+                                        const Epi& epi = Epi{}) {
+  using Y = Sym<LOGN, NP>;
+  using Pd = CoreLay<T>;
+  constexpr int n = Y::n, H = Y::H, NL = Y::NL, G = Y::G, RP = Y::RP;
+  const SymLane<LOGN, NP> t;
+  {
+    const T* ra = buf + t.pair_a * Y::template pitch<T>();
+    const T* rb = ra + Pd::rlen(n);
+    Cplx<T>* s = reinterpret_cast<Cplx<T>*>(buf + t.pair_a * Y::template pitch<T>() +
+                                            Y::template soff<T>());
+    if (t.main) {
+      const int l = t.l;
+      Cplx<T> v[16];
 #pragma unroll
-  for (int m = P / 2; m < P; ++m) {
-    const int jm = 128 * (P - m) - L;         // in [1, n], n only for L = 0, m = P/2
-    const int j = Pd::ridx(jm < n ? jm : 0);
-    const float fa = ra[j], fb = rb[j];
-    v[m] = {jm < n ? -fa : 0.f, jm < n ? -fb : 0.f};
-  }
-  dft_reg<P>(v);
+      for (int m = 0; m < 8; ++m) {
+        const int j = Pd::ridx(l + NL * m);
+        v[m] = {ra[j], rb[j]};
+      }
 #pragma unroll
-  for (int k1 = 0; k1 < P; ++k1) {
-    const Cplx<float> y = v[dft_pos<P>(k1)];
-    s[k1 * kCore2Pitch + L] = k1 ? cmul(y, twa[k1 * 128 + L]) : y;
+      for (int m = 8; m < 16; ++m) {
+        const int jm = NL * (16 - m) - l;       // in [1, n], n only for l = 0, m = 8
+        const int j = Pd::ridx(jm < n ? jm : 0);
+        const T fa = ra[j], fb = rb[j];
+        v[m] = {jm < n ? -fa : T(0), jm < n ? -fb : T(0)};
+      }
+      dft_reg<16>(v);
+      // both ends of every row (the mirror end of l = 0 falls on the unused
+      // entry NL of the row)
+      s[l] = v[dft_pos<16>(0)];
+      s[NL - l] = {-v[dft_pos<16>(0)].re, -v[dft_pos<16>(0)].im};
+#pragma unroll
+      for (int k = 1; k <= 8; ++k) {
+        const Cplx<T> c = w.a[k - 1];
+        s[k * RP + l] = cmul(v[dft_pos<16>(k)], c);
+        const Cplx<T> m = cmul(v[dft_pos<16>(16 - k)], Cplx<T>{c.re, -c.im});
+        s[k * RP + NL - l] = {-m.re, -m.im};
+      }
+    } else if (t.mid) {
+      T sa = T(0), sb = T(0);
+#pragma unroll
+      for (int m = 0; m < 8; ++m) {
+        const int j = Pd::ridx(H + NL * m);
+        sa += ra[j] * w.a[m].re;
+        sb += rb[j] * w.a[m].re;
+      }
+      s[t.l * RP + H] = {T(2) * sb, T(-2) * sa};
+    }
   }
   __syncthreads();
-  // B1: lane (la, kb) of wave w handles rows k1 = w HR + kb + 4 t
-  const int l6 = L & 63, w = L >> 6;
-  const int la = l6 & 15, kb = l6 >> 4;
-  constexpr int NT = HR / 4;
-  Cplx<float> u[NT][8];
-#pragma unroll
-  for (int t = 0; t < NT; ++t) {
-    const Cplx<float>* r = s + (w * HR + kb + 4 * t) * kCore2Pitch + la;
-#pragma unroll
-    for (int lb = 0; lb < 8; ++lb) u[t][lb] = r[16 * lb];
-  }
-  Cplx<float> wl[8];
-  wl[0] = {1.f, 0.f};
-#pragma unroll
-  for (int c1 = 1; c1 < 8; ++c1) wl[c1] = w128[la * 9 + c1];
-  wave_sync();
-#pragma unroll
-  for (int t = 0; t < NT; ++t) {
-    dft8(u[t]);
-    Cplx<float>* r = s + (w * HR + kb + 4 * t) * kCore2Pitch + la * 9;
-    r[0] = u[t][0];
-#pragma unroll
-    for (int c1 = 1; c1 < 8; ++c1) r[c1] = cmul(u[t][c1], wl[c1]);
-  }
-  wave_sync();
-  // B2: lane (k1, c1) = (w HR + l6 >> 3, l6 & 7) for l6 < 8 HR; DFT_16 over la
-  if ((l6 >> 3) < HR) {
-    const int k1 = w * HR + (l6 >> 3), c1 = l6 & 7;
-    Cplx<float> x[16];
-    const Cplx<float>* r = s + k1 * kCore2Pitch + c1;
-#pragma unroll
-    for (int a = 0; a < 16; ++a) x[a] = r[9 * a];
-    dft_reg<16>(x);
-#pragma unroll
-    for (int q = 0; q < 8; ++q) {
-      const Cplx<float> y = x[dft_pos<16>(q)];
-      const int k = k1 + P * c1 + 8 * P * q;
+  if (!t.row) return;
+  T* ra = buf + t.pair_b * Y::template pitch<T>();
+  T* rb = ra + Pd::rlen(n);
+  Cplx<T>* s = reinterpret_cast<Cplx<T>*>(ra + Y::template soff<T>()) + t.k1 * RP;
+  auto put = [&](int q, const Cplx<T>& X) {
+    bool stored;
+    const int k = sym_out_k(t, q, stored);
+    const int c1 = G > 1 ? t.g + G * (q / G) : q;
+    const int k2 = G > 1 ? c1 + 16 * (q % G) : q;
+    T oa = k2 < H ? T(-0.5) * X.im : T(0.5) * X.im;
+    T ob = k2 < H ? T(0.5) * X.re : T(-0.5) * X.re;
+    epi(q, oa, ob);
+    if (stored) {
       const int j = Pd::ridx(k);
-      float oa = -0.5f * y.im, ob = 0.5f * y.re;
-      epi(q, oa, ob);
-      ra[j] = k ? oa : 0.f;
-      rb[j] = k ? ob : 0.f;
+      ra[j] = k ? oa : T(0);
+      rb[j] = k ? ob : T(0);
+    }
+  };
+  Cplx<T> x[16];
+#pragma unroll
+  for (int lb = 0; lb < 16; ++lb) x[lb] = s[t.g + G * lb];
+  Cplx<T> wb[G > 1 ? 15 : 1];
+  if constexpr (G > 1) {
+#pragma unroll
+    for (int c = 1; c < 16; ++c) wb[c - 1] = tb[17 * t.g + c];
+  }
+  dft_reg<16>(x);
+  if constexpr (G == 1) {
+#pragma unroll
+    for (int q = 0; q < 16; ++q) put(q, x[dft_pos<16>(q)]);
+  } else {
+    wave_sync();
+#pragma unroll
+    for (int c = 0; c < 16; ++c)
+      s[c * Y::GP + t.g] = c ? cmul(x[dft_pos<16>(c)], wb[c > 0 ? c - 1 : 0]) : x[dft_pos<16>(0)];
+    wave_sync();
+#pragma unroll
+    for (int si = 0; si < 16 / G; ++si) {
+      const Cplx<T>* r = s + (t.g + G * si) * Y::GP;
+      Cplx<T> u[G];
+#pragma unroll
+      for (int a = 0; a < G; ++a) u[a] = r[a];
+      if constexpr (G == 2) {
+        const Cplx<T> u0 = u[0];
+        u[0] = cadd(u0, u[1]);
+        u[1] = csub(u0, u[1]);
+      } else if constexpr (G == 4) {
+        dft4(u[0], u[1], u[2], u[3]);
+      } else if constexpr (G == 8) {
+        dft8(u);
+      } else {
+        dft_reg<16>(u);
+      }
+#pragma unroll
+      for (int c2 = 0; c2 < G; ++c2) put(G * si + c2, u[G == 16 ? dft_pos<16>(c2) : c2]);
     }
   }
 }
 
-// Floats per row pair in LDS: the two padded rows, or for the FP32 core the
-// P rows of its transposes (which the one-wave core lays over the rows), or
-// for the two-wave core the rows followed by its transposes.
+// T units per row pair in LDS: the two padded rows, for the wave core the P
+// rows of its transposes (laid over the rows), for the symmetric core the
+// rows followed by its exchange region.
 template <typename T>
-__host__ __device__ inline int pair_pitch(int n) {
-  if (fast_core(sizeof(T), n) && core_lanes(sizeof(T), n) == 128)   // rows, transposes; = 16 (mod 32)
-    return core2_soff(n) + (n / 64) * kCore2Pitch * 2 + 16;
-  if (fast_core(sizeof(T), n)) return (n / 32) * kCorePitch * 2 + 8;   // = 8 (mod 32)
+__host__ __device__ constexpr int pair_pitch(int n) {
+  if (sym_core(sizeof(T), n))
+    return n == 128    ? Sym<7>::pitch<T>()
+           : n == 256  ? Sym<8>::pitch<T>()
+           : n == 512  ? Sym<9>::pitch<T>()
+           : n == 1024 ? Sym<10>::pitch<T>()
+                       : Sym<11>::pitch<T>();
+  if (wave_core(sizeof(T), n)) return (n / 32) * kCorePitch * 2 + 8;   // = 8 (mod 32)
   return Pad<T>::pitch(n);
+}
+
+// Row pairs per workgroup of a row pass (template argument of the symmetric
+// core's pieces; the others take theirs at run time).
+template <typename T, int LOGN>
+__host__ __device__ constexpr int row_pairs() {
+  return sym_core(sizeof(T), 1 << LOGN) ? sym_rows(1 << LOGN) / 2 : 0;
 }
 
 // The LDS row layout of a pass over rows of 2^LOGN values.
 template <typename T, int LOGN>
-using RowLay = std::conditional_t<fast_core(sizeof(T), 1 << LOGN), CoreLay, Pad<T>>;
+using RowLay = std::conditional_t<sym_core(sizeof(T), 1 << LOGN) || wave_core(sizeof(T), 1 << LOGN),
+                                  CoreLay<T>, Pad<T>>;
 
-// Type-I sine transform of nrow rows (nrow even) of length n = 2^logn held
+// What a pass's transforms need besides the rows.  The tables' loads are
+// issued when it is made (stage_tables), in front of the pass's own loads;
+// commit() then writes to LDS what the transform reads there, after those
+// loads, so that no wait for a table delays them.
+//   symmetric core: the lane's stage-A twiddles in registers, stage B's in LDS
+//   wave core:      the lane's W_N^{l k1} in registers, W_64 (72) in LDS
+//   half-length:    twiddles and pre-twiddles in LDS
+template <int N>
+struct WaveTw {
+  Cplx<float> a[N / 32 - 1];   // k1 = 1 .. P - 1
+  Cplx<float> w64;
+};
+template <typename T>
+struct HalfTw {
+  Cplx<T> tw;
+  T pre;
+};
+template <typename T, int LOGN, int NP>   // NP: row pairs per workgroup (symmetric core)
+struct Xform {
+  static constexpr int n = 1 << LOGN;
+  static constexpr bool sym = sym_core(sizeof(T), n), wav = wave_core(sizeof(T), n);
+  unsigned char* lds;
+  std::conditional_t<sym, SymTw<T, (LOGN >= 7 ? LOGN : 7)>,
+                     std::conditional_t<wav, WaveTw<(wav ? n : 64)>, HalfTw<T>>>
+      w;
+  // LDS places of the tables
+  __device__ Cplx<T>* tw() const { return reinterpret_cast<Cplx<T>*>(lds); }
+  __device__ T* pre() const { return reinterpret_cast<T*>(lds + n * sizeof(Cplx<T>)); }
+  __device__ __forceinline__ void commit() const {
+    if constexpr (sym) {
+      // the stage-B table, entry W_2H^{g c} at 17 g + c
+      constexpr int NB = Sym<(sym ? LOGN : 7)>::G > 1 ? 16 * Sym<(sym ? LOGN : 7)>::G : 0;
+      const int tid = static_cast<int>(threadIdx.x);
+      if (tid < NB) tw()[17 * (tid >> 4) + (tid & 15)] = w.b;
+    } else if constexpr (wav) {
+      if (threadIdx.x < 72) tw()[threadIdx.x] = w.w64;
+    } else {
+      if (threadIdx.x < n) {   // n < kBlock
+        tw()[threadIdx.x] = w.tw;
+        pre()[threadIdx.x] = w.pre;
+      }
+    }
+  }
+};
+
+// Type-I sine transform of nrow rows (nrow even) of length n = 2^LOGN held
 // in LDS; pair f = rows (2f, 2f+1) occupies buf[f*ppitch ..) (row 2f first,
 // ppitch = pair_pitch(n)).  Entry 0 of every input row must be 0; on output
-// entry p holds S_p (entry 0 = 0).  FP32 rows of 256-1024 go to the
-// recurrence-free core, one pair per wave; otherwise groups of max(1, 512/n)
-// pairs are handed to the workgroup's waves in turn.  Ends with a workgroup
-// barrier.
-template <typename T, int LOGN>
-__device__ __forceinline__ void block_dst(T* buf, int logn, int nrow, int ppitch,
-                                          const Cplx<T>* __restrict__ tw,
-                                          const T* __restrict__ pre) {
+// entry p holds S_p (entry 0 = 0).  The symmetric core takes 2 NP rows, the
+// wave core one pair per wave; otherwise groups of max(1, 512/n) pairs
+// are handed to the workgroup's waves in turn.  Ends with a workgroup barrier.
+template <typename T, int LOGN, int NP>
+__device__ __forceinline__ void block_dst(T* buf, int nrow, int ppitch, const Xform<T, LOGN, NP>& x) {
   constexpr int n = 1 << LOGN;
-  (void)logn;
   const int npair = nrow >> 1;
   const int wave = threadIdx.x >> 6;
-  if constexpr (fast_core(sizeof(T), n)) {
-    // tw: W_N^{l k1} by [k1][lane]; pre: the W_64 (W_128) table (complex)
-    const Cplx<float>* wt = reinterpret_cast<const Cplx<float>*>(pre);
-    if constexpr (core_lanes(sizeof(T), n) == 128) {
-      // two waves per pair, every thread (the launchers give 4 rows: 2 pairs)
-      const int pr = threadIdx.x >> 7;
-      pair2_dst_core<n / 64>(buf + static_cast<size_t>(pr) * ppitch, threadIdx.x & 127, tw, wt);
-    } else {
-      // one pair per wave (the launchers keep nrow <= 2 * waves): no loop,
-      // whose invariant hoisting would keep the core's per-lane addresses live
-      if (wave < npair) wave_dst_core<n / 32>(buf + static_cast<size_t>(wave) * ppitch, tw, wt);
-    }
+  if constexpr (sym_core(sizeof(T), n)) {
+    sym_dst<T, LOGN, NP>(buf, x.w, x.tw());
+  } else if constexpr (wave_core(sizeof(T), n)) {
+    // One pair per wave (the launchers keep nrow <= 2 * waves): no loop, whose
+    // invariant hoisting would keep the core's per-lane addresses live
+    if (wave < npair) wave_dst_core<n / 32>(buf + static_cast<size_t>(wave) * ppitch, x.w.a, x.tw());
   } else {
     constexpr int per = n >= 512 ? 1 : 512 / n;
     constexpr int E = n <= 512 ? 8 : n / 64;
@@ -686,7 +867,7 @@ __device__ __forceinline__ void block_dst(T* buf, int logn, int nrow, int ppitch
     const int ngroup = (npair + per - 1) / per;
     if (wave < ngroup) {
       const int npg = min(per, npair - wave * per);
-      wave_dst<T, E, LOGN>(buf + static_cast<size_t>(wave) * per * ppitch, npg, ppitch, tw, pre);
+      wave_dst<T, E, LOGN>(buf + static_cast<size_t>(wave) * per * ppitch, npg, ppitch, x.tw(), x.pre());
     }
   }
   __syncthreads();
@@ -710,15 +891,13 @@ void with_logn(int n, F&& f) {
 }
 
 // Bytes of the per-axis tables a transform pass stages in LDS: twiddles and
-// pre-twiddles of the half-length transform; for the one-wave FP32 core the
-// W_64 table (72 complex; its W_N^{l k1} table is read from global memory);
-// for the two-wave core both (2n + 144 complex), so that its transforms
-// issue no global loads (a wait on a load also waits on earlier stores).
+// pre-twiddles of the half-length transform; for the wave core the W_64
+// table (72 complex); the stage-B table for the symmetric core.
 template <typename T>
 __host__ __device__ inline size_t table_bytes(int n) {
-  if (fast_core(sizeof(T), n) && core_lanes(sizeof(T), n) == 128)   // W_N and W_128 tables
-    return static_cast<size_t>(2 * n + 144) * sizeof(Cplx<T>);
-  if (fast_core(sizeof(T), n)) return static_cast<size_t>(core_lanes(sizeof(T), n) / 8 * 9) * sizeof(Cplx<T>);
+  if (sym_core(sizeof(T), n))
+    return static_cast<size_t>(sym_g(n) > 1 ? 17 * sym_g(n) : 0) * sizeof(Cplx<T>);
+  if (wave_core(sizeof(T), n)) return size_t(72) * sizeof(Cplx<T>);
   return static_cast<size_t>(n) * (sizeof(Cplx<T>) + sizeof(T));
 }
 
@@ -733,12 +912,13 @@ inline int pass_waves(const char* env, int dflt) {
   return dflt;
 }
 
-// Eigenvalue bytes the column pass stages after the tables: the strip's W
-// x eigenvalues, and the n y eigenvalues except with the FP32 core (which
-// reads them from global memory so that two workgroups fit a CU at 1024).
+// Eigenvalue bytes the half-length column pass stages after the tables: the
+// strip's W x eigenvalues and the n y eigenvalues (the cores hold theirs in
+// registers).
 template <typename T>
 __host__ __device__ inline size_t lam_bytes(int n, int w) {
-  return static_cast<size_t>((fast_core(sizeof(T), n) ? 0 : n) + w) * sizeof(double);
+  if (sym_core(sizeof(T), n) || wave_core(sizeof(T), n)) return 0;
+  return static_cast<size_t>(n + w) * sizeof(double);
 }
 
 template <typename T>
@@ -747,21 +927,16 @@ inline size_t pass_lds(int rows, int n) {
          lam_bytes<T>(n, rows);
 }
 
-// columns per column-pass workgroup (even, at most nx, within 80 KiB of LDS).
-// One busy wave (one column pair) per workgroup up to 512 rows (FP32) or
-// 256 rows (FP64); beyond, two, whose four-column strips halve the strided
-// row segments each workgroup reads (measured from HIP graphs: 8 % off a
-// 1024^2 time step in FP32, 2 % off the 512^2 box in FP64).
-// The FP32 core at 1024 rows: two pairs of two waves (four-column strips),
-// two workgroups per CU.
+// columns per column-pass workgroup (even, at most nx, within 80 KiB of LDS):
+// sym_rows with the symmetric core; else one busy wave (one column pair, or
+// 512 / ny of them with the half-length transform) per workgroup.
 template <typename T>
 inline int col_strip(int nx, int ny, int nfield) {
   (void)nfield;
-  if (core_lanes(sizeof(T), ny) == 128) return 4;   // two-wave core: two pairs per workgroup
-  const bool core = fast_core(sizeof(T), ny);
-  const int per = ny >= 512 || core ? 1 : 512 / ny;
-  const int waves = core ? (ny >= 1024 ? 4 : 1) : (ny >= (sizeof(T) == 8 ? 512 : 1024) ? 2 : 1);
-  int w = 2 * per * pass_waves("QSP_COL_WAVES", waves);
+  if (sym_core(sizeof(T), ny)) return sym_cols(ny);
+  const bool core = wave_core(sizeof(T), ny);
+  const int per = core ? 1 : 512 / ny;
+  int w = 2 * per * pass_waves("QSP_COL_WAVES", 1);
   if (const char* e = std::getenv("QSP_COL_W")) {   // tuning override
     const int v = std::atoi(e);
     if (v >= 2 && v <= 64 && (v & (v - 1)) == 0) w = v;
@@ -773,119 +948,86 @@ inline int col_strip(int nx, int ny, int nfield) {
   return w;
 }
 
-// Copies an axis' transform tables into LDS right after the workgroup's data
-// region, so the FFT stages never wait on global memory.  Every load of a
-// thread is issued before its first LDS store (one memory latency, not one
-// per loop trip).
-template <typename T, int LOGN>
-__device__ inline void stage_tables(const AxisTables<T>& t, unsigned char* base,
-                                    const Cplx<T>*& tw, const T*& pre) {
+// Issues the loads of an axis' transform tables; the LDS part goes right
+// after the workgroup's data region (Xform::commit).  Lanes without a part
+// (and the wave core's waves beyond the workgroup's npair pairs) load entry 0.
+template <typename T, int LOGN, int NP>
+__device__ __forceinline__ Xform<T, LOGN, NP> stage_tables(const AxisTables<T>& t, unsigned char* base,
+                                                           int npair) {
   constexpr int n = 1 << LOGN;
-  Cplx<T>* stw = reinterpret_cast<Cplx<T>*>(base);
-  if constexpr (fast_core(sizeof(T), n)) {
-    // the W_N^{l k1} table (2n entries by [k1][lane]) stays in global
-    // memory, where each wave reads it coalesced (L1/L2 resident); the 72
-    // (144) entries of W_64 (W_128) go to LDS
-    Cplx<T>* sw = stw;
-    const Cplx<T>* gw = reinterpret_cast<const Cplx<T>*>(t.pre);
-    if constexpr (core_lanes(sizeof(T), n) == 128) {
-      // W_N^{L k1} (2n entries) then W_128 (144) in LDS
-      constexpr int NT = 2 * n / kBlock;
-      Cplx<T> v[NT];
+  Xform<T, LOGN, NP> x;
+  x.lds = base;
+  const int tid = static_cast<int>(threadIdx.x);
+  if constexpr (sym_core(sizeof(T), n)) {
+    x.w = sym_load<T, LOGN, NP>(t.tw);
+  } else if constexpr (wave_core(sizeof(T), n)) {
 #pragma unroll
-      for (int u = 0; u < NT; ++u) v[u] = t.tw[threadIdx.x + u * kBlock];
-      const Cplx<T> wv = threadIdx.x < 144 ? gw[threadIdx.x] : Cplx<T>{T(0), T(0)};
-#pragma unroll
-      for (int u = 0; u < NT; ++u) sw[threadIdx.x + u * kBlock] = v[u];
-      if (threadIdx.x < 144) sw[2 * n + threadIdx.x] = wv;
-      tw = sw;
-      pre = reinterpret_cast<const T*>(sw + 2 * n);
-    } else {
-      if (threadIdx.x < core_lanes(sizeof(T), n) / 8 * 9) sw[threadIdx.x] = gw[threadIdx.x];
-      tw = t.tw;
-      pre = reinterpret_cast<const T*>(sw);
-    }
+    for (int k = 1; k < n / 32; ++k) x.w.a[k - 1] = t.tw[(tid >> 6) < npair ? k * 64 + (tid & 63) : 0];
+    x.w.w64 = reinterpret_cast<const Cplx<T>*>(t.pre)[tid < 72 ? tid : 0];
   } else {
-    T* spre = reinterpret_cast<T*>(base + n * sizeof(Cplx<T>));
-    if constexpr (n % kBlock == 0) {
-      constexpr int NT = n / kBlock;
-      Cplx<T> v[NT];
-      T q[NT];
-#pragma unroll
-      for (int u = 0; u < NT; ++u) {
-        v[u] = t.tw[threadIdx.x + u * kBlock];
-        q[u] = t.pre[threadIdx.x + u * kBlock];
-      }
-#pragma unroll
-      for (int u = 0; u < NT; ++u) {
-        stw[threadIdx.x + u * kBlock] = v[u];
-        spre[threadIdx.x + u * kBlock] = q[u];
-      }
-    } else if (threadIdx.x < n) {   // n < kBlock
-      stw[threadIdx.x] = t.tw[threadIdx.x];
-      spre[threadIdx.x] = t.pre[threadIdx.x];
-    }
-    tw = stw;
-    pre = spre;
+    x.w.tw = t.tw[tid < n ? tid : 0];
+    x.w.pre = t.pre[tid < n ? tid : 0];
   }
-}
-
-// dst[i] = src[i] for i < N, all of a thread's loads before its stores
-template <int N>
-__device__ inline void stage_doubles(double* dst, const double* __restrict__ src) {
-  if constexpr (N % kBlock == 0) {
-    constexpr int NT = N / kBlock;
-    double v[NT];
-#pragma unroll
-    for (int u = 0; u < NT; ++u) v[u] = src[threadIdx.x + u * kBlock];
-#pragma unroll
-    for (int u = 0; u < NT; ++u) dst[threadIdx.x + u * kBlock] = v[u];
-  } else if (threadIdx.x < N) {   // N < kBlock
-    dst[threadIdx.x] = src[threadIdx.x];
-  }
+  return x;
 }
 
 // clears the planes of z, workgroup `bid` of `nblk` taking every nblk-th
 // block of kBlock elements
-__device__ inline void zero_job(const ZeroJob& z, size_t bid, size_t nblk) {
+__device__ __forceinline__ void zero_job(const ZeroJob& z, size_t bid, size_t nblk) {
   if (z.count == 0) return;
-  const size_t stride = nblk * blockDim.x;
-  const size_t start = bid * blockDim.x + threadIdx.x;
-  for (int c = 0; c < z.count; ++c)
-    for (size_t i = start; i < z.n; i += stride) z.p[c][i] = 0.0;
+  const unsigned int n = static_cast<unsigned int>(z.n);
+  const unsigned int stride = static_cast<unsigned int>(nblk) * kBlock;
+  for (unsigned int i = static_cast<unsigned int>(bid) * kBlock + threadIdx.x; i < n; i += stride) {
+#pragma unroll
+    for (int c = 0; c < 8; ++c)   // plane pointers by constant index: kernel arguments
+      if (c < z.count) store_at(z.p[c], i, 0.0);
+  }
+}
+
+// The guess is loaded in front of the pass's transform (up to kGuess elements
+// a thread; with them behind it, its round trip came on top) and stored
+// after it.
+constexpr int kGuess = 6;
+template <typename T>
+struct GuessRegs {
+  T x[kGuess], y[kGuess];
+};
+
+template <typename T>
+__device__ __forceinline__ void guess_load(const GuessJob<T>& q, size_t n, size_t i0, size_t stride,
+                                           GuessRegs<T>& g) {
+  T x1[kGuess], x2[kGuess], y1[kGuess], y2[kGuess];
+#pragma unroll
+  for (int u = 0; u < kGuess; ++u) {
+    const size_t i = i0 + u * stride;
+    const size_t c = i < n ? i : 0;   // clamped: every load in bounds
+    x1[u] = load_at(q.bx1, static_cast<unsigned int>(c));
+    x2[u] = load_at(q.bx2, static_cast<unsigned int>(c));
+    y1[u] = load_at(q.by1, static_cast<unsigned int>(c));
+    y2[u] = load_at(q.by2, static_cast<unsigned int>(c));
+  }
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int u = 0; u < kGuess; ++u) {
+    g.x[u] = T(2) * x1[u] - x2[u];
+    g.y[u] = T(2) * y1[u] - y2[u];
+    pin(g.x[u]);
+    pin(g.y[u]);
+  }
 }
 
 template <typename T>
-__device__ inline void guess_job(const GuessJob<T>& q, size_t n) {
-  if (!q.ctr) return;
-  const size_t stride = static_cast<size_t>(gridDim.x) * gridDim.y * blockDim.x;
-  const size_t bid = static_cast<size_t>(blockIdx.y) * gridDim.x + blockIdx.x;
-  if (bid == 0 && threadIdx.x == 0) {
-    q.ctr->pc_done = 0u;
-    q.ctr->pc_iters = 0u;
-    q.ctr->pc_resid = 0.0;
-  }
-  // rounds of 8 elements per thread with all their loads issued first
-  constexpr int U = 8;
-  for (size_t i0 = bid * blockDim.x + threadIdx.x; i0 < n; i0 += U * stride) {
-    T vx[U], vy[U];
+__device__ __forceinline__ void guess_store(const GuessJob<T>& q, size_t n, size_t i0, size_t stride,
+                                            const GuessRegs<T>& g) {
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const size_t i = i0 + u * stride;
-      const size_t c = i < n ? i : 0;   // clamped: every load in bounds
-      vx[u] = T(2) * q.bx1[c] - q.bx2[c];
-      vy[u] = T(2) * q.by1[c] - q.by2[c];
-    }
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const size_t i = i0 + u * stride;
-      if (i < n) {
-        q.bx[i] = vx[u];
-        q.by[i] = vy[u];
-        if (q.tape_bx) {
-          q.tape_bx[i] = vx[u];
-          q.tape_by[i] = vy[u];
-        }
+  for (int u = 0; u < kGuess; ++u) {
+    const size_t i = i0 + u * stride;
+    if (i < n) {
+      q.bx[i] = g.x[u];
+      q.by[i] = g.y[u];
+      if (q.tape_bx) {
+        q.tape_bx[i] = g.x[u];
+        q.tape_by[i] = g.y[u];
       }
     }
   }
@@ -901,25 +1043,15 @@ __device__ inline int xcd_strip(int b, int nstrip) {
   return (b & 7) * per + (b >> 3);
 }
 
-// Workgroups per CU the transform kernels are compiled for: four (<= 128
-// VGPRs) while a lane holds at most 8 FP32 complex points, fewer for the
-// long FP64 transforms whose register arrays would otherwise spill.
-// The FP32 core holds P = 2n/64 complex points per lane (one pair per wave,
-// up to ~140 VGPRs at 1024 points): two workgroups per CU at 1024, four
-// below.
-constexpr int dst_blocks_per_cu(int logn, int tsize) {
-  if (fast_core(tsize, 1 << logn)) return logn >= 10 ? 2 : 4;
-  const int u = (logn <= 9 ? 8 : (1 << logn) / 64) * tsize / 4;
-  return u <= 8 ? 4 : (u <= 16 ? 2 : 1);
-}
+// Workgroups per CU the transform kernels are compiled for: two (<= 256
+// VGPRs) with the symmetric core, whose lanes keep 16 complex points and
+// their twiddles; four (<= 128 VGPRs) else, except the wave core's column
+// pass, which keeps its eigenvalue divisors and a strip load in flight
+// beside the core's registers.
+constexpr int dst_blocks_per_cu(int logn, int tsize) { return sym_core(tsize, 1 << logn) ? 2 : 4; }
 
-// The column pass with the FP32 core keeps its eigenvalue divisors and a
-// strip load in flight beside the core's registers: two workgroups per CU
-// (its grids hold at most two per CU at 512 and 1024 rows).
 constexpr int col_blocks_per_cu(int logn, int tsize) {
-  if (fast_core(tsize, 1 << logn)) return 2;
-  const int u = (logn <= 9 ? 8 : (1 << logn) / 64) * tsize / 4;
-  return u <= 8 ? 4 : (u <= 16 ? 2 : 1);
+  return sym_core(tsize, 1 << logn) || wave_core(tsize, 1 << logn) ? 2 : 4;
 }
 
 // Calls f(e) for the workgroup's elements e = threadIdx.x + it*kBlock,
@@ -973,65 +1105,159 @@ __device__ __forceinline__ void for_row_elems(int R, F&& f) {
     for_elems<CH>(R << LOGN, f);
 }
 
-// Element e of a block of 4 rows in the strip order (Geom::strip): e = 16 s
-// + 4 r + c is row r, column 4 s + c, stored at offset (s ny + j0 + r) 4 + c
-// of the plane, so 16 consecutive elements are one 64-byte block.
-__device__ __forceinline__ void strip_elem(int e, int& r, int& i) {
-  const int w = e & 15;
-  r = w >> 2;
-  i = ((e >> 4) << 2) | (w & 3);
+// The elements of a block of rows in batches of up to U: load(e, v) for every
+// element of a batch, then V::pin, then use(u, e, v) (u = e / kBlock).  Every
+// load of a batch is in flight before the first use.
+template <int B, typename V, typename L, typename S>
+__device__ __forceinline__ void elem_batch(int it, L& load, S& use) {
+  V v[B];
+#pragma unroll
+  for (int u = 0; u < B; ++u) load(static_cast<int>(threadIdx.x) + (it + u) * kBlock, v[u]);
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int u = 0; u < B; ++u) v[u].pin();
+#pragma unroll
+  for (int u = 0; u < B; ++u) use(it + u, static_cast<int>(threadIdx.x) + (it + u) * kBlock, v[u]);
 }
-__device__ __forceinline__ size_t strip_off(int e, int j0, int ny) {
-  return static_cast<size_t>(e >> 4) * (static_cast<size_t>(ny) << 2) + (static_cast<size_t>(j0) << 2) +
-         (e & 15);
+template <int RC, int LOGN, int U, typename V, typename L, typename S>
+__device__ __forceinline__ void for_row_batches(int R, L&& load, S&& use) {
+  if constexpr (RC > 0) {
+    constexpr int NIT = (RC << LOGN) / kBlock;
+    constexpr int B = NIT < U ? NIT : U;
+    static_assert(NIT >= 1 && NIT % B == 0, "whole batches");
+#pragma unroll
+    for (int it = 0; it < NIT; it += B) elem_batch<B, V>(it, load, use);
+  } else {
+    const int total = R << LOGN;
+    const int nit = total / kBlock;   // uniform across the workgroup
+    int it = 0;
+    for (; it + U <= nit; it += U) elem_batch<U, V>(it, load, use);
+    for (; it < nit; ++it) elem_batch<1, V>(it, load, use);
+    const int e = nit * kBlock + static_cast<int>(threadIdx.x);
+    if (e < total) {
+      V v;
+      load(e, v);
+      use(nit, e, v);
+    }
+  }
+}
+
+// Elements per batch of a source assembly with five to seven loads each:
+// what the register budget of the pass holds in flight.
+template <typename T, int LOGN>
+constexpr int src_batch() {
+  return sizeof(T) == 4 && sym_core(4, 1 << LOGN) && (1 << LOGN) >= 256 ? 8 : 4;
+}
+
+// Element e of a block of R = 2^lr rows in the strip order (Geom::strip): e =
+// 4 R s + 4 r + c is row r, column 4 s + c, stored at offset (s ny + j0 + r) 4
+// + c of the plane, so 4 R consecutive elements are one block in memory.
+__device__ __forceinline__ void strip_elem(int e, int lr, int& r, int& i) {
+  const int w = e & ((4 << lr) - 1);
+  r = w >> 2;
+  i = ((e >> (lr + 2)) << 2) | (w & 3);
+}
+__device__ __forceinline__ unsigned int strip_off(int e, int lr, int j0, int ny) {
+  return static_cast<unsigned int>(e >> (lr + 2)) * (static_cast<unsigned int>(ny) << 2) +
+         (static_cast<unsigned int>(j0) << 2) + (e & ((4 << lr) - 1));
+}
+__host__ __device__ constexpr int log2_rows(int R) {
+  int l = 0;
+  while ((1 << l) < R) ++l;
+  return l;
 }
 
 // The R rows j0.. of a row block between LDS and an intermediate plane of a
-// solve: row-major, or in the strip order (Geom::strip, R = 4).
+// solve: row-major, or in the strip order (Geom::strip).
 template <typename T, int RC, int LOGN, int CH = 8>
 __device__ __forceinline__ void rows_to_plane(const Geom& g, int R, int j0, const T* buf, int ppitch,
                                               T* __restrict__ out) {
   constexpr int n = 1 << LOGN;
   if (g.strip) {
+    const int lr = log2_rows(RC > 0 ? RC : R);
     for_row_elems<RC, LOGN, CH>(R, [&](int e) {
       int r, i;
-      strip_elem(e, r, i);
-      out[strip_off(e, j0, g.ny)] = buf[RowLay<T, LOGN>::rpos(n, ppitch, r, i)];
+      strip_elem(e, lr, r, i);
+      store_at(out, strip_off(e, lr, j0, g.ny), buf[RowLay<T, LOGN>::rpos(n, ppitch, r, i)]);
     });
   } else {
     for_row_elems<RC, LOGN, CH>(R, [&](int e) {
       const int r = e >> LOGN, i = e & (n - 1);
-      out[(j0 + r) * n + i] = buf[RowLay<T, LOGN>::rpos(n, ppitch, r, i)];
+      store_at(out, (j0 + r) * n + i, buf[RowLay<T, LOGN>::rpos(n, ppitch, r, i)]);
     });
   }
 }
+// The compile-time form in two halves: all loads, then (after whatever other
+// loads the pass has) the LDS stores.
+template <typename T, int RC, int LOGN>
+struct RowFetch {
+  static constexpr int N = (RC << LOGN) / kBlock;
+  T v[N];
+  // (one branch on the plane order around all of them: a select per address
+  // becomes a branch per load)
+  __device__ __forceinline__ void load(const Geom& g, int j0, const T* __restrict__ in) {
+    const unsigned int t = threadIdx.x;
+    if (g.strip) {
+#pragma unroll
+      for (int u = 0; u < N; ++u)
+        v[u] = load_at(in, strip_off(t + u * kBlock, log2_rows(RC), j0, g.ny));
+    } else {
+#pragma unroll
+      for (int u = 0; u < N; ++u) v[u] = load_at(in, (static_cast<unsigned int>(j0) << LOGN) + t + u * kBlock);
+    }
+  }
+  __device__ __forceinline__ void put(const Geom& g, T* buf, int ppitch) {
+    constexpr int n = 1 << LOGN;
+    const int t = static_cast<int>(threadIdx.x);
+#pragma unroll
+    for (int u = 0; u < N; ++u) pin(v[u]);
+    if (g.strip) {
+#pragma unroll
+      for (int u = 0; u < N; ++u) {
+        int r, i;
+        strip_elem(t + u * kBlock, log2_rows(RC), r, i);
+        buf[RowLay<T, LOGN>::rpos(n, ppitch, r, i)] = v[u];
+      }
+    } else {
+#pragma unroll
+      for (int u = 0; u < N; ++u) {
+        const int e = t + u * kBlock;
+        buf[RowLay<T, LOGN>::rpos(n, ppitch, e >> LOGN, e & (n - 1))] = v[u];
+      }
+    }
+  }
+};
+
 template <typename T, int RC, int LOGN, int CH = 32>
 __device__ __forceinline__ void plane_to_rows(const Geom& g, int R, int j0, const T* __restrict__ in,
                                               T* buf, int ppitch) {
   constexpr int n = 1 << LOGN;
   if (g.strip) {
+    const int lr = log2_rows(RC > 0 ? RC : R);
     for_row_elems<RC, LOGN, CH>(R, [&](int e) {
       int r, i;
-      strip_elem(e, r, i);
-      buf[RowLay<T, LOGN>::rpos(n, ppitch, r, i)] = in[strip_off(e, j0, g.ny)];
+      strip_elem(e, lr, r, i);
+      buf[RowLay<T, LOGN>::rpos(n, ppitch, r, i)] = load_at(in, strip_off(e, lr, j0, g.ny));
     });
   } else {
     for_row_elems<RC, LOGN, CH>(R, [&](int e) {
       const int r = e >> LOGN, i = e & (n - 1);
-      buf[RowLay<T, LOGN>::rpos(n, ppitch, r, i)] = in[(j0 + r) * n + i];
+      buf[RowLay<T, LOGN>::rpos(n, ppitch, r, i)] = load_at(in, (j0 + r) * n + i);
     });
   }
 }
 
-// Runs f(std::integral_constant<int, RC>) with RC = R (2, 4 or 8; 4 for
-// the two-wave core) for row passes of the FP32 core, RC = 0 (rows at run
-// time) otherwise.
+// Runs f(std::integral_constant<int, RC>) with RC = R (2, 4 or 8 with the
+// wave core, sym_rows with the symmetric core) for row passes of the cores,
+// RC = 0 (rows at run time) otherwise.
 template <typename T, int LOGN, typename F>
 void with_rows(int R, F&& f) {
-  if constexpr (core_lanes(sizeof(T), 1 << LOGN) == 128) {   // the two-wave core: 4 rows only
-    if (R != 4) throw std::invalid_argument("row pass: the two-wave core takes 4 rows");
-    f(std::integral_constant<int, 4>{});
-  } else if constexpr (fast_core(sizeof(T), 1 << LOGN)) {
+  constexpr int n = 1 << LOGN;
+  if constexpr (sym_core(sizeof(T), n)) {
+    constexpr int RC = sym_rows(n);
+    if (R != RC) throw std::invalid_argument("row pass: wrong rows for the symmetric core");
+    f(std::integral_constant<int, RC>{});
+  } else if constexpr (wave_core(sizeof(T), n)) {
     switch (R) {
       case 2: f(std::integral_constant<int, 2>{}); break;
       case 4: f(std::integral_constant<int, 4>{}); break;
@@ -1041,6 +1267,86 @@ void with_rows(int R, F&& f) {
   } else {
     f(std::integral_constant<int, 0>{});
   }
+}
+
+// Source assembly (FP64) of the R rows j0.. of the Bx/By predictor-corrector:
+//   FX:      -d_y Jz + (Jy_{k-1} - Jy_{k+1}) / (2 dzeta) - shift * Bx_old
+//   else:     d_x Jz - (Jx_{k-1} - Jx_{k+1}) / (2 dzeta) - shift * By_old
+template <typename T, int LOGN, int RC, bool FX>
+__device__ __forceinline__ void src_bxby_rows(const Geom& g, const SrcBxBy<T>& a, int R, int j0,
+                                              T* buf, int ppitch) {
+  constexpr int n = 1 << LOGN;
+  const double ih = FX ? -0.5 / g.hy : 0.5 / g.hx;
+  const double idz = FX ? 0.5 / a.dzeta : -0.5 / a.dzeta;
+  const double amp = a.beam_amp;
+  const double* __restrict__ jz = a.jz;
+  const double* __restrict__ prev = FX ? a.jy_prev : a.jx_prev;
+  const double* __restrict__ next = FX ? a.jy_next : a.jx_next;
+  const double* __restrict__ shrd = FX ? a.sy_next : a.sx_next;
+  const T* __restrict__ bold = FX ? a.bx : a.by;
+  // Gaussian profile factors: along x those of the thread's columns i = t +
+  // 256 c, along y those of the block's rows where a row is whole workgroups
+  // wide (uniform), else per element
+  constexpr int NC = n > kBlock ? n / kBlock : 1;
+  constexpr bool rows_uniform = RC > 0 && n >= kBlock;
+  double gx0[NC], gx1[NC];
+#pragma unroll
+  for (int c = 0; c < NC; ++c) {
+    const int i = (static_cast<int>(threadIdx.x) + c * kBlock) & (n - 1);
+    gx0[c] = load_at(a.bgx, FX ? i : (i > 0 ? i - 1 : 0));
+    gx1[c] = FX ? gx0[c] : load_at(a.bgx, i + 1);
+  }
+  double gy[rows_uniform ? RC + 2 : 1];
+  if constexpr (rows_uniform) {
+#pragma unroll
+    for (int q = 0; q < RC + 2; ++q) gy[q] = a.bgy[j0 + q > 0 ? j0 + q - 1 : 0];
+  }
+  struct In {
+    double z0, z1, p, t, s, g0, g1;
+    T b;
+    __device__ void pin() {
+      dst_detail::pin(z0);
+      dst_detail::pin(z1);
+      dst_detail::pin(p);
+      dst_detail::pin(t);
+      dst_detail::pin(s);
+      dst_detail::pin(b);
+      if constexpr (!rows_uniform) {
+        dst_detail::pin(g0);
+        dst_detail::pin(g1);
+      }
+    }
+  };
+  for_row_batches<RC, LOGN, src_batch<T, LOGN>(), In>(
+      R,
+      [&](int e, In& v) {
+        const int i = e & (n - 1), j = j0 + (e >> LOGN);
+        const int o = j * n + i;
+        // neighbours with clamped indices, replaced by selects below
+        v.z0 = load_at(jz, FX ? (j > 0 ? o - n : o) : (i > 0 ? o - 1 : o));
+        v.z1 = load_at(jz, FX ? (j + 1 < g.ny ? o + n : o) : (i + 1 < n ? o + 1 : o));
+        v.p = load_at(prev, o);
+        v.t = load_at(next, o);
+        v.s = load_at(shrd, o);
+        v.b = load_at(bold, o);
+        if constexpr (!rows_uniform) {
+          v.g0 = load_at(a.bgy, FX ? (j > 0 ? j - 1 : 0) : j);
+          v.g1 = load_at(a.bgy, FX ? j + 1 : j);
+        }
+      },
+      [&](int u, int e, const In& v) {
+        const int r = e >> LOGN, i = e & (n - 1), j = j0 + r;
+        const int c = u % NC;
+        double g0 = v.g0, g1 = v.g1;
+        if constexpr (rows_uniform) {
+          g0 = gy[FX ? u / NC : u / NC + 1];
+          g1 = gy[FX ? u / NC + 2 : u / NC + 1];
+        }
+        const double q0 = v.z0 - amp * gx0[c] * g0;
+        const double q1 = (FX ? j + 1 < g.ny : i + 1 < n) ? v.z1 - amp * gx1[c] * g1 : 0.0;
+        const double q = (q1 - q0) * ih + (v.p - (v.t + v.s)) * idz - a.shift * static_cast<double>(v.b);
+        buf[RowLay<T, LOGN>::rpos(n, ppitch, r, i)] = static_cast<T>((i > 0 && j > 0) ? q : 0.0);
+      });
 }
 
 // Source assembly (FP64) + forward DST along x of row block bxi of field
@@ -1054,43 +1360,15 @@ __device__ __forceinline__ void src_bxby_block(const Geom& g, const SrcBxBy<T>& 
   constexpr int n = 1 << LOGN;   // = nx
   const int R = RC > 0 ? RC : g.rr;
   const int ppitch = pair_pitch<T>(n);
-  const Cplx<T>* tw;
-  const T* pre;
-  stage_tables<T, LOGN>(tx, smem_raw + static_cast<size_t>(R / 2) * ppitch * sizeof(T), tw, pre);
+  const auto xf = stage_tables<T, LOGN, row_pairs<T, LOGN>()>(tx, smem_raw + static_cast<size_t>(R / 2) * ppitch * sizeof(T), R / 2);
   const int j0 = bxi * R;
-  const double ihx = 0.5 / g.hx, ihy = 0.5 / g.hy;
-  const double idz = 0.5 / a.dzeta;
-  const double amp = a.beam_amp;
-  for_row_elems<RC, LOGN>(R, [&](int e) {
-    const int r = e >> LOGN, i = e & (n - 1);
-    const int j = j0 + r;
-    const int o = j * n + i;
-    double s;
-    if (fld == 0) {
-      // -d_y Jz + (Jy_{k-1} - Jy_{k+1}) / (2 dzeta) - shift * Bx_old
-      const int js = j > 0 ? j - 1 : 0;
-      const double zs = a.jz[js * n + i], zn = a.jz[(j + 1 < g.ny ? j + 1 : j) * n + i];
-      const double yp = a.jy_prev[o], yt = a.jy_next[o] + a.sy_next[o];
-      const double bo = static_cast<double>(a.bx[o]);
-      const double gx = a.bgx[i], gs = a.bgy[js], gn = a.bgy[j + 1];
-      const double jz_s = zs - amp * gx * gs;
-      const double jz_n = j + 1 < g.ny ? zn - amp * gx * gn : 0.0;
-      s = -(jz_n - jz_s) * ihy + (yp - yt) * idz - a.shift * bo;
-    } else {
-      // d_x Jz - (Jx_{k-1} - Jx_{k+1}) / (2 dzeta) - shift * By_old
-      const int iw = i > 0 ? i - 1 : 0;
-      const double zw = a.jz[j * n + iw], ze = a.jz[j * n + (i + 1 < n ? i + 1 : i)];
-      const double xp = a.jx_prev[o], xt = a.jx_next[o] + a.sx_next[o];
-      const double bo = static_cast<double>(a.by[o]);
-      const double gy = a.bgy[j], gw = a.bgx[iw], ge = a.bgx[i + 1];
-      const double jz_w = zw - amp * gw * gy;
-      const double jz_e = i + 1 < n ? ze - amp * ge * gy : 0.0;
-      s = (jz_e - jz_w) * ihx - (xp - xt) * idz - a.shift * bo;
-    }
-    buf[RowLay<T, LOGN>::rpos(n, ppitch, r, i)] = static_cast<T>((i > 0 && j > 0) ? s : 0.0);
-  });
+  if (fld == 0)
+    src_bxby_rows<T, LOGN, RC, true>(g, a, R, j0, buf, ppitch);
+  else
+    src_bxby_rows<T, LOGN, RC, false>(g, a, R, j0, buf, ppitch);
+  xf.commit();
   __syncthreads();
-  block_dst<T, LOGN>(buf, g.lx, R, ppitch, tw, pre);
+  block_dst<T, LOGN>(buf, R, ppitch, xf);
   rows_to_plane<T, RC, LOGN>(g, R, j0, buf, ppitch, a.out + static_cast<size_t>(fld) * g.nx * g.ny);
 }
 
@@ -1105,145 +1383,182 @@ __device__ __forceinline__ void for_iters(F&& f) {
   }
 }
 
-// Column pass with the FP32 core (n = ny = 256..1024, W = 2, 4 or 8
-// columns; at 1024 the two-wave core on 4 columns): strip load, forward
-// core whose output stage divides by the eigenvalues, inverse core, store.  Thread t handles column c = t mod W and
-// rows j = t / W + it (256 / W); the row step is a multiple of 32, so the
-// padded LDS index ridx(j) = j + 4 (j / 32) is affine in it as well.
-template <int LOGN, int W>
-__device__ __forceinline__ void col_block_core(const Geom& g, const ColArgs<float>& a,
-                                               const AxisTables<float>& ty,
+// Column pass with one of the FFT cores (W = 2, 4 or 8 columns): strip load,
+// forward core whose output stage divides by the eigenvalues, inverse core,
+// store.  Strip-ordered planes (W = 4): the strip is one contiguous block, 4
+// consecutive values per row and thread.  Row-major planes: thread t handles
+// column c = t mod W and rows j = t / W + it (256 / W); the row step is a
+// multiple of the LDS layout's run, so the padded index of a thread's rows is
+// affine in it.
+template <typename T, int LOGN, int W>
+__device__ __forceinline__ void col_block_core(const Geom& g, const ColArgs<T>& a,
+                                               const AxisTables<T>& ty,
                                                const double* __restrict__ lamx, int strip, int fld,
                                                unsigned char* smem_raw) {
-  using Pd = CoreLay;
+  using Pd = CoreLay<T>;
   constexpr int n = 1 << LOGN;
-  constexpr bool two = core_lanes(4, n) == 128;   // two waves per pair (W = 4)
-  constexpr int P = n / 32, NB = P / 8;
-  constexpr int NK = two ? 8 : 4 * NB;            // output slots per lane
+  constexpr bool sym = sym_core(sizeof(T), n);
+  constexpr int NK = sym ? 16 : n / 64;       // output slots per lane
   constexpr int LW = W == 2 ? 1 : (W == 4 ? 2 : 3);
   constexpr int JS = kBlock / W;              // row step of a thread
-  constexpr int NIT = n / JS;                 // rows per thread
+  constexpr int NIT = n >= JS ? n / JS : 1;   // rows per thread
   constexpr int LS = Pd::ridx(JS);            // LDS step of ridx
-  static_assert(JS % 32 == 0, "row step must keep the LDS padding affine");
-  static_assert(!two || W == 4, "the two-wave core takes four-column strips");
-  __syncthreads();   // the workgroup's previous use of LDS is complete
-  float* buf = reinterpret_cast<float*>(smem_raw);
+  constexpr int rl = Pd::rlen(n);
+  static_assert(JS % (1 << Pd::S) == 0, "row step must keep the LDS padding affine");
+  T* buf = reinterpret_cast<T*>(smem_raw);
   const int nx = g.nx;
-  const int ppitch = pair_pitch<float>(n);
+  constexpr int ppitch = pair_pitch<T>(n);
   const int p0 = strip * W;
   const int tid = static_cast<int>(threadIdx.x);
-  const int pr = two ? tid >> 7 : tid >> 6;     // the thread's pair
-  const int l = two ? tid & 127 : tid & 63;     // its lane in the pair
-  const bool busy = two || pr < W / 2;
-  const Cplx<float>* tw;   // W_N^{l k1}: LDS for the two-wave core, else global
-  const float* wpre;
-  stage_tables<float, LOGN>(ty, smem_raw + static_cast<size_t>(W / 2) * ppitch * sizeof(float), tw, wpre);
-  const Cplx<float>* wt = reinterpret_cast<const Cplx<float>*>(wpre);
-  // the y eigenvalues of the lane's core outputs, fetched under the strip load
+  const Xform<T, LOGN, W / 2> xf =
+      stage_tables<T, LOGN, W / 2>(ty, smem_raw + static_cast<size_t>(W / 2) * ppitch * sizeof(T), W / 2);
+  // the y eigenvalues of the lane's core outputs, fetched under the strip
+  // load: by the lane itself (wave core), or through the exchange region of
+  // the first pair (symmetric core: 16 scattered values a lane)
   double ly[NK];
   double lxa = 0.0, lxb = 0.0;
-  if (busy) {
+  bool busy;
+  int pr;                                     // pair whose outputs the lane scales
+  constexpr int NLAM = n >= kBlock ? n / kBlock : 1;
+  double lam_v[NLAM];
+  double* lam_s = nullptr;
+  if constexpr (sym) {
+    const SymLane<LOGN, W / 2> t;
+    pr = t.pair_b;
+    busy = t.row;
+    lam_s = reinterpret_cast<double*>(buf + Sym<LOGN>::template soff<T>());
+    static_assert(sizeof(double) * n <= sizeof(Cplx<T>) * 9 * Sym<LOGN>::RP, "eigenvalues fit the exchange region");
 #pragma unroll
-    for (int q = 0; q < NK; ++q) ly[q] = ty.lam[two ? core2_out_k<n / 64>(l, q) : core_out_k<P>(l, q)];
-    lxa = lamx[p0 + 2 * pr];
-    lxb = lamx[p0 + 2 * pr + 1];
+    for (int u = 0; u < NLAM; ++u) lam_v[u] = ty.lam[n >= kBlock ? tid + u * kBlock : tid & (n - 1)];
+  } else {
+    pr = tid >> 6;
+    busy = pr < W / 2;
+    if (busy) {
+#pragma unroll
+      for (int q = 0; q < NK; ++q) ly[q] = ty.lam[core_out_k<n / 32>(tid & 63, q)];
+    }
   }
+  lxa = lamx[p0 + (busy ? 2 * pr : 0)];
+  lxb = lamx[p0 + (busy ? 2 * pr + 1 : 1)];
   const size_t plane = static_cast<size_t>(nx) * n;
   const int c = tid & (W - 1), j0 = tid >> LW;
-  const int lcol = (c >> 1) * ppitch + (c & 1) * Pd::rlen(n) + Pd::ridx(j0);
-  // strip-ordered planes (Geom::strip): the strip is one contiguous block of
-  // n rows x 4 columns, read and written as one float4 per row
-  const bool cont = two && g.strip != 0;
-  constexpr int NQ = n / kBlock;
-  const int rl = Pd::rlen(n);
+  const int lcol = (c >> 1) * ppitch + (c & 1) * rl + Pd::ridx(j0);
+  const bool cont = W == 4 && g.strip != 0;
+  constexpr int NQ = n >= kBlock ? n / kBlock : 1;
+  struct alignas(16) Vec {
+    T v[4];
+  };
   if (cont) {
-    const float4* src = reinterpret_cast<const float4*>(a.in + fld * plane + static_cast<size_t>(strip) * 4 * n);
-    float4 v[NQ];
+    const Vec* src = reinterpret_cast<const Vec*>(a.in + fld * plane + static_cast<size_t>(strip) * 4 * n);
+    Vec v[NQ];
 #pragma unroll
-    for (int u = 0; u < NQ; ++u) v[u] = src[tid + u * kBlock];
+    for (int u = 0; u < NQ; ++u)
+      if (n >= kBlock || tid < n) v[u] = src[tid + u * kBlock];
 #pragma unroll
-    for (int u = 0; u < NQ; ++u) {
-      float* d = buf + Pd::ridx(tid) + Pd::ridx(u * kBlock);
-      d[0] = v[u].x;
-      d[rl] = v[u].y;
-      d[ppitch] = v[u].z;
-      d[ppitch + rl] = v[u].w;
-    }
-  } else {
-    const float* in = a.in + fld * plane + p0 + c + static_cast<size_t>(j0) * nx;
-    float* d = buf + lcol;
+    for (int u = 0; u < NQ; ++u)
+      if (n >= kBlock || tid < n) {
+        T* d = buf + Pd::ridx(tid) + Pd::ridx(u * kBlock);
+        d[0] = v[u].v[0];
+        d[rl] = v[u].v[1];
+        d[ppitch] = v[u].v[2];
+        d[ppitch + rl] = v[u].v[3];
+      }
+  } else if (n >= JS || j0 < n) {
+    const T* in = a.in + fld * plane + p0 + c + static_cast<size_t>(j0) * nx;
+    T* d = buf + lcol;
     for_iters<NIT>([&](int it) { d[it * LS] = in[static_cast<size_t>(it) * JS * nx]; });
   }
+  xf.commit();
+  if constexpr (sym) {
+#pragma unroll
+    for (int u = 0; u < NLAM; ++u)
+      if (n >= kBlock || tid < n) lam_s[tid + u * kBlock] = lam_v[u];
+  }
   __syncthreads();
-  if (busy) {
+  {
+    if constexpr (sym) {
+      const SymLane<LOGN, W / 2> t;
+      if (busy) {
+#pragma unroll
+        for (int q = 0; q < NK; ++q) {
+          bool stored;
+          const int k = sym_out_k(t, q, stored);
+          ly[q] = lam_s[stored ? k : 1];      // an unstored slot divides by something finite
+        }
+      }
+    }
     const double shift = a.shift[fld];
     const double inorm = 0.25 * static_cast<double>(nx) * n;
-    EigenScale<NK> sc;
+    EigenScale<T, NK> sc;
+    if (busy) {
 #pragma unroll
-    for (int q = 0; q < NK; ++q) sc.ry[q] = static_cast<float>((ly[q] - shift) * inorm);
-    sc.xa = static_cast<float>(lxa * inorm);
-    sc.xb = static_cast<float>(lxb * inorm);
-    sc.za = p0 + 2 * pr == 0;
-    float* g2 = buf + static_cast<size_t>(pr) * ppitch;
-    if constexpr (two) {
+      for (int q = 0; q < NK; ++q) sc.ry[q] = static_cast<T>((ly[q] - shift) * inorm);
+      sc.xa = static_cast<T>(lxa * inorm);
+      sc.xb = static_cast<T>(lxb * inorm);
+      sc.za = p0 + 2 * pr == 0;
+    }
+    if constexpr (sym) {
       // the side job's stores drain under the transforms (which issue no
       // global loads here: a wait on a load also waits on earlier stores)
       zero_job(a.zero, static_cast<size_t>(blockIdx.y) * gridDim.x + blockIdx.x,
                static_cast<size_t>(gridDim.x) * gridDim.y);
-      pair2_dst_core<n / 64>(g2, l, tw, wt, sc);
-      __syncthreads();   // both waves' outputs are the next transform's input
-      pair2_dst_core<n / 64>(g2, l, tw, wt);
-    } else {
-      wave_dst_core<P>(g2, tw, wt, sc);
-      wave_dst_core<P>(g2, tw, wt);
+      __syncthreads();   // the eigenvalues have left the exchange region
+      sym_dst<T, LOGN, W / 2>(buf, xf.w, xf.tw(), sc);
+      __syncthreads();   // the rows are the next transform's input
+      sym_dst<T, LOGN, W / 2>(buf, xf.w, xf.tw());
+    } else if (busy) {
+      float* g2 = buf + static_cast<size_t>(pr) * ppitch;
+      wave_dst_core<n / 32>(g2, xf.w.a, xf.tw(), sc);
+      wave_dst_core<n / 32>(g2, xf.w.a, xf.tw());
     }
   }
   __syncthreads();
+  const T mihy = static_cast<T>(-0.5 / g.hy);
+  const bool with_dy = fld == 0 && a.out_dy;
   if (cont) {
-    const size_t sb = fld * plane + static_cast<size_t>(strip) * 4 * n;
-    float4* dst = reinterpret_cast<float4*>(a.out + sb);
-    float4* dy = fld == 0 && a.out_dy ? reinterpret_cast<float4*>(a.out_dy + static_cast<size_t>(strip) * 4 * n)
-                                      : nullptr;
-    const float mihy = static_cast<float>(-0.5 / g.hy);
+    const size_t sb = static_cast<size_t>(strip) * 4 * n;
+    Vec* dst = reinterpret_cast<Vec*>(a.out + fld * plane + sb);
+    Vec* dy = with_dy ? reinterpret_cast<Vec*>(a.out_dy + sb) : nullptr;
 #pragma unroll
     for (int u = 0; u < NQ; ++u) {
       const int j = tid + u * kBlock;
-      const float* q = buf + Pd::ridx(j);
-      dst[j] = float4{q[0], q[rl], q[ppitch], q[ppitch + rl]};
+      if (n < kBlock && j >= n) break;
+      const T* q = buf + Pd::ridx(j);
+      dst[j] = Vec{{q[0], q[rl], q[ppitch], q[ppitch + rl]}};
       if (dy) {
         // -d_y by central differences, zero on row 0 and beyond row n - 1
         // (neighbour indices clamped into the strip)
-        const float* qu = buf + Pd::ridx(j + 1 < n ? j + 1 : j);
-        const float* qd = buf + Pd::ridx(j > 0 ? j - 1 : 0);
+        const T* qu = buf + Pd::ridx(j + 1 < n ? j + 1 : j);
+        const T* qd = buf + Pd::ridx(j > 0 ? j - 1 : 0);
         const bool hu = j + 1 < n, in = j > 0;
-        float4 d4;
-        d4.x = in ? mihy * ((hu ? qu[0] : 0.f) - qd[0]) : 0.f;
-        d4.y = in ? mihy * ((hu ? qu[rl] : 0.f) - qd[rl]) : 0.f;
-        d4.z = in ? mihy * ((hu ? qu[ppitch] : 0.f) - qd[ppitch]) : 0.f;
-        d4.w = in ? mihy * ((hu ? qu[ppitch + rl] : 0.f) - qd[ppitch + rl]) : 0.f;
+        Vec d4;
+        constexpr int off[4] = {0, rl, ppitch, ppitch + rl};
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          d4.v[e] = in ? mihy * ((hu ? qu[off[e]] : T(0)) - qd[off[e]]) : T(0);
         dy[j] = d4;
       }
     }
     return;
   }
-  float* out = a.out + fld * plane + p0 + c + static_cast<size_t>(j0) * nx;
-  const float* r = buf + lcol;
-  if (fld == 0 && a.out_dy) {
+  if (n < JS && j0 >= n) return;
+  T* out = a.out + fld * plane + p0 + c + static_cast<size_t>(j0) * nx;
+  const T* r = buf + lcol;
+  if (with_dy) {
     // -d_y by central differences, zero on the boundary rows j = 0 and the
     // clamped neighbour beyond j = ny - 1; j + 1 (j - 1) crosses a padding
-    // gap (4 words) exactly when j0 + 1 (j0) is a multiple of 32
-    float* dy = a.out_dy + p0 + c + static_cast<size_t>(j0) * nx;
-    const float mihy = static_cast<float>(-0.5 / g.hy);
+    // gap exactly when j0 + 1 (j0) is a multiple of the layout's run
+    T* dy = a.out_dy + p0 + c + static_cast<size_t>(j0) * nx;
     const int up = Pd::ridx(j0 + 1) - Pd::ridx(j0), dn = Pd::ridx(j0 - 1) - Pd::ridx(j0);
     for_iters<NIT>([&](int it) {
-      const float* q = r + it * LS;
+      const T* q = r + it * LS;
       const int j = j0 + it * JS;
       // the neighbour reads stay inside the strip (clamped at the two ends)
-      const float v = q[0];
-      const float vu = j + 1 < n ? q[it == NIT - 1 && j0 == JS - 1 ? 0 : up] : 0.f;
-      const float vd = j > 0 ? q[it == 0 && j0 == 0 ? 0 : dn] : 0.f;
+      const T v = q[0];
+      const T vu = j + 1 < n ? q[j == n - 1 ? 0 : up] : T(0);
+      const T vd = j > 0 ? q[j == 0 ? 0 : dn] : T(0);
       out[static_cast<size_t>(it) * JS * nx] = v;
-      dy[static_cast<size_t>(it) * JS * nx] = j > 0 ? mihy * (vu - vd) : 0.f;
+      dy[static_cast<size_t>(it) * JS * nx] = j > 0 ? mihy * (vu - vd) : T(0);
     });
   } else {
     for_iters<NIT>([&](int it) { out[static_cast<size_t>(it) * JS * nx] = r[it * LS]; });
@@ -1256,18 +1571,18 @@ template <typename T, int LOGN>
 __device__ __forceinline__ void col_block(const Geom& g, const ColArgs<T>& a,
                                           const AxisTables<T>& ty, const double* __restrict__ lamx,
                                           int strip, int fld, unsigned char* smem_raw) {
-  if constexpr (fast_core(sizeof(T), 1 << LOGN) && core_lanes(sizeof(T), 1 << LOGN) == 128) {
-    col_block_core<LOGN, 4>(g, a, ty, lamx, strip, fld, smem_raw);   // the launcher checks w = 4
+  if constexpr (sym_core(sizeof(T), 1 << LOGN)) {
+    col_block_core<T, LOGN, sym_cols(1 << LOGN)>(g, a, ty, lamx, strip, fld, smem_raw);   // the launcher checks w
     return;
-  } else if constexpr (fast_core(sizeof(T), 1 << LOGN)) {
+  } else if constexpr (wave_core(sizeof(T), 1 << LOGN)) {
     if (a.w == 8)
-      col_block_core<LOGN, 8>(g, a, ty, lamx, strip, fld, smem_raw);
+      col_block_core<T, LOGN, 8>(g, a, ty, lamx, strip, fld, smem_raw);
     else if (a.w == 4)
-      col_block_core<LOGN, 4>(g, a, ty, lamx, strip, fld, smem_raw);
+      col_block_core<T, LOGN, 4>(g, a, ty, lamx, strip, fld, smem_raw);
     else
-      col_block_core<LOGN, 2>(g, a, ty, lamx, strip, fld, smem_raw);
+      col_block_core<T, LOGN, 2>(g, a, ty, lamx, strip, fld, smem_raw);
     return;
-  }
+  } else {
   __syncthreads();   // the workgroup's previous use of LDS is complete
   T* buf = reinterpret_cast<T*>(smem_raw);
   const int ny = g.ny, nx = g.nx;
@@ -1275,16 +1590,10 @@ __device__ __forceinline__ void col_block(const Geom& g, const ColArgs<T>& a,
   const int ppitch = pair_pitch<T>(ny);
   const int p0 = strip * W;
   unsigned char* tbase = smem_raw + static_cast<size_t>(W / 2) * ppitch * sizeof(T);
-  const Cplx<T>* tw;
-  const T* pre;
-  stage_tables<T, LOGN>(ty, tbase, tw, pre);
-  double* slamx = reinterpret_cast<double*>(tbase + table_bytes<T>(ny));   // the strip's
-  const double* slam = ty.lam;                                              // x, y eigenvalues
-  if constexpr (!fast_core(sizeof(T), 1 << LOGN)) {
-    stage_doubles<(1 << LOGN)>(slamx, ty.lam);
-    slam = slamx;
-    slamx += ny;
-  }
+  const Xform<T, LOGN, 0> xf = stage_tables<T, LOGN, 0>(ty, tbase, W / 2);
+  double* slam = reinterpret_cast<double*>(tbase + table_bytes<T>(ny));   // y eigenvalues,
+  double* slamx = slam + ny;                                               // the strip's x ones
+  if (static_cast<int>(threadIdx.x) < ny) slam[threadIdx.x] = ty.lam[threadIdx.x];   // ny < kBlock
   if (static_cast<int>(threadIdx.x) < W) slamx[threadIdx.x] = lamx[strip * W + threadIdx.x];
   const size_t plane = static_cast<size_t>(nx) * ny;
   const T* in = a.in + fld * plane;
@@ -1293,8 +1602,9 @@ __device__ __forceinline__ void col_block(const Geom& g, const ColArgs<T>& a,
     const int c = e & (W - 1), j = e >> lw;
     buf[Pad<T>::rpos(ny, ppitch, c, j)] = in[j * nx + p0 + c];
   });
+  xf.commit();
   __syncthreads();
-  block_dst<T, LOGN>(buf, g.ly, W, ppitch, tw, pre);
+  block_dst<T, LOGN>(buf, W, ppitch, xf);
   const double shift = a.shift[fld];
   // 1 / normalisation (nx ny / 4, exact): the eigenvalue sum in FP64 without
   // a division, the one division in the field precision
@@ -1309,7 +1619,7 @@ __device__ __forceinline__ void col_block(const Geom& g, const ColArgs<T>& a,
     r[iq] = (p > 0 && q > 0) ? v : T(0);
   });
   __syncthreads();
-  block_dst<T, LOGN>(buf, g.ly, W, ppitch, tw, pre);
+  block_dst<T, LOGN>(buf, W, ppitch, xf);
   T* out = a.out + fld * plane;
   T* out_dy = (fld == 0) ? a.out_dy : nullptr;
   const T mihy = static_cast<T>(-0.5 / g.hy);
@@ -1323,6 +1633,7 @@ __device__ __forceinline__ void col_block(const Geom& g, const ColArgs<T>& a,
       out_dy[j * nx + p0 + c] = j > 0 ? d : T(0);
     }
   });
+  }
 }
 
 // Predictor-corrector epilogue: B_new from the inverse transform, FP64 sums
@@ -1339,46 +1650,75 @@ __device__ __forceinline__ void row_inv_pc_block(const Geom& g, const PCArgs<T>&
   constexpr int n = 1 << LOGN;   // = nx
   const int R = RC > 0 ? RC : g.rr;
   const int ppitch = pair_pitch<T>(n);
-  const Cplx<T>* tw;
-  const T* pre;
-  stage_tables<T, LOGN>(tx, smem_raw + static_cast<size_t>(R / 2) * ppitch * sizeof(T), tw, pre);
+  const auto xf = stage_tables<T, LOGN, row_pairs<T, LOGN>()>(tx, smem_raw + static_cast<size_t>(R / 2) * ppitch * sizeof(T), R / 2);
   const int j0 = bxi * R;
-  plane_to_rows<T, RC, LOGN>(g, R, j0, a.in + static_cast<size_t>(fld) * g.nx * g.ny, buf, ppitch);
-  __syncthreads();
-  block_dst<T, LOGN>(buf, g.lx, R, ppitch, tw, pre);
   T* b = fld == 0 ? a.bx : a.by;
   T* tp = fld == 0 ? a.tape_bx : a.tape_by;
+  const T* in = a.in + static_cast<size_t>(fld) * g.nx * g.ny;
+  // with a compile-time row block the old iterate is fetched under the plane
+  // load (its own round trip after the transform took 2.8k of 18.4k cycles)
+  constexpr int NOLD = RC > 0 ? (RC << LOGN) / kBlock : 1;
+  T old_b[NOLD];
+  if constexpr (RC > 0) {
+    RowFetch<T, RC, LOGN> rows;
+    rows.load(g, j0, in);
+#pragma unroll
+    for (int u = 0; u < NOLD; ++u) old_b[u] = load_at(b, j0 * n + static_cast<int>(threadIdx.x) + u * kBlock);
+    __builtin_amdgcn_sched_barrier(0);
+    rows.put(g, buf, ppitch);
+#pragma unroll
+    for (int u = 0; u < NOLD; ++u) pin(old_b[u]);
+  } else {
+    plane_to_rows<T, RC, LOGN>(g, R, j0, in, buf, ppitch);
+  }
+  xf.commit();
+  __syncthreads();
+  block_dst<T, LOGN>(buf, R, ppitch, xf);
   double dsum = 0.0, nsum = 0.0;
-  for_row_elems<RC, LOGN, 32>(R, [&](int e) {
+  auto update = [&](int e, T prev, auto taped) {
     const int r = e >> LOGN, i = e & (n - 1);
     const int j = j0 + r;
     const T v = buf[RowLay<T, LOGN>::rpos(n, ppitch, r, i)];
     const T u = j > 0 ? v : T(0);
-    const double old = static_cast<double>(b[j * n + i]);
-    const double d = static_cast<double>(u) - old;
+    const double d = static_cast<double>(u) - static_cast<double>(prev);
     dsum += d * d;
     nsum += static_cast<double>(u) * static_cast<double>(u);
-    b[j * n + i] = u;
-    if (tp) tp[j * n + i] = u;
-  });
+    store_at(b, j * n + i, u);
+    if constexpr (decltype(taped)::value) store_at(tp, j * n + i, u);
+  };
+  auto finish = [&](auto taped) {   // the tape tested once, not per element
+    if constexpr (RC > 0) {
+#pragma unroll
+      for (int u = 0; u < NOLD; ++u) update(static_cast<int>(threadIdx.x) + u * kBlock, old_b[u], taped);
+    } else {
+      struct In {
+        T b;
+        __device__ void pin() { dst_detail::pin(b); }
+      };
+      for_row_batches<RC, LOGN, 8, In>(
+          R, [&](int e, In& v) { v.b = b[j0 * n + e]; },
+          [&](int, int e, const In& v) { update(e, v.b, taped); });
+    }
+  };
+  if (tp)
+    finish(std::true_type{});
+  else
+    finish(std::false_type{});
   double v[2] = {dsum, nsum};
   partials::store<2>(v, a.partial, fld * (g.ny / R) + bxi);
 }
 
 }  // namespace dst_detail
 
-// rows per row-pass workgroup (even, at most ny, within 144 KiB of LDS).
-// Up to 512 columns one busy wave per workgroup (more, smaller workgroups
-// fill the chip; measured best from HIP graphs at 64^2 and 512^2), above
-// two in FP32 with the half-length transform and four in FP64 (measured at
-// 1024^2), four with the FP32 core (two pairs of two waves at 1024).
+// rows per row-pass workgroup (even, at most ny, within 144 KiB of LDS):
+// sym_rows with the symmetric core; else one busy wave per workgroup (more,
+// smaller workgroups fill the chip; measured best from HIP graphs at 64^2 and
+// 512^2).
 template <typename T>
 int row_rows(int nx, int ny) {
-  if (core_lanes(sizeof(T), nx) == 128) return 4;   // two-wave core: two pairs per workgroup
-  const bool core = fast_core(sizeof(T), nx);
-  const int per = nx >= 512 || core ? 1 : 512 / nx;
-  const int waves = nx <= 512 ? 1 : (sizeof(T) == 8 || core ? 4 : 2);
-  int r = 2 * per * dst_detail::pass_waves("QSP_ROW_WAVES", waves);
+  if (sym_core(sizeof(T), nx)) return sym_rows(nx);
+  const int per = wave_core(sizeof(T), nx) ? 1 : 512 / nx;
+  int r = 2 * per * dst_detail::pass_waves("QSP_ROW_WAVES", 1);
   if (r > ny) r = ny;
   if (r > 2 * per * (kBlock / 64)) r = 2 * per * (kBlock / 64);   // one pair group per wave
   while (r > 2 && dst_detail::pass_lds<T>(r, nx) > 147456) r >>= 1;

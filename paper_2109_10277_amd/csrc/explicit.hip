@@ -67,9 +67,7 @@ k_expl_setup(Geom g, ExplicitArgs<T> a, AxisTables<T> tx, DevCounters* ctr) {
   const int n = g.nx, ny = g.ny;
   const int R = g.rr;
   const int ppitch = pair_pitch<T>(n);
-  const Cplx<T>* tw;
-  const T* pre;
-  stage_tables<T, LOGN>(tx, smem_raw + static_cast<size_t>(R / 2) * ppitch * sizeof(T), tw, pre);
+  const auto xf = stage_tables<T, LOGN, row_pairs<T, LOGN>()>(tx, smem_raw + static_cast<size_t>(R / 2) * ppitch * sizeof(T), R / 2);
   const int fld = blockIdx.y;
   const int j0 = blockIdx.x * R;
   const size_t plane = static_cast<size_t>(n) * ny;
@@ -119,8 +117,9 @@ k_expl_setup(Geom g, ExplicitArgs<T> a, AxisTables<T> tx, DevCounters* ctr) {
     rn += r0 * r0;
     buf[RowLay<T, LOGN>::rpos(n, ppitch, rr, i)] = static_cast<T>(-r0);
   });
+  xf.commit();
   __syncthreads();
-  block_dst<T, LOGN>(buf, g.lx, R, ppitch, tw, pre);
+  block_dst<T, LOGN>(buf, R, ppitch, xf);
   rows_to_plane<T, 0, LOGN>(g, R, j0, buf, ppitch, a.fwd + fld * plane);
   double v[2] = {bn, rn};
   partials::store<2>(v, a.part_s, fld * (ny / R) + blockIdx.x);
@@ -158,16 +157,15 @@ k_expl_rowinv(Geom g, ExplicitArgs<T> a, AxisTables<T> tx, DevCounters* ctr) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   T* buf = reinterpret_cast<T*>(smem_raw);
   const int ppitch = pair_pitch<T>(n);
-  const Cplx<T>* tw;
-  const T* pre;
-  stage_tables<T, LOGN>(tx, smem_raw + static_cast<size_t>(R / 2) * ppitch * sizeof(T), tw, pre);
+  const auto xf = stage_tables<T, LOGN, row_pairs<T, LOGN>()>(tx, smem_raw + static_cast<size_t>(R / 2) * ppitch * sizeof(T), R / 2);
   const int fld = blockIdx.y;
   const int j0 = blockIdx.x * R;
   const size_t plane = static_cast<size_t>(n) * ny;
   const int lx = g.lx;
   plane_to_rows<T, 0, LOGN>(g, R, j0, a.col + fld * plane, buf, ppitch);
+  xf.commit();
   __syncthreads();
-  block_dst<T, LOGN>(buf, g.lx, R, ppitch, tw, pre);
+  block_dst<T, LOGN>(buf, R, ppitch, xf);
   T* z = a.z + fld * plane;
   const double* r = a.r + fld * plane;
   const double* q = a.q + fld * plane;
@@ -278,9 +276,7 @@ k_expl_update(Geom g, ExplicitArgs<T> a, AxisTables<T> tx, DevCounters* ctr) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   T* buf = reinterpret_cast<T*>(smem_raw);
   const int ppitch = pair_pitch<T>(n);
-  const Cplx<T>* tw;
-  const T* pre;
-  stage_tables<T, LOGN>(tx, smem_raw + static_cast<size_t>(R / 2) * ppitch * sizeof(T), tw, pre);
+  const auto xf = stage_tables<T, LOGN, row_pairs<T, LOGN>()>(tx, smem_raw + static_cast<size_t>(R / 2) * ppitch * sizeof(T), R / 2);
   const int j0 = blockIdx.x * R;
   const size_t plane = static_cast<size_t>(n) * ny;
   const double* p = a.p[it & 1] + fld * plane;
@@ -303,8 +299,9 @@ k_expl_update(Geom g, ExplicitArgs<T> a, AxisTables<T> tx, DevCounters* ctr) {
     rn += rv * rv;
     buf[RowLay<T, LOGN>::rpos(n, ppitch, rw, i)] = static_cast<T>(-rv);
   });
+  xf.commit();
   __syncthreads();
-  block_dst<T, LOGN>(buf, g.lx, R, ppitch, tw, pre);
+  block_dst<T, LOGN>(buf, R, ppitch, xf);
   rows_to_plane<T, 0, LOGN>(g, R, j0, buf, ppitch, a.fwd + fld * plane);
   double v[1] = {rn};
   partials::store<1>(v, a.part_u, fld * (ny / R) + blockIdx.x);

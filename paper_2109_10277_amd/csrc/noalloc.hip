@@ -62,15 +62,20 @@ __global__ void k_axis_tables(AxisJob<T> x, AxisJob<T> y) {
   const int m = blockIdx.x * blockDim.x + threadIdx.x;
   if (m >= 2 * n) return;
   double s, c;
-  if (qsp::fast_core(sizeof(T), n)) {
-    const int NL = qsp::core_lanes(sizeof(T), n);
-    const int k1 = m / NL, l = m % NL;
+  if (qsp::sym_core(sizeof(T), n)) {
+    if (m < qsp::sym_table_size(n)) {
+      sincospi(qsp::sym_table_angle(n, m), &s, &c);
+      tw[m] = m < qsp::sym_table_s(n) ? qsp::Cplx<T>{static_cast<T>(c), static_cast<T>(-s)}
+                                      : qsp::Cplx<T>{static_cast<T>(s), T(0)};
+    }
+  } else if (qsp::wave_core(sizeof(T), n)) {
+    const int k1 = m / 64, l = m % 64;
     sincospi(-2.0 * static_cast<double>((l * k1) % (2 * n)) / (2 * n), &s, &c);
     tw[m] = {static_cast<T>(c), static_cast<T>(s)};
-    if (m < NL / 8 * 9) {
+    if (m < 72) {
       auto* w = reinterpret_cast<qsp::Cplx<T>*>(pre);
       const int la = m / 9, c1 = m % 9;
-      sincospi(-2.0 * (la * c1) / static_cast<double>(NL), &s, &c);
+      sincospi(-2.0 * (la * c1) / 64.0, &s, &c);
       w[m] = c1 < 8 ? qsp::Cplx<T>{static_cast<T>(c), static_cast<T>(s)}
                     : qsp::Cplx<T>{T(0), T(0)};
     }

@@ -44,15 +44,6 @@ __host__ __device__ inline TileShape tile_shape(const Lattice& L, int rows, int 
   return t;
 }
 
-// base[i] with the byte offset formed in 32 bits (the caller guarantees
-// i * sizeof(T) < 2^32), so that a uniform base loads through one VGPR of
-// offset instead of a 64-bit address per lane
-template <typename T>
-__device__ __forceinline__ T load_at(const T* base, unsigned int i) {
-  return *reinterpret_cast<const T*>(reinterpret_cast<const char*>(base) +
-                                     i * static_cast<unsigned int>(sizeof(T)));
-}
-
 template <typename T>
 __device__ inline bool inside(int c0, T t, int n) {
   const T fl = floor(t);

@@ -197,10 +197,9 @@ class Box final : public BoxBase {
     geom_.hy = (cfg.y_hi - cfg.y_lo) / cfg.ny;
     geom_.rr = row_rows<T>(cfg.nx, cfg.ny);
     geom_.order = cfg.shape_order;
-    // both axes on the two-wave core at 1024 points: strip-ordered
-    // intermediate planes
-    geom_.strip = core_lanes(sizeof(T), cfg.nx) == 128 && core_lanes(sizeof(T), cfg.ny) == 128 &&
-                  cfg.nx >= 1024 && cfg.ny >= 1024;
+    // column strips of 4 columns: strip-ordered intermediate planes
+    geom_.strip = col_width<T>(geom_, 2) == 4 &&
+                  (sym_core(sizeof(T), cfg.ny) || wave_core(sizeof(T), cfg.ny));
     lat_.ppc_x = cfg.ppc_x;
     lat_.ppc_y = cfg.ppc_y;
     lat_.nX = cfg.nx * cfg.ppc_x;
@@ -1429,11 +1428,8 @@ class Box final : public BoxBase {
     if (cfg_.mem_cap_bytes > 0 && bytes_ > cfg_.mem_cap_bytes) throw std::bad_alloc();
   }
 
-  // Per-axis tables of the sine transform (tw holds 2n entries, pre n):
-  // the half-length transform's twiddles e^{-2 pi i m/n} and pre-twiddles
-  // sin(pi m/n), or for the FP32 core of 256-1024 points the twiddles
-  // W_2n^{l k1} at [k1 * 64 + l] and, in pre, the W_64^{la c1} table at
-  // [la * 9 + c1] (complex); and the Laplacian eigenvalues.
+  // Per-axis tables of the sine transform (tw holds 2n entries, pre n, laid
+  // out as AxisTables says) and the Laplacian eigenvalues.
   void axis_tables(int n, double h, Cplx<T>* tw, T* pre, double* lam) {
     std::vector<Cplx<T>> htw(2 * n);
     std::vector<T> hpre(n);
@@ -1443,14 +1439,21 @@ class Box final : public BoxBase {
       const double a = -2.0 * pi * static_cast<double>(q % m) / static_cast<double>(m);
       return Cplx<T>{static_cast<T>(std::cos(a)), static_cast<T>(std::sin(a))};
     };
-    if (fast_core(sizeof(T), n)) {
-      const int NL = core_lanes(sizeof(T), n), P = 2 * n / NL;
-      for (int k1 = 0; k1 < P; ++k1)
-        for (int l = 0; l < NL; ++l) htw[k1 * NL + l] = unit(static_cast<long>(l) * k1, 2 * n);
+    if (sym_core(sizeof(T), n)) {
+      for (int m = 0; m < sym_table_size(n); ++m) {
+        const double a = pi * sym_table_angle(n, m);
+        if (m < sym_table_s(n))
+          htw[m] = {static_cast<T>(std::cos(a)), static_cast<T>(-std::sin(a))};
+        else
+          htw[m] = {static_cast<T>(std::sin(a)), T(0)};
+      }
+    } else if (wave_core(sizeof(T), n)) {
+      for (int k1 = 0; k1 < n / 32; ++k1)
+        for (int l = 0; l < 64; ++l) htw[k1 * 64 + l] = unit(static_cast<long>(l) * k1, 2 * n);
       Cplx<T>* w = reinterpret_cast<Cplx<T>*>(hpre.data());
-      for (int i = 0; i < NL / 8 * 9; ++i) w[i] = Cplx<T>{T(0), T(0)};
-      for (int la = 0; la < NL / 8; ++la)
-        for (int c1 = 0; c1 < 8; ++c1) w[la * 9 + c1] = unit(la * c1, NL);
+      for (int i = 0; i < 72; ++i) w[i] = Cplx<T>{T(0), T(0)};
+      for (int la = 0; la < 8; ++la)
+        for (int c1 = 0; c1 < 8; ++c1) w[la * 9 + c1] = unit(la * c1, 64);
     } else {
       for (int m = 0; m < n; ++m) {
         htw[m] = unit(m, n);
@@ -1770,32 +1773,29 @@ class Box final : public BoxBase {
     a.part_u = ex_partial_ + 8 * np;
     a.s = ex_s_;
     a.tol = cfg_.pc_tol;
-    // the solver's planes between its row and column passes stay row-major
-    Geom ge = geom_;
-    ge.strip = 0;
     ColArgs<T> c{};
     c.in = t1_;
     c.out = t2_;
     c.out_dy = nullptr;
     c.shift[0] = c.shift[1] = shift_;
     c.honor_done = 1;
-    c.w = col_width<T>(ge, 2);
+    c.w = col_width<T>(geom_, 2);
     auto precondition = [&](int it) {
       a.it = it;
-      timed(QSP_K_COL, [&] { launch_col_solve<T>(ge, c, 2, ty(), lamx_, ctr_, st_); });
-      timed(QSP_K_ROW_INV, [&] { launch_explicit<T>(ge, a, kExplRowInv, tx(), ctr_, st_); });
+      timed(QSP_K_COL, [&] { launch_col_solve<T>(geom_, c, 2, ty(), lamx_, ctr_, st_); });
+      timed(QSP_K_ROW_INV, [&] { launch_explicit<T>(geom_, a, kExplRowInv, tx(), ctr_, st_); });
     };
     a.it = 0;
-    timed(QSP_K_ROW_FWD, [&] { launch_explicit<T>(ge, a, kExplSetup, tx(), ctr_, st_); });
+    timed(QSP_K_ROW_FWD, [&] { launch_explicit<T>(geom_, a, kExplSetup, tx(), ctr_, st_); });
     precondition(0);
     for (int m = 1; m <= cfg_.pc_max_iter; ++m) {
       a.it = m;
-      timed(QSP_K_OTHER, [&] { launch_explicit<T>(ge, a, kExplMatvec, tx(), ctr_, st_); });
-      timed(QSP_K_ROW_FWD, [&] { launch_explicit<T>(ge, a, kExplUpdate, tx(), ctr_, st_); });
+      timed(QSP_K_OTHER, [&] { launch_explicit<T>(geom_, a, kExplMatvec, tx(), ctr_, st_); });
+      timed(QSP_K_ROW_FWD, [&] { launch_explicit<T>(geom_, a, kExplUpdate, tx(), ctr_, st_); });
       if (m < cfg_.pc_max_iter) precondition(m);
     }
     a.it = cfg_.pc_max_iter;
-    timed(QSP_K_OTHER, [&] { launch_explicit<T>(ge, a, kExplClose, tx(), ctr_, st_); });
+    timed(QSP_K_OTHER, [&] { launch_explicit<T>(geom_, a, kExplClose, tx(), ctr_, st_); });
     dst_solves_ += 2 * (cfg_.pc_max_iter);
   }
 
