@@ -300,8 +300,8 @@ void launch_col_solve(const Geom& g, const ColArgs<T>& a, int nfield, const Axis
   const int W = a.w;
   if (W < 2 || (W & (W - 1)) || g.nx % W || nfield < 1 || nfield > 4)
     throw std::invalid_argument("column pass: bad strip width or field count");
-  if (sym_core(sizeof(T), g.ny) ? W != sym_cols(g.ny) : false)
-    throw std::invalid_argument("column pass: wrong columns for the symmetric core");
+  if (sym_core(sizeof(T), g.ny) ? W != sym_cols(g.ny) : wave_core(sizeof(T), g.ny) && W != 4)
+    throw std::invalid_argument("column pass: wrong columns for the transform core");
   if (!sym_core(sizeof(T), g.ny)) check_rows<T>(g.ny, W);
   if (g.strip && W != 4)   // a strip of the intermediate planes is 4 columns
     throw std::invalid_argument("column pass: strip-ordered planes need strips of 4 columns");

@@ -24,7 +24,6 @@
 //   eigenvalue division of P2.
 #pragma once
 
-#include <cstdlib>
 #include <stdexcept>
 #include <type_traits>
 
@@ -901,17 +900,6 @@ __host__ __device__ inline size_t table_bytes(int n) {
   return static_cast<size_t>(n) * (sizeof(Cplx<T>) + sizeof(T));
 }
 
-// Busy waves per workgroup of a transform pass: each wave transforms a group
-// of max(1, 512/n) row pairs.  The QSP_ROW_WAVES / QSP_COL_WAVES environment
-// variables (1, 2 or 4) override the defaults for tuning.
-inline int pass_waves(const char* env, int dflt) {
-  if (const char* e = std::getenv(env)) {
-    const int v = std::atoi(e);
-    if (v == 1 || v == 2 || v == 4) return v;
-  }
-  return dflt;
-}
-
 // Eigenvalue bytes the half-length column pass stages after the tables: the
 // strip's W x eigenvalues and the n y eigenvalues (the cores hold theirs in
 // registers).
@@ -921,31 +909,19 @@ __host__ __device__ inline size_t lam_bytes(int n, int w) {
   return static_cast<size_t>(n + w) * sizeof(double);
 }
 
-template <typename T>
-inline size_t pass_lds(int rows, int n) {
-  return static_cast<size_t>(rows / 2) * pair_pitch<T>(n) * sizeof(T) + table_bytes<T>(n) +
-         lam_bytes<T>(n, rows);
-}
-
-// columns per column-pass workgroup (even, at most nx, within 80 KiB of LDS):
-// sym_rows with the symmetric core; else one busy wave (one column pair, or
-// 512 / ny of them with the half-length transform) per workgroup.
+// columns per column-pass workgroup: sym_cols with the symmetric core; four
+// with the wave core, which makes the strip order of the intermediate planes
+// possible (16-byte loads of whole strips; with two columns a lane's 8-byte
+// segments took the pass 10.7 us at 512^2 in FP32, against 9.7, and twice the
+// columns per workgroup 10.9); 512 / ny pairs (one busy wave) with the
+// half-length transform.
 template <typename T>
 inline int col_strip(int nx, int ny, int nfield) {
   (void)nfield;
   if (sym_core(sizeof(T), ny)) return sym_cols(ny);
-  const bool core = wave_core(sizeof(T), ny);
-  const int per = core ? 1 : 512 / ny;
-  int w = 2 * per * pass_waves("QSP_COL_WAVES", 1);
-  if (const char* e = std::getenv("QSP_COL_W")) {   // tuning override
-    const int v = std::atoi(e);
-    if (v >= 2 && v <= 64 && (v & (v - 1)) == 0) w = v;
-  }
-  if (w > nx) w = nx;
-  if (w > 2 * per * (kBlock / 64)) w = 2 * per * (kBlock / 64);   // one pair group per wave
-  const size_t cap = 81920;   // two workgroups per CU
-  while (w > 2 && pass_lds<T>(w, ny) > cap) w >>= 1;
-  return w;
+  if (wave_core(sizeof(T), ny)) return 4;
+  const int w = 2 * (512 / ny);
+  return w > nx ? nx : w;
 }
 
 // Issues the loads of an axis' transform tables; the LDS part goes right
@@ -1258,12 +1234,8 @@ void with_rows(int R, F&& f) {
     if (R != RC) throw std::invalid_argument("row pass: wrong rows for the symmetric core");
     f(std::integral_constant<int, RC>{});
   } else if constexpr (wave_core(sizeof(T), n)) {
-    switch (R) {
-      case 2: f(std::integral_constant<int, 2>{}); break;
-      case 4: f(std::integral_constant<int, 4>{}); break;
-      case 8: f(std::integral_constant<int, 8>{}); break;
-      default: throw std::invalid_argument("row pass: rows per workgroup must be 2, 4 or 8");
-    }
+    if (R != 2) throw std::invalid_argument("row pass: wrong rows for the wave core");
+    f(std::integral_constant<int, 2>{});
   } else {
     f(std::integral_constant<int, 0>{});
   }
@@ -1575,12 +1547,7 @@ __device__ __forceinline__ void col_block(const Geom& g, const ColArgs<T>& a,
     col_block_core<T, LOGN, sym_cols(1 << LOGN)>(g, a, ty, lamx, strip, fld, smem_raw);   // the launcher checks w
     return;
   } else if constexpr (wave_core(sizeof(T), 1 << LOGN)) {
-    if (a.w == 8)
-      col_block_core<T, LOGN, 8>(g, a, ty, lamx, strip, fld, smem_raw);
-    else if (a.w == 4)
-      col_block_core<T, LOGN, 4>(g, a, ty, lamx, strip, fld, smem_raw);
-    else
-      col_block_core<T, LOGN, 2>(g, a, ty, lamx, strip, fld, smem_raw);
+    col_block_core<T, LOGN, 4>(g, a, ty, lamx, strip, fld, smem_raw);
     return;
   } else {
   __syncthreads();   // the workgroup's previous use of LDS is complete
@@ -1710,19 +1677,14 @@ __device__ __forceinline__ void row_inv_pc_block(const Geom& g, const PCArgs<T>&
 
 }  // namespace dst_detail
 
-// rows per row-pass workgroup (even, at most ny, within 144 KiB of LDS):
-// sym_rows with the symmetric core; else one busy wave per workgroup (more,
-// smaller workgroups fill the chip; measured best from HIP graphs at 64^2 and
-// 512^2).
+// rows per row-pass workgroup: sym_rows with the symmetric core; else those
+// of one busy wave (more, smaller workgroups fill the chip; measured best from
+// HIP graphs at 64^2 and 512^2).
 template <typename T>
 int row_rows(int nx, int ny) {
   if (sym_core(sizeof(T), nx)) return sym_rows(nx);
-  const int per = wave_core(sizeof(T), nx) ? 1 : 512 / nx;
-  int r = 2 * per * dst_detail::pass_waves("QSP_ROW_WAVES", 1);
-  if (r > ny) r = ny;
-  if (r > 2 * per * (kBlock / 64)) r = 2 * per * (kBlock / 64);   // one pair group per wave
-  while (r > 2 && dst_detail::pass_lds<T>(r, nx) > 147456) r >>= 1;
-  return r;
+  const int r = wave_core(sizeof(T), nx) ? 2 : 2 * (512 / nx);
+  return r > ny ? ny : r;
 }
 
 }  // namespace qsp
