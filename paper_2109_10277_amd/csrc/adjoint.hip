@@ -511,15 +511,15 @@ __global__ void __launch_bounds__(kBlock) k_adj_seed(Geom g, AdjSeedArgs<T> a) {
 // source lsb of the iteration after it; p0 is then cleared for the next
 // scatter and lsb joins `sum` (stored or added), from which the slice's
 // Jz and J_perp adjoints are formed once.  Zero on the Dirichlet nodes.
-template <typename T, int LOGN, int RC>
+template <typename T, int LOGN>
 __global__ void __launch_bounds__(kBlock, dst_blocks_per_cu(LOGN, sizeof(T)))
 k_adj_src(Geom g, AdjSrcArgs<T> a, AxisTables<T> tx) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   T* buf = reinterpret_cast<T*>(smem_raw);
   constexpr int n = 1 << LOGN;   // = nx
-  const int R = RC > 0 ? RC : g.rr;
-  const int ppitch = pair_pitch<T>(n);
-  const auto xf = stage_tables<T, LOGN, row_pairs<T, LOGN>()>(tx, smem_raw + static_cast<size_t>(R / 2) * ppitch * sizeof(T), R / 2);
+  constexpr int R = pass_rows<T>(n);
+  constexpr int ppitch = pair_pitch<T>(n);
+  const auto xf = stage_row_tables<T, LOGN>(tx, smem_raw);
   const int j0 = xcd_strip(blockIdx.x, gridDim.x) * R;
   const int fld = blockIdx.y;
   const double ihx = 0.5 / g.hx, ihy = 0.5 / g.hy;
@@ -540,8 +540,7 @@ k_adj_src(Geom g, AdjSrcArgs<T> a, AxisTables<T> tx) {
       dst_detail::pin(l);
     }
   };
-  for_row_batches<RC, LOGN, src_batch<T, LOGN>(), In>(
-      R,
+  for_row_batches<R, LOGN, src_batch<T, LOGN>(), In>(
       [&](int e, In& v) {
         const int i = e & (n - 1), j = j0 + (e >> LOGN);
         const int o = j * n + i;
@@ -574,8 +573,8 @@ k_adj_src(Geom g, AdjSrcArgs<T> a, AxisTables<T> tx) {
       });
   xf.commit();
   __syncthreads();
-  block_dst<T, LOGN>(buf, R, ppitch, xf);
-  rows_to_plane<T, RC, LOGN>(g, R, j0, buf, ppitch, a.out + static_cast<size_t>(fld) * g.nx * g.ny);
+  block_dst<T, LOGN>(buf, ppitch, xf);
+  rows_to_plane<T, R, LOGN>(g, j0, buf, ppitch, a.out + static_cast<size_t>(fld) * g.nx * g.ny);
 }
 
 // End of a slice on the grid.  With S the sum over the iterations of the
@@ -764,18 +763,14 @@ void launch_adj_src(const Geom& g, const AdjSrcArgs<T>& a, const AxisTables<T>& 
   for (int q = 0; q < a.count; ++q)
     if (!a.p0[q] || (a.p1[q] != nullptr) != (a.p2[q] != nullptr) || (a.lsb[q] && (!a.sum[q] || a.p1[q])))
       throw std::invalid_argument("adjoint source: missing planes");
-  const int R = g.rr;
-  const size_t lds = static_cast<size_t>(R / 2) * pair_pitch<T>(g.nx) * sizeof(T) + table_bytes<T>(g.nx);
+  const int R = pass_rows<T>(g.nx);
+  const size_t lds = pass_lds<T>(R, g.nx);
   with_logn(g.nx, [&](auto e) {
     constexpr int E = decltype(e)::value;
-    with_rows<T, E>(R, [&](auto rc) {
-      constexpr int RC = decltype(rc)::value;
-      if (lds > 65536)
-        QSP_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&k_adj_src<T, E, RC>),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds)));
-      hipLaunchKernelGGL((k_adj_src<T, E, RC>), dim3(g.ny / R, a.count), dim3(kBlock), lds, st, g, a,
-                         tx);
-    });
+    if (lds > 65536)
+      QSP_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&k_adj_src<T, E>),
+                                  hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds)));
+    hipLaunchKernelGGL((k_adj_src<T, E>), dim3(g.ny / R, a.count), dim3(kBlock), lds, st, g, a, tx);
   });
   QSP_LAUNCH_CHECK();
 }

@@ -103,7 +103,7 @@ struct Lattice {
 //                    one wave per row pair.  These sizes are bound by the
 //                    length of a lane's chain, which the symmetric core does
 //                    not shorten;
-//   half-length      16-64 points: with a prefix sum for the odd outputs.
+//   matrix core      16-64 points: a product with the sine matrix.
 __host__ __device__ constexpr bool sym_core(int elem_size, int n) {
   return n >= 1024 || n == 128 || (elem_size == 8 && n >= 128);
 }
@@ -116,9 +116,18 @@ __host__ __device__ constexpr bool wave_core(int elem_size, int n) {
 __host__ __device__ constexpr int sym_rows(int n) { return n >= 2048 ? 2 : 4; }
 __host__ __device__ constexpr int sym_cols(int n) { return n >= 2048 ? 2 : 4; }
 
-// Per-axis transform tables (device pointers): for the half-length
-// transform tw[m] = e^{-2 pi i m / n} and pre[j] = sin(pi j / n); for the
-// wave core tw[k1 * 64 + l] = e^{-2 pi i l k1 / 2n} (2n entries) and pre holds
+// Shape of the matrix core's products (see Dense in dst_impl.hpp): rows folded
+// onto n / 2 operands (from 32 points up), operands per lane, and the output
+// that column c of tile t holds.
+__host__ __device__ constexpr bool dense_fold(int n) { return n >= 32; }
+__host__ __device__ constexpr int dense_lane(int n) { return (dense_fold(n) ? n / 2 : n) / 4; }
+__host__ __device__ constexpr int dense_out(int n, int t, int c) {
+  return dense_fold(n) ? 2 * (16 * (t >> 1) + c) + (t & 1) : c;
+}
+
+// Per-axis transform tables (device pointers): for the matrix core tw holds
+// real values, entry (t 64 + l) dense_lane + s the operand s of lane l for
+// tile t (dense_angle), and pre is unused; for the wave core tw[k1 * 64 + l] = e^{-2 pi i l k1 / 2n} (2n entries) and pre holds
 // the complex table W_64^{la c1} at [la * 9 + c1] (la < 8, c1 < 8, entry 8 of
 // a row 0); for the symmetric core tw as in sym_table_* and pre unused.
 template <typename T>
@@ -146,6 +155,21 @@ __host__ __device__ inline double sym_table_angle(int n, int m) {
   }
   const int q = m - sym_table_s(n);
   return static_cast<double>(((2 * (q % 8) + 1) * (q / 8)) % 32) / 16.0;
+}
+
+// Matrix core: number of table values, and whole-number angle a of entry m
+// (the value is sin(pi a / n), exactly 0 for multiples of n): output o times
+// the operand index, which for the folded pair 0 means row entry n / 2 (and
+// nothing for the even outputs, o n / 2 being a multiple of n).
+__host__ __device__ constexpr int dense_table_size(int n) { return n / 16 * 64 * dense_lane(n); }
+__host__ __device__ inline int dense_angle(int n, int m) {
+  const int s = m % dense_lane(n), l = m / dense_lane(n) % 64, t = m / dense_lane(n) / 64;
+  const int o = dense_out(n, t, l % 16), k = dense_lane(n) * (l / 16) + s;
+  return o * (dense_fold(n) && k == 0 ? n / 2 : k) % (2 * n);
+}
+// Cplx<T> entries of AxisTables::tw
+__host__ __device__ constexpr int axis_tw_size(int n) {
+  return 2 * n > (dense_table_size(n) + 1) / 2 || n > 64 ? 2 * n : (dense_table_size(n) + 1) / 2;
 }
 
 // Device-side scalars of the predictor-corrector and counters.

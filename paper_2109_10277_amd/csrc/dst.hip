@@ -12,15 +12,15 @@ using namespace dst_detail;
 // ---------------------------------------------------------------------------
 
 // field ids of the psi / Ez / Bz batch
-template <typename T, int LOGN, int RC>
+template <typename T, int LOGN>
 __global__ void __launch_bounds__(kBlock, dst_blocks_per_cu(LOGN, sizeof(T)))
 k_src_fwd_pez(Geom g, SrcPEZ<T> a, AxisTables<T> tx) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   T* buf = reinterpret_cast<T*>(smem_raw);
   constexpr int n = 1 << LOGN;   // = nx
-  const int R = RC > 0 ? RC : g.rr;
-  const int ppitch = pair_pitch<T>(n);
-  const auto xf = stage_tables<T, LOGN, row_pairs<T, LOGN>()>(tx, smem_raw + static_cast<size_t>(R / 2) * ppitch * sizeof(T), R / 2);
+  constexpr int R = pass_rows<T>(n);
+  constexpr int ppitch = pair_pitch<T>(n);
+  const auto xf = stage_row_tables<T, LOGN>(tx, smem_raw);
   // neighbouring row blocks share the 128-byte lines of strip-ordered
   // planes: keep them on one XCD (one L2)
   const int j0 = xcd_strip(blockIdx.x, gridDim.x) * R;
@@ -48,16 +48,15 @@ k_src_fwd_pez(Geom g, SrcPEZ<T> a, AxisTables<T> tx) {
       __device__ void pin() { dst_detail::pin(r); }
     };
     const bool ions = a.ionx != nullptr;
-    for_row_batches<RC, LOGN, 2 * src_batch<T, LOGN>(), Rho>(
-        R, [&](int e, Rho& v) { v.r = load_at(ax, j0 * n + e); },
+    for_row_batches<R, LOGN, 2 * src_batch<T, LOGN>(), Rho>(
+        [&](int e, Rho& v) { v.r = load_at(ax, j0 * n + e); },
         [&](int, int e, const Rho& v) {
           put(e, -(v.r + (ions ? a.n0 * a.ionx[e & (n - 1)] * a.iony[j0 + (e >> LOGN)] : a.n0)));
         });
   } else {
     // neighbour indices are clamped so that every load is in bounds; values
     // outside the interior are replaced by selects
-    for_row_batches<RC, LOGN, src_batch<T, LOGN>(), In>(
-        R,
+    for_row_batches<R, LOGN, src_batch<T, LOGN>(), In>(
         [&](int e, In& v) {
           const int i = e & (n - 1), j = j0 + (e >> LOGN);
           const int o = j * n + i;
@@ -73,16 +72,16 @@ k_src_fwd_pez(Geom g, SrcPEZ<T> a, AxisTables<T> tx) {
   }
   xf.commit();
   __syncthreads();
-  block_dst<T, LOGN>(buf, R, ppitch, xf);
-  rows_to_plane<T, RC, LOGN>(g, R, j0, buf, ppitch, a.out + static_cast<size_t>(fld) * g.nx * g.ny);
+  block_dst<T, LOGN>(buf, ppitch, xf);
+  rows_to_plane<T, R, LOGN>(g, j0, buf, ppitch, a.out + static_cast<size_t>(fld) * g.nx * g.ny);
 }
 
-template <typename T, int LOGN, int RC>
+template <typename T, int LOGN>
 __global__ void __launch_bounds__(kBlock, dst_blocks_per_cu(LOGN, sizeof(T)))
 k_src_fwd_bxby(Geom g, SrcBxBy<T> a, AxisTables<T> tx, const DevCounters* ctr) {
   if (ctr->pc_done) return;
   extern __shared__ __align__(16) unsigned char smem_raw[];
-  src_bxby_block<T, LOGN, RC>(g, a, tx, xcd_strip(blockIdx.x, gridDim.x), blockIdx.y, smem_raw);
+  src_bxby_block<T, LOGN>(g, a, tx, xcd_strip(blockIdx.x, gridDim.x), blockIdx.y, smem_raw);
 }
 
 // ---------------------------------------------------------------------------
@@ -106,15 +105,15 @@ k_col_solve(Geom g, ColArgs<T> a, AxisTables<T> ty, const double* __restrict__ l
 // ---------------------------------------------------------------------------
 // P3: inverse DST along x with epilogues
 // ---------------------------------------------------------------------------
-template <typename T, int LOGN, int RC>
+template <typename T, int LOGN>
 __global__ void __launch_bounds__(kBlock, dst_blocks_per_cu(LOGN, sizeof(T)))
 k_row_inv(Geom g, RowInvArgs<T> a, AxisTables<T> tx) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   T* buf = reinterpret_cast<T*>(smem_raw);
   constexpr int n = 1 << LOGN;   // = nx
-  const int R = RC > 0 ? RC : g.rr;
-  const int ppitch = pair_pitch<T>(n);
-  const auto xf = stage_tables<T, LOGN, row_pairs<T, LOGN>()>(tx, smem_raw + static_cast<size_t>(R / 2) * ppitch * sizeof(T), R / 2);
+  constexpr int R = pass_rows<T>(n);
+  constexpr int ppitch = pair_pitch<T>(n);
+  const auto xf = stage_row_tables<T, LOGN>(tx, smem_raw);
   const int j0 = xcd_strip(blockIdx.x, gridDim.x) * R;   // neighbours on one XCD
   const int fld = blockIdx.y;
   Geom gi = g;
@@ -123,16 +122,11 @@ k_row_inv(Geom g, RowInvArgs<T> a, AxisTables<T> tx) {
   const size_t gstride = static_cast<size_t>(gridDim.x) * gridDim.y * kBlock;
   const size_t gi0 = (static_cast<size_t>(blockIdx.y) * gridDim.x + blockIdx.x) * kBlock + threadIdx.x;
   GuessRegs<T> gr;
-  if constexpr (RC > 0) {
-    RowFetch<T, RC, LOGN> rows;
-    rows.load(gi, j0, a.in[fld]);
-    if (a.guess.ctr) guess_load(a.guess, plane, gi0, gstride, gr);
-    __builtin_amdgcn_sched_barrier(0);
-    rows.put(gi, buf, ppitch);
-  } else {
-    plane_to_rows<T, RC, LOGN>(gi, R, j0, a.in[fld], buf, ppitch);
-    if (a.guess.ctr) guess_load(a.guess, plane, gi0, gstride, gr);
-  }
+  RowFetch<T, R, LOGN> rows;
+  rows.load(gi, j0, a.in[fld]);
+  if (a.guess.ctr) guess_load(a.guess, plane, gi0, gstride, gr);
+  __builtin_amdgcn_sched_barrier(0);
+  rows.put(gi, buf, ppitch);
   xf.commit();
   if (a.guess.ctr) {   // its stores drain under the transform
     if (gi0 == 0) {
@@ -147,18 +141,18 @@ k_row_inv(Geom g, RowInvArgs<T> a, AxisTables<T> tx) {
     }
   }
   __syncthreads();
-  block_dst<T, LOGN>(buf, R, ppitch, xf);
+  block_dst<T, LOGN>(buf, ppitch, xf);
   T* out = a.out[fld];
   T* out_dx = a.out_dx[fld];
   if (a.out_strip) {   // an intermediate plane (no -d_x)
     Geom go = g;
     go.strip = 1;
-    rows_to_plane<T, RC, LOGN>(go, R, j0, buf, ppitch, out);
+    rows_to_plane<T, R, LOGN>(go, j0, buf, ppitch, out);
     return;
   }
   const T mihx = static_cast<T>(-0.5 / g.hx);
   auto put = [&](auto with_dx) {   // tested once: per element the loop stays rolled
-    for_row_elems<RC, LOGN>(R, [&](int e) {
+    for_row_elems<R, LOGN>([&](int e) {
       const int r = e >> LOGN, i = e & (n - 1);
       const int j = j0 + r;
       const T* row = buf + RowLay<T, LOGN>::rpos(n, ppitch, r, 0);
@@ -183,38 +177,41 @@ k_row_inv(Geom g, RowInvArgs<T> a, AxisTables<T> tx) {
 // plane, OUT = true reads one and writes the solution with its zero boundary.
 // Both ends are bound by latency and launches: as separate layout copies they
 // took 4.6 us a plane, 27 of the 66 us of a batch of three at 1024^2 in FP32.
-template <typename T, int LOGN, int RC, bool OUT>
+template <typename T, int LOGN, bool OUT>
 __global__ void __launch_bounds__(kBlock, dst_blocks_per_cu(LOGN, sizeof(T)))
 k_row_nodes(Geom g, NodeRowArgs<T> a, AxisTables<T> tx) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   T* buf = reinterpret_cast<T*>(smem_raw);
   constexpr int n = 1 << LOGN;   // = nx
-  const int R = RC > 0 ? RC : g.rr;
-  const int ppitch = pair_pitch<T>(n);
-  const auto xf = stage_tables<T, LOGN, row_pairs<T, LOGN>()>(tx, smem_raw + static_cast<size_t>(R / 2) * ppitch * sizeof(T), R / 2);
+  constexpr int R = pass_rows<T>(n);
+  constexpr int ppitch = pair_pitch<T>(n);
+  const auto xf = stage_row_tables<T, LOGN>(tx, smem_raw);
   const int j0 = xcd_strip(blockIdx.x, gridDim.x) * R;
   const int b = blockIdx.y;
   const size_t plane = static_cast<size_t>(n) * g.ny;
   const size_t nodes = static_cast<size_t>(n + 1) * (g.ny + 1);
   if constexpr (!OUT) {
     const T* __restrict__ src = a.nodes_in + b * nodes;
-    for_row_elems<RC, LOGN, 16>(R, [&](int e) {
+    for_row_elems<R, LOGN>([&](int e) {
       const int r = e >> LOGN, i = e & (n - 1);
       const int j = j0 + r;
       const T v = load_at(src, j * (n + 1) + i);
       buf[RowLay<T, LOGN>::rpos(n, ppitch, r, i)] = i > 0 && j > 0 ? v : T(0);
     });
   } else {
-    plane_to_rows<T, RC, LOGN>(g, R, j0, a.plane + b * plane, buf, ppitch);
+    RowFetch<T, R, LOGN> rows;
+    rows.load(g, j0, a.plane + b * plane);
+    __builtin_amdgcn_sched_barrier(0);
+    rows.put(g, buf, ppitch);
   }
   xf.commit();
   __syncthreads();
-  block_dst<T, LOGN>(buf, R, ppitch, xf);
+  block_dst<T, LOGN>(buf, ppitch, xf);
   if constexpr (!OUT) {
-    rows_to_plane<T, RC, LOGN>(g, R, j0, buf, ppitch, a.plane + b * plane);
+    rows_to_plane<T, R, LOGN>(g, j0, buf, ppitch, a.plane + b * plane);
   } else {
     T* __restrict__ dst = a.nodes_out + b * nodes;
-    for_row_elems<RC, LOGN, 16>(R, [&](int e) {
+    for_row_elems<R, LOGN>([&](int e) {
       const int r = e >> LOGN, i = e & (n - 1);
       const int j = j0 + r;
       const T v = buf[RowLay<T, LOGN>::rpos(n, ppitch, r, i)];
@@ -226,12 +223,12 @@ k_row_nodes(Geom g, NodeRowArgs<T> a, AxisTables<T> tx) {
   }
 }
 
-template <typename T, int LOGN, int RC>
+template <typename T, int LOGN>
 __global__ void __launch_bounds__(kBlock, dst_blocks_per_cu(LOGN, sizeof(T)))
 k_row_inv_pc(Geom g, PCArgs<T> a, AxisTables<T> tx, DevCounters* ctr) {
   if (ctr->pc_done) return;
   extern __shared__ __align__(16) unsigned char smem_raw[];
-  row_inv_pc_block<T, LOGN, RC>(g, a, tx, xcd_strip(blockIdx.x, gridDim.x), blockIdx.y, smem_raw);
+  row_inv_pc_block<T, LOGN>(g, a, tx, xcd_strip(blockIdx.x, gridDim.x), blockIdx.y, smem_raw);
 }
 
 // ---------------------------------------------------------------------------
@@ -245,33 +242,15 @@ static void allow_lds(const void* fn, size_t lds) {
                                 static_cast<int>(lds)));
 }
 
-// A pass must not give a workgroup other rows than its transform takes:
-// sym_rows for the symmetric core, at most one group of row pairs (one pair
-// for the wave core, max(1, 512/n) otherwise) per wave for the others.
-template <typename T>
-static void check_rows(int n, int rows) {
-  if (sym_core(sizeof(T), n)) {
-    if (rows != sym_rows(n)) throw std::invalid_argument("transform pass: wrong rows for the symmetric core");
-    return;
-  }
-  const int per = wave_core(sizeof(T), n) || n >= 512 ? 1 : 512 / n;
-  if (rows > 2 * per * (kBlock / 64))
-    throw std::invalid_argument("transform pass: more row pairs than its waves take");
-}
-
 template <typename T>
 void launch_src_fwd_pez(const Geom& g, const SrcPEZ<T>& a, const AxisTables<T>& tx,
                         hipStream_t st) {
-  const int R = g.rr;
-  check_rows<T>(g.nx, R);
-  const size_t lds = static_cast<size_t>(R / 2) * pair_pitch<T>(g.nx) * sizeof(T) + table_bytes<T>(g.nx);
+  const int R = pass_rows<T>(g.nx);
+  const size_t lds = pass_lds<T>(R, g.nx);
   with_logn(g.nx, [&](auto e) {
     constexpr int E = decltype(e)::value;
-    with_rows<T, E>(R, [&](auto rc) {
-      constexpr int RC = decltype(rc)::value;
-      allow_lds(reinterpret_cast<const void*>(&k_src_fwd_pez<T, E, RC>), lds);
-      hipLaunchKernelGGL((k_src_fwd_pez<T, E, RC>), dim3(g.ny / R, 3), dim3(kBlock), lds, st, g, a, tx);
-    });
+    allow_lds(reinterpret_cast<const void*>(&k_src_fwd_pez<T, E>), lds);
+    hipLaunchKernelGGL((k_src_fwd_pez<T, E>), dim3(g.ny / R, 3), dim3(kBlock), lds, st, g, a, tx);
   });
   QSP_LAUNCH_CHECK();
 }
@@ -279,17 +258,13 @@ void launch_src_fwd_pez(const Geom& g, const SrcPEZ<T>& a, const AxisTables<T>& 
 template <typename T>
 void launch_src_fwd_bxby(const Geom& g, const SrcBxBy<T>& a, const AxisTables<T>& tx,
                          const DevCounters* ctr, hipStream_t st) {
-  const int R = g.rr;
-  check_rows<T>(g.nx, R);
-  const size_t lds = static_cast<size_t>(R / 2) * pair_pitch<T>(g.nx) * sizeof(T) + table_bytes<T>(g.nx);
+  const int R = pass_rows<T>(g.nx);
+  const size_t lds = pass_lds<T>(R, g.nx);
   with_logn(g.nx, [&](auto e) {
     constexpr int E = decltype(e)::value;
-    with_rows<T, E>(R, [&](auto rc) {
-      constexpr int RC = decltype(rc)::value;
-      allow_lds(reinterpret_cast<const void*>(&k_src_fwd_bxby<T, E, RC>), lds);
-      hipLaunchKernelGGL((k_src_fwd_bxby<T, E, RC>), dim3(g.ny / R, 2), dim3(kBlock), lds, st, g, a, tx,
-                         ctr);
-    });
+    allow_lds(reinterpret_cast<const void*>(&k_src_fwd_bxby<T, E>), lds);
+    hipLaunchKernelGGL((k_src_fwd_bxby<T, E>), dim3(g.ny / R, 2), dim3(kBlock), lds, st, g, a, tx,
+                       ctr);
   });
   QSP_LAUNCH_CHECK();
 }
@@ -298,15 +273,11 @@ template <typename T>
 void launch_col_solve(const Geom& g, const ColArgs<T>& a, int nfield, const AxisTables<T>& ty,
                       const double* lamx, const DevCounters* ctr, hipStream_t st) {
   const int W = a.w;
-  if (W < 2 || (W & (W - 1)) || g.nx % W || nfield < 1 || nfield > 4)
+  if (W != pass_cols<T>(g.ny) || nfield < 1 || nfield > 4)
     throw std::invalid_argument("column pass: bad strip width or field count");
-  if (sym_core(sizeof(T), g.ny) ? W != sym_cols(g.ny) : wave_core(sizeof(T), g.ny) && W != 4)
-    throw std::invalid_argument("column pass: wrong columns for the transform core");
-  if (!sym_core(sizeof(T), g.ny)) check_rows<T>(g.ny, W);
   if (g.strip && W != 4)   // a strip of the intermediate planes is 4 columns
     throw std::invalid_argument("column pass: strip-ordered planes need strips of 4 columns");
-  const size_t lds = static_cast<size_t>(W / 2) * pair_pitch<T>(g.ny) * sizeof(T) + table_bytes<T>(g.ny) +
-                     lam_bytes<T>(g.ny, W);
+  const size_t lds = pass_lds<T>(W, g.ny);
   with_logn(g.ny, [&](auto e) {
     constexpr int E = decltype(e)::value;
     allow_lds(reinterpret_cast<const void*>(&k_col_solve<T, E>), lds);
@@ -319,16 +290,12 @@ void launch_col_solve(const Geom& g, const ColArgs<T>& a, int nfield, const Axis
 template <typename T>
 void launch_row_inv(const Geom& g, const RowInvArgs<T>& a, int nfield, const AxisTables<T>& tx,
                     hipStream_t st) {
-  const int R = g.rr;
-  check_rows<T>(g.nx, R);
-  const size_t lds = static_cast<size_t>(R / 2) * pair_pitch<T>(g.nx) * sizeof(T) + table_bytes<T>(g.nx);
+  const int R = pass_rows<T>(g.nx);
+  const size_t lds = pass_lds<T>(R, g.nx);
   with_logn(g.nx, [&](auto e) {
     constexpr int E = decltype(e)::value;
-    with_rows<T, E>(R, [&](auto rc) {
-      constexpr int RC = decltype(rc)::value;
-      allow_lds(reinterpret_cast<const void*>(&k_row_inv<T, E, RC>), lds);
-      hipLaunchKernelGGL((k_row_inv<T, E, RC>), dim3(g.ny / R, nfield), dim3(kBlock), lds, st, g, a, tx);
-    });
+    allow_lds(reinterpret_cast<const void*>(&k_row_inv<T, E>), lds);
+    hipLaunchKernelGGL((k_row_inv<T, E>), dim3(g.ny / R, nfield), dim3(kBlock), lds, st, g, a, tx);
   });
   QSP_LAUNCH_CHECK();
 }
@@ -336,24 +303,20 @@ void launch_row_inv(const Geom& g, const RowInvArgs<T>& a, int nfield, const Axi
 template <typename T>
 void launch_row_nodes(const Geom& g, const NodeRowArgs<T>& a, bool out, int nbatch,
                       const AxisTables<T>& tx, hipStream_t st) {
-  const int R = g.rr;
+  const int R = pass_rows<T>(g.nx);
   if (nbatch < 1 || nbatch > 4 || !a.plane || (out ? !a.nodes_out : !a.nodes_in))
     throw std::invalid_argument("node row pass: bad planes or batch");
-  check_rows<T>(g.nx, R);
-  const size_t lds = static_cast<size_t>(R / 2) * pair_pitch<T>(g.nx) * sizeof(T) + table_bytes<T>(g.nx);
+  const size_t lds = pass_lds<T>(R, g.nx);
   with_logn(g.nx, [&](auto e) {
     constexpr int E = decltype(e)::value;
-    with_rows<T, E>(R, [&](auto rc) {
-      constexpr int RC = decltype(rc)::value;
-      const dim3 grid(g.ny / R, nbatch);
-      if (out) {
-        allow_lds(reinterpret_cast<const void*>(&k_row_nodes<T, E, RC, true>), lds);
-        hipLaunchKernelGGL((k_row_nodes<T, E, RC, true>), grid, dim3(kBlock), lds, st, g, a, tx);
-      } else {
-        allow_lds(reinterpret_cast<const void*>(&k_row_nodes<T, E, RC, false>), lds);
-        hipLaunchKernelGGL((k_row_nodes<T, E, RC, false>), grid, dim3(kBlock), lds, st, g, a, tx);
-      }
-    });
+    const dim3 grid(g.ny / R, nbatch);
+    if (out) {
+      allow_lds(reinterpret_cast<const void*>(&k_row_nodes<T, E, true>), lds);
+      hipLaunchKernelGGL((k_row_nodes<T, E, true>), grid, dim3(kBlock), lds, st, g, a, tx);
+    } else {
+      allow_lds(reinterpret_cast<const void*>(&k_row_nodes<T, E, false>), lds);
+      hipLaunchKernelGGL((k_row_nodes<T, E, false>), grid, dim3(kBlock), lds, st, g, a, tx);
+    }
   });
   QSP_LAUNCH_CHECK();
 }
@@ -361,17 +324,13 @@ void launch_row_nodes(const Geom& g, const NodeRowArgs<T>& a, bool out, int nbat
 template <typename T>
 void launch_row_inv_pc(const Geom& g, const PCArgs<T>& a, const AxisTables<T>& tx,
                        DevCounters* ctr, hipStream_t st) {
-  const int R = g.rr;
-  check_rows<T>(g.nx, R);
-  const size_t lds = static_cast<size_t>(R / 2) * pair_pitch<T>(g.nx) * sizeof(T) + table_bytes<T>(g.nx);
+  const int R = pass_rows<T>(g.nx);
+  const size_t lds = pass_lds<T>(R, g.nx);
   with_logn(g.nx, [&](auto e) {
     constexpr int E = decltype(e)::value;
-    with_rows<T, E>(R, [&](auto rc) {
-      constexpr int RC = decltype(rc)::value;
-      allow_lds(reinterpret_cast<const void*>(&k_row_inv_pc<T, E, RC>), lds);
-      hipLaunchKernelGGL((k_row_inv_pc<T, E, RC>), dim3(g.ny / R, 2), dim3(kBlock), lds, st, g, a, tx,
-                         ctr);
-    });
+    allow_lds(reinterpret_cast<const void*>(&k_row_inv_pc<T, E>), lds);
+    hipLaunchKernelGGL((k_row_inv_pc<T, E>), dim3(g.ny / R, 2), dim3(kBlock), lds, st, g, a, tx,
+                       ctr);
   });
   QSP_LAUNCH_CHECK();
 }
@@ -379,11 +338,15 @@ void launch_row_inv_pc(const Geom& g, const PCArgs<T>& a, const AxisTables<T>& t
 int pc_partial_count(const Geom& g) { return 2 * (g.ny / g.rr); }
 
 template <typename T>
-int col_width(const Geom& g, int nfield) {
-  return col_strip<T>(g.nx, g.ny, nfield);
+int col_width(const Geom& g, int) {
+  return pass_cols<T>(g.ny);
 }
 template int col_width<float>(const Geom&, int);
 template int col_width<double>(const Geom&, int);
+template <typename T>
+int row_rows(int nx, int) {
+  return pass_rows<T>(nx);
+}
 template int row_rows<float>(int, int);
 template int row_rows<double>(int, int);
 

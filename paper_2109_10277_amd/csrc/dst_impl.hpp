@@ -1,9 +1,6 @@
 // Batched 2D Dirichlet Poisson / Helmholtz solves with type-I sine transforms
 // (fast Poisson solver of HiPACE++, arXiv:2109.10277 Sec. III.B), written for
-// gfx950: every 1D transform runs inside LDS, two real rows packed into one
-// complex FFT (Stockham, radix 8 with a radix-4/2 tail, one wavefront per
-// group of row pairs), with a pre-twiddle that reduces the DST-I of length
-// n-1 to a complex FFT of length n per row pair.
+// gfx950: every 1D transform runs inside LDS.
 //
 // Three passes per solve:
 //   P1 (row pass)     source assembly (FP64 deposits -> T) fused with the
@@ -16,12 +13,10 @@
 //                      its FP64 residual reduction).
 //
 // Transform used (per row x_0..x_{n-1}, x_0 = x_n = 0):
-//   S_p = sum_j x_j sin(pi j p / n).  With y_j = sin(pi j/n)(x_j + x_{n-j})
-//   + (x_j - x_{n-j})/2 and Y = DFT_n(y): S_{2q} = -Im Y_q and
-//   S_{2q+1} = S_{2q-1} + Re Y_q (S_1 = Re Y_0 / 2), i.e. odd outputs are a
-//   prefix sum.  Two rows a, b are transformed together as DFT(y_a + i y_b).
-//   Inverse: x = (2/n) S(S(x)); the 2D factor 4/(nx ny) is folded into the
-//   eigenvalue division of P2.
+//   S_p = sum_j x_j sin(pi j p / n); inverse x = (2/n) S(S(x)), the 2D factor
+//   4/(nx ny) folded into the eigenvalue division of P2.  Three cores, chosen
+//   by the row length (sym_core, wave_core in common.hpp): a matrix product
+//   for 16 to 64 points, complex FFTs of the odd extension for the others.
 #pragma once
 
 #include <stdexcept>
@@ -39,34 +34,8 @@ __device__ inline Cplx<T> cmul(Cplx<T> a, Cplx<T> b) {
   return {a.re * b.re - a.im * b.im, a.re * b.im + a.im * b.re};
 }
 
-// LDS layout of a row pair.  One pad element per 128-byte bank row keeps the
-// strided accesses of the FFT stages and of the odd-entry scan from piling
-// onto the same banks.  Complex element m of a pair sits at cidx(m); real
-// element i of row a at ridx(i), of row b at rlen(n) + ridx(i).
-template <typename T>
-struct Pad {
-  static constexpr int cs = sizeof(T) == 4 ? 4 : 3;
-  static constexpr int rs = sizeof(T) == 4 ? 5 : 4;
-  __host__ __device__ static int cidx(int m) { return m + (m >> cs); }
-  __host__ __device__ static int ridx(int i) { return i + (i >> rs); }
-  __host__ __device__ static int rlen(int n) { return n + (n >> rs); }
-  // T units per row pair (even, so complex views stay aligned)
-  __host__ __device__ static int pitch(int n) {
-    const int c = 2 * (n + (n >> cs)), r = 2 * rlen(n);
-    return (c > r ? c : r) + 2;
-  }
-  __host__ __device__ static int rpos(int n, int pitch, int r, int i) {
-    return (r >> 1) * pitch + (r & 1) * rlen(n) + ridx(i);
-  }
-};
-
-// ---------------------------------------------------------------------------
-// Wave-level transforms.  Each wavefront owns a group of P row pairs
-// (P * n >= 512 complex points, P = max(1, 512 / n)) and transforms them in
-// its own part of LDS: no workgroup barrier inside a transform.  LDS
-// operations of one wavefront execute in order, so a wave-local exchange
-// only needs the compiler kept from reordering across the sync point.
-// ---------------------------------------------------------------------------
+// Orders the LDS accesses of one wavefront: they execute in order, so an
+// exchange inside a wave only needs the compiler kept from reordering them.
 __device__ inline void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
@@ -122,214 +91,10 @@ __device__ __forceinline__ void dft8(Cplx<T>* v) {
   }
 }
 
-// One Stockham pass of radix R (8, 4 or 2) over the npg sequences of a
-// group (sequence f at z + f*cp, complex units), stride ns = 8^.. so far:
-// butterfly j reads s[j + m n/R] * w^(m k n/(R ns)) (k = j mod ns) and
-// writes its DFT_R outputs to s[(j/ns) R ns + k + r ns].  NB bounds the
-// butterflies per lane.
-template <typename T, int R, int NB, int logn, int lns>
-__device__ __forceinline__ void wave_pass(Cplx<T>* z, int cp, int npg, const Cplx<T>* __restrict__ tw) {
-  using P = Pad<T>;
-  constexpr int LR = R == 8 ? 3 : (R == 4 ? 2 : 1);
-  const int lane = threadIdx.x & 63;
-  constexpr int n = 1 << logn;
-  constexpr int q = n >> LR;
-  constexpr int ns = 1 << lns;
-  const int nbf = q * npg;
-  Cplx<T> v[NB][R];
-#pragma unroll
-  for (int it = 0; it < NB; ++it) {
-    const int b = lane + it * 64;
-    if (b < nbf) {
-      const int f = b >> (logn - LR);
-      const int j = b & (q - 1);
-      const int k = j & (ns - 1);
-      const int step = k << (logn - LR - lns);
-      const Cplx<T>* s = z + f * cp;
-      v[it][0] = s[P::cidx(j)];
-#pragma unroll
-      for (int m = 1; m < R; ++m) v[it][m] = cmul(s[P::cidx(j + m * q)], tw[m * step]);
-    }
-  }
-  wave_sync();
-#pragma unroll
-  for (int it = 0; it < NB; ++it) {
-    const int b = lane + it * 64;
-    if (b < nbf) {
-      if (R == 8) dft8(v[it]);
-      if (R == 4) dft4(v[it][0], v[it][1], v[it][2], v[it][3]);
-      if (R == 2) {
-        const Cplx<T> t0 = v[it][0];
-        v[it][0] = cadd(t0, v[it][1]);
-        v[it][1] = csub(t0, v[it][1]);
-      }
-      const int f = b >> (logn - LR);
-      const int j = b & (q - 1);
-      const int k = j & (ns - 1);
-      const int d0 = ((j >> lns) << (lns + LR)) + k;
-      Cplx<T>* o = z + f * cp;
-#pragma unroll
-      for (int r = 0; r < R; ++r) o[P::cidx(d0 + r * ns)] = v[it][r];
-    }
-  }
-  wave_sync();
-}
-
-// Stockham passes after the first: radix 8 while three or more factors of
-// 2 are left, then one radix-4 or radix-2 pass (schedule fixed at compile
-// time, so every index is a constant shift)
-template <typename T, int E, int logn, int lns>
-__device__ __forceinline__ void wave_passes(Cplx<T>* z, int cp, int npg, const Cplx<T>* __restrict__ tw) {
-  if constexpr (lns + 3 <= logn) {
-    wave_pass<T, 8, E / 8, logn, lns>(z, cp, npg, tw);
-    wave_passes<T, E, logn, lns + 3>(z, cp, npg, tw);
-  } else if constexpr (lns + 2 == logn) {
-    wave_pass<T, 4, E / 4, logn, lns>(z, cp, npg, tw);
-  } else if constexpr (lns + 1 == logn) {
-    wave_pass<T, 2, E / 2, logn, lns>(z, cp, npg, tw);
-  }
-}
-
-// Type-I sine transform of the npg row pairs of one group, by one wave.
-// Pair f holds rows a (at g + f*ppitch) and b (at + rlen(n)), entry 0 = 0;
-// on return entry p of each row holds S_p.  E = complex points per lane.
-template <typename T, int E, int logn>
-__device__ __forceinline__ void wave_dst(T* g, int npg, int ppitch, const Cplx<T>* __restrict__ tw,
-                         const T* __restrict__ pre) {
-  using P = Pad<T>;
-  const int lane = threadIdx.x & 63;
-  constexpr int n = 1 << logn;
-  const int cp = ppitch / 2;
-  Cplx<T>* z = reinterpret_cast<Cplx<T>*>(g);
-  // A + first radix-8 pass: pre-twiddle straight into the butterfly inputs
-  // (the first pass has no twiddles: k = 0)
-  {
-    constexpr int NB = E / 8;
-    constexpr int q = n >> 3;
-    const int nbf = q * npg;
-    Cplx<T> v[NB][8];
-#pragma unroll
-    for (int it = 0; it < NB; ++it) {
-      const int b = lane + it * 64;
-      if (b < nbf) {
-        const int f = b >> (logn - 3);
-        const int j = b & (q - 1);
-        const T* ra = g + f * ppitch;
-        const T* rb = ra + P::rlen(n);
-#pragma unroll
-        for (int m = 0; m < 8; ++m) {
-          const int p = j + m * q;
-          const T s = pre[p];
-          const T a0 = ra[P::ridx(p)], b0 = rb[P::ridx(p)];
-          const T a1 = p ? ra[P::ridx(n - p)] : T(0);
-          const T b1 = p ? rb[P::ridx(n - p)] : T(0);
-          v[it][m] = {s * (a0 + a1) + T(0.5) * (a0 - a1), s * (b0 + b1) + T(0.5) * (b0 - b1)};
-        }
-      }
-    }
-    wave_sync();
-#pragma unroll
-    for (int it = 0; it < NB; ++it) {
-      const int b = lane + it * 64;
-      if (b < nbf) {
-        dft8(v[it]);
-        const int f = b >> (logn - 3);
-        const int j = b & (q - 1);
-        Cplx<T>* o = z + f * cp;
-#pragma unroll
-        for (int r = 0; r < 8; ++r) o[P::cidx(8 * j + r)] = v[it][r];
-      }
-    }
-    wave_sync();
-  }
-  wave_passes<T, E, logn, 3>(z, cp, npg, tw);
-  // C: unpack the two real spectra; even outputs directly, odd ones as the
-  //    increments of the prefix sum
-  {
-    constexpr int NQ = E / 2;
-    constexpr int h = n >> 1;
-    const int nq = h * npg;
-    T sa[NQ], ra_[NQ], sb[NQ], rb_[NQ];
-#pragma unroll
-    for (int it = 0; it < NQ; ++it) {
-      const int e = lane + it * 64;
-      if (e < nq) {
-        const int f = e >> (logn - 1);
-        const int q = e & (h - 1);
-        const Cplx<T>* zz = z + f * cp;
-        const Cplx<T> zq = zz[P::cidx(q)];
-        const Cplx<T> zm = zz[P::cidx((n - q) & (n - 1))];
-        sa[it] = q ? T(0.5) * (zm.im - zq.im) : T(0);
-        sb[it] = q ? T(0.5) * (zq.re - zm.re) : T(0);
-        ra_[it] = q ? T(0.5) * (zq.re + zm.re) : T(0.5) * zq.re;
-        rb_[it] = q ? T(0.5) * (zq.im + zm.im) : T(0.5) * zq.im;
-      }
-    }
-    wave_sync();
-#pragma unroll
-    for (int it = 0; it < NQ; ++it) {
-      const int e = lane + it * 64;
-      if (e < nq) {
-        const int f = e >> (logn - 1);
-        const int q = e & (h - 1);
-        T* a = g + f * ppitch;
-        T* b = a + P::rlen(n);
-        a[P::ridx(2 * q)] = sa[it];
-        a[P::ridx(2 * q + 1)] = ra_[it];
-        b[P::ridx(2 * q)] = sb[it];
-        b[P::ridx(2 * q + 1)] = rb_[it];
-      }
-    }
-    wave_sync();
-  }
-  // D: odd outputs = inclusive prefix sums of the odd entries, per row.
-  //    The 2*npg rows of the group hold n/2 odd entries each; a lane takes
-  //    c = E/... consecutive entries of one row, the lanes of a row scan
-  //    their chunk totals with shuffles.
-  {
-    constexpr int h = n >> 1;
-    const int total = 2 * npg * h;              // odd entries in the group
-    const int c = total >= 64 ? total / 64 : 1; // entries per lane
-    const int active = total / c;
-    const int tpr = h / c;                      // lanes per row (power of 2, <= 64)
-    T loc[E];
-    T run = T(0);
-    int row = 0, q0 = 0;
-    if (lane < active) {
-      row = (lane * c) / h;
-      q0 = (lane * c) % h;
-      T* r = g + (row >> 1) * ppitch + (row & 1) * P::rlen(n);
-#pragma unroll
-      for (int t = 0; t < E; ++t) {
-        if (t < c) {
-          run += r[P::ridx(2 * (q0 + t) + 1)];
-          loc[t] = run;
-        }
-      }
-    }
-    T incl = run;
-    for (int off = 1; off < tpr; off <<= 1) {
-      const T o = __shfl_up(incl, off, 64);
-      if ((lane & (tpr - 1)) >= off) incl += o;
-    }
-    const T excl = incl - run;
-    wave_sync();
-    if (lane < active) {
-      T* r = g + (row >> 1) * ppitch + (row & 1) * P::rlen(n);
-#pragma unroll
-      for (int t = 0; t < E; ++t)
-        if (t < c) r[P::ridx(2 * (q0 + t) + 1)] = loc[t] + excl;
-    }
-    wave_sync();
-  }
-}
-
-
 // ---------------------------------------------------------------------------
-// FP32 core for n = 256 and 512 without a recurrence.  The odd outputs of
-// the half-length transform above come from a prefix sum, whose FP32
-// round-off grows like sqrt(n) and, through the centred differences taken of
-// the solved fields, reaches ~1e-4 of Ey+Bx at 512^2-1024^2.  Here the two
+// FP32 core for n = 256 and 512, without a recurrence (a half-length FFT with
+// a prefix sum for the odd outputs loses ~1e-4 of Ey+Bx at 512^2-1024^2 through
+// the centred differences taken of the solved fields).  The two
 // rows a, b of a pair are extended oddly to length N = 2n (z_j = a_j + i b_j,
 // z_{2n-j} = -z_j, z_0 = z_n = 0) and transformed by one complex FFT of
 // length N: with X = DFT_N(z), S^a_p = -Im X_p / 2 and S^b_p = Re X_p / 2.
@@ -770,9 +535,105 @@ __device__ __forceinline__ void sym_dst(T* buf, const SymTw<T, LOGN>& w, const C
   }
 }
 
-// T units per row pair in LDS: the two padded rows, for the wave core the P
-// rows of its transposes (laid over the rows), for the symmetric core the
-// rows followed by its exchange region.
+// ---------------------------------------------------------------------------
+// Matrix core (n = 16, 32, 64): the transform of 16 rows as a product with the
+// sine matrix on the matrix cores (16x16x4 in the field's own precision, FP32
+// or FP64).  Such rows are bound by the length of the chain, not by
+// operations: one LDS read of the operand, at most 8 dependent matrix
+// instructions and one LDS write take the place of a half-length FFT with its
+// three exchanges and a prefix sum (64^2 in FP32: column pass 8.8 us, row
+// passes 5.8-6.0).
+// From 32 points up sin(pi (n - m) k / n) = -(-1)^k sin(pi m k / n) folds a row
+// to f_m + f_{n-m} for the odd outputs and f_m - f_{n-m} for the even ones,
+// m < n/2, with f_{n/2} in the place of the pair m = 0 (odd outputs only): each
+// wave forms 16 outputs of one parity from n/2 products.
+// A lane holds row l % 16 and the K/4 operands m = (K/4) (l / 16) + s, s < K/4,
+// of step s, both of the rows and of the matrix, so it reads consecutive
+// values: rows lie in LDS with f_m at m and f_{n-m} at n/2 + m (pos), 16 bytes
+// of padding after each row, which puts a quarter wave's 16-byte reads on
+// distinct banks.
+// ---------------------------------------------------------------------------
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ f32x4 mfma4(float a, float b, f32x4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
+__device__ __forceinline__ f64x4 mfma4(double a, double b, f64x4 c) {
+  return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+}
+
+constexpr int kDenseRows = 16;   // rows (columns) per workgroup
+
+template <typename T, int LOGN>
+struct Dense {
+  static constexpr int n = 1 << LOGN;
+  static constexpr bool fold = dense_fold(n);
+  static constexpr int KL = dense_lane(n);     // operands per lane
+  static constexpr int NT = n / 16;            // tiles of 16 outputs, one wave each
+  static constexpr int pitch = n + 16 / static_cast<int>(sizeof(T));
+  using V4 = std::conditional_t<sizeof(T) == 4, f32x4, f64x4>;
+  __host__ __device__ static constexpr int ridx(int i) {
+    return fold && i >= n / 2 ? n / 2 + ((n - i) & (n / 2 - 1)) : i;
+  }
+  __host__ __device__ static constexpr int rlen(int) { return pitch; }
+  __host__ __device__ static constexpr int rpos(int, int, int r, int i) { return r * pitch + ridx(i); }
+  // row of the 16x16 result that register r of a lane holds (column l % 16)
+  __device__ static __forceinline__ int row_of(int lane, int r) {
+    return sizeof(T) == 4 ? 4 * (lane >> 4) + r : (lane >> 4) + 4 * r;
+  }
+  // the lane's matrix operands: tile `tile` of an axis' table
+  struct Tab {
+    T a[KL];
+  };
+  static __device__ __forceinline__ Tab load(const Cplx<T>* tw, int tile) {
+    Tab t;
+    const T* p = reinterpret_cast<const T*>(tw) + (tile * 64 + (static_cast<int>(threadIdx.x) & 63)) * KL;
+#pragma unroll
+    for (int s = 0; s < KL; ++s) t.a[s] = p[s];
+    return t;
+  }
+  // 16 outputs of 16 rows at f (pitch `pitch`): the tile's columns
+  static __device__ __forceinline__ V4 tile_of(const T* f, const Tab& t, bool odd) {
+    const int lane = static_cast<int>(threadIdx.x) & 63;
+    const T* p = f + (lane & 15) * pitch + KL * (lane >> 4);
+    T v[KL];
+#pragma unroll
+    for (int s = 0; s < KL; ++s) v[s] = p[s];
+    if constexpr (fold) {
+      const T sign = odd ? T(1) : T(-1);
+#pragma unroll
+      for (int s = 0; s < KL; ++s) v[s] += sign * p[n / 2 + s];
+    }
+    V4 acc = {T(0), T(0), T(0), T(0)};
+#pragma unroll
+    for (int s = 0; s < KL; ++s) acc = mfma4(v[s], t.a[s], acc);
+    return acc;
+  }
+};
+
+// One transform of the kDenseRows rows at buf; epi(row, output, value) gives
+// what is stored.  Ends without a barrier.
+template <typename T, int LOGN, typename Epi>
+__device__ __forceinline__ void dense_dst(T* buf, const typename Dense<T, LOGN>::Tab& t, Epi&& epi) {
+  using D = Dense<T, LOGN>;
+  const int wave = static_cast<int>(threadIdx.x) >> 6, lane = static_cast<int>(threadIdx.x) & 63;
+  typename D::V4 v;
+  if (wave < D::NT) v = D::tile_of(buf, t, wave & 1);
+  __syncthreads();   // the rows are read
+  if (wave < D::NT) {
+    const int o = dense_out(D::n, wave, lane & 15);
+    T* out = buf + D::ridx(o);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int row = D::row_of(lane, r);
+      out[row * D::pitch] = epi(row, o, v[r]);
+    }
+  }
+}
+
+// T units per row pair in LDS: the two padded rows with the matrix core, for
+// the wave core the P rows of its transposes (laid over the rows), for the
+// symmetric core the rows followed by its exchange region.
 template <typename T>
 __host__ __device__ constexpr int pair_pitch(int n) {
   if (sym_core(sizeof(T), n))
@@ -782,20 +643,20 @@ __host__ __device__ constexpr int pair_pitch(int n) {
            : n == 1024 ? Sym<10>::pitch<T>()
                        : Sym<11>::pitch<T>();
   if (wave_core(sizeof(T), n)) return (n / 32) * kCorePitch * 2 + 8;   // = 8 (mod 32)
-  return Pad<T>::pitch(n);
+  return 2 * (n + 16 / static_cast<int>(sizeof(T)));
 }
 
-// Row pairs per workgroup of a row pass (template argument of the symmetric
-// core's pieces; the others take theirs at run time).
-template <typename T, int LOGN>
-__host__ __device__ constexpr int row_pairs() {
-  return sym_core(sizeof(T), 1 << LOGN) ? sym_rows(1 << LOGN) / 2 : 0;
+// Rows per workgroup of a row pass over rows of n values.  With the wave core
+// two, one busy wave (more, smaller workgroups fill the chip).
+template <typename T>
+__host__ __device__ constexpr int pass_rows(int n) {
+  return sym_core(sizeof(T), n) ? sym_rows(n) : (wave_core(sizeof(T), n) ? 2 : kDenseRows);
 }
 
 // The LDS row layout of a pass over rows of 2^LOGN values.
 template <typename T, int LOGN>
 using RowLay = std::conditional_t<sym_core(sizeof(T), 1 << LOGN) || wave_core(sizeof(T), 1 << LOGN),
-                                  CoreLay<T>, Pad<T>>;
+                                  CoreLay<T>, Dense<T, LOGN>>;
 
 // What a pass's transforms need besides the rows.  The tables' loads are
 // issued when it is made (stage_tables), in front of the pass's own loads;
@@ -803,16 +664,11 @@ using RowLay = std::conditional_t<sym_core(sizeof(T), 1 << LOGN) || wave_core(si
 // loads, so that no wait for a table delays them.
 //   symmetric core: the lane's stage-A twiddles in registers, stage B's in LDS
 //   wave core:      the lane's W_N^{l k1} in registers, W_64 (72) in LDS
-//   half-length:    twiddles and pre-twiddles in LDS
+//   matrix core:    the lane's matrix operands in registers
 template <int N>
 struct WaveTw {
   Cplx<float> a[N / 32 - 1];   // k1 = 1 .. P - 1
   Cplx<float> w64;
-};
-template <typename T>
-struct HalfTw {
-  Cplx<T> tw;
-  T pre;
 };
 template <typename T, int LOGN, int NP>   // NP: row pairs per workgroup (symmetric core)
 struct Xform {
@@ -820,11 +676,11 @@ struct Xform {
   static constexpr bool sym = sym_core(sizeof(T), n), wav = wave_core(sizeof(T), n);
   unsigned char* lds;
   std::conditional_t<sym, SymTw<T, (LOGN >= 7 ? LOGN : 7)>,
-                     std::conditional_t<wav, WaveTw<(wav ? n : 64)>, HalfTw<T>>>
+                     std::conditional_t<wav, WaveTw<(wav ? n : 64)>,
+                                        typename Dense<T, (LOGN <= 6 ? LOGN : 6)>::Tab>>
       w;
   // LDS places of the tables
   __device__ Cplx<T>* tw() const { return reinterpret_cast<Cplx<T>*>(lds); }
-  __device__ T* pre() const { return reinterpret_cast<T*>(lds + n * sizeof(Cplx<T>)); }
   __device__ __forceinline__ void commit() const {
     if constexpr (sym) {
       // the stage-B table, entry W_2H^{g c} at 17 g + c
@@ -833,41 +689,26 @@ struct Xform {
       if (tid < NB) tw()[17 * (tid >> 4) + (tid & 15)] = w.b;
     } else if constexpr (wav) {
       if (threadIdx.x < 72) tw()[threadIdx.x] = w.w64;
-    } else {
-      if (threadIdx.x < n) {   // n < kBlock
-        tw()[threadIdx.x] = w.tw;
-        pre()[threadIdx.x] = w.pre;
-      }
     }
   }
 };
 
-// Type-I sine transform of nrow rows (nrow even) of length n = 2^LOGN held
-// in LDS; pair f = rows (2f, 2f+1) occupies buf[f*ppitch ..) (row 2f first,
-// ppitch = pair_pitch(n)).  Entry 0 of every input row must be 0; on output
-// entry p holds S_p (entry 0 = 0).  The symmetric core takes 2 NP rows, the
-// wave core one pair per wave; otherwise groups of max(1, 512/n) pairs
-// are handed to the workgroup's waves in turn.  Ends with a workgroup barrier.
+// Type-I sine transform of 2 NP rows of length n = 2^LOGN held in LDS; pair f
+// = rows (2f, 2f+1) occupies buf[f*ppitch ..) (row 2f first, ppitch =
+// pair_pitch(n)).  Entry 0 of every input row must be 0; on output entry p
+// holds S_p (entry 0 = 0).  The wave core takes one pair per wave, the matrix
+// core kDenseRows rows.  Ends with a workgroup barrier.
 template <typename T, int LOGN, int NP>
-__device__ __forceinline__ void block_dst(T* buf, int nrow, int ppitch, const Xform<T, LOGN, NP>& x) {
+__device__ __forceinline__ void block_dst(T* buf, int ppitch, const Xform<T, LOGN, NP>& x) {
   constexpr int n = 1 << LOGN;
-  const int npair = nrow >> 1;
-  const int wave = threadIdx.x >> 6;
   if constexpr (sym_core(sizeof(T), n)) {
     sym_dst<T, LOGN, NP>(buf, x.w, x.tw());
   } else if constexpr (wave_core(sizeof(T), n)) {
-    // One pair per wave (the launchers keep nrow <= 2 * waves): no loop, whose
-    // invariant hoisting would keep the core's per-lane addresses live
-    if (wave < npair) wave_dst_core<n / 32>(buf + static_cast<size_t>(wave) * ppitch, x.w.a, x.tw());
+    const int wave = threadIdx.x >> 6;
+    if (wave < NP) wave_dst_core<n / 32>(buf + static_cast<size_t>(wave) * ppitch, x.w.a, x.tw());
   } else {
-    constexpr int per = n >= 512 ? 1 : 512 / n;
-    constexpr int E = n <= 512 ? 8 : n / 64;
-    // at most one group per wave (the launchers keep nrow <= 2 * per * waves)
-    const int ngroup = (npair + per - 1) / per;
-    if (wave < ngroup) {
-      const int npg = min(per, npair - wave * per);
-      wave_dst<T, E, LOGN>(buf + static_cast<size_t>(wave) * per * ppitch, npg, ppitch, x.tw(), x.pre());
-    }
+    static_assert(2 * NP == kDenseRows, "rows of the matrix core");
+    dense_dst<T, LOGN>(buf, x.w, [](int, int, T v) { return v; });
   }
   __syncthreads();
 }
@@ -889,47 +730,30 @@ void with_logn(int n, F&& f) {
   }
 }
 
-// Bytes of the per-axis tables a transform pass stages in LDS: twiddles and
-// pre-twiddles of the half-length transform; for the wave core the W_64
-// table (72 complex); the stage-B table for the symmetric core.
+// Bytes of the per-axis tables a transform pass stages in LDS: the W_64 table
+// (72 complex) of the wave core, the stage-B table of the symmetric core.
 template <typename T>
 __host__ __device__ inline size_t table_bytes(int n) {
   if (sym_core(sizeof(T), n))
     return static_cast<size_t>(sym_g(n) > 1 ? 17 * sym_g(n) : 0) * sizeof(Cplx<T>);
-  if (wave_core(sizeof(T), n)) return size_t(72) * sizeof(Cplx<T>);
-  return static_cast<size_t>(n) * (sizeof(Cplx<T>) + sizeof(T));
-}
-
-// Eigenvalue bytes the half-length column pass stages after the tables: the
-// strip's W x eigenvalues and the n y eigenvalues (the cores hold theirs in
-// registers).
-template <typename T>
-__host__ __device__ inline size_t lam_bytes(int n, int w) {
-  if (sym_core(sizeof(T), n) || wave_core(sizeof(T), n)) return 0;
-  return static_cast<size_t>(n + w) * sizeof(double);
+  return wave_core(sizeof(T), n) ? size_t(72) * sizeof(Cplx<T>) : 0;
 }
 
 // columns per column-pass workgroup: sym_cols with the symmetric core; four
 // with the wave core, which makes the strip order of the intermediate planes
 // possible (16-byte loads of whole strips; with two columns a lane's 8-byte
 // segments took the pass 10.7 us at 512^2 in FP32, against 9.7, and twice the
-// columns per workgroup 10.9); 512 / ny pairs (one busy wave) with the
-// half-length transform.
+// columns per workgroup 10.9); kDenseRows with the matrix core.
 template <typename T>
-inline int col_strip(int nx, int ny, int nfield) {
-  (void)nfield;
-  if (sym_core(sizeof(T), ny)) return sym_cols(ny);
-  if (wave_core(sizeof(T), ny)) return 4;
-  const int w = 2 * (512 / ny);
-  return w > nx ? nx : w;
+__host__ __device__ constexpr int pass_cols(int ny) {
+  return sym_core(sizeof(T), ny) ? sym_cols(ny) : (wave_core(sizeof(T), ny) ? 4 : kDenseRows);
 }
 
-// Issues the loads of an axis' transform tables; the LDS part goes right
-// after the workgroup's data region (Xform::commit).  Lanes without a part
-// (and the wave core's waves beyond the workgroup's npair pairs) load entry 0.
+// Issues the loads of an axis' transform tables for NP row pairs; the LDS part
+// goes right after the workgroup's data region (Xform::commit).  Lanes without
+// a part (and the wave and matrix cores' idle waves) load entry 0.
 template <typename T, int LOGN, int NP>
-__device__ __forceinline__ Xform<T, LOGN, NP> stage_tables(const AxisTables<T>& t, unsigned char* base,
-                                                           int npair) {
+__device__ __forceinline__ Xform<T, LOGN, NP> stage_tables(const AxisTables<T>& t, unsigned char* base) {
   constexpr int n = 1 << LOGN;
   Xform<T, LOGN, NP> x;
   x.lds = base;
@@ -938,13 +762,24 @@ __device__ __forceinline__ Xform<T, LOGN, NP> stage_tables(const AxisTables<T>& 
     x.w = sym_load<T, LOGN, NP>(t.tw);
   } else if constexpr (wave_core(sizeof(T), n)) {
 #pragma unroll
-    for (int k = 1; k < n / 32; ++k) x.w.a[k - 1] = t.tw[(tid >> 6) < npair ? k * 64 + (tid & 63) : 0];
+    for (int k = 1; k < n / 32; ++k) x.w.a[k - 1] = t.tw[(tid >> 6) < NP ? k * 64 + (tid & 63) : 0];
     x.w.w64 = reinterpret_cast<const Cplx<T>*>(t.pre)[tid < 72 ? tid : 0];
   } else {
-    x.w.tw = t.tw[tid < n ? tid : 0];
-    x.w.pre = t.pre[tid < n ? tid : 0];
+    x.w = Dense<T, LOGN>::load(t.tw, (tid >> 6) < Dense<T, LOGN>::NT ? tid >> 6 : 0);
   }
   return x;
+}
+
+// The tables of a row pass, placed after its rows.
+template <typename T, int LOGN>
+__device__ __forceinline__ auto stage_row_tables(const AxisTables<T>& t, unsigned char* smem_raw) {
+  constexpr int n = 1 << LOGN, np = pass_rows<T>(n) / 2;
+  return stage_tables<T, LOGN, np>(t, smem_raw + static_cast<size_t>(np) * pair_pitch<T>(n) * sizeof(T));
+}
+// LDS bytes of a pass over r rows (columns) of n values.
+template <typename T>
+inline size_t pass_lds(int r, int n) {
+  return static_cast<size_t>(r / 2) * pair_pitch<T>(n) * sizeof(T) + table_bytes<T>(n);
 }
 
 // clears the planes of z, workgroup `bid` of `nblk` taking every nblk-th
@@ -1030,35 +865,6 @@ constexpr int col_blocks_per_cu(int logn, int tsize) {
   return sym_core(tsize, 1 << logn) || wave_core(tsize, 1 << logn) ? 2 : 4;
 }
 
-// Calls f(e) for the workgroup's elements e = threadIdx.x + it*kBlock,
-// e < total.  The whole multiples of kBlock run as unrolled straight-line
-// chunks of up to CH (8, 16 or 32), so with a branch-free f the global loads
-// of a chunk are in flight together instead of one load latency per element
-// (plain copies take 32, source assembly with several loads per element 8).
-template <int CH, typename F>
-__device__ __forceinline__ void elem_chunk(int& it, F& f) {
-#pragma unroll
-  for (int u = 0; u < CH; ++u) f(static_cast<int>(threadIdx.x) + (it + u) * kBlock);
-  it += CH;
-}
-
-template <int CH = 8, typename F>
-__device__ __forceinline__ void for_elems(int total, F&& f) {
-  const int nit = total / kBlock;   // uniform across the workgroup
-  int it = 0;
-  if constexpr (CH >= 32)
-    while (it + 32 <= nit) elem_chunk<32>(it, f);
-  if constexpr (CH >= 16)
-    while (it + 16 <= nit) elem_chunk<16>(it, f);
-  while (it + 8 <= nit) elem_chunk<8>(it, f);
-  if (nit & 4) elem_chunk<4>(it, f);
-  if (nit & 2) elem_chunk<2>(it, f);
-  if (nit & 1) elem_chunk<1>(it, f);
-  for (int e = nit * kBlock + static_cast<int>(threadIdx.x); e < total; e += kBlock) f(e);
-}
-
-
-
 // Calls f(e) for e = t + u kBlock, u = 0 .. TOTAL / kBlock - 1 (TOTAL a
 // multiple of kBlock known at compile time), fully unrolled: with the row
 // length a compile-time power of two, the row and column of e and their LDS
@@ -1071,14 +877,10 @@ __device__ __forceinline__ void for_elems_ct(F&& f) {
   for (int u = 0; u < TOTAL / kBlock; ++u) f(t + u * kBlock);
 }
 
-// The elements of a block of rows of n = 2^LOGN: RC rows when RC > 0 (a
-// compile-time row count), else R rows in chunks of CH (see for_elems).
-template <int RC, int LOGN, int CH = 8, typename F>
-__device__ __forceinline__ void for_row_elems(int R, F&& f) {
-  if constexpr (RC > 0)
-    for_elems_ct<(RC << LOGN)>(f);
-  else
-    for_elems<CH>(R << LOGN, f);
+// The elements of a block of RC rows of n = 2^LOGN.
+template <int RC, int LOGN, typename F>
+__device__ __forceinline__ void for_row_elems(F&& f) {
+  for_elems_ct<(RC << LOGN)>(f);
 }
 
 // The elements of a block of rows in batches of up to U: load(e, v) for every
@@ -1096,26 +898,12 @@ __device__ __forceinline__ void elem_batch(int it, L& load, S& use) {
   for (int u = 0; u < B; ++u) use(it + u, static_cast<int>(threadIdx.x) + (it + u) * kBlock, v[u]);
 }
 template <int RC, int LOGN, int U, typename V, typename L, typename S>
-__device__ __forceinline__ void for_row_batches(int R, L&& load, S&& use) {
-  if constexpr (RC > 0) {
-    constexpr int NIT = (RC << LOGN) / kBlock;
-    constexpr int B = NIT < U ? NIT : U;
-    static_assert(NIT >= 1 && NIT % B == 0, "whole batches");
+__device__ __forceinline__ void for_row_batches(L&& load, S&& use) {
+  constexpr int NIT = (RC << LOGN) / kBlock;
+  constexpr int B = NIT < U ? NIT : U;
+  static_assert(NIT >= 1 && NIT % B == 0, "whole batches");
 #pragma unroll
-    for (int it = 0; it < NIT; it += B) elem_batch<B, V>(it, load, use);
-  } else {
-    const int total = R << LOGN;
-    const int nit = total / kBlock;   // uniform across the workgroup
-    int it = 0;
-    for (; it + U <= nit; it += U) elem_batch<U, V>(it, load, use);
-    for (; it < nit; ++it) elem_batch<1, V>(it, load, use);
-    const int e = nit * kBlock + static_cast<int>(threadIdx.x);
-    if (e < total) {
-      V v;
-      load(e, v);
-      use(nit, e, v);
-    }
-  }
+  for (int it = 0; it < NIT; it += B) elem_batch<B, V>(it, load, use);
 }
 
 // Elements per batch of a source assembly with five to seven loads each:
@@ -1143,27 +931,26 @@ __host__ __device__ constexpr int log2_rows(int R) {
   return l;
 }
 
-// The R rows j0.. of a row block between LDS and an intermediate plane of a
+// The RC rows j0.. of a row block between LDS and an intermediate plane of a
 // solve: row-major, or in the strip order (Geom::strip).
-template <typename T, int RC, int LOGN, int CH = 8>
-__device__ __forceinline__ void rows_to_plane(const Geom& g, int R, int j0, const T* buf, int ppitch,
+template <typename T, int RC, int LOGN>
+__device__ __forceinline__ void rows_to_plane(const Geom& g, int j0, const T* buf, int ppitch,
                                               T* __restrict__ out) {
   constexpr int n = 1 << LOGN;
   if (g.strip) {
-    const int lr = log2_rows(RC > 0 ? RC : R);
-    for_row_elems<RC, LOGN, CH>(R, [&](int e) {
+    for_row_elems<RC, LOGN>([&](int e) {
       int r, i;
-      strip_elem(e, lr, r, i);
-      store_at(out, strip_off(e, lr, j0, g.ny), buf[RowLay<T, LOGN>::rpos(n, ppitch, r, i)]);
+      strip_elem(e, log2_rows(RC), r, i);
+      store_at(out, strip_off(e, log2_rows(RC), j0, g.ny), buf[RowLay<T, LOGN>::rpos(n, ppitch, r, i)]);
     });
   } else {
-    for_row_elems<RC, LOGN, CH>(R, [&](int e) {
+    for_row_elems<RC, LOGN>([&](int e) {
       const int r = e >> LOGN, i = e & (n - 1);
       store_at(out, (j0 + r) * n + i, buf[RowLay<T, LOGN>::rpos(n, ppitch, r, i)]);
     });
   }
 }
-// The compile-time form in two halves: all loads, then (after whatever other
+// The way back in two halves: all loads, then (after whatever other
 // loads the pass has) the LDS stores.
 template <typename T, int RC, int LOGN>
 struct RowFetch {
@@ -1204,50 +991,13 @@ struct RowFetch {
   }
 };
 
-template <typename T, int RC, int LOGN, int CH = 32>
-__device__ __forceinline__ void plane_to_rows(const Geom& g, int R, int j0, const T* __restrict__ in,
-                                              T* buf, int ppitch) {
-  constexpr int n = 1 << LOGN;
-  if (g.strip) {
-    const int lr = log2_rows(RC > 0 ? RC : R);
-    for_row_elems<RC, LOGN, CH>(R, [&](int e) {
-      int r, i;
-      strip_elem(e, lr, r, i);
-      buf[RowLay<T, LOGN>::rpos(n, ppitch, r, i)] = load_at(in, strip_off(e, lr, j0, g.ny));
-    });
-  } else {
-    for_row_elems<RC, LOGN, CH>(R, [&](int e) {
-      const int r = e >> LOGN, i = e & (n - 1);
-      buf[RowLay<T, LOGN>::rpos(n, ppitch, r, i)] = load_at(in, (j0 + r) * n + i);
-    });
-  }
-}
-
-// Runs f(std::integral_constant<int, RC>) with RC = R (2, 4 or 8 with the
-// wave core, sym_rows with the symmetric core) for row passes of the cores,
-// RC = 0 (rows at run time) otherwise.
-template <typename T, int LOGN, typename F>
-void with_rows(int R, F&& f) {
-  constexpr int n = 1 << LOGN;
-  if constexpr (sym_core(sizeof(T), n)) {
-    constexpr int RC = sym_rows(n);
-    if (R != RC) throw std::invalid_argument("row pass: wrong rows for the symmetric core");
-    f(std::integral_constant<int, RC>{});
-  } else if constexpr (wave_core(sizeof(T), n)) {
-    if (R != 2) throw std::invalid_argument("row pass: wrong rows for the wave core");
-    f(std::integral_constant<int, 2>{});
-  } else {
-    f(std::integral_constant<int, 0>{});
-  }
-}
-
-// Source assembly (FP64) of the R rows j0.. of the Bx/By predictor-corrector:
+// Source assembly (FP64) of the rows j0.. of the Bx/By predictor-corrector:
 //   FX:      -d_y Jz + (Jy_{k-1} - Jy_{k+1}) / (2 dzeta) - shift * Bx_old
 //   else:     d_x Jz - (Jx_{k-1} - Jx_{k+1}) / (2 dzeta) - shift * By_old
-template <typename T, int LOGN, int RC, bool FX>
-__device__ __forceinline__ void src_bxby_rows(const Geom& g, const SrcBxBy<T>& a, int R, int j0,
-                                              T* buf, int ppitch) {
-  constexpr int n = 1 << LOGN;
+template <typename T, int LOGN, bool FX>
+__device__ __forceinline__ void src_bxby_rows(const Geom& g, const SrcBxBy<T>& a, int j0, T* buf,
+                                              int ppitch) {
+  constexpr int n = 1 << LOGN, R = pass_rows<T>(n);
   const double ih = FX ? -0.5 / g.hy : 0.5 / g.hx;
   const double idz = FX ? 0.5 / a.dzeta : -0.5 / a.dzeta;
   const double amp = a.beam_amp;
@@ -1260,7 +1010,7 @@ __device__ __forceinline__ void src_bxby_rows(const Geom& g, const SrcBxBy<T>& a
   // 256 c, along y those of the block's rows where a row is whole workgroups
   // wide (uniform), else per element
   constexpr int NC = n > kBlock ? n / kBlock : 1;
-  constexpr bool rows_uniform = RC > 0 && n >= kBlock;
+  constexpr bool rows_uniform = n >= kBlock;
   double gx0[NC], gx1[NC];
 #pragma unroll
   for (int c = 0; c < NC; ++c) {
@@ -1268,10 +1018,10 @@ __device__ __forceinline__ void src_bxby_rows(const Geom& g, const SrcBxBy<T>& a
     gx0[c] = load_at(a.bgx, FX ? i : (i > 0 ? i - 1 : 0));
     gx1[c] = FX ? gx0[c] : load_at(a.bgx, i + 1);
   }
-  double gy[rows_uniform ? RC + 2 : 1];
+  double gy[rows_uniform ? R + 2 : 1];
   if constexpr (rows_uniform) {
 #pragma unroll
-    for (int q = 0; q < RC + 2; ++q) gy[q] = a.bgy[j0 + q > 0 ? j0 + q - 1 : 0];
+    for (int q = 0; q < R + 2; ++q) gy[q] = a.bgy[j0 + q > 0 ? j0 + q - 1 : 0];
   }
   struct In {
     double z0, z1, p, t, s, g0, g1;
@@ -1289,8 +1039,7 @@ __device__ __forceinline__ void src_bxby_rows(const Geom& g, const SrcBxBy<T>& a
       }
     }
   };
-  for_row_batches<RC, LOGN, src_batch<T, LOGN>(), In>(
-      R,
+  for_row_batches<R, LOGN, src_batch<T, LOGN>(), In>(
       [&](int e, In& v) {
         const int i = e & (n - 1), j = j0 + (e >> LOGN);
         const int o = j * n + i;
@@ -1323,25 +1072,25 @@ __device__ __forceinline__ void src_bxby_rows(const Geom& g, const SrcBxBy<T>& a
 
 // Source assembly (FP64) + forward DST along x of row block bxi of field
 // fld (0 Bx, 1 By) of the Bx/By predictor-corrector.
-template <typename T, int LOGN, int RC>
+template <typename T, int LOGN>
 __device__ __forceinline__ void src_bxby_block(const Geom& g, const SrcBxBy<T>& a,
                                                const AxisTables<T>& tx, int bxi, int fld,
                                                unsigned char* smem_raw) {
   __syncthreads();   // the workgroup's previous use of LDS is complete
   T* buf = reinterpret_cast<T*>(smem_raw);
   constexpr int n = 1 << LOGN;   // = nx
-  const int R = RC > 0 ? RC : g.rr;
-  const int ppitch = pair_pitch<T>(n);
-  const auto xf = stage_tables<T, LOGN, row_pairs<T, LOGN>()>(tx, smem_raw + static_cast<size_t>(R / 2) * ppitch * sizeof(T), R / 2);
+  constexpr int R = pass_rows<T>(n);
+  constexpr int ppitch = pair_pitch<T>(n);
+  const auto xf = stage_row_tables<T, LOGN>(tx, smem_raw);
   const int j0 = bxi * R;
   if (fld == 0)
-    src_bxby_rows<T, LOGN, RC, true>(g, a, R, j0, buf, ppitch);
+    src_bxby_rows<T, LOGN, true>(g, a, j0, buf, ppitch);
   else
-    src_bxby_rows<T, LOGN, RC, false>(g, a, R, j0, buf, ppitch);
+    src_bxby_rows<T, LOGN, false>(g, a, j0, buf, ppitch);
   xf.commit();
   __syncthreads();
-  block_dst<T, LOGN>(buf, R, ppitch, xf);
-  rows_to_plane<T, RC, LOGN>(g, R, j0, buf, ppitch, a.out + static_cast<size_t>(fld) * g.nx * g.ny);
+  block_dst<T, LOGN>(buf, ppitch, xf);
+  rows_to_plane<T, R, LOGN>(g, j0, buf, ppitch, a.out + static_cast<size_t>(fld) * g.nx * g.ny);
 }
 
 // Calls f(it) for it = 0 .. NIT-1 in unrolled chunks of up to 32 (NIT a
@@ -1383,7 +1132,7 @@ __device__ __forceinline__ void col_block_core(const Geom& g, const ColArgs<T>& 
   const int p0 = strip * W;
   const int tid = static_cast<int>(threadIdx.x);
   const Xform<T, LOGN, W / 2> xf =
-      stage_tables<T, LOGN, W / 2>(ty, smem_raw + static_cast<size_t>(W / 2) * ppitch * sizeof(T), W / 2);
+      stage_tables<T, LOGN, W / 2>(ty, smem_raw + static_cast<size_t>(W / 2) * ppitch * sizeof(T));
   // the y eigenvalues of the lane's core outputs, fetched under the strip
   // load: by the lane itself (wave core), or through the exchange region of
   // the first pair (symmetric core: 16 scattered values a lane)
@@ -1537,70 +1286,77 @@ __device__ __forceinline__ void col_block_core(const Geom& g, const ColArgs<T>& 
   }
 }
 
+// The same with the matrix core: kDenseRows columns per workgroup, the
+// eigenvalue division on the product's result registers.
+template <typename T, int LOGN>
+__device__ __forceinline__ void col_block_dense(const Geom& g, const ColArgs<T>& a, const AxisTables<T>& ty,
+                                                const double* __restrict__ lamx, int strip, int fld,
+                                                unsigned char* smem_raw) {
+  using D = Dense<T, LOGN>;
+  constexpr int n = D::n, W = kDenseRows, N = W * n / kBlock;
+  T* buf = reinterpret_cast<T*>(smem_raw);
+  const auto xf = stage_tables<T, LOGN, W / 2>(ty, smem_raw);
+  const int p0 = strip * W;
+  const int tid = static_cast<int>(threadIdx.x), wave = tid >> 6, lane = tid & 63;
+  const unsigned int nx = g.nx;
+  const size_t plane = static_cast<size_t>(nx) * n;
+  const T* in = a.in + fld * plane;
+  // element u of a thread: column c, row j0 + u kBlock / W
+  const int c = tid & (W - 1), j0 = tid / W;
+  constexpr int JS = kBlock / W;
+  T v[N];
+#pragma unroll
+  for (int u = 0; u < N; ++u) v[u] = load_at(in, (j0 + u * JS) * nx + p0 + c);
+  double lx[4];
+#pragma unroll
+  for (int r = 0; r < 4; ++r) lx[r] = lamx[p0 + D::row_of(lane, r)];
+  const double ly = ty.lam[wave < D::NT ? dense_out(n, wave, lane & 15) : 0];
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int u = 0; u < N; ++u) buf[c * D::pitch + D::ridx(j0 + u * JS)] = v[u];
+  __syncthreads();
+  // 1 / normalisation (nx ny / 4, exact): the eigenvalue sum in FP64, the one
+  // division in the field precision
+  const double inorm = 0.25 * static_cast<double>(nx) * n;
+  const double lys = ly - a.shift[fld];
+  T den[4];
+#pragma unroll
+  for (int r = 0; r < 4; ++r) den[r] = static_cast<T>((lx[r] + lys) * inorm);
+  int q = 0;
+  dense_dst<T, LOGN>(buf, xf.w, [&](int row, int o, T s) {
+    const T z = s / den[q++];
+    return p0 + row > 0 && o > 0 ? z : T(0);
+  });
+  __syncthreads();
+  dense_dst<T, LOGN>(buf, xf.w, [](int, int, T s) { return s; });
+  __syncthreads();
+  T* out = a.out + fld * plane;
+  const T* row = buf + c * D::pitch;
+#pragma unroll
+  for (int u = 0; u < N; ++u) store_at(out, (j0 + u * JS) * nx + p0 + c, row[D::ridx(j0 + u * JS)]);
+  if (fld == 0 && a.out_dy) {
+    const T mihy = static_cast<T>(-0.5 / g.hy);
+#pragma unroll
+    for (int u = 0; u < N; ++u) {
+      const int j = j0 + u * JS;
+      const T up = row[D::ridx(j + 1 < n ? j + 1 : j)], dn = row[D::ridx(j > 0 ? j - 1 : 0)];
+      const T d = mihy * ((j + 1 < n ? up : T(0)) - dn);
+      store_at(a.out_dy, j * nx + p0 + c, j > 0 ? d : T(0));
+    }
+  }
+}
+
 // DST along y, eigenvalue division, inverse DST along y (and -d_y for
 // field 0 when requested) of column strip `strip` of field fld.
 template <typename T, int LOGN>
 __device__ __forceinline__ void col_block(const Geom& g, const ColArgs<T>& a,
                                           const AxisTables<T>& ty, const double* __restrict__ lamx,
                                           int strip, int fld, unsigned char* smem_raw) {
-  if constexpr (sym_core(sizeof(T), 1 << LOGN)) {
-    col_block_core<T, LOGN, sym_cols(1 << LOGN)>(g, a, ty, lamx, strip, fld, smem_raw);   // the launcher checks w
-    return;
-  } else if constexpr (wave_core(sizeof(T), 1 << LOGN)) {
-    col_block_core<T, LOGN, 4>(g, a, ty, lamx, strip, fld, smem_raw);
-    return;
-  } else {
-  __syncthreads();   // the workgroup's previous use of LDS is complete
-  T* buf = reinterpret_cast<T*>(smem_raw);
-  const int ny = g.ny, nx = g.nx;
-  const int W = a.w;
-  const int ppitch = pair_pitch<T>(ny);
-  const int p0 = strip * W;
-  unsigned char* tbase = smem_raw + static_cast<size_t>(W / 2) * ppitch * sizeof(T);
-  const Xform<T, LOGN, 0> xf = stage_tables<T, LOGN, 0>(ty, tbase, W / 2);
-  double* slam = reinterpret_cast<double*>(tbase + table_bytes<T>(ny));   // y eigenvalues,
-  double* slamx = slam + ny;                                               // the strip's x ones
-  if (static_cast<int>(threadIdx.x) < ny) slam[threadIdx.x] = ty.lam[threadIdx.x];   // ny < kBlock
-  if (static_cast<int>(threadIdx.x) < W) slamx[threadIdx.x] = lamx[strip * W + threadIdx.x];
-  const size_t plane = static_cast<size_t>(nx) * ny;
-  const T* in = a.in + fld * plane;
-  const int lw = 31 - __clz(W), ly = g.ly;
-  for_elems<32>(W * ny, [&](int e) {
-    const int c = e & (W - 1), j = e >> lw;
-    buf[Pad<T>::rpos(ny, ppitch, c, j)] = in[j * nx + p0 + c];
-  });
-  xf.commit();
-  __syncthreads();
-  block_dst<T, LOGN>(buf, W, ppitch, xf);
-  const double shift = a.shift[fld];
-  // 1 / normalisation (nx ny / 4, exact): the eigenvalue sum in FP64 without
-  // a division, the one division in the field precision
-  const double inorm = 0.25 * static_cast<double>(nx) * ny;
-  for_elems(W * ny, [&](int e) {
-    const int c = e >> ly, q = e & (ny - 1);
-    const int p = p0 + c;
-    T* r = buf + Pad<T>::rpos(ny, ppitch, c, 0);
-    const int iq = Pad<T>::ridx(q);
-    const T den = static_cast<T>((slamx[c] + slam[q] - shift) * inorm);
-    const T v = r[iq] / den;
-    r[iq] = (p > 0 && q > 0) ? v : T(0);
-  });
-  __syncthreads();
-  block_dst<T, LOGN>(buf, W, ppitch, xf);
-  T* out = a.out + fld * plane;
-  T* out_dy = (fld == 0) ? a.out_dy : nullptr;
-  const T mihy = static_cast<T>(-0.5 / g.hy);
-  for_elems(W * ny, [&](int e) {
-    const int c = e & (W - 1), j = e >> lw;
-    const T* r = buf + Pad<T>::rpos(ny, ppitch, c, 0);
-    out[j * nx + p0 + c] = r[Pad<T>::ridx(j)];
-    if (out_dy) {
-      const T up = r[Pad<T>::ridx(j + 1 < ny ? j + 1 : j)], dn = r[Pad<T>::ridx(j > 0 ? j - 1 : 0)];
-      const T d = mihy * ((j + 1 < ny ? up : T(0)) - dn);
-      out_dy[j * nx + p0 + c] = j > 0 ? d : T(0);
-    }
-  });
-  }
+  constexpr int n = 1 << LOGN, W = pass_cols<T>(n);   // the launcher checks the width
+  if constexpr (sym_core(sizeof(T), n) || wave_core(sizeof(T), n))
+    col_block_core<T, LOGN, W>(g, a, ty, lamx, strip, fld, smem_raw);
+  else
+    col_block_dense<T, LOGN>(g, a, ty, lamx, strip, fld, smem_raw);
 }
 
 // Predictor-corrector epilogue: B_new from the inverse transform, FP64 sums
@@ -1608,39 +1364,35 @@ __device__ __forceinline__ void col_block(const Geom& g, const ColArgs<T>& a,
 // Each workgroup leaves its two sums in a.partial; the next trial push (or
 // the real push after the last iteration) forms the relative change and
 // decides convergence.
-template <typename T, int LOGN, int RC>
+template <typename T, int LOGN>
 __device__ __forceinline__ void row_inv_pc_block(const Geom& g, const PCArgs<T>& a,
                                                  const AxisTables<T>& tx, int bxi, int fld,
                                                  unsigned char* smem_raw) {
   __syncthreads();   // the workgroup's previous use of LDS is complete
   T* buf = reinterpret_cast<T*>(smem_raw);
   constexpr int n = 1 << LOGN;   // = nx
-  const int R = RC > 0 ? RC : g.rr;
-  const int ppitch = pair_pitch<T>(n);
-  const auto xf = stage_tables<T, LOGN, row_pairs<T, LOGN>()>(tx, smem_raw + static_cast<size_t>(R / 2) * ppitch * sizeof(T), R / 2);
+  constexpr int R = pass_rows<T>(n);
+  constexpr int ppitch = pair_pitch<T>(n);
+  const auto xf = stage_row_tables<T, LOGN>(tx, smem_raw);
   const int j0 = bxi * R;
   T* b = fld == 0 ? a.bx : a.by;
   T* tp = fld == 0 ? a.tape_bx : a.tape_by;
   const T* in = a.in + static_cast<size_t>(fld) * g.nx * g.ny;
-  // with a compile-time row block the old iterate is fetched under the plane
-  // load (its own round trip after the transform took 2.8k of 18.4k cycles)
-  constexpr int NOLD = RC > 0 ? (RC << LOGN) / kBlock : 1;
+  // the old iterate is fetched under the plane load (its own round trip after
+  // the transform took 2.8k of 18.4k cycles at 1024^2 in FP32)
+  constexpr int NOLD = (R << LOGN) / kBlock;
   T old_b[NOLD];
-  if constexpr (RC > 0) {
-    RowFetch<T, RC, LOGN> rows;
-    rows.load(g, j0, in);
+  RowFetch<T, R, LOGN> rows;
+  rows.load(g, j0, in);
 #pragma unroll
-    for (int u = 0; u < NOLD; ++u) old_b[u] = load_at(b, j0 * n + static_cast<int>(threadIdx.x) + u * kBlock);
-    __builtin_amdgcn_sched_barrier(0);
-    rows.put(g, buf, ppitch);
+  for (int u = 0; u < NOLD; ++u) old_b[u] = load_at(b, j0 * n + static_cast<int>(threadIdx.x) + u * kBlock);
+  __builtin_amdgcn_sched_barrier(0);
+  rows.put(g, buf, ppitch);
 #pragma unroll
-    for (int u = 0; u < NOLD; ++u) pin(old_b[u]);
-  } else {
-    plane_to_rows<T, RC, LOGN>(g, R, j0, in, buf, ppitch);
-  }
+  for (int u = 0; u < NOLD; ++u) pin(old_b[u]);
   xf.commit();
   __syncthreads();
-  block_dst<T, LOGN>(buf, R, ppitch, xf);
+  block_dst<T, LOGN>(buf, ppitch, xf);
   double dsum = 0.0, nsum = 0.0;
   auto update = [&](int e, T prev, auto taped) {
     const int r = e >> LOGN, i = e & (n - 1);
@@ -1654,18 +1406,8 @@ __device__ __forceinline__ void row_inv_pc_block(const Geom& g, const PCArgs<T>&
     if constexpr (decltype(taped)::value) store_at(tp, j * n + i, u);
   };
   auto finish = [&](auto taped) {   // the tape tested once, not per element
-    if constexpr (RC > 0) {
 #pragma unroll
-      for (int u = 0; u < NOLD; ++u) update(static_cast<int>(threadIdx.x) + u * kBlock, old_b[u], taped);
-    } else {
-      struct In {
-        T b;
-        __device__ void pin() { dst_detail::pin(b); }
-      };
-      for_row_batches<RC, LOGN, 8, In>(
-          R, [&](int e, In& v) { v.b = b[j0 * n + e]; },
-          [&](int, int e, const In& v) { update(e, v.b, taped); });
-    }
+    for (int u = 0; u < NOLD; ++u) update(static_cast<int>(threadIdx.x) + u * kBlock, old_b[u], taped);
   };
   if (tp)
     finish(std::true_type{});
@@ -1676,15 +1418,5 @@ __device__ __forceinline__ void row_inv_pc_block(const Geom& g, const PCArgs<T>&
 }
 
 }  // namespace dst_detail
-
-// rows per row-pass workgroup: sym_rows with the symmetric core; else those
-// of one busy wave (more, smaller workgroups fill the chip; measured best from
-// HIP graphs at 64^2 and 512^2).
-template <typename T>
-int row_rows(int nx, int ny) {
-  if (sym_core(sizeof(T), nx)) return sym_rows(nx);
-  const int r = wave_core(sizeof(T), nx) ? 2 : 2 * (512 / nx);
-  return r > ny ? ny : r;
-}
 
 }  // namespace qsp

@@ -64,10 +64,10 @@ __global__ void __launch_bounds__(kBlock, dst_blocks_per_cu(LOGN, sizeof(T)))
 k_expl_setup(Geom g, ExplicitArgs<T> a, AxisTables<T> tx, DevCounters* ctr) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   T* buf = reinterpret_cast<T*>(smem_raw);
-  const int n = g.nx, ny = g.ny;
-  const int R = g.rr;
-  const int ppitch = pair_pitch<T>(n);
-  const auto xf = stage_tables<T, LOGN, row_pairs<T, LOGN>()>(tx, smem_raw + static_cast<size_t>(R / 2) * ppitch * sizeof(T), R / 2);
+  constexpr int n = 1 << LOGN, R = pass_rows<T>(n);   // n = nx
+  const int ny = g.ny;
+  constexpr int ppitch = pair_pitch<T>(n);
+  const auto xf = stage_row_tables<T, LOGN>(tx, smem_raw);
   const int fld = blockIdx.y;
   const int j0 = blockIdx.x * R;
   const size_t plane = static_cast<size_t>(n) * ny;
@@ -77,10 +77,9 @@ k_expl_setup(Geom g, ExplicitArgs<T> a, AxisTables<T> tx, DevCounters* ctr) {
   const T* B = a.b[fld];
   double* x = a.x + fld * plane;
   double* r = a.r + fld * plane;
-  const int lx = g.lx;
   double bn = 0.0, rn = 0.0;
-  for_elems(R * n, [&](int e) {
-    const int rr = e >> lx, i = e & (n - 1);
+  for_row_elems<R, LOGN>([&](int e) {
+    const int rr = e >> LOGN, i = e & (n - 1);
     const int j = j0 + rr;
     const int o = j * n + i;
     const bool inner = i > 0 && j > 0;
@@ -119,8 +118,8 @@ k_expl_setup(Geom g, ExplicitArgs<T> a, AxisTables<T> tx, DevCounters* ctr) {
   });
   xf.commit();
   __syncthreads();
-  block_dst<T, LOGN>(buf, R, ppitch, xf);
-  rows_to_plane<T, 0, LOGN>(g, R, j0, buf, ppitch, a.fwd + fld * plane);
+  block_dst<T, LOGN>(buf, ppitch, xf);
+  rows_to_plane<T, R, LOGN>(g, j0, buf, ppitch, a.fwd + fld * plane);
   double v[2] = {bn, rn};
   partials::store<2>(v, a.part_s, fld * (ny / R) + blockIdx.x);
 }
@@ -132,8 +131,8 @@ template <typename T, int LOGN>
 __global__ void __launch_bounds__(kBlock, dst_blocks_per_cu(LOGN, sizeof(T)))
 k_expl_rowinv(Geom g, ExplicitArgs<T> a, AxisTables<T> tx, DevCounters* ctr) {
   if (ctr->pc_done) return;
-  const int n = g.nx, ny = g.ny;
-  const int R = g.rr;
+  constexpr int n = 1 << LOGN, R = pass_rows<T>(n);   // n = nx
+  const int ny = g.ny;
   const int nblk = 2 * (ny / R);
   double bn, rr;
   if (a.it == 0) {
@@ -156,23 +155,25 @@ k_expl_rowinv(Geom g, ExplicitArgs<T> a, AxisTables<T> tx, DevCounters* ctr) {
   if (stop) return;
   extern __shared__ __align__(16) unsigned char smem_raw[];
   T* buf = reinterpret_cast<T*>(smem_raw);
-  const int ppitch = pair_pitch<T>(n);
-  const auto xf = stage_tables<T, LOGN, row_pairs<T, LOGN>()>(tx, smem_raw + static_cast<size_t>(R / 2) * ppitch * sizeof(T), R / 2);
+  constexpr int ppitch = pair_pitch<T>(n);
+  const auto xf = stage_row_tables<T, LOGN>(tx, smem_raw);
   const int fld = blockIdx.y;
   const int j0 = blockIdx.x * R;
   const size_t plane = static_cast<size_t>(n) * ny;
-  const int lx = g.lx;
-  plane_to_rows<T, 0, LOGN>(g, R, j0, a.col + fld * plane, buf, ppitch);
+  RowFetch<T, R, LOGN> rows;
+  rows.load(g, j0, a.col + fld * plane);
+  __builtin_amdgcn_sched_barrier(0);
+  rows.put(g, buf, ppitch);
   xf.commit();
   __syncthreads();
-  block_dst<T, LOGN>(buf, R, ppitch, xf);
+  block_dst<T, LOGN>(buf, ppitch, xf);
   T* z = a.z + fld * plane;
   const double* r = a.r + fld * plane;
   const double* q = a.q + fld * plane;
   const bool with_q = a.it > 0;
   double zr = 0.0, zq = 0.0;
-  for_elems(R * n, [&](int e) {
-    const int rw = e >> lx, i = e & (n - 1);
+  for_row_elems<R, LOGN>([&](int e) {
+    const int rw = e >> LOGN, i = e & (n - 1);
     const int j = j0 + rw;
     const int o = j * n + i;
     const T u = buf[RowLay<T, LOGN>::rpos(n, ppitch, rw, i)];
@@ -189,11 +190,11 @@ k_expl_rowinv(Geom g, ExplicitArgs<T> a, AxisTables<T> tx, DevCounters* ctr) {
 // matvec(it): rho_{it-1} = z.r and the Polak-Ribiere
 // beta = -alpha_{it-1} (z.q) / rho_{it-2}; p = z + beta p_old (p_old unused
 // in the first iteration), q = A p and partials of p.q.  Grid (ny/R, 2).
-template <typename T>
+template <typename T, int LOGN>
 __global__ void __launch_bounds__(kBlock) k_expl_matvec(Geom g, ExplicitArgs<T> a, DevCounters* ctr) {
   if (ctr->pc_done) return;
-  const int n = g.nx, ny = g.ny;
-  const int R = g.rr;
+  constexpr int n = 1 << LOGN, R = pass_rows<T>(n);   // n = nx
+  const int ny = g.ny;
   const int nblk = 2 * (ny / R);
   const int fld = blockIdx.y;
   double t[4];
@@ -218,10 +219,9 @@ __global__ void __launch_bounds__(kBlock) k_expl_matvec(Geom g, ExplicitArgs<T> 
   const double* chi = a.chi;
   const double ihx2 = 1.0 / (g.hx * g.hx), ihy2 = 1.0 / (g.hy * g.hy);
   const int j0 = blockIdx.x * R;
-  const int lx = g.lx;
   double pq = 0.0;
-  for_elems(R * n, [&](int e) {
-    const int rw = e >> lx, i = e & (n - 1);
+  for_row_elems<R, LOGN>([&](int e) {
+    const int rw = e >> LOGN, i = e & (n - 1);
     const int j = j0 + rw;
     const int o = j * n + i;
     // neighbours with clamped indices; nodes on or beyond the Dirichlet
@@ -260,8 +260,8 @@ template <typename T, int LOGN>
 __global__ void __launch_bounds__(kBlock, dst_blocks_per_cu(LOGN, sizeof(T)))
 k_expl_update(Geom g, ExplicitArgs<T> a, AxisTables<T> tx, DevCounters* ctr) {
   if (ctr->pc_done) return;
-  const int n = g.nx, ny = g.ny;
-  const int R = g.rr;
+  constexpr int n = 1 << LOGN, R = pass_rows<T>(n);   // n = nx
+  const int ny = g.ny;
   const int nblk = 2 * (ny / R);
   const int fld = blockIdx.y;
   const int it = a.it;
@@ -275,8 +275,8 @@ k_expl_update(Geom g, ExplicitArgs<T> a, AxisTables<T> tx, DevCounters* ctr) {
   }
   extern __shared__ __align__(16) unsigned char smem_raw[];
   T* buf = reinterpret_cast<T*>(smem_raw);
-  const int ppitch = pair_pitch<T>(n);
-  const auto xf = stage_tables<T, LOGN, row_pairs<T, LOGN>()>(tx, smem_raw + static_cast<size_t>(R / 2) * ppitch * sizeof(T), R / 2);
+  constexpr int ppitch = pair_pitch<T>(n);
+  const auto xf = stage_row_tables<T, LOGN>(tx, smem_raw);
   const int j0 = blockIdx.x * R;
   const size_t plane = static_cast<size_t>(n) * ny;
   const double* p = a.p[it & 1] + fld * plane;
@@ -284,10 +284,9 @@ k_expl_update(Geom g, ExplicitArgs<T> a, AxisTables<T> tx, DevCounters* ctr) {
   double* x = a.x + fld * plane;
   double* r = a.r + fld * plane;
   T* B = a.b[fld];
-  const int lx = g.lx;
   double rn = 0.0;
-  for_elems(R * n, [&](int e) {
-    const int rw = e >> lx, i = e & (n - 1);
+  for_row_elems<R, LOGN>([&](int e) {
+    const int rw = e >> LOGN, i = e & (n - 1);
     const int j = j0 + rw;
     const int o = j * n + i;
     const bool inner = i > 0 && j > 0;
@@ -301,8 +300,8 @@ k_expl_update(Geom g, ExplicitArgs<T> a, AxisTables<T> tx, DevCounters* ctr) {
   });
   xf.commit();
   __syncthreads();
-  block_dst<T, LOGN>(buf, R, ppitch, xf);
-  rows_to_plane<T, 0, LOGN>(g, R, j0, buf, ppitch, a.fwd + fld * plane);
+  block_dst<T, LOGN>(buf, ppitch, xf);
+  rows_to_plane<T, R, LOGN>(g, j0, buf, ppitch, a.fwd + fld * plane);
   double v[1] = {rn};
   partials::store<1>(v, a.part_u, fld * (ny / R) + blockIdx.x);
 }
@@ -329,11 +328,6 @@ void allow_lds_e(const void* fn, size_t lds) {
                                 static_cast<int>(lds)));
 }
 
-template <typename T>
-size_t row_lds(const Geom& g) {
-  return static_cast<size_t>(g.rr / 2) * pair_pitch<T>(g.nx) * sizeof(T) + table_bytes<T>(g.nx);
-}
-
 }  // namespace
 
 // partial records of one row-blocked grid: one per workgroup of (ny/rr, 2)
@@ -342,13 +336,8 @@ int explicit_partial_count(const Geom& g) { return 2 * (g.ny / g.rr); }
 template <typename T>
 void launch_explicit(const Geom& g, const ExplicitArgs<T>& a, ExplicitStep step,
                      const AxisTables<T>& tx, DevCounters* ctr, hipStream_t st) {
-  const int R = g.rr;
-  const size_t lds = row_lds<T>(g);
-  if (step == kExplMatvec) {
-    hipLaunchKernelGGL((k_expl_matvec<T>), dim3(g.ny / R, 2), dim3(kBlock), 0, st, g, a, ctr);
-    QSP_LAUNCH_CHECK();
-    return;
-  }
+  const int R = pass_rows<T>(g.nx);
+  const size_t lds = pass_lds<T>(R, g.nx);
   if (step == kExplClose) {
     hipLaunchKernelGGL((k_expl_close<T>), dim3(1), dim3(kBlock), 0, st, g, a, ctr);
     QSP_LAUNCH_CHECK();
@@ -357,6 +346,9 @@ void launch_explicit(const Geom& g, const ExplicitArgs<T>& a, ExplicitStep step,
   with_logn(g.nx, [&](auto e) {
     constexpr int E = decltype(e)::value;
     switch (step) {
+      case kExplMatvec:
+        hipLaunchKernelGGL((k_expl_matvec<T, E>), dim3(g.ny / R, 2), dim3(kBlock), 0, st, g, a, ctr);
+        break;
       case kExplSetup:
         allow_lds_e(reinterpret_cast<const void*>(&k_expl_setup<T, E>), lds);
         hipLaunchKernelGGL((k_expl_setup<T, E>), dim3(g.ny / R, 2), dim3(kBlock), lds, st, g, a,

@@ -60,7 +60,6 @@ __global__ void k_axis_tables(AxisJob<T> x, AxisJob<T> y) {
   double* lam = q.lam;
   const double h = q.h;
   const int m = blockIdx.x * blockDim.x + threadIdx.x;
-  if (m >= 2 * n) return;
   double s, c;
   if (qsp::sym_core(sizeof(T), n)) {
     if (m < qsp::sym_table_size(n)) {
@@ -70,6 +69,7 @@ __global__ void k_axis_tables(AxisJob<T> x, AxisJob<T> y) {
     }
   } else if (qsp::wave_core(sizeof(T), n)) {
     const int k1 = m / 64, l = m % 64;
+    if (m >= 2 * n) return;
     sincospi(-2.0 * static_cast<double>((l * k1) % (2 * n)) / (2 * n), &s, &c);
     tw[m] = {static_cast<T>(c), static_cast<T>(s)};
     if (m < 72) {
@@ -79,10 +79,9 @@ __global__ void k_axis_tables(AxisJob<T> x, AxisJob<T> y) {
       w[m] = c1 < 8 ? qsp::Cplx<T>{static_cast<T>(c), static_cast<T>(s)}
                     : qsp::Cplx<T>{T(0), T(0)};
     }
-  } else if (m < n) {
-    sincospi(-2.0 * m / n, &s, &c);
-    tw[m] = {static_cast<T>(c), static_cast<T>(s)};
-    pre[m] = static_cast<T>(sinpi(static_cast<double>(m) / n));
+  } else if (m < qsp::dense_table_size(n)) {
+    const int q_a = qsp::dense_angle(n, m);
+    reinterpret_cast<T*>(tw)[m] = q_a % n ? static_cast<T>(sinpi(static_cast<double>(q_a) / n)) : T(0);
   }
   if (m < n) {
     const double sm = sinpi(0.5 * m / n);
@@ -92,15 +91,15 @@ __global__ void k_axis_tables(AxisJob<T> x, AxisJob<T> y) {
 
 template <typename T>
 size_t axis_table_bytes(int n) {
-  return static_cast<size_t>(n) * (2 * sizeof(qsp::Cplx<T>) + sizeof(T) + sizeof(double));
+  return static_cast<size_t>(qsp::axis_tw_size(n)) * sizeof(qsp::Cplx<T>) +
+         static_cast<size_t>(n) * (sizeof(T) + sizeof(double));
 }
 
 template <typename T>
 qsp::AxisTables<T> axis_at(unsigned char* base, int n) {
   auto* tw = reinterpret_cast<qsp::Cplx<T>*>(base);
-  auto* pre = reinterpret_cast<T*>(base + static_cast<size_t>(n) * 2 * sizeof(qsp::Cplx<T>));
-  auto* lam = reinterpret_cast<double*>(base + static_cast<size_t>(n) *
-                                                   (2 * sizeof(qsp::Cplx<T>) + sizeof(T)));
+  auto* pre = reinterpret_cast<T*>(tw + qsp::axis_tw_size(n));
+  auto* lam = reinterpret_cast<double*>(pre + n);
   return {tw, pre, lam};
 }
 
@@ -129,8 +128,9 @@ void solve(const qsp_config& c, unsigned char* ptr, int nb, const T* src, T* dst
                       const_cast<double*>(tx.lam)};
   const AxisJob<T> jy{c.ny, g.hy, const_cast<Cplx<T>*>(ty.tw), const_cast<T*>(ty.pre),
                       const_cast<double*>(ty.lam)};
-  const int nmax = c.nx > c.ny ? c.nx : c.ny;
-  hipLaunchKernelGGL(k_axis_tables<T>, dim3((2 * nmax + 255) / 256, 2), dim3(256), 0, st, jx, jy);
+  auto entries = [](int n) { return n <= 64 ? dense_table_size(n) : 2 * n; };   // one thread each
+  const int mx = entries(c.nx), my = entries(c.ny);
+  hipLaunchKernelGGL(k_axis_tables<T>, dim3(((mx > my ? mx : my) + 255) / 256, 2), dim3(256), 0, st, jx, jy);
   QSP_LAUNCH_CHECK();
   // each pass reads its rows or column strips into LDS before writing them
   // back, so all three work on the same planes

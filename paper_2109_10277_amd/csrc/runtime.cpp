@@ -1398,10 +1398,10 @@ class Box final : public BoxBase {
     p_.w = alloc<T>(np);
     p_.hist = alloc<T>(20 * np);
     p_.pab = alloc<T>(5 * np);
-    twx_ = alloc<Cplx<T>>(2 * cfg_.nx);
+    twx_ = alloc<Cplx<T>>(axis_tw_size(cfg_.nx));
     prex_ = alloc<T>(cfg_.nx);
     lamx_ = alloc<double>(cfg_.nx);
-    twy_ = alloc<Cplx<T>>(2 * cfg_.ny);
+    twy_ = alloc<Cplx<T>>(axis_tw_size(cfg_.ny));
     prey_ = alloc<T>(cfg_.ny);
     lamy_ = alloc<double>(cfg_.ny);
     bgx_ = alloc<double>(cfg_.nx + 1);
@@ -1428,10 +1428,10 @@ class Box final : public BoxBase {
     if (cfg_.mem_cap_bytes > 0 && bytes_ > cfg_.mem_cap_bytes) throw std::bad_alloc();
   }
 
-  // Per-axis tables of the sine transform (tw holds 2n entries, pre n, laid
-  // out as AxisTables says) and the Laplacian eigenvalues.
+  // Per-axis tables of the sine transform (tw holds axis_tw_size entries, pre
+  // n, laid out as AxisTables says) and the Laplacian eigenvalues.
   void axis_tables(int n, double h, Cplx<T>* tw, T* pre, double* lam) {
-    std::vector<Cplx<T>> htw(2 * n);
+    std::vector<Cplx<T>> htw(axis_tw_size(n));
     std::vector<T> hpre(n);
     std::vector<double> hlam(n);
     const double pi = 3.14159265358979323846;
@@ -1455,16 +1455,17 @@ class Box final : public BoxBase {
       for (int la = 0; la < 8; ++la)
         for (int c1 = 0; c1 < 8; ++c1) w[la * 9 + c1] = unit(la * c1, 64);
     } else {
-      for (int m = 0; m < n; ++m) {
-        htw[m] = unit(m, n);
-        hpre[m] = static_cast<T>(std::sin(pi * m / n));
+      T* d = reinterpret_cast<T*>(htw.data());
+      for (int m = 0; m < dense_table_size(n); ++m) {
+        const int q = dense_angle(n, m);
+        d[m] = q % n ? static_cast<T>(std::sin(pi * q / n)) : T(0);
       }
     }
     for (int m = 0; m < n; ++m) {
       const double s = std::sin(pi * m / (2.0 * n));
       hlam[m] = -4.0 / (h * h) * s * s;
     }
-    QSP_HIP(hipMemcpy(tw, htw.data(), 2 * n * sizeof(Cplx<T>), hipMemcpyHostToDevice));
+    QSP_HIP(hipMemcpy(tw, htw.data(), htw.size() * sizeof(Cplx<T>), hipMemcpyHostToDevice));
     QSP_HIP(hipMemcpy(pre, hpre.data(), n * sizeof(T), hipMemcpyHostToDevice));
     QSP_HIP(hipMemcpy(lam, hlam.data(), n * sizeof(double), hipMemcpyHostToDevice));
   }

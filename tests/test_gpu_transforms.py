@@ -1,4 +1,4 @@
-"""The sine transforms at the edges of their families (half-length for
+"""The sine transforms at the edges of their families (matrix product for
 n <= 64, wave for FP32 256 and 512, symmetric for the rest) and with a
 different family on each axis: batched solves against a dense sine basis in
 FP64, and one slice of the loop against the FP64 oracle on grids whose two
@@ -7,8 +7,8 @@ axes use different families and plane orders.
 Solve tolerances: each of the four transform passes is a chain of at most
 log2(2n) + 3 rounded levels of about 3 eps each, relative in L2, and the
 round-off of the passes in front of the division by the eigenvalues is white
-like the sources, so it is amplified like the source itself; the half-length
-transform has a prefix sum over its n odd outputs, which adds n eps."""
+like the sources, so it is amplified like the source itself; a sum of up to 32
+products rounds no worse."""
 import dataclasses
 import math
 
@@ -61,12 +61,10 @@ def dense_solve(cfg, src, shift):
 
 def tolerance(prec, nx, ny):
     eps = 1.2e-7 if prec == "fp32" else 2.3e-16
-    n = max(nx, ny)
-    half = [m for m in (nx, ny) if m <= 64]
-    return eps * (4 * 3 * (math.log2(2 * n) + 3) + 4 * sum(half))
+    return eps * 4 * 3 * (math.log2(2 * max(nx, ny)) + 3)
 
 
-@pytest.mark.parametrize("nx,ny", [(128, 16), (16, 128), (128, 128), (128, 256), (512, 128),
+@pytest.mark.parametrize("nx,ny", [(16, 16), (32, 64), (64, 32), (128, 16), (16, 128), (128, 128), (128, 256), (512, 128),
                                    (256, 1024), (1024, 256), (64, 512), (1024, 64), (2048, 128),
                                    (512, 2048), (2048, 16), (32, 2048)])
 @pytest.mark.parametrize("prec", ["fp32", "fp64"])
@@ -96,7 +94,7 @@ def test_solves_at_the_edges_of_the_transform_families(nx, ny, prec):
                 assert not edge.any(), name
 
 
-@pytest.mark.parametrize("nx,ny", [(128, 16), (16, 128), (128, 256), (256, 128), (512, 32)])
+@pytest.mark.parametrize("nx,ny", [(64, 32), (128, 16), (16, 128), (128, 256), (256, 128), (512, 32)])
 @pytest.mark.parametrize("prec", ["fp32", "fp64"])
 def test_one_slice_with_two_transform_families(nx, ny, prec):
     # same cells as the square 32-node case, more of them along the long axes
