@@ -97,15 +97,18 @@ struct Lattice {
 };
 
 // Which transform rows of n points use, by element size (see dst_impl.hpp):
-//   symmetric core   128 points, FP64 from 128, FP32 from 1024 up: the FFT of
-//                    the odd extension with its redundant half left out;
+//   symmetric core   FP64 from 128, FP32 from 1024 points up: the FFT of the
+//                    odd extension with its redundant half left out;
 //   wave core        FP32 of 256 and 512 points: the whole odd extension,
 //                    one wave per row pair.  These sizes are bound by the
 //                    length of a lane's chain, which the symmetric core does
 //                    not shorten;
-//   matrix core      16-64 points: a product with the sine matrix.
+//   matrix core      16-64 points, FP32 also 128: a product with the sine
+//                    matrix.  At 128 points (128^2 box) it takes 5.5 ms
+//                    against 6.1 with the symmetric core in FP32, 7.1 against
+//                    6.8 in FP64, whose matrix rate is half.
 __host__ __device__ constexpr bool sym_core(int elem_size, int n) {
-  return n >= 1024 || n == 128 || (elem_size == 8 && n >= 128);
+  return n >= 1024 || (elem_size == 8 && n >= 128);
 }
 __host__ __device__ constexpr bool wave_core(int elem_size, int n) {
   return elem_size == 4 && (n == 256 || n == 512);
@@ -168,8 +171,11 @@ __host__ __device__ inline int dense_angle(int n, int m) {
   return o * (dense_fold(n) && k == 0 ? n / 2 : k) % (2 * n);
 }
 // Cplx<T> entries of AxisTables::tw
-__host__ __device__ constexpr int axis_tw_size(int n) {
-  return 2 * n > (dense_table_size(n) + 1) / 2 || n > 64 ? 2 * n : (dense_table_size(n) + 1) / 2;
+__host__ __device__ constexpr bool dense_core(int elem_size, int n) {
+  return !sym_core(elem_size, n) && !wave_core(elem_size, n);
+}
+__host__ __device__ constexpr int axis_tw_size(int elem_size, int n) {
+  return dense_core(elem_size, n) ? dense_table_size(n) / 2 : 2 * n;
 }
 
 // Device-side scalars of the predictor-corrector and counters.

@@ -16,7 +16,7 @@
 //   S_p = sum_j x_j sin(pi j p / n); inverse x = (2/n) S(S(x)), the 2D factor
 //   4/(nx ny) folded into the eigenvalue division of P2.  Three cores, chosen
 //   by the row length (sym_core, wave_core in common.hpp): a matrix product
-//   for 16 to 64 points, complex FFTs of the odd extension for the others.
+//   for 16 to 64 points (FP32: 128), complex FFTs of the odd extension for the others.
 #pragma once
 
 #include <stdexcept>
@@ -536,11 +536,11 @@ __device__ __forceinline__ void sym_dst(T* buf, const SymTw<T, LOGN>& w, const C
 }
 
 // ---------------------------------------------------------------------------
-// Matrix core (n = 16, 32, 64): the transform of 16 rows as a product with the
+// Matrix core (n = 16 to 64, in FP32 128): the transform of 16 rows as a product with the
 // sine matrix on the matrix cores (16x16x4 in the field's own precision, FP32
 // or FP64).  Such rows are bound by the length of the chain, not by
 // operations: one LDS read of the operand, at most 8 dependent matrix
-// instructions and one LDS write take the place of a half-length FFT with its
+// instructions (two chains of 16 at 128 points) and one LDS write take the place of a half-length FFT with its
 // three exchanges and a prefix sum (64^2 in FP32: column pass 8.8 us, row
 // passes 5.8-6.0).
 // From 32 points up sin(pi (n - m) k / n) = -(-1)^k sin(pi m k / n) folds a row
@@ -569,7 +569,9 @@ struct Dense {
   static constexpr int n = 1 << LOGN;
   static constexpr bool fold = dense_fold(n);
   static constexpr int KL = dense_lane(n);     // operands per lane
-  static constexpr int NT = n / 16;            // tiles of 16 outputs, one wave each
+  static constexpr int NT = n / 16;            // tiles of 16 outputs
+  static constexpr int TW = NT > 4 ? NT / 4 : 1;   // tiles per wave (both parities from two up)
+  static constexpr int NW = NT / TW;           // busy waves
   static constexpr int pitch = n + 16 / static_cast<int>(sizeof(T));
   using V4 = std::conditional_t<sizeof(T) == 4, f32x4, f64x4>;
   __host__ __device__ static constexpr int ridx(int i) {
@@ -581,52 +583,63 @@ struct Dense {
   __device__ static __forceinline__ int row_of(int lane, int r) {
     return sizeof(T) == 4 ? 4 * (lane >> 4) + r : (lane >> 4) + 4 * r;
   }
-  // the lane's matrix operands: tile `tile` of an axis' table
+  // the lane's matrix operands: the wave's tiles of an axis' table
   struct Tab {
-    T a[KL];
+    T a[TW][KL];
   };
-  static __device__ __forceinline__ Tab load(const Cplx<T>* tw, int tile) {
+  static __device__ __forceinline__ Tab load(const Cplx<T>* tw) {
     Tab t;
-    const T* p = reinterpret_cast<const T*>(tw) + (tile * 64 + (static_cast<int>(threadIdx.x) & 63)) * KL;
+    const int wave = static_cast<int>(threadIdx.x) >> 6, lane = static_cast<int>(threadIdx.x) & 63;
+    const T* p = reinterpret_cast<const T*>(tw) + ((wave < NW ? wave * TW : 0) * 64 + lane) * KL;
 #pragma unroll
-    for (int s = 0; s < KL; ++s) t.a[s] = p[s];
+    for (int q = 0; q < TW; ++q)
+#pragma unroll
+      for (int s = 0; s < KL; ++s) t.a[q][s] = p[q * 64 * KL + s];
     return t;
   }
-  // 16 outputs of 16 rows at f (pitch `pitch`): the tile's columns
-  static __device__ __forceinline__ V4 tile_of(const T* f, const Tab& t, bool odd) {
+  // the outputs of the wave's tiles of the rows at f
+  static __device__ __forceinline__ void tiles_of(const T* f, const Tab& t, int wave, V4 (&acc)[TW]) {
     const int lane = static_cast<int>(threadIdx.x) & 63;
     const T* p = f + (lane & 15) * pitch + KL * (lane >> 4);
-    T v[KL];
+    T v[KL], w[fold ? KL : 1];
 #pragma unroll
     for (int s = 0; s < KL; ++s) v[s] = p[s];
     if constexpr (fold) {
-      const T sign = odd ? T(1) : T(-1);
 #pragma unroll
-      for (int s = 0; s < KL; ++s) v[s] += sign * p[n / 2 + s];
+      for (int s = 0; s < KL; ++s) w[s] = p[n / 2 + s];
     }
-    V4 acc = {T(0), T(0), T(0), T(0)};
 #pragma unroll
-    for (int s = 0; s < KL; ++s) acc = mfma4(v[s], t.a[s], acc);
-    return acc;
+    for (int q = 0; q < TW; ++q) acc[q] = V4{T(0), T(0), T(0), T(0)};
+#pragma unroll
+    for (int s = 0; s < KL; ++s)
+#pragma unroll
+      for (int q = 0; q < TW; ++q) {
+        const bool odd = TW > 1 ? q & 1 : wave & 1;
+        const T x = !fold ? v[s] : odd ? v[s] + w[fold ? s : 0] : v[s] - w[fold ? s : 0];
+        acc[q] = mfma4(x, t.a[q][s], acc[q]);
+      }
   }
 };
 
-// One transform of the kDenseRows rows at buf; epi(row, output, value) gives
-// what is stored.  Ends without a barrier.
+// One transform of the kDenseRows rows at buf; epi(slot, row, output, value)
+// gives what is stored, slot = 0 .. 4 TW - 1 in order.  Ends without a barrier.
 template <typename T, int LOGN, typename Epi>
 __device__ __forceinline__ void dense_dst(T* buf, const typename Dense<T, LOGN>::Tab& t, Epi&& epi) {
   using D = Dense<T, LOGN>;
   const int wave = static_cast<int>(threadIdx.x) >> 6, lane = static_cast<int>(threadIdx.x) & 63;
-  typename D::V4 v;
-  if (wave < D::NT) v = D::tile_of(buf, t, wave & 1);
+  typename D::V4 v[D::TW];
+  if (wave < D::NW) D::tiles_of(buf, t, wave, v);
   __syncthreads();   // the rows are read
-  if (wave < D::NT) {
-    const int o = dense_out(D::n, wave, lane & 15);
-    T* out = buf + D::ridx(o);
+  if (wave < D::NW) {
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int row = D::row_of(lane, r);
-      out[row * D::pitch] = epi(row, o, v[r]);
+    for (int q = 0; q < D::TW; ++q) {
+      const int o = dense_out(D::n, wave * D::TW + q, lane & 15);
+      T* out = buf + D::ridx(o);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int row = D::row_of(lane, r);
+        out[row * D::pitch] = epi(4 * q + r, row, o, v[q][r]);
+      }
     }
   }
 }
@@ -677,7 +690,7 @@ struct Xform {
   unsigned char* lds;
   std::conditional_t<sym, SymTw<T, (LOGN >= 7 ? LOGN : 7)>,
                      std::conditional_t<wav, WaveTw<(wav ? n : 64)>,
-                                        typename Dense<T, (LOGN <= 6 ? LOGN : 6)>::Tab>>
+                                        typename Dense<T, (LOGN <= 7 ? LOGN : 7)>::Tab>>
       w;
   // LDS places of the tables
   __device__ Cplx<T>* tw() const { return reinterpret_cast<Cplx<T>*>(lds); }
@@ -708,7 +721,7 @@ __device__ __forceinline__ void block_dst(T* buf, int ppitch, const Xform<T, LOG
     if (wave < NP) wave_dst_core<n / 32>(buf + static_cast<size_t>(wave) * ppitch, x.w.a, x.tw());
   } else {
     static_assert(2 * NP == kDenseRows, "rows of the matrix core");
-    dense_dst<T, LOGN>(buf, x.w, [](int, int, T v) { return v; });
+    dense_dst<T, LOGN>(buf, x.w, [](int, int, int, T v) { return v; });
   }
   __syncthreads();
 }
@@ -765,7 +778,7 @@ __device__ __forceinline__ Xform<T, LOGN, NP> stage_tables(const AxisTables<T>& 
     for (int k = 1; k < n / 32; ++k) x.w.a[k - 1] = t.tw[(tid >> 6) < NP ? k * 64 + (tid & 63) : 0];
     x.w.w64 = reinterpret_cast<const Cplx<T>*>(t.pre)[tid < 72 ? tid : 0];
   } else {
-    x.w = Dense<T, LOGN>::load(t.tw, (tid >> 6) < Dense<T, LOGN>::NT ? tid >> 6 : 0);
+    x.w = Dense<T, LOGN>::load(t.tw);
   }
   return x;
 }
@@ -856,13 +869,16 @@ __device__ inline int xcd_strip(int b, int nstrip) {
 
 // Workgroups per CU the transform kernels are compiled for: two (<= 256
 // VGPRs) with the symmetric core, whose lanes keep 16 complex points and
-// their twiddles; four (<= 128 VGPRs) else, except the wave core's column
-// pass, which keeps its eigenvalue divisors and a strip load in flight
-// beside the core's registers.
-constexpr int dst_blocks_per_cu(int logn, int tsize) { return sym_core(tsize, 1 << logn) ? 2 : 4; }
+// their twiddles, and FP32 rows of 128 points, whose lanes keep 32 matrix operands;
+// four (<= 128 VGPRs) else, except the wave core's column pass, which keeps
+// its eigenvalue divisors and a strip load in flight beside the core's
+// registers.
+constexpr int dst_blocks_per_cu(int logn, int tsize) {
+  return sym_core(tsize, 1 << logn) || logn == 7 ? 2 : 4;
+}
 
 constexpr int col_blocks_per_cu(int logn, int tsize) {
-  return sym_core(tsize, 1 << logn) || wave_core(tsize, 1 << logn) ? 2 : 4;
+  return (1 << logn) >= 128 ? 2 : 4;
 }
 
 // Calls f(e) for e = t + u kBlock, u = 0 .. TOTAL / kBlock - 1 (TOTAL a
@@ -1310,7 +1326,9 @@ __device__ __forceinline__ void col_block_dense(const Geom& g, const ColArgs<T>&
   double lx[4];
 #pragma unroll
   for (int r = 0; r < 4; ++r) lx[r] = lamx[p0 + D::row_of(lane, r)];
-  const double ly = ty.lam[wave < D::NT ? dense_out(n, wave, lane & 15) : 0];
+  double ly[D::TW];
+#pragma unroll
+  for (int q = 0; q < D::TW; ++q) ly[q] = ty.lam[wave < D::NW ? dense_out(n, wave * D::TW + q, lane & 15) : 0];
   __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
   for (int u = 0; u < N; ++u) buf[c * D::pitch + D::ridx(j0 + u * JS)] = v[u];
@@ -1318,17 +1336,18 @@ __device__ __forceinline__ void col_block_dense(const Geom& g, const ColArgs<T>&
   // 1 / normalisation (nx ny / 4, exact): the eigenvalue sum in FP64, the one
   // division in the field precision
   const double inorm = 0.25 * static_cast<double>(nx) * n;
-  const double lys = ly - a.shift[fld];
-  T den[4];
+  const double shift = a.shift[fld];
+  T den[4 * D::TW];
 #pragma unroll
-  for (int r = 0; r < 4; ++r) den[r] = static_cast<T>((lx[r] + lys) * inorm);
-  int q = 0;
-  dense_dst<T, LOGN>(buf, xf.w, [&](int row, int o, T s) {
-    const T z = s / den[q++];
+  for (int q = 0; q < D::TW; ++q)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) den[4 * q + r] = static_cast<T>((lx[r] + (ly[q] - shift)) * inorm);
+  dense_dst<T, LOGN>(buf, xf.w, [&](int q, int row, int o, T s) {
+    const T z = s / den[q];
     return p0 + row > 0 && o > 0 ? z : T(0);
   });
   __syncthreads();
-  dense_dst<T, LOGN>(buf, xf.w, [](int, int, T s) { return s; });
+  dense_dst<T, LOGN>(buf, xf.w, [](int, int, int, T s) { return s; });
   __syncthreads();
   T* out = a.out + fld * plane;
   const T* row = buf + c * D::pitch;

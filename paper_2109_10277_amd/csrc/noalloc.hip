@@ -91,14 +91,14 @@ __global__ void k_axis_tables(AxisJob<T> x, AxisJob<T> y) {
 
 template <typename T>
 size_t axis_table_bytes(int n) {
-  return static_cast<size_t>(qsp::axis_tw_size(n)) * sizeof(qsp::Cplx<T>) +
+  return static_cast<size_t>(qsp::axis_tw_size(sizeof(T), n)) * sizeof(qsp::Cplx<T>) +
          static_cast<size_t>(n) * (sizeof(T) + sizeof(double));
 }
 
 template <typename T>
 qsp::AxisTables<T> axis_at(unsigned char* base, int n) {
   auto* tw = reinterpret_cast<qsp::Cplx<T>*>(base);
-  auto* pre = reinterpret_cast<T*>(tw + qsp::axis_tw_size(n));
+  auto* pre = reinterpret_cast<T*>(tw + qsp::axis_tw_size(sizeof(T), n));
   auto* lam = reinterpret_cast<double*>(pre + n);
   return {tw, pre, lam};
 }
@@ -128,7 +128,7 @@ void solve(const qsp_config& c, unsigned char* ptr, int nb, const T* src, T* dst
                       const_cast<double*>(tx.lam)};
   const AxisJob<T> jy{c.ny, g.hy, const_cast<Cplx<T>*>(ty.tw), const_cast<T*>(ty.pre),
                       const_cast<double*>(ty.lam)};
-  auto entries = [](int n) { return n <= 64 ? dense_table_size(n) : 2 * n; };   // one thread each
+  auto entries = [](int n) { return dense_core(sizeof(T), n) ? dense_table_size(n) : 2 * n; };   // one thread each
   const int mx = entries(c.nx), my = entries(c.ny);
   hipLaunchKernelGGL(k_axis_tables<T>, dim3(((mx > my ? mx : my) + 255) / 256, 2), dim3(256), 0, st, jx, jy);
   QSP_LAUNCH_CHECK();

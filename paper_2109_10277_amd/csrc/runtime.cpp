@@ -1398,10 +1398,10 @@ class Box final : public BoxBase {
     p_.w = alloc<T>(np);
     p_.hist = alloc<T>(20 * np);
     p_.pab = alloc<T>(5 * np);
-    twx_ = alloc<Cplx<T>>(axis_tw_size(cfg_.nx));
+    twx_ = alloc<Cplx<T>>(axis_tw_size(sizeof(T), cfg_.nx));
     prex_ = alloc<T>(cfg_.nx);
     lamx_ = alloc<double>(cfg_.nx);
-    twy_ = alloc<Cplx<T>>(axis_tw_size(cfg_.ny));
+    twy_ = alloc<Cplx<T>>(axis_tw_size(sizeof(T), cfg_.ny));
     prey_ = alloc<T>(cfg_.ny);
     lamy_ = alloc<double>(cfg_.ny);
     bgx_ = alloc<double>(cfg_.nx + 1);
@@ -1431,7 +1431,7 @@ class Box final : public BoxBase {
   // Per-axis tables of the sine transform (tw holds axis_tw_size entries, pre
   // n, laid out as AxisTables says) and the Laplacian eigenvalues.
   void axis_tables(int n, double h, Cplx<T>* tw, T* pre, double* lam) {
-    std::vector<Cplx<T>> htw(axis_tw_size(n));
+    std::vector<Cplx<T>> htw(axis_tw_size(sizeof(T), n));
     std::vector<T> hpre(n);
     std::vector<double> hlam(n);
     const double pi = 3.14159265358979323846;
