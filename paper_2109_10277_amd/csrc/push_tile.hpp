@@ -20,7 +20,8 @@ namespace qsp {
 namespace push_detail {
 
 struct TileShape {
-  int tx, ty;      // lattice sites per tile
+  int tx, ty;      // lattice sites per tile (tx a power of two)
+  int ltx;         // log2 tx
   int lpx, lpy;    // log2 ppc
   int nw, nh;      // LDS node tile (cells + 1 + 2 halo)
   int halo;        // cells around the tile's own cells covered in LDS
@@ -37,6 +38,7 @@ __host__ __device__ inline TileShape tile_shape(const Lattice& L, int rows, int 
   t.halo = halo;
   t.tx = L.nX < 64 ? L.nX : 64;
   t.ty = L.nY < rows ? L.nY : rows;
+  t.ltx = ilog2(t.tx);
   t.lpx = ilog2(L.ppc_x);
   t.lpy = ilog2(L.ppc_y);
   t.nw = (t.tx >> t.lpx) + 1 + 2 * halo;
@@ -51,18 +53,57 @@ __device__ inline bool inside(int c0, T t, int n) {
   return c >= 0 && (c < n || (c == n && t == fl));
 }
 
-// CIC interpolation in cell (i, j), 0 <= i < nx, 0 <= j < ny; the upper
-// Dirichlet nodes (index n, not stored) are zero.  All four loads are
-// unconditional (clamped indices) so that they issue together.
+// Keeps a loaded value where it was loaded: without it the compiler moves a
+// load next to its first use, behind the particle's decisions, and a batch of
+// loads becomes a chain of memory round trips.
+__device__ __forceinline__ void pin(float& x) { asm volatile("" : "+v"(x)); }
+__device__ __forceinline__ void pin(double& x) { asm volatile("" : "+v"(x)); }
+
+// CIC interpolation in cell (i, j), 0 <= i < nx, 0 <= j < ny, of several
+// planes; the upper Dirichlet nodes (index n, not stored) are zero.  The two
+// nodes of a row come with one load of two values (aligned to one value
+// only), clamped to stay in the row: half the load instructions and
+// addresses of a load per node.  32-bit offsets (a plane is below 4 GiB).
 template <typename T>
-__device__ inline T gather(const T* __restrict__ F, int i, int j, T w00, T w10, T w01, T w11,
-                           int nx, int ny) {
-  const bool ie = i + 1 < nx, jn = j + 1 < ny;
-  const int i1 = ie ? i + 1 : i, j1 = jn ? j + 1 : j;
-  const T f00 = F[j * nx + i], f10 = F[j * nx + i1], f01 = F[j1 * nx + i], f11 = F[j1 * nx + i1];
-  return w00 * f00 + w10 * (ie ? f10 : T(0)) + w01 * (jn ? f01 : T(0)) +
-         w11 * ((ie && jn) ? f11 : T(0));
-}
+struct Cic {
+  T w00, w10, w01, w11;
+  unsigned int r0, r1;   // offsets of the pairs of rows j, j + 1
+  bool ie, jn;           // node i + 1 (j + 1) is stored
+  struct alignas(sizeof(T)) Two {
+    T a, b;
+  };
+  struct Node {          // the four nodes of a plane
+    T a0, b0, a1, b1;
+    __device__ __forceinline__ void pin() {
+      push_detail::pin(a0);
+      push_detail::pin(b0);
+      push_detail::pin(a1);
+      push_detail::pin(b1);
+    }
+  };
+  __device__ __forceinline__ void at(int i, int j, T fx, T fy, int nx, int ny) {
+    w00 = (T(1) - fx) * (T(1) - fy);
+    w10 = fx * (T(1) - fy);
+    w01 = (T(1) - fx) * fy;
+    w11 = fx * fy;
+    ie = i + 1 < nx;
+    jn = j + 1 < ny;
+    const int i0 = ie ? i : i - 1;   // nx >= 16
+    r0 = static_cast<unsigned int>(j * nx + i0);
+    r1 = jn ? r0 + static_cast<unsigned int>(nx) : r0;
+  }
+  __device__ __forceinline__ Node load(const T* __restrict__ F) const {
+    const char* f = reinterpret_cast<const char*>(F);
+    const Two u = *reinterpret_cast<const Two*>(f + r0 * static_cast<unsigned int>(sizeof(T)));
+    const Two v = *reinterpret_cast<const Two*>(f + r1 * static_cast<unsigned int>(sizeof(T)));
+    return {u.a, u.b, v.a, v.b};
+  }
+  __device__ __forceinline__ T sum(const Node& f) const {
+    const T f00 = ie ? f.a0 : f.b0, f01 = ie ? f.a1 : f.b1;
+    return w00 * f00 + w10 * (ie ? f.b0 : T(0)) + w01 * (jn ? f01 : T(0)) +
+           w11 * ((ie && jn) ? f.b1 : T(0));
+  }
+};
 
 __device__ inline void lds_add(double* p, double v) {
   __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
@@ -210,10 +251,11 @@ __device__ __forceinline__ void gather_bxby(const SliceFields<T>& f, int ci0, in
     int ci, cj;
     const T fx = shape::locate<1>(ci0, fx0 + xk, nx, ci);
     const T fy = shape::locate<1>(cj0, fy0 + ek, ny, cj);
-    const T w00 = (T(1) - fx) * (T(1) - fy), w10 = fx * (T(1) - fy);
-    const T w01 = (T(1) - fx) * fy, w11 = fx * fy;
-    bx = gather(f.bx, ci, cj, w00, w10, w01, w11, nx, ny);
-    by = gather(f.by, ci, cj, w00, w10, w01, w11, nx, ny);
+    Cic<T> cic;
+    cic.at(ci, cj, fx, fy, nx, ny);
+    const auto nb = cic.load(f.bx), mb = cic.load(f.by);
+    bx = cic.sum(nb);
+    by = cic.sum(mb);
   } else {
     int bi, bj;
     const T dx = shape::locate<O>(ci0, fx0 + xk, nx, bi);
@@ -248,86 +290,82 @@ __device__ __forceinline__ void gather_bxby(const SliceFields<T>& f, int ci0, in
 constexpr int kLaterBatch = 2;
 
 template <typename T, int O, int nch>
-__device__ __forceinline__ void trial_later_particles(const Lattice& L, const PushArgs<T>& a,
-                                                      double* tile, const TileShape& ts, int I0,
-                                                      int J0, int ox, int oy, int nx, int ny,
-                                                      bool tiled, bool owner, unsigned int& nglob) {
-  constexpr int U = sizeof(T) == 4 && O == 1 ? kLaterBatch : 1;
-  const size_t np = static_cast<size_t>(L.np);
-  const T* r = a.rec;
-  const T kick = static_cast<T>(a.dzeta) * T(kAB5[0]);
-  const int ntot = ts.tx * ts.ty;
-  for (int e0 = 0; e0 < ntot; e0 += U * kBlock) {
-    T fac[U], xk[U], ek[U], xn[U], en[U], cx[U], cy[U], bx[U], by[U];
-    int ci0[U], cj0[U];
-    T fx0[U], fy0[U];
+struct LaterBatch {
+  static constexpr int U = sizeof(T) == 4 && O == 1 ? kLaterBatch : 1;
+  T fac[U], xk[U], ek[U], xn[U], en[U], cx[U], cy[U];
+
+  static __device__ __forceinline__ void site(const TileShape& ts, int I0, int J0, int e, int& I, int& J) {
+    const int ec = e < ts.tx * ts.ty ? e : 0;   // a missing particle reads the tile's first
+    I = I0 + (ec & (ts.tx - 1));
+    J = J0 + (ec >> ts.ltx);
+  }
+  __device__ __forceinline__ void load(const Lattice& L, const PushArgs<T>& a, const TileShape& ts,
+                                       int I0, int J0, int e0) {
+    const size_t np = static_cast<size_t>(L.np);
+    const T* r = a.rec;
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const int e = e0 + u * kBlock + static_cast<int>(threadIdx.x);
-      const int ec = e < ntot ? e : 0;   // a missing particle reads the tile's first
-      const int I = I0 + ec % ts.tx, J = J0 + ec / ts.tx;
+      int I, J;
+      site(ts, I0, J0, e0 + u * kBlock + static_cast<int>(threadIdx.x), I, J);
       // 32-bit offsets from uniform plane bases (the launch checks that a
       // particle plane is below 4 GiB)
       const unsigned int p = static_cast<unsigned int>(J) * static_cast<unsigned int>(L.nX) +
                              static_cast<unsigned int>(I);
-      fac[u] = load_at(r + 4 * np, p);
       xk[u] = load_at(a.p.xi_x, p);
       ek[u] = load_at(a.p.xi_y, p);
-      xn[u] = load_at(r, p);
-      en[u] = load_at(r + np, p);
-      cx[u] = load_at(r + 2 * np, p);
-      cy[u] = load_at(r + 3 * np, p);
-      ci0[u] = I >> ts.lpx;
-      cj0[u] = J >> ts.lpy;
-      fx0[u] = (T(2 * (I & (L.ppc_x - 1)) + 1)) / T(2 * L.ppc_x);
-      fy0[u] = (T(2 * (J & (L.ppc_y - 1)) + 1)) / T(2 * L.ppc_y);
+      const T* q = r;
+      xn[u] = load_at(q, p);
+      en[u] = load_at(q += np, p);
+      cx[u] = load_at(q += np, p);
+      cy[u] = load_at(q += np, p);
+      fac[u] = load_at(q += np, p);
     }
     // keep the scheduler from moving a later particle's loads behind an
     // earlier one's gather (the wait for a load also waits for every load
     // issued before it)
     __builtin_amdgcn_sched_barrier(0);
+  }
+  __device__ __forceinline__ void deposit(const Lattice& L, const PushArgs<T>& a, double* tile,
+                                          const TileShape& ts, int I0, int J0, int e0, int ox, int oy,
+                                          int nx, int ny, bool tiled, bool owner, unsigned int& nglob) {
+    const T kick = static_cast<T>(a.dzeta) * T(kAB5[0]);
+    T bx[U], by[U], fx0[U], fy0[U];
+    int ci0[U], cj0[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      int I, J;
+      site(ts, I0, J0, e0 + u * kBlock + static_cast<int>(threadIdx.x), I, J);
+      ci0[u] = I >> ts.lpx;
+      cj0[u] = J >> ts.lpy;
+      fx0[u] = (T(2 * (I & (L.ppc_x - 1)) + 1)) / T(2 * L.ppc_x);
+      fy0[u] = (T(2 * (J & (L.ppc_y - 1)) + 1)) / T(2 * L.ppc_y);
+      pin(xk[u]);
+      pin(ek[u]);
+    }
     if constexpr (O == 1) {
       // the gather of every particle of the batch: addresses and weights,
-      // then all loads, then the sums (the same sums as gather())
-      unsigned int off[U][4];
-      T wt[U][4];
-      bool ie[U], jn[U];
+      // then all loads, then the sums
+      Cic<T> cic[U];
+      typename Cic<T>::Node gx[U], gy[U];
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         int ci, cj;
         const T fx = shape::locate<1>(ci0[u], fx0[u] + xk[u], nx, ci);
         const T fy = shape::locate<1>(cj0[u], fy0[u] + ek[u], ny, cj);
-        wt[u][0] = (T(1) - fx) * (T(1) - fy);
-        wt[u][1] = fx * (T(1) - fy);
-        wt[u][2] = (T(1) - fx) * fy;
-        wt[u][3] = fx * fy;
-        ie[u] = ci + 1 < nx;
-        jn[u] = cj + 1 < ny;
-        const unsigned int r0 = static_cast<unsigned int>(cj * nx);
-        const unsigned int r1 = static_cast<unsigned int>((jn[u] ? cj + 1 : cj) * nx);
-        const unsigned int c0 = static_cast<unsigned int>(ci);
-        const unsigned int c1 = static_cast<unsigned int>(ie[u] ? ci + 1 : ci);
-        off[u][0] = r0 + c0;
-        off[u][1] = r0 + c1;
-        off[u][2] = r1 + c0;
-        off[u][3] = r1 + c1;
+        cic[u].at(ci, cj, fx, fy, nx, ny);
       }
-      T gx[U][4], gy[U][4];
 #pragma unroll
-      for (int u = 0; u < U; ++u)
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          gx[u][q] = load_at(a.f.bx, off[u][q]);
-          gy[u][q] = load_at(a.f.by, off[u][q]);
-        }
+      for (int u = 0; u < U; ++u) {
+        gx[u] = cic[u].load(a.f.bx);
+        gy[u] = cic[u].load(a.f.by);
+      }
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int u = 0; u < U; ++u) {
-        const bool e1 = ie[u], n1 = jn[u], en1 = ie[u] && jn[u];
-        bx[u] = wt[u][0] * gx[u][0] + wt[u][1] * (e1 ? gx[u][1] : T(0)) +
-                wt[u][2] * (n1 ? gx[u][2] : T(0)) + wt[u][3] * (en1 ? gx[u][3] : T(0));
-        by[u] = wt[u][0] * gy[u][0] + wt[u][1] * (e1 ? gy[u][1] : T(0)) +
-                wt[u][2] * (n1 ? gy[u][2] : T(0)) + wt[u][3] * (en1 ? gy[u][3] : T(0));
+        gx[u].pin();
+        gy[u].pin();
+        bx[u] = cic[u].sum(gx[u]);
+        by[u] = cic[u].sum(gy[u]);
       }
     } else {
 #pragma unroll
@@ -337,7 +375,7 @@ __device__ __forceinline__ void trial_later_particles(const Lattice& L, const Pu
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      if (e0 + u * kBlock + static_cast<int>(threadIdx.x) >= ntot) continue;
+      if (e0 + u * kBlock + static_cast<int>(threadIdx.x) >= ts.tx * ts.ty) continue;
       const bool live = fac[u] != T(0);   // selects, not branches
       const double v[4] = {live ? static_cast<double>(fac[u] * (cx[u] - kick * by[u])) : 0.0,
                            live ? static_cast<double>(fac[u] * (cy[u] + kick * bx[u])) : 0.0, 0.0,
@@ -346,7 +384,45 @@ __device__ __forceinline__ void trial_later_particles(const Lattice& L, const Pu
                                   fx0[u], fy0[u], xn[u], en[u], v, nglob, live);
     }
   }
-}
+};
+
+// What a particle's push reads of the particle itself, all issued at once: the
+// state, the history part P_k of the step (left by the previous real push)
+// and, for the real push, f_{k-1}, f_{k-2}, f_{k-3}, which form P_{k+1} with
+// f_k.  A thread beyond the tile reads the tile's first particle.
+template <typename T, int MODE>
+struct ParticleLoad {
+  T y[5], w, pk[5], h[3][5];
+  __device__ __forceinline__ void load(const Lattice& L, const PushArgs<T>& a, const TileShape& ts,
+                                       int I0, int J0, int e) {
+    const size_t np = static_cast<size_t>(L.np);
+    const int ec = e < ts.tx * ts.ty ? e : 0;
+    const unsigned int p =
+        static_cast<unsigned int>(J0 + (ec >> ts.ltx)) * static_cast<unsigned int>(L.nX) +
+        static_cast<unsigned int>(I0 + (ec & (ts.tx - 1)));
+    y[0] = load_at(a.p.xi_x, p);
+    y[1] = load_at(a.p.xi_y, p);
+    y[2] = load_at(a.p.ux, p);
+    y[3] = load_at(a.p.uy, p);
+    y[4] = load_at(a.p.psi, p);
+    w = load_at(a.p.w, p);
+    if constexpr (MODE == kPushReal || MODE == kPushTrial) {
+      const T* q = a.p.pab;   // planes by stepping: a product per plane is a chain of scalar work
+#pragma unroll
+      for (int c = 0; c < 5; ++c, q += np) pk[c] = load_at(q, p);
+    }
+    if constexpr (MODE == kPushReal) {
+      const size_t np5 = 5 * np;
+#pragma unroll
+      for (int m = 0; m < 3; ++m) {
+        const T* q = a.p.hist + ((a.k + 3 - m) & 3) * np5;
+#pragma unroll
+        for (int c = 0; c < 5; ++c, q += np) h[m][c] = load_at(q, p);
+      }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  }
+};
 
 // Gather, push and deposit of the particles of lattice tile (tbx, tby) by
 // one workgroup with the transverse shape of order O; `tile` is the
@@ -365,11 +441,6 @@ __device__ __forceinline__ void push_tile(const Geom& g, const Lattice& L, const
   const int ntile = ts.nw * ts.nh;
   const bool tiled = a.tiled != 0;
   const bool owner = tiled && a.dep.sh[0] != nullptr;
-  if (tiled) {
-    __syncthreads();   // a previous tile's flush has read the histogram
-    for (int e = threadIdx.x; e < nch * ntile; e += kBlock) tile[e] = 0.0;
-    __syncthreads();
-  }
   const int I0 = tbx * ts.tx, J0 = tby * ts.ty;
   const int ox = (I0 >> ts.lpx) - ts.halo, oy = (J0 >> ts.lpy) - ts.halo;
   const int nx = g.nx, ny = g.ny;
@@ -378,63 +449,75 @@ __device__ __forceinline__ void push_tile(const Geom& g, const Lattice& L, const
   const T dz = static_cast<T>(a.dzeta);
   const T b0 = T(kAB5[0]);
   const size_t np = static_cast<size_t>(L.np);
-  T* hist = a.p.hist;
-  const int s_new = a.k & 3;
-  const int s1 = (a.k + 3) & 3, s2 = (a.k + 2) & 3, s3 = (a.k + 1) & 3;
   unsigned int nclamp = 0, nabs = 0, nglob = 0;
+  const int ntot = ts.tx * ts.ty;
 
+  // The first loads are in flight while the histogram is cleared.
+  ParticleLoad<T, MODE> in;
+  LaterBatch<T, O, nch> later;
   if constexpr (MODE == kTrialLater)
-    trial_later_particles<T, O, nch>(L, a, tile, ts, I0, J0, ox, oy, nx, ny, tiled, owner, nglob);
-  for (int e = threadIdx.x; MODE != kTrialLater && e < ts.tx * ts.ty; e += kBlock) {
-    const int I = I0 + e % ts.tx, J = J0 + e / ts.tx;
-    const size_t p = static_cast<size_t>(J) * L.nX + I;
-    // every load of the particle is issued before any decision on it
-    const T w = a.p.w[p];
-    T xi = a.p.xi_x[p], eta = a.p.xi_y[p];
-    T ux = a.p.ux[p], uy = a.p.uy[p], psi = a.p.psi[p];
+    later.load(L, a, ts, I0, J0, 0);
+  else
+    in.load(L, a, ts, I0, J0, static_cast<int>(threadIdx.x));
+  if (tiled) {
+    __syncthreads();   // a previous tile's flush has read the histogram
+    for (int e = threadIdx.x; e < nch * ntile; e += kBlock) tile[e] = 0.0;
+    __syncthreads();
+  }
+  if constexpr (MODE == kTrialLater) {
+    constexpr int step = LaterBatch<T, O, nch>::U * kBlock;
+    for (int e0 = 0;;) {
+      later.deposit(L, a, tile, ts, I0, J0, e0, ox, oy, nx, ny, tiled, owner, nglob);
+      e0 += step;
+      if (e0 >= ntot) break;
+      later.load(L, a, ts, I0, J0, e0);
+    }
+  }
+  for (int e = threadIdx.x; MODE != kTrialLater && e < ntot; e += kBlock) {
+    if (e >= kBlock) in.load(L, a, ts, I0, J0, e);
+    const int I = I0 + (e & (ts.tx - 1)), J = J0 + (e >> ts.ltx);
+    const unsigned int p = static_cast<unsigned int>(J) * static_cast<unsigned int>(L.nX) +
+                           static_cast<unsigned int>(I);
+    T xi = in.y[0], eta = in.y[1], ux = in.y[2], uy = in.y[3], psi = in.y[4];
+    const T w = in.w;
+    pin(xi);
+    pin(eta);
     const int ci0 = I >> ts.lpx, cj0 = J >> ts.lpy;
     const T fx0 = (T(2 * (I & (L.ppc_x - 1)) + 1)) / T(2 * L.ppc_x);
     const T fy0 = (T(2 * (J & (L.ppc_y - 1)) + 1)) / T(2 * L.ppc_y);
     bool alive = w != T(0);
 
     if (MODE != kDepositOnly) {
-      // the history part P_k of the step (written by the previous real push)
-      // and, for the real push, f_{k-1}, f_{k-2}, f_{k-3} (which form P_{k+1}
-      // with f_k)
-      T pk[5];
-      T h[3][5];
-#pragma unroll
-      for (int c = 0; c < 5; ++c) {
-        pk[c] = a.p.pab[c * np + p];
-        if constexpr (MODE == kPushReal) {
-          h[0][c] = hist[(s1 * 5 + c) * np + p];
-          h[1][c] = hist[(s2 * 5 + c) * np + p];
-          h[2][c] = hist[(s3 * 5 + c) * np + p];
-        }
-      }
       if constexpr (MODE == kPushTrial && TAPE) {
         // the state the reverse pass of this slice starts from
         T* t = a.tape;
-        t[p] = xi;
-        t[np + p] = eta;
-        t[2 * np + p] = ux;
-        t[3 * np + p] = uy;
-        t[4 * np + p] = psi;
-        t[5 * np + p] = w;
+        store_at(t, p, xi);
+        store_at(t + np, p, eta);
+        store_at(t + 2 * np, p, ux);
+        store_at(t + 3 * np, p, uy);
+        store_at(t + 4 * np, p, psi);
+        store_at(t + 5 * np, p, w);
       }
       T e1, e2, ez, bx, by, bz;
       if constexpr (O == 1) {
         int ci, cj;
         const T fx = shape::locate<1>(ci0, fx0 + xi, nx, ci);
         const T fy = shape::locate<1>(cj0, fy0 + eta, ny, cj);
-        const T w00 = (T(1) - fx) * (T(1) - fy), w10 = fx * (T(1) - fy);
-        const T w01 = (T(1) - fx) * fy, w11 = fx * fy;
-        e1 = gather(a.f.exmby, ci, cj, w00, w10, w01, w11, nx, ny);
-        e2 = gather(a.f.eypbx, ci, cj, w00, w10, w01, w11, nx, ny);
-        ez = gather(a.f.ez, ci, cj, w00, w10, w01, w11, nx, ny);
-        bx = gather(a.f.bx, ci, cj, w00, w10, w01, w11, nx, ny);
-        by = gather(a.f.by, ci, cj, w00, w10, w01, w11, nx, ny);
-        bz = gather(a.f.bz, ci, cj, w00, w10, w01, w11, nx, ny);
+        Cic<T> cic;
+        cic.at(ci, cj, fx, fy, nx, ny);
+        const T* const planes[6] = {a.f.exmby, a.f.eypbx, a.f.ez, a.f.bx, a.f.by, a.f.bz};
+        typename Cic<T>::Node nd[6];
+#pragma unroll
+        for (int q = 0; q < 6; ++q) nd[q] = cic.load(planes[q]);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int q = 0; q < 6; ++q) nd[q].pin();
+        e1 = cic.sum(nd[0]);
+        e2 = cic.sum(nd[1]);
+        ez = cic.sum(nd[2]);
+        bx = cic.sum(nd[3]);
+        by = cic.sum(nd[4]);
+        bz = cic.sum(nd[5]);
       } else {
         int bi, bj;
         const T dx = shape::locate<O>(ci0, fx0 + xi, nx, bi);
@@ -477,7 +560,7 @@ __device__ __forceinline__ void push_tile(const Geom& g, const Lattice& L, const
       f[4] = (ux * e1 + uy * e2) * id - ez;
       T y[5];
 #pragma unroll
-      for (int c = 0; c < 5; ++c) y[c] = pk[c] - dz * (b0 * f[c]);
+      for (int c = 0; c < 5; ++c) y[c] = in.pk[c] - dz * (b0 * f[c]);
       if constexpr (MODE == kPushTrial) {
         const T cx = y[2], cy = y[3];
         const T kick = dz * b0;
@@ -488,18 +571,18 @@ __device__ __forceinline__ void push_tile(const Geom& g, const Lattice& L, const
           const T dn = T(1) + y[4];
           const T idn = T(1) / (dn < floor_d ? floor_d : dn);
           T* r = a.rec;
-          r[p] = y[0];
-          r[np + p] = y[1];
-          r[2 * np + p] = cx;
-          r[3 * np + p] = cy;
-          r[4 * np + p] = alive && in_box ? -w * idn : T(0);
-          r[5 * np + p] = y[4];
+          store_at(r, p, y[0]);
+          store_at(r + np, p, y[1]);
+          store_at(r + 2 * np, p, cx);
+          store_at(r + 3 * np, p, cy);
+          store_at(r + 4 * np, p, alive && in_box ? -w * idn : T(0));
+          if constexpr (TAPE) store_at(r + 5 * np, p, y[4]);
         }
       }
       if (!alive) continue;
       if (!inside(ci0, fx0 + y[0], nx) || !inside(cj0, fy0 + y[1], ny)) {
         ++nabs;
-        if (MODE == kPushReal) a.p.w[p] = T(0);
+        if (MODE == kPushReal) store_at(a.p.w, p, T(0));
         continue;
       }
       xi = y[0];
@@ -508,15 +591,15 @@ __device__ __forceinline__ void push_tile(const Geom& g, const Lattice& L, const
       uy = y[3];
       psi = y[4];
       if constexpr (MODE == kPushReal) {
-        a.p.xi_x[p] = xi;
-        a.p.xi_y[p] = eta;
-        a.p.ux[p] = ux;
-        a.p.uy[p] = uy;
-        a.p.psi[p] = psi;
+        store_at(a.p.xi_x, p, xi);
+        store_at(a.p.xi_y, p, eta);
+        store_at(a.p.ux, p, ux);
+        store_at(a.p.uy, p, uy);
+        store_at(a.p.psi, p, psi);
 #pragma unroll
         for (int c = 0; c < 5; ++c) {
-          hist[(s_new * 5 + c) * np + p] = f[c];
-          a.p.pab[c * np + p] = ab5_history(y[c], f[c], h[0][c], h[1][c], h[2][c], dz);
+          store_at(a.p.hist + ((a.k & 3) * 5 + c) * np, p, f[c]);
+          store_at(a.p.pab + c * np, p, ab5_history(y[c], f[c], in.h[0][c], in.h[1][c], in.h[2][c], dz));
         }
       }
     } else if (!alive) {
