@@ -17,7 +17,7 @@ OUT = os.path.join(HERE, "libqsp.so")
 BUILD = os.path.join(HERE, "_build")
 ARCH = "gfx950"
 
-SOURCES = ["dst.hip", "explicit.hip", "particles.hip", "fields.hip", "beam.hip", "adjoint.hip",
+SOURCES = ["dst.hip", "small.hip", "explicit.hip", "particles.hip", "fields.hip", "beam.hip", "adjoint.hip",
            "noalloc.hip", "runtime.cpp", "abi.cpp"]
 
 FLAGS = ["-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}",

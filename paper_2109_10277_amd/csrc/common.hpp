@@ -178,6 +178,17 @@ __host__ __device__ constexpr int axis_tw_size(int elem_size, int n) {
   return dense_core(elem_size, n) ? dense_table_size(n) / 2 : 2 * n;
 }
 
+// Grids whose solves run in one workgroup per field (small.hip): batches on
+// node arrays up to 64 x 64 (one launch of 5.5 us against three that take 11.7
+// eagerly, FP32; 10.2 in FP64), the slice loop's up to 2048 nodes (32 x 64 box:
+// 3.29 ms against 4.01; at 64 x 64 one CU's loads and products take as long as
+// three passes' launches from a graph, 4.36 against 4.30 ms, in FP64 5.6
+// against 4.7).
+__host__ __device__ constexpr bool small_solve(int nx, int ny) { return nx <= 64 && ny <= 64; }
+__host__ __device__ constexpr bool small_grid(int nx, int ny) {
+  return small_solve(nx, ny) && nx * ny <= 2048;
+}
+
 // Device-side scalars of the predictor-corrector and counters.
 struct DevCounters {
   unsigned int pc_done;        // 1 once the current slice's P-C converged

@@ -335,7 +335,9 @@ void launch_row_inv_pc(const Geom& g, const PCArgs<T>& a, const AxisTables<T>& t
   QSP_LAUNCH_CHECK();
 }
 
-int pc_partial_count(const Geom& g) { return 2 * (g.ny / g.rr); }
+int pc_partial_count(const Geom& g) {
+  return small_grid(g.nx, g.ny) ? 2 : 2 * (g.ny / g.rr);   // one record a field, or a row block
+}
 
 template <typename T>
 int col_width(const Geom& g, int) {

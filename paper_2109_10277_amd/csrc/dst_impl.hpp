@@ -597,27 +597,32 @@ struct Dense {
       for (int s = 0; s < KL; ++s) t.a[q][s] = p[q * 64 * KL + s];
     return t;
   }
+  // 16 outputs (of one parity with folded rows) of the 16 rows at f
+  static __device__ __forceinline__ V4 product(const T* f, const T (&a)[KL], bool odd) {
+    T v[KL], w[KL];
+    fetch(f, v, w);
+    return chain(v, w, a, odd);
+  }
   // the outputs of the wave's tiles of the rows at f
   static __device__ __forceinline__ void tiles_of(const T* f, const Tab& t, int wave, V4 (&acc)[TW]) {
+    T v[KL], w[KL];
+    fetch(f, v, w);
+#pragma unroll
+    for (int q = 0; q < TW; ++q) acc[q] = chain(v, w, t.a[q], TW > 1 ? q & 1 : wave & 1);
+  }
+  static __device__ __forceinline__ void fetch(const T* f, T (&v)[KL], T (&w)[KL]) {
     const int lane = static_cast<int>(threadIdx.x) & 63;
     const T* p = f + (lane & 15) * pitch + KL * (lane >> 4);
-    T v[KL], w[fold ? KL : 1];
 #pragma unroll
     for (int s = 0; s < KL; ++s) v[s] = p[s];
-    if constexpr (fold) {
 #pragma unroll
-      for (int s = 0; s < KL; ++s) w[s] = p[n / 2 + s];
-    }
+    for (int s = 0; s < KL; ++s) w[s] = fold ? p[n / 2 + s] : T(0);
+  }
+  static __device__ __forceinline__ V4 chain(const T (&v)[KL], const T (&w)[KL], const T (&a)[KL], bool odd) {
+    V4 acc = {T(0), T(0), T(0), T(0)};
 #pragma unroll
-    for (int q = 0; q < TW; ++q) acc[q] = V4{T(0), T(0), T(0), T(0)};
-#pragma unroll
-    for (int s = 0; s < KL; ++s)
-#pragma unroll
-      for (int q = 0; q < TW; ++q) {
-        const bool odd = TW > 1 ? q & 1 : wave & 1;
-        const T x = !fold ? v[s] : odd ? v[s] + w[fold ? s : 0] : v[s] - w[fold ? s : 0];
-        acc[q] = mfma4(x, t.a[q][s], acc[q]);
-      }
+    for (int s = 0; s < KL; ++s) acc = mfma4(!fold ? v[s] : odd ? v[s] + w[s] : v[s] - w[s], a[s], acc);
+    return acc;
   }
 };
 

@@ -117,6 +117,18 @@ void launch_row_nodes(const Geom&, const NodeRowArgs<T>&, bool out, int nbatch, 
 template <typename T>
 void launch_row_inv_pc(const Geom&, const PCArgs<T>&, const AxisTables<T>&, DevCounters*,
                        hipStream_t);
+// The same solves in one workgroup per field (small_grid): a corrector solve
+// with its update, psi, Ez and Bz with the guess, a batch on node arrays.
+template <typename T>
+void launch_small_bxby(const Geom&, const SrcBxBy<T>&, const PCArgs<T>&, const ZeroJob&,
+                       const AxisTables<T>& tx, const AxisTables<T>& ty, const DevCounters*,
+                       hipStream_t);
+template <typename T>
+void launch_small_pez(const Geom&, const SrcPEZ<T>&, const RowInvArgs<T>&, const ZeroJob&,
+                      const AxisTables<T>& tx, const AxisTables<T>& ty, hipStream_t);
+template <typename T>
+void launch_small_nodes(const Geom&, const T* src, T* dst, int nbatch, double shift,
+                        const AxisTables<T>& tx, const AxisTables<T>& ty, hipStream_t);
 int pc_partial_count(const Geom&);
 // column-strip width of a column pass over nfield planes
 template <typename T>

@@ -132,6 +132,10 @@ void solve(const qsp_config& c, unsigned char* ptr, int nb, const T* src, T* dst
   const int mx = entries(c.nx), my = entries(c.ny);
   hipLaunchKernelGGL(k_axis_tables<T>, dim3(((mx > my ? mx : my) + 255) / 256, 2), dim3(256), 0, st, jx, jy);
   QSP_LAUNCH_CHECK();
+  if (small_solve(c.nx, c.ny)) {
+    launch_small_nodes<T>(g, src, dst, nb, shift, tx, ty, st);
+    return;
+  }
   // each pass reads its rows or column strips into LDS before writing them
   // back, so all three work on the same planes
   NodeRowArgs<T> r{src, dst, planes};

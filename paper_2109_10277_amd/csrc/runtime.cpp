@@ -534,6 +534,10 @@ class Box final : public BoxBase {
 
   void solve_poisson(int nb, const void* src, void* dst, double shift) override {
     QSP_HIP(hipSetDevice(device_));
+    if (small_solve(cfg_.nx, cfg_.ny)) {
+      launch_small_nodes<T>(geom_, static_cast<const T*>(src), static_cast<T*>(dst), nb, shift, tx(), ty(), st_);
+      return;
+    }
     // rows of the sources, columns, rows of the solutions: all in t2_
     NodeRowArgs<T> r{static_cast<const T*>(src), static_cast<T*>(dst), t2_};
     launch_row_nodes<T>(geom_, r, false, nb, tx(), st_);
@@ -1573,7 +1577,6 @@ class Box final : public BoxBase {
     // psi, Ez, Bz (Sec. II steps 4-6)
     {
       SrcPEZ<T> s{dc[0], dc[1], dc[2], cfg_.n0, ionx_, iony_, t1_};
-      timed(QSP_K_ROW_FWD, [&] { launch_src_fwd_pez<T>(geom_, s, tx(), st_); });
       ColArgs<T> c{};
       c.in = t1_;
       c.out = t2_;
@@ -1587,7 +1590,6 @@ class Box final : public BoxBase {
       if (explicit_)   // and the explicit solver's deposits for slice k
         for (int q = 0; q < 3; ++q) c.zero.p[c.zero.count++] = ex_dep_[q];
       c.zero.n = pl;
-      timed(QSP_K_COL, [&] { launch_col_solve<T>(geom_, c, 3, ty(), lamx_, ctr_, st_); });
       RowInvArgs<T> r{};
       r.in[0] = t2_;
       r.out[0] = psi_;
@@ -1603,7 +1605,13 @@ class Box final : public BoxBase {
       r.guess = {bxk, byk, b_[i1_][0], b_[i1_][1], b_[i2_][0], b_[i2_][1], ctr_,
                  tape_slot_ ? tape_b(*tape_slot_, 0, 0) : nullptr,
                  tape_slot_ ? tape_b(*tape_slot_, 0, 1) : nullptr};
-      timed(QSP_K_ROW_INV, [&] { launch_row_inv<T>(geom_, r, 4, tx(), st_); });
+      if (small_grid(cfg_.nx, cfg_.ny)) {
+        timed(QSP_K_COL, [&] { launch_small_pez<T>(geom_, s, r, c.zero, tx(), ty(), st_); });
+      } else {
+        timed(QSP_K_ROW_FWD, [&] { launch_src_fwd_pez<T>(geom_, s, tx(), st_); });
+        timed(QSP_K_COL, [&] { launch_col_solve<T>(geom_, c, 3, ty(), lamx_, ctr_, st_); });
+        timed(QSP_K_ROW_INV, [&] { launch_row_inv<T>(geom_, r, 4, tx(), st_); });
+      }
       dst_solves_ += 3;
     }
     // predictor-corrector iterations launched for this slice
@@ -1657,11 +1665,15 @@ class Box final : public BoxBase {
           // ones start from (and on a taped slice the slice-k particle state)
           const PushMode tm = m == 0 ? first_trial : kTrialLater;
           timed(QSP_K_TRIAL, [&] { launch_push<T>(geom_, lat_, a, tm, ctr_, st_); });
-          timed(QSP_K_ROW_FWD, [&] { launch_src_fwd_bxby<T>(geom_, s, tx(), ctr_, st_); });
-          timed(QSP_K_COL, [&] { launch_col_solve<T>(geom_, c, 2, ty(), lamx_, ctr_, st_); });
           PCArgs<T> pc{t2_, bxk, byk, partial_, cfg_.pc_tol,
                        tape_slot_ ? tape_b(*tape_slot_, m + 1, 0) : nullptr,
                        tape_slot_ ? tape_b(*tape_slot_, m + 1, 1) : nullptr};
+          if (small_grid(cfg_.nx, cfg_.ny)) {
+            timed(QSP_K_COL, [&] { launch_small_bxby<T>(geom_, s, pc, c.zero, tx(), ty(), ctr_, st_); });
+            continue;
+          }
+          timed(QSP_K_ROW_FWD, [&] { launch_src_fwd_bxby<T>(geom_, s, tx(), ctr_, st_); });
+          timed(QSP_K_COL, [&] { launch_col_solve<T>(geom_, c, 2, ty(), lamx_, ctr_, st_); });
           timed(QSP_K_ROW_INV, [&] { launch_row_inv_pc<T>(geom_, pc, tx(), ctr_, st_); });
         }
       }

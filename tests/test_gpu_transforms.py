@@ -94,7 +94,8 @@ def test_solves_at_the_edges_of_the_transform_families(nx, ny, prec):
                 assert not edge.any(), name
 
 
-@pytest.mark.parametrize("nx,ny", [(64, 32), (128, 16), (16, 128), (128, 256), (256, 128), (512, 32)])
+@pytest.mark.parametrize("nx,ny", [(16, 32), (32, 64), (64, 32), (128, 16), (16, 128), (128, 256), (256, 128),
+                                   (512, 32)])
 @pytest.mark.parametrize("prec", ["fp32", "fp64"])
 def test_one_slice_with_two_transform_families(nx, ny, prec):
     # same cells as the square 32-node case, more of them along the long axes
