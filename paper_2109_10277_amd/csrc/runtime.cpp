@@ -592,11 +592,13 @@ class Box final : public BoxBase {
     }
   }
 
-  // Whole boxes from HIP graphs.  With the predictor-corrector to a
-  // tolerance, a box started from a fresh plasma launches per slice only as
+  // Whole boxes from HIP graphs.  With the predictor-corrector or the
+  // explicit solver to a tolerance, a box started from a fresh plasma launches per slice only as
   // many iterations as the budget of the slice holds instead of
   // pc_max_iter (the launches after convergence would read the device's
-  // converged flag and return).  A budget is the most iterations the slice
+  // converged flag and return: 4 launches an iteration, 2 us each even then;
+  // the explicit 512^2 box, which needs 1.8 iterations of 5 on average, took
+  // 23.8 ms with all of them launched, 20.4 with its budgets).  A budget is the most iterations the slice
   // needed in the boxes run so far, plus one where the slice's count has
   // risen before.  A slice that ends its budget unconverged below
   // pc_max_iter is counted on the device; the box is then run again from
@@ -609,7 +611,7 @@ class Box final : public BoxBase {
   // budgets save there.
   void run_box_graphs(const qsp_box_out* out, bool fresh) {
     const bool moving = beam_n_ > 0 && beam_dt_ != 0.0;
-    const bool pc = !explicit_ && cfg_.pc_tol > 0.0 && spec_mode_ != 0 && (!moving || spec_mode_ < 0);
+    const bool pc = cfg_.pc_tol > 0.0 && spec_mode_ != 0 && (!moving || spec_mode_ < 0);
     const bool spec = pc && fresh && budget_ready_ && budget_version_ == launch_version_;
     bool fell_short = false;
     if (spec) {
@@ -1619,7 +1621,7 @@ class Box final : public BoxBase {
     const int budgeted = pc_launch < cfg_.pc_max_iter ? 1 : 0;
     // Bx/By (Sec. II step 7, Sec. III.B): explicit solver or predictor-corrector
     if (explicit_) {
-      explicit_bxby(k, dc, amp, bxk, byk);
+      explicit_bxby(k, dc, amp, bxk, byk, pc_launch);
     } else {
       {
         PushArgs<T> a = push_args(fields(bxk, byk), trial_, k, 2, trial_sh_);
@@ -1755,9 +1757,9 @@ class Box final : public BoxBase {
   // Explicit Bx/By solver of slice k (Sec. III.B): deposit chi, DJx, DJy
   // from the slice-k plasma in the final psi, Ez, Bz, then solve
   // (lap - chi) B = R by preconditioned conjugate gradients, starting from
-  // the guess 2 B_{k-1} - B_{k-2} already in bxk, byk; at most pc_max_iter
-  // iterations, relative residual target pc_tol.
-  void explicit_bxby(int k, double* const* dc, double amp, T* bxk, T* byk) {
+  // the guess 2 B_{k-1} - B_{k-2} already in bxk, byk; `launch` iterations
+  // (pc_max_iter or the slice's budget), relative residual target pc_tol.
+  void explicit_bxby(int k, double* const* dc, double amp, T* bxk, T* byk, int launch) {
     const size_t pl = plane();
     PushArgs<T> d = push_args(fields(bxk, byk), ex_dep_, k, 3);
     timed(QSP_K_TRIAL, [&] { launch_push<T>(geom_, lat_, d, kExplicitDep, ctr_, st_); });
@@ -1801,13 +1803,13 @@ class Box final : public BoxBase {
     a.it = 0;
     timed(QSP_K_ROW_FWD, [&] { launch_explicit<T>(geom_, a, kExplSetup, tx(), ctr_, st_); });
     precondition(0);
-    for (int m = 1; m <= cfg_.pc_max_iter; ++m) {
+    for (int m = 1; m <= launch; ++m) {
       a.it = m;
       timed(QSP_K_OTHER, [&] { launch_explicit<T>(geom_, a, kExplMatvec, tx(), ctr_, st_); });
       timed(QSP_K_ROW_FWD, [&] { launch_explicit<T>(geom_, a, kExplUpdate, tx(), ctr_, st_); });
-      if (m < cfg_.pc_max_iter) precondition(m);
+      if (m < launch) precondition(m);
     }
-    a.it = cfg_.pc_max_iter;
+    a.it = launch;
     timed(QSP_K_OTHER, [&] { launch_explicit<T>(geom_, a, kExplClose, tx(), ctr_, st_); });
     dst_solves_ += 2 * (cfg_.pc_max_iter);
   }
