@@ -2,6 +2,7 @@
 // initial guess and bookkeeping, output copies and layout conversions.
 #include "common.hpp"
 #include "kernels.hpp"
+#include "out_body.hpp"
 #include "partials.hpp"
 
 namespace qsp {
@@ -67,43 +68,8 @@ __global__ void k_slice_end(DevCounters* ctr, int32_t* iters_out, int32_t* iters
   }
 }
 
-__global__ void k_out_copy(Geom g, OutCopy c) {
-  const int id = blockIdx.y;
-  const int kind = c.kind[id];
-  const int nx = g.nx, ny = g.ny;
-  const size_t total = kind == 0 ? static_cast<size_t>(nx + 1) * (ny + 1)
-                                 : (kind == 1 ? static_cast<size_t>(nx + 1) : 1);
-  for (size_t e = blockIdx.x * static_cast<size_t>(blockDim.x) + threadIdx.x; e < total;
-       e += static_cast<size_t>(gridDim.x) * blockDim.x) {
-    int i, j;
-    if (kind == 0) {
-      i = static_cast<int>(e % (nx + 1));
-      j = static_cast<int>(e / (nx + 1));
-    } else if (kind == 1) {
-      i = static_cast<int>(e);
-      j = ny / 2;
-    } else {
-      i = nx / 2;
-      j = ny / 2;
-    }
-    const bool stored = i < nx && j < ny;
-    const bool interior = i > 0 && j > 0 && i < nx && j < ny;
-    double v = 0.0;
-    if (stored) {
-      const size_t o = static_cast<size_t>(j) * nx + i;
-      v = c.is_double[id] ? static_cast<const double*>(c.src[id])[o]
-                          : static_cast<double>(static_cast<const float*>(c.src[id])[o]);
-      if (c.src2[id]) v += c.src2[id][o];
-    }
-    if (interior) {
-      if (c.add_beam[id]) v -= c.beam_amp * c.bgx[i] * c.bgy[j];
-      if (c.add_ion[id]) v += c.ionx ? c.n0 * c.ionx[i] * c.iony[j] : c.n0;
-    }
-    if (c.is_double[id])
-      static_cast<double*>(c.dst[id])[e] = v;
-    else
-      static_cast<float*>(c.dst[id])[e] = static_cast<float>(v);
-  }
+__global__ void __launch_bounds__(kBlock) k_out_copy(Geom g, OutCopy c) {
+  out_detail::out_copy_all(g, c, static_cast<int>(blockIdx.x));
 }
 
 template <typename S, typename T>
@@ -170,11 +136,8 @@ void launch_slice_end(DevCounters* ctr, int32_t* iters_out, int32_t* iters_own, 
 
 void launch_out_copy(const Geom& g, const OutCopy& c, hipStream_t st) {
   if (c.count == 0) return;
-  const size_t plane = static_cast<size_t>(g.nx + 1) * (g.ny + 1);
-  size_t b = (plane + kBlock - 1) / kBlock;
-  if (b > 4096) b = 4096;
-  hipLaunchKernelGGL(k_out_copy, dim3(static_cast<unsigned>(b), c.count), dim3(kBlock), 0, st,
-                     g, c);
+  hipLaunchKernelGGL(k_out_copy, dim3(static_cast<unsigned>(out_detail::out_wgs_all(g, c))), dim3(kBlock),
+                     0, st, g, c);
   QSP_LAUNCH_CHECK();
 }
 

@@ -238,9 +238,11 @@ struct PushArgs {
 
 template <typename T>
 void launch_init_plasma(const Lattice&, const Particles<T>&, double w0, hipStream_t);
+struct OutCopy;
+// out: outputs of the slice being left, carried by a real push
 template <typename T>
 void launch_push(const Geom&, const Lattice&, const PushArgs<T>&, PushMode, DevCounters*,
-                 hipStream_t);
+                 hipStream_t, const OutCopy* out = nullptr);
 template <typename T>
 void launch_import_state(const Geom&, const Lattice&, const Particles<T>&, const double* x,
                          const double* y, const double* ux, const double* uy,
@@ -312,7 +314,8 @@ void launch_slice_end(DevCounters*, int32_t* iters_out, int32_t* iters_own, doub
                       double tol, int max_iter, int budgeted, const double* pc_partial, int pc_nblk,
                       hipStream_t);
 
-// copy a stored [ny][nx] grid into an [ny+1][nx+1] node array
+// outputs of a slice: stored [ny][nx] grids to [ny+1][nx+1] node arrays, their
+// middle row or node
 struct OutCopy {
   const void* src[kMaxOut];
   const double* src2[kMaxOut];  // FP64 plane added to an FP64 source, may be null

@@ -1697,7 +1697,9 @@ class Box final : public BoxBase {
     oc.iony = iony_;
     oc.bgx = bgx_;
     oc.bgy = bgy_;
-    if (oc.count) timed(QSP_K_OTHER, [&] { launch_out_copy(geom_, oc, st_); });
+    // (with the real push below, unless the timer samples that launch)
+    const bool out_rides = k + 1 < cfg_.nzeta && !timer_.active(cursor_);
+    if (oc.count && !out_rides) timed(QSP_K_OTHER, [&] { launch_out_copy(geom_, oc, st_); });
     // real push to slice k+1 with deposit there (Sec. II step 1 of the next
     // slice); it also closes the predictor-corrector bookkeeping of slice k
     if (k + 1 < cfg_.nzeta) {
@@ -1724,7 +1726,9 @@ class Box final : public BoxBase {
         if (beam_push_here) beam_dirty_ = true;
         beam_ahead_ = true;
       }
-      const auto job = [this, a] { launch_push<T>(geom_, lat_, a, kPushReal, ctr_, st_); };
+      const auto job = [this, a, out = out_rides && oc.count ? &oc : nullptr] {
+        launch_push<T>(geom_, lat_, a, kPushReal, ctr_, st_, out);
+      };
       if (capturing_ && timer_.active(cursor_)) {
         // the sampled launch runs between graph segments, under its events
         end_segment();
