@@ -270,7 +270,7 @@ __global__ void __launch_bounds__(kBlock) k_adj_push(Geom g, Lattice L, AdjPushA
   const int nx = g.nx, ny = g.ny;
   for (int e = threadIdx.x; e < 6 * ntile; e += kBlock) tile[e] = 0.0;
   __syncthreads();
-  const int I0 = blockIdx.x * ts.tx, J0 = blockIdx.y * ts.ty;
+  const int I0 = push_detail::tile_column(false) * ts.tx, J0 = blockIdx.y * ts.ty;
   const int ox = (I0 >> ts.lpx) - ts.halo, oy = (J0 >> ts.lpy) - ts.halo;
   auto scat = [&](int c, const Axis<O, T>& X, const Axis<O, T>& Y, double v) {
     if (v == 0.0) return;
@@ -374,7 +374,7 @@ __global__ void __launch_bounds__(kBlock) k_adj_trial_later(Geom g, Lattice L, A
   const int nx = g.nx, ny = g.ny;
   for (int e = threadIdx.x; e < 2 * ntile; e += kBlock) tile[e] = 0.0;
   __syncthreads();
-  const int I0 = blockIdx.x * ts.tx, J0 = blockIdx.y * ts.ty;
+  const int I0 = push_detail::tile_column(false) * ts.tx, J0 = blockIdx.y * ts.ty;
   const int ox = (I0 >> ts.lpx) - ts.halo, oy = (J0 >> ts.lpy) - ts.halo;
   auto scat = [&](int c, const Axis<O, T>& X, const Axis<O, T>& Y, double v) {
     if (v == 0.0) return;

@@ -85,14 +85,15 @@ k_push(Geom g, Lattice L, PushArgs<T> a, DevCounters* ctr, PushRide<MODE> ride) 
     }
   }
   extern __shared__ __align__(16) unsigned char smem_raw[];
+  const int tbx = push_detail::tile_column(MODE == kPushReal);
   if constexpr (MODE == kExplicitDep)
-    push_detail::explicit_tile<T, O>(g, L, a, blockIdx.x, blockIdx.y,
+    push_detail::explicit_tile<T, O>(g, L, a, tbx, blockIdx.y,
                                      reinterpret_cast<double*>(smem_raw));
   else if constexpr (MODE == kPushTrialTape)
-    push_tile<T, kPushTrial, O, true>(g, L, a, ctr, blockIdx.x, blockIdx.y,
+    push_tile<T, kPushTrial, O, true>(g, L, a, ctr, tbx, blockIdx.y,
                                       reinterpret_cast<double*>(smem_raw));
   else
-    push_tile<T, MODE, O>(g, L, a, ctr, blockIdx.x, blockIdx.y,
+    push_tile<T, MODE, O>(g, L, a, ctr, tbx, blockIdx.y,
                           reinterpret_cast<double*>(smem_raw));
 }
 

@@ -46,6 +46,22 @@ __host__ __device__ inline TileShape tile_shape(const Lattice& L, int rows, int 
   return t;
 }
 
+// Tile column of the workgroup, its row being blockIdx.y.  Workgroups go round-
+// robin to the 8 XCDs, so with whole rows of tiles a column of tiles would stay
+// on one XCD, and the expensive tiles, those of the wake around the axis (same-
+// address LDS atomics, particles outside their tile), on two or three of them:
+// each row starts one tile further on.  1024^2 with 2x2 particles: real push
+// 224 -> 186 us, later trial 79 -> 67, first trial 116 -> 99; one particle a
+// cell: real push 69.9 -> 65.7.  The price is the field rows that vertical
+// neighbours no longer share in an L2: with 16 tiles a row or fewer it takes
+// what the trial pushes gain (1024^2: 20.3 against 19.6 us in quiet plasma, no
+// difference in the wake; 512^2 box 23.46 against 23.36 ms), so these rotate
+// from 32 tiles a row up.
+__device__ __forceinline__ int tile_column(bool real_push) {
+  const unsigned int gx = gridDim.x;   // a power of two, like the lattice
+  return static_cast<int>(real_push || gx >= 32 ? (blockIdx.x + blockIdx.y) & (gx - 1) : blockIdx.x);
+}
+
 template <typename T>
 __device__ inline bool inside(int c0, T t, int n) {
   const T fl = floor(t);
