@@ -680,45 +680,66 @@ __device__ __forceinline__ void explicit_tile(const Geom& g, const Lattice& L,
   const TileShape ts = tile_shape(L, a.tile_rows, a.tile_halo);
   const int ntile = ts.nw * ts.nh;
   const bool tiled = a.tiled != 0;
-  if (tiled) {
-    __syncthreads();
-    for (int e = threadIdx.x; e < nch * ntile; e += kBlock) tile[e] = 0.0;
-    __syncthreads();
-  }
   const int I0 = tbx * ts.tx, J0 = tby * ts.ty;
   const int ox = (I0 >> ts.lpx) - ts.halo, oy = (J0 >> ts.lpy) - ts.halo;
   const int nx = g.nx, ny = g.ny;
   const double ihx = 1.0 / a.hx, ihy = 1.0 / a.hy;
   const T floor_d = static_cast<T>(a.psi_floor);
+  // the first loads are in flight while the histogram is cleared
+  ParticleLoad<T, kDepositOnly> in;
+  in.load(L, a, ts, I0, J0, static_cast<int>(threadIdx.x));
+  if (tiled) {
+    __syncthreads();
+    for (int e = threadIdx.x; e < nch * ntile; e += kBlock) tile[e] = 0.0;
+    __syncthreads();
+  }
 
   for (int e = threadIdx.x; e < ts.tx * ts.ty; e += kBlock) {
-    const int I = I0 + e % ts.tx, J = J0 + e / ts.tx;
-    const size_t p = static_cast<size_t>(J) * L.nX + I;
-    const T w = a.p.w[p];
-    const T xi = a.p.xi_x[p], eta = a.p.xi_y[p];
-    const T ux = a.p.ux[p], uy = a.p.uy[p], psi = a.p.psi[p];
+    if (e >= kBlock) in.load(L, a, ts, I0, J0, e);
+    const int I = I0 + (e & (ts.tx - 1)), J = J0 + (e >> ts.ltx);
+    const T w = in.w;
+    T xi = in.y[0], eta = in.y[1];
+    const T ux = in.y[2], uy = in.y[3], psi = in.y[4];
+    pin(xi);
+    pin(eta);
     const int ci0 = I >> ts.lpx, cj0 = J >> ts.lpy;
     const T fx0 = (T(2 * (I & (L.ppc_x - 1)) + 1)) / T(2 * L.ppc_x);
     const T fy0 = (T(2 * (J & (L.ppc_y - 1)) + 1)) / T(2 * L.ppc_y);
     int bi, bj;
     const T dx = shape::locate<O>(ci0, fx0 + xi, nx, bi);
     const T dy = shape::locate<O>(cj0, fy0 + eta, ny, bj);
-    T wx[O + 1], wy[O + 1];
-    int ix[O + 1], iy[O + 1];
-    bool okx[O + 1], oky[O + 1];
-    shape::weights<O>(dx, wx);
-    shape::weights<O>(dy, wy);
-    shape::axis_nodes<O>(bi, nx, ix, okx);
-    shape::axis_nodes<O>(bj, ny, iy, oky);
+    T e1, e2, ez, bz;
+    if constexpr (O == 1) {
+      Cic<T> cic;
+      cic.at(bi, bj, dx, dy, nx, ny);
+      auto n1 = cic.load(a.f.exmby), n2 = cic.load(a.f.eypbx), n3 = cic.load(a.f.ez), n4 = cic.load(a.f.bz);
+      __builtin_amdgcn_sched_barrier(0);
+      n1.pin();
+      n2.pin();
+      n3.pin();
+      n4.pin();
+      e1 = cic.sum(n1);
+      e2 = cic.sum(n2);
+      ez = cic.sum(n3);
+      bz = cic.sum(n4);
+    } else {
+      T wx[O + 1], wy[O + 1];
+      int ix[O + 1], iy[O + 1];
+      bool okx[O + 1], oky[O + 1];
+      shape::weights<O>(dx, wx);
+      shape::weights<O>(dy, wy);
+      shape::axis_nodes<O>(bi, nx, ix, okx);
+      shape::axis_nodes<O>(bj, ny, iy, oky);
 #pragma unroll
-    for (int q = 0; q <= O; ++q) {
-      wx[q] = okx[q] ? wx[q] : T(0);
-      wy[q] = oky[q] ? wy[q] : T(0);
+      for (int q = 0; q <= O; ++q) {
+        wx[q] = okx[q] ? wx[q] : T(0);
+        wy[q] = oky[q] ? wy[q] : T(0);
+      }
+      e1 = shape::interp<O>(a.f.exmby, ix, iy, wx, wy, nx);
+      e2 = shape::interp<O>(a.f.eypbx, ix, iy, wx, wy, nx);
+      ez = shape::interp<O>(a.f.ez, ix, iy, wx, wy, nx);
+      bz = shape::interp<O>(a.f.bz, ix, iy, wx, wy, nx);
     }
-    const T e1 = shape::interp<O>(a.f.exmby, ix, iy, wx, wy, nx);
-    const T e2 = shape::interp<O>(a.f.eypbx, ix, iy, wx, wy, nx);
-    const T ez = shape::interp<O>(a.f.ez, ix, iy, wx, wy, nx);
-    const T bz = shape::interp<O>(a.f.bz, ix, iy, wx, wy, nx);
     if (w == T(0)) continue;
     const T draw = T(1) + psi;
     const bool clamped = draw < floor_d;
