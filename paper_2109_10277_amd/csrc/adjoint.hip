@@ -132,15 +132,63 @@ __device__ __forceinline__ void trial_deposit_adjoint(const AdjPushArgs<T>& a, i
 // record.  Bound by HBM: with the history read and every slot of the ring
 // read, modified and written in both pushes (76 and 83 values a particle
 // instead of 43 and 39) they took 364 and 431 us at 1024^2, 4 ppc, FP32.
+// Every value of a particle is fetched at once (AdjPushLoad), in front of the
+// histogram's clear: the compiler keeps each read-modify-write in its place
+// otherwise, ten memory round trips in a row (1024^2, 4 ppc, FP32: trial 226 ->
+// 168 us, real 194 -> 173, later trials 97 -> 79).
+template <typename T, int MODE>
+struct AdjPushLoad {
+  T w, fac, y[5], ly[5];
+  T ring[MODE == 0 ? 4 : 1][5];   // real: Lambda_{k+m}, m = 1..4; trial: Lambda_k
+  T rec[5], acc[7];               // trial: position and momentum, Psi; later iterations' sums
+  __device__ __forceinline__ void load(const Lattice& L, const AdjPushArgs<T>& a, unsigned int p) {
+    const size_t np = static_cast<size_t>(L.np), np5 = 5 * np;
+    w = load_at(a.p.w, p);
+    y[0] = load_at(a.p.xi_x, p);
+    y[1] = load_at(a.p.xi_y, p);
+    y[2] = load_at(a.p.ux, p);
+    y[3] = load_at(a.p.uy, p);
+    y[4] = load_at(a.p.psi, p);
+    const T* q = a.rec;
+#pragma unroll
+    for (int c = 0; c < 6; ++c, q += np) {
+      if (c == 4)
+        fac = load_at(q, p);   // 0: absorbed by the step
+      else if constexpr (MODE == 1)
+        rec[c < 4 ? c : 4] = load_at(q, p);
+    }
+    q = a.lam_y;
+#pragma unroll
+    for (int c = 0; c < 5; ++c, q += np) ly[c] = load_at(q, p);
+#pragma unroll
+    for (int m = 0; m < (MODE == 0 ? 4 : 1); ++m) {
+      q = a.lam_ring + static_cast<size_t>((a.k + (MODE == 0 ? m + 1 : 0)) & 3) * np5;
+#pragma unroll
+      for (int c = 0; c < 5; ++c, q += np) ring[m][c] = load_at(q, p);
+    }
+    if (MODE == 1 && a.acc) {
+      q = a.acc;
+#pragma unroll
+      for (int c = 0; c < 7; ++c, q += np) acc[c] = load_at(q, p);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  }
+};
+
 template <typename T, int MODE, int O, typename Scatter>
 __device__ __forceinline__ void adj_push_one(const Geom& g, const Lattice& L,
-                                             const AdjPushArgs<T>& a, int I, int J,
-                                             Scatter&& scat) {
-  const int64_t np = L.np;
-  const int64_t p = static_cast<int64_t>(J) * L.nX + I;
-  const T w = a.p.w[p];
-  const T fac = a.rec[4 * np + p];   // 0: absorbed by the step
-  T y[5] = {a.p.xi_x[p], a.p.xi_y[p], a.p.ux[p], a.p.uy[p], a.p.psi[p]};
+                                             const AdjPushArgs<T>& a, AdjPushLoad<T, MODE>& in,
+                                             int I, int J, Scatter&& scat) {
+  const size_t np = static_cast<size_t>(L.np);
+  const unsigned int p = static_cast<unsigned int>(J) * static_cast<unsigned int>(L.nX) +
+                         static_cast<unsigned int>(I);
+#pragma unroll
+  for (int c = 0; c < 5; ++c) {
+    push_detail::pin(in.y[c]);
+    push_detail::pin(in.ly[c]);
+  }
+  const T w = in.w, fac = in.fac;
+  const T (&y)[5] = in.y;
   const T dz = static_cast<T>(a.dzeta);
   const T b[5] = {T(kAB5[0]), T(kAB5[1]), T(kAB5[2]), T(kAB5[3]), T(kAB5[4])};
   T* ly = a.lam_y;
@@ -150,26 +198,21 @@ __device__ __forceinline__ void adj_push_one(const Geom& g, const Lattice& L,
   T lf[5] = {0, 0, 0, 0, 0};
   T lf_own[2] = {0, 0};   // trial: lf[2], lf[3] of this iteration's deposit alone
   if (MODE == 0) {
-    T lam4[5][5];   // Lambda_{k+m}, m = 1..4
+    constexpr int M = MODE == 0 ? 4 : 1;   // rows of in.ring
 #pragma unroll
-    for (int c = 0; c < 5; ++c) lnew[c] = ly[c * np + p];
-#pragma unroll
-    for (int m = 1; m <= 4; ++m)
-#pragma unroll
-      for (int c = 0; c < 5; ++c)
-        lam4[m][c] = a.lam_ring[(static_cast<size_t>((a.k + m) & 3) * 5 + c) * np + p];
+    for (int c = 0; c < 5; ++c) lnew[c] = in.ly[c];
     if (w == T(0)) return;
 #pragma unroll
     for (int c = 0; c < 5; ++c) {
       if (!moved) lnew[c] = T(0);
-      const T sum = b[0] * lnew[c] + (b[1] * lam4[1][c] + b[2] * lam4[2][c] + b[3] * lam4[3][c] +
-                                      b[4] * lam4[4][c]);
+      const T sum = b[0] * lnew[c] + (b[1] * in.ring[0][c] + b[2] * in.ring[1 % M][c] +
+                                      b[3] * in.ring[2 % M][c] + b[4] * in.ring[3 % M][c]);
       lf[c] = moved ? -dz * sum : T(0);
-      own[c * np + p] = lnew[c];
+      store_at(own + c * np, p, lnew[c]);
     }
     if (!moved) {
 #pragma unroll
-      for (int c = 0; c < 5; ++c) ly[c * np + p] = T(0);
+      for (int c = 0; c < 5; ++c) store_at(ly + c * np, p, T(0));
       return;
     }
   } else {
@@ -200,20 +243,19 @@ __device__ __forceinline__ void adj_push_one(const Geom& g, const Lattice& L,
   const T G = gam * id;                              // gamma / D
   if (MODE == 1) {
     const T kick = dz * b[0];
-    trial_deposit_adjoint<T, O>(a, ci0, cj0, fx0, fy0, a.rec[p], a.rec[np + p],
-                                a.rec[2 * np + p] - kick * by, a.rec[3 * np + p] + kick * bx,
-                                a.rec[5 * np + p], w, nx, ny, lnew);
+    trial_deposit_adjoint<T, O>(a, ci0, cj0, fx0, fy0, in.rec[0], in.rec[1], in.rec[2] - kick * by,
+                                in.rec[3] + kick * bx, in.rec[4], w, nx, ny, lnew);
     // this iteration's own Bx, By terms use its own deposit adjoint only;
     // the later iterations' sums join everything they share with it
 #pragma unroll
     for (int c = 2; c < 4; ++c) lf_own[c - 2] = -dz * b[0] * lnew[c];
     if (a.acc)
 #pragma unroll
-      for (int c = 0; c < 5; ++c) lnew[c] += a.acc[c * np + p];
+      for (int c = 0; c < 5; ++c) lnew[c] += in.acc[c];
 #pragma unroll
     for (int c = 0; c < 5; ++c) {
       lf[c] = -dz * b[0] * lnew[c];
-      own[c * np + p] += lnew[c];
+      store_at(own + c * np, p, in.ring[0][c] + lnew[c]);
     }
   }
   // the identity part of the step
@@ -244,15 +286,15 @@ __device__ __forceinline__ void adj_push_one(const Geom& g, const Lattice& L,
     scat(c, X, Y, static_cast<double>(lg[c]));
   }
   if (MODE == 1 && a.acc) {   // the later iterations' own Bx, By position terms
-    lam[0] += a.acc[5 * np + p];
-    lam[1] += a.acc[6 * np + p];
+    lam[0] += in.acc[5];
+    lam[1] += in.acc[6];
   }
   if (MODE == 0) {
 #pragma unroll
-    for (int c = 0; c < 5; ++c) ly[c * np + p] = lam[c];
+    for (int c = 0; c < 5; ++c) store_at(ly + c * np, p, lam[c]);
   } else {
 #pragma unroll
-    for (int c = 0; c < 5; ++c) ly[c * np + p] += lam[c];
+    for (int c = 0; c < 5; ++c) store_at(ly + c * np, p, in.ly[c] + lam[c]);
   }
 }
 
@@ -268,9 +310,11 @@ __global__ void __launch_bounds__(kBlock) k_adj_push(Geom g, Lattice L, AdjPushA
   const push_detail::TileShape ts = push_detail::tile_shape(L, a.tile_rows, a.tile_halo);
   const int ntile = ts.nw * ts.nh;
   const int nx = g.nx, ny = g.ny;
+  const int I0 = push_detail::tile_column(false) * ts.tx, J0 = blockIdx.y * ts.ty;
+  AdjPushLoad<T, MODE> in;
+  in.load(L, a, push_detail::tile_particle(L, ts, I0, J0, static_cast<int>(threadIdx.x)));
   for (int e = threadIdx.x; e < 6 * ntile; e += kBlock) tile[e] = 0.0;
   __syncthreads();
-  const int I0 = push_detail::tile_column(false) * ts.tx, J0 = blockIdx.y * ts.ty;
   const int ox = (I0 >> ts.lpx) - ts.halo, oy = (J0 >> ts.lpy) - ts.halo;
   auto scat = [&](int c, const Axis<O, T>& X, const Axis<O, T>& Y, double v) {
     if (v == 0.0) return;
@@ -297,8 +341,10 @@ __global__ void __launch_bounds__(kBlock) k_adj_push(Geom g, Lattice L, AdjPushA
       }
     }
   };
-  for (int e = threadIdx.x; e < ts.tx * ts.ty; e += kBlock)
-    adj_push_one<T, MODE, O>(g, L, a, I0 + e % ts.tx, J0 + e / ts.tx, scat);
+  for (int e = threadIdx.x; e < ts.tx * ts.ty; e += kBlock) {
+    if (e >= kBlock) in.load(L, a, push_detail::tile_particle(L, ts, I0, J0, e));
+    adj_push_one<T, MODE, O>(g, L, a, in, I0 + (e & (ts.tx - 1)), J0 + (e >> ts.ltx), scat);
+  }
   __syncthreads();
   push_detail::flush_tile<6>(a.lam_F, tile, ts, ox, oy, nx, ny);
 }
@@ -311,26 +357,50 @@ __global__ void __launch_bounds__(kBlock) k_adj_push(Geom g, Lattice L, AdjPushA
 // trial push's transpose carries back to the state, history and E fields,
 // are summed per particle into acc (with the slice-k position terms of this
 // iteration's own Bx, By gradients).
+template <typename T>
+struct AdjLaterLoad {   // fetched at once, like AdjPushLoad
+  T w, xk, ek, rec[6], acc[7];
+  __device__ __forceinline__ void load(const Lattice& L, const AdjPushArgs<T>& a, unsigned int p) {
+    const size_t np = static_cast<size_t>(L.np);
+    w = load_at(a.p.w, p);
+    xk = load_at(a.p.xi_x, p);
+    ek = load_at(a.p.xi_y, p);
+    const T* q = a.rec;
+#pragma unroll
+    for (int c = 0; c < 6; ++c, q += np) rec[c] = load_at(q, p);
+    if (a.acc_mode != 1) {
+      q = a.acc;
+#pragma unroll
+      for (int c = 0; c < 7; ++c, q += np) acc[c] = load_at(q, p);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  }
+};
+
 template <typename T, int O, typename Scatter>
 __device__ __forceinline__ void adj_trial_later_one(const Geom& g, const Lattice& L,
-                                                    const AdjPushArgs<T>& a, int I, int J,
-                                                    Scatter&& scat) {
-  const int64_t np = L.np;
-  const int64_t p = static_cast<int64_t>(J) * L.nX + I;
-  const T* r = a.rec;
+                                                    const AdjPushArgs<T>& a, AdjLaterLoad<T>& in,
+                                                    int I, int J, Scatter&& scat) {
+  const size_t np = static_cast<size_t>(L.np);
+  const unsigned int p = static_cast<unsigned int>(J) * static_cast<unsigned int>(L.nX) +
+                         static_cast<unsigned int>(I);
   T* acc = a.acc;
   const bool store = a.acc_mode == 1;
-  const T fac = r[4 * np + p];
+  push_detail::pin(in.xk);
+  push_detail::pin(in.ek);
+#pragma unroll
+  for (int c = 0; c < 6; ++c) push_detail::pin(in.rec[c]);
+  const T fac = in.rec[4];
   if (fac == T(0)) {   // dead, or absorbed by the step: nothing deposited
     if (store)
 #pragma unroll
-      for (int c = 0; c < 7; ++c) acc[c * np + p] = T(0);
+      for (int c = 0; c < 7; ++c) store_at(acc + c * np, p, T(0));
     return;
   }
-  const T w = a.p.w[p];
-  const T xk = a.p.xi_x[p], ek = a.p.xi_y[p];
-  const T xn = r[p], en = r[np + p], cx = r[2 * np + p], cy = r[3 * np + p];
-  const T psin = r[5 * np + p];
+  const T w = in.w;
+  const T xk = in.xk, ek = in.ek;
+  const T xn = in.rec[0], en = in.rec[1], cx = in.rec[2], cy = in.rec[3];
+  const T psin = in.rec[5];
   const int nx = g.nx, ny = g.ny;
   const int lpx = 31 - __clz(L.ppc_x), lpy = 31 - __clz(L.ppc_y);
   const int ci0 = I >> lpx, cj0 = J >> lpy;
@@ -360,7 +430,7 @@ __device__ __forceinline__ void adj_trial_later_one(const Geom& g, const Lattice
   v[5] = lgbx * bx_x + lgby * by_x;
   v[6] = lgbx * bx_y + lgby * by_y;
 #pragma unroll
-  for (int c = 0; c < 7; ++c) acc[c * np + p] = store ? v[c] : acc[c * np + p] + v[c];
+  for (int c = 0; c < 7; ++c) store_at(acc + c * np, p, store ? v[c] : in.acc[c] + v[c]);
 }
 
 // Tiles as in k_adj_push; two LDS histograms (Bx, By adjoints of the
@@ -372,9 +442,11 @@ __global__ void __launch_bounds__(kBlock) k_adj_trial_later(Geom g, Lattice L, A
   const push_detail::TileShape ts = push_detail::tile_shape(L, a.tile_rows, a.tile_halo);
   const int ntile = ts.nw * ts.nh;
   const int nx = g.nx, ny = g.ny;
+  const int I0 = push_detail::tile_column(false) * ts.tx, J0 = blockIdx.y * ts.ty;
+  AdjLaterLoad<T> in;
+  in.load(L, a, push_detail::tile_particle(L, ts, I0, J0, static_cast<int>(threadIdx.x)));
   for (int e = threadIdx.x; e < 2 * ntile; e += kBlock) tile[e] = 0.0;
   __syncthreads();
-  const int I0 = push_detail::tile_column(false) * ts.tx, J0 = blockIdx.y * ts.ty;
   const int ox = (I0 >> ts.lpx) - ts.halo, oy = (J0 >> ts.lpy) - ts.halo;
   auto scat = [&](int c, const Axis<O, T>& X, const Axis<O, T>& Y, double v) {
     if (v == 0.0) return;
@@ -401,8 +473,10 @@ __global__ void __launch_bounds__(kBlock) k_adj_trial_later(Geom g, Lattice L, A
       }
     }
   };
-  for (int e = threadIdx.x; e < ts.tx * ts.ty; e += kBlock)
-    adj_trial_later_one<T, O>(g, L, a, I0 + e % ts.tx, J0 + e / ts.tx, scat);
+  for (int e = threadIdx.x; e < ts.tx * ts.ty; e += kBlock) {
+    if (e >= kBlock) in.load(L, a, push_detail::tile_particle(L, ts, I0, J0, e));
+    adj_trial_later_one<T, O>(g, L, a, in, I0 + (e & (ts.tx - 1)), J0 + (e >> ts.ltx), scat);
+  }
   __syncthreads();
   push_detail::flush_tile<2>(a.lam_F + 3, tile, ts, ox, oy, nx, ny);
 }
@@ -422,17 +496,26 @@ __global__ void __launch_bounds__(kBlock) k_adj_deposit(Geom g, Lattice L, AdjDe
       a.grad_sigma[1] += -a.amp * t[2];
     }
   }
-  const int64_t np = L.np;
-  const int64_t p = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x;
+  const size_t np = static_cast<size_t>(L.np);
+  const unsigned int p = blockIdx.x * static_cast<unsigned int>(kBlock) + threadIdx.x;   // np < 2^30
   if (p >= np) return;
-  const T w = a.p.w[p];
+  T w = load_at(a.p.w, p);
+  T xi = load_at(a.p.xi_x, p), eta = load_at(a.p.xi_y, p);
+  T ux = load_at(a.p.ux, p), uy = load_at(a.p.uy, p), psi = load_at(a.p.psi, p);
+  T ly[5];
+#pragma unroll
+  for (int c = 0; c < 5; ++c) ly[c] = load_at(static_cast<const T*>(a.lam_y) + c * np, p);
+  __builtin_amdgcn_sched_barrier(0);
+  push_detail::pin(xi);
+  push_detail::pin(eta);
+#pragma unroll
+  for (int c = 0; c < 5; ++c) push_detail::pin(ly[c]);
   if (w == T(0)) return;
   const int nx = g.nx, ny = g.ny;
-  const int I = static_cast<int>(p % L.nX), J = static_cast<int>(p / L.nX);
+  const int I = static_cast<int>(p & static_cast<unsigned int>(L.nX - 1)), J = static_cast<int>(p >> (31 - __clz(L.nX)));
   const int lpx = 31 - __clz(L.ppc_x), lpy = 31 - __clz(L.ppc_y);
   const T fx0 = (T(2 * (I & (L.ppc_x - 1)) + 1)) / T(2 * L.ppc_x);
   const T fy0 = (T(2 * (J & (L.ppc_y - 1)) + 1)) / T(2 * L.ppc_y);
-  const T xi = a.p.xi_x[p], eta = a.p.xi_y[p], ux = a.p.ux[p], uy = a.p.uy[p], psi = a.p.psi[p];
   int bi, bj;
   const T dx = shape::locate<O>(I >> lpx, fx0 + xi, nx, bi);
   const T dy = shape::locate<O>(J >> lpy, fy0 + eta, ny, bj);
@@ -461,7 +544,7 @@ __global__ void __launch_bounds__(kBlock) k_adj_deposit(Geom g, Lattice L, AdjDe
     if (un) l[4] += dd[c] * static_cast<T>(v);
   }
 #pragma unroll
-  for (int c = 0; c < 5; ++c) a.lam_y[c * np + p] += l[c];
+  for (int c = 0; c < 5; ++c) store_at(a.lam_y + c * np, p, ly[c] + l[c]);
 }
 
 // ------------------------------------------------------------------ grid side

@@ -62,6 +62,15 @@ __device__ __forceinline__ int tile_column(bool real_push) {
   return static_cast<int>(real_push || gx >= 32 ? (blockIdx.x + blockIdx.y) & (gx - 1) : blockIdx.x);
 }
 
+// Index of particle e of the tile at site (I0, J0) (the tile's first one for e
+// beyond it).
+__device__ __forceinline__ unsigned int tile_particle(const Lattice& L, const TileShape& ts, int I0,
+                                                      int J0, int e) {
+  const int ec = e < ts.tx * ts.ty ? e : 0;
+  return static_cast<unsigned int>(J0 + (ec >> ts.ltx)) * static_cast<unsigned int>(L.nX) +
+         static_cast<unsigned int>(I0 + (ec & (ts.tx - 1)));
+}
+
 template <typename T>
 __device__ inline bool inside(int c0, T t, int n) {
   const T fl = floor(t);
@@ -412,10 +421,7 @@ struct ParticleLoad {
   __device__ __forceinline__ void load(const Lattice& L, const PushArgs<T>& a, const TileShape& ts,
                                        int I0, int J0, int e) {
     const size_t np = static_cast<size_t>(L.np);
-    const int ec = e < ts.tx * ts.ty ? e : 0;
-    const unsigned int p =
-        static_cast<unsigned int>(J0 + (ec >> ts.ltx)) * static_cast<unsigned int>(L.nX) +
-        static_cast<unsigned int>(I0 + (ec & (ts.tx - 1)));
+    const unsigned int p = tile_particle(L, ts, I0, J0, e);
     y[0] = load_at(a.p.xi_x, p);
     y[1] = load_at(a.p.xi_y, p);
     y[2] = load_at(a.p.ux, p);
