@@ -151,7 +151,9 @@ k_row_inv(Geom g, RowInvArgs<T> a, AxisTables<T> tx) {
     return;
   }
   const T mihx = static_cast<T>(-0.5 / g.hx);
-  auto put = [&](auto with_dx) {   // tested once: per element the loop stays rolled
+  // tested once: per element the loop stays rolled (21.7 against 20.2 us at
+  // 1024^2 in FP32)
+  auto put = [&](auto with_dx) {
     for_row_elems<R, LOGN>([&](int e) {
       const int r = e >> LOGN, i = e & (n - 1);
       const int j = j0 + r;

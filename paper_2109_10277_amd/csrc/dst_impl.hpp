@@ -813,9 +813,9 @@ __device__ __forceinline__ void zero_job(const ZeroJob& z, size_t bid, size_t nb
   }
 }
 
-// The guess is loaded in front of the pass's transform (up to kGuess elements
-// a thread; with them behind it, its round trip came on top) and stored
-// after it.
+// The guess is loaded and stored in front of the pass's transform (up to kGuess
+// elements a thread): behind it, its round trip came on top, and its stores
+// now drain under the transform.
 constexpr int kGuess = 6;
 template <typename T>
 struct GuessRegs {

@@ -225,10 +225,10 @@ struct PushArgs {
   const double* pc_partial;
   int pc_nblk;
   int pc_iter;              // trial push: P-C iteration index within the slice
-  // trial record (6 planes of np): position at k+1 (x and y offsets), the
-  // momentum at k+1 without the Bx/By kick, -w/D at k+1 (0: no deposit),
-  // Psi at k+1.  The first trial push of a slice writes it (if non-null),
-  // later ones read it.
+  // trial record, planes of np: position at k+1 (x and y offsets), the
+  // momentum at k+1 without the Bx/By kick, -w/D at k+1 (0: no deposit) and,
+  // on taped slices only, Psi at k+1.  The first trial push of a slice writes
+  // it (if non-null), later ones read it.
   T* rec;
   // kPushTrialTape: copy of the slice-k particle state the push reads, 6
   // planes of np in the order xi_x, xi_y, ux, uy, psi, w

@@ -1392,9 +1392,9 @@ class Box final : public BoxBase {
       for (int c = 0; c < 5; ++c) dep_[d][c] = alloc<double>(pl);
     trial_[0] = alloc<double>(pl);
     trial_[1] = alloc<double>(pl);
-    trial_sh_[0] = alloc<double>(pl);
-    trial_sh_[1] = alloc<double>(pl);
-    if (!explicit_) trial_rec_ = alloc<T>(6 * static_cast<size_t>(lat_.np));
+    if (!explicit_)
+      for (int c = 0; c < 2; ++c) trial_sh_[c] = alloc<double>(pl);
+    if (!explicit_) trial_rec_ = alloc<T>(5 * static_cast<size_t>(lat_.np));   // the sixth plane: tapes only
     const size_t np = static_cast<size_t>(lat_.np);
     p_.xi_x = alloc<T>(np);
     p_.xi_y = alloc<T>(np);
@@ -1404,11 +1404,14 @@ class Box final : public BoxBase {
     p_.w = alloc<T>(np);
     p_.hist = alloc<T>(20 * np);
     p_.pab = alloc<T>(5 * np);
-    twx_ = alloc<Cplx<T>>(axis_tw_size(sizeof(T), cfg_.nx));
-    prex_ = alloc<T>(cfg_.nx);
+    // transform tables (pre: wave core only), one set for two axes of one length
+    twx_ = twy_ = alloc<Cplx<T>>(axis_tw_size(sizeof(T), cfg_.nx));
+    if (wave_core(sizeof(T), cfg_.nx)) prex_ = prey_ = alloc<T>(cfg_.nx);
+    if (cfg_.ny != cfg_.nx) {
+      twy_ = alloc<Cplx<T>>(axis_tw_size(sizeof(T), cfg_.ny));
+      prey_ = wave_core(sizeof(T), cfg_.ny) ? alloc<T>(cfg_.ny) : nullptr;
+    }
     lamx_ = alloc<double>(cfg_.nx);
-    twy_ = alloc<Cplx<T>>(axis_tw_size(sizeof(T), cfg_.ny));
-    prey_ = alloc<T>(cfg_.ny);
     lamy_ = alloc<double>(cfg_.ny);
     bgx_ = alloc<double>(cfg_.nx + 1);
     bgy_ = alloc<double>(cfg_.ny + 1);
@@ -1434,8 +1437,8 @@ class Box final : public BoxBase {
     if (cfg_.mem_cap_bytes > 0 && bytes_ > cfg_.mem_cap_bytes) throw std::bad_alloc();
   }
 
-  // Per-axis tables of the sine transform (tw holds axis_tw_size entries, pre
-  // n, laid out as AxisTables says) and the Laplacian eigenvalues.
+  // Per-axis tables of the sine transform (tw holds axis_tw_size entries, pre,
+  // if not null, n, laid out as AxisTables says) and the Laplacian eigenvalues.
   void axis_tables(int n, double h, Cplx<T>* tw, T* pre, double* lam) {
     std::vector<Cplx<T>> htw(axis_tw_size(sizeof(T), n));
     std::vector<T> hpre(n);
@@ -1461,18 +1464,18 @@ class Box final : public BoxBase {
       for (int la = 0; la < 8; ++la)
         for (int c1 = 0; c1 < 8; ++c1) w[la * 9 + c1] = unit(la * c1, 64);
     } else {
+      std::vector<T> sn(2 * n, T(0));   // sin(pi q / n)
+      for (int q = 1; q < 2 * n; ++q)
+        if (q != n) sn[q] = static_cast<T>(std::sin(pi * q / n));
       T* d = reinterpret_cast<T*>(htw.data());
-      for (int m = 0; m < dense_table_size(n); ++m) {
-        const int q = dense_angle(n, m);
-        d[m] = q % n ? static_cast<T>(std::sin(pi * q / n)) : T(0);
-      }
+      for (int m = 0; m < dense_table_size(n); ++m) d[m] = sn[dense_angle(n, m)];
     }
     for (int m = 0; m < n; ++m) {
       const double s = std::sin(pi * m / (2.0 * n));
       hlam[m] = -4.0 / (h * h) * s * s;
     }
     QSP_HIP(hipMemcpy(tw, htw.data(), htw.size() * sizeof(Cplx<T>), hipMemcpyHostToDevice));
-    QSP_HIP(hipMemcpy(pre, hpre.data(), n * sizeof(T), hipMemcpyHostToDevice));
+    if (pre) QSP_HIP(hipMemcpy(pre, hpre.data(), n * sizeof(T), hipMemcpyHostToDevice));
     QSP_HIP(hipMemcpy(lam, hlam.data(), n * sizeof(double), hipMemcpyHostToDevice));
   }
 
@@ -1499,6 +1502,7 @@ class Box final : public BoxBase {
   AxisTables<T> ty() const { return {twy_, prey_, lamy_}; }
 
   void zero_shared() {
+    if (explicit_) return;   // no trial pushes
     launch_zero(trial_sh_[0], plane(), st_);
     launch_zero(trial_sh_[1], plane(), st_);
   }
