@@ -389,11 +389,6 @@ struct SymTw {
   Cplx<T> a[8];        // W_N^{l k}, k = 1..8; middle lane: sines in re
   Cplx<T> b;           // the thread's entry of the stage-B table
 };
-template <int LOGN>
-__host__ __device__ constexpr int sym_b_entries() {   // complex, in LDS
-  return Sym<LOGN>::G > 1 ? 17 * Sym<LOGN>::G : 0;
-}
-
 template <typename T, int LOGN, int NP>
 __device__ __forceinline__ SymTw<T, LOGN> sym_load(const Cplx<T>* __restrict__ tw) {
   using Y = Sym<LOGN, NP>;

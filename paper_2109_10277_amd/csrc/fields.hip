@@ -23,23 +23,6 @@ __global__ void k_zero(T* p, size_t n) {
     p[i] = T(0);
 }
 
-// B^(0) = 2 B_{k-1} - B_{k-2} (linear extrapolation from the two previous
-// slices); also opens the predictor-corrector of the slice.
-template <typename T>
-__global__ void k_guess(size_t n, T* bx, T* by, const T* bx1, const T* by1, const T* bx2,
-                        const T* by2, DevCounters* ctr) {
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
-    ctr->pc_done = 0u;
-    ctr->pc_iters = 0u;
-    ctr->pc_resid = 0.0;
-  }
-  for (size_t i = blockIdx.x * static_cast<size_t>(blockDim.x) + threadIdx.x; i < n;
-       i += static_cast<size_t>(gridDim.x) * blockDim.x) {
-    bx[i] = T(2) * bx1[i] - bx2[i];
-    by[i] = T(2) * by1[i] - by2[i];
-  }
-}
-
 // explicit beam current of a slice: an ultra-relativistic beam has
 // rho_b = Jz_b and rho_b - Jz_b = 0, so the plane is added to Jz (and to a
 // separate rho channel if one is kept)
@@ -53,14 +36,15 @@ __global__ void k_add_current(size_t n, const double* src, double* jz, double* r
 }
 
 __global__ void k_slice_end(DevCounters* ctr, int32_t* iters_out, int32_t* iters_own,
-                            double* resid_out, double tol, int max_iter, int budgeted,
-                            const double* pc_partial, int pc_nblk) {
+                            double* resid_out, double* resid_own, double tol, int max_iter,
+                            int budgeted, const double* pc_partial, int pc_nblk) {
   if (pc_partial && !ctr->pc_done) partials::pc_consume(pc_partial, pc_nblk, tol, ctr, true);
   if (threadIdx.x != 0) return;
   const double r = ctr->pc_resid;
   if (iters_out) *iters_out = static_cast<int32_t>(ctr->pc_iters);
   if (iters_own) *iters_own = static_cast<int32_t>(ctr->pc_iters);
   if (resid_out) *resid_out = r;
+  if (resid_own) *resid_own = r;
   if (r > ctr->max_resid || r != r) ctr->max_resid = r;
   if (tol > 0.0 && !ctr->pc_done) {
     if (static_cast<int>(ctr->pc_iters) >= max_iter) ctr->pc_not_converged += 1ull;
@@ -112,25 +96,16 @@ void launch_zero_t(T* p, size_t n, hipStream_t st) {
   QSP_LAUNCH_CHECK();
 }
 
-template <typename T>
-void launch_guess(const Geom& g, T* bx, T* by, const T* bx1, const T* by1, const T* bx2,
-                  const T* by2, DevCounters* ctr, hipStream_t st) {
-  const size_t n = static_cast<size_t>(g.nx) * g.ny;
-  hipLaunchKernelGGL(k_guess<T>, grid_for(n), dim3(kBlock), 0, st, n, bx, by, bx1, by1, bx2,
-                     by2, ctr);
-  QSP_LAUNCH_CHECK();
-}
-
 void launch_add_current(size_t n, const double* src, double* jz, double* rho, hipStream_t st) {
   hipLaunchKernelGGL(k_add_current, grid_for(n), dim3(kBlock), 0, st, n, src, jz, rho);
   QSP_LAUNCH_CHECK();
 }
 
 void launch_slice_end(DevCounters* ctr, int32_t* iters_out, int32_t* iters_own, double* resid_out,
-                      double tol, int max_iter, int budgeted, const double* pc_partial, int pc_nblk,
+                      double* resid_own, double tol, int max_iter, int budgeted, const double* pc_partial, int pc_nblk,
                       hipStream_t st) {
   hipLaunchKernelGGL(k_slice_end, dim3(1), dim3(kBlock), 0, st, ctr, iters_out, iters_own,
-                     resid_out, tol, max_iter, budgeted, pc_partial, pc_nblk);
+                     resid_out, resid_own, tol, max_iter, budgeted, pc_partial, pc_nblk);
   QSP_LAUNCH_CHECK();
 }
 
@@ -157,8 +132,6 @@ void launch_to_nodes(const Geom& g, const T* src, double* dst, hipStream_t st) {
 
 #define QSP_INST(T)                                                                       \
   template void launch_zero_t<T>(T*, size_t, hipStream_t);                                \
-  template void launch_guess<T>(const Geom&, T*, T*, const T*, const T*, const T*,        \
-                                const T*, DevCounters*, hipStream_t);                     \
   template void launch_from_nodes<double, T>(const Geom&, const double*, T*, hipStream_t); \
   template void launch_to_nodes<T>(const Geom&, const T*, double*, hipStream_t);
 QSP_INST(float)

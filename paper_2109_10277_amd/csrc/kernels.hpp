@@ -217,6 +217,7 @@ struct PushArgs {
   int32_t* iters_out;
   int32_t* iters_own;
   double* resid_out;
+  double* resid_own;        // (library; may be null)
   int pc_budgeted;
   double pc_tol;
   int pc_max_iter;
@@ -307,10 +308,8 @@ int explicit_partial_count(const Geom&);
 void launch_zero(double* p, size_t n, hipStream_t);
 template <typename T>
 void launch_zero_t(T* p, size_t n, hipStream_t);
-template <typename T>
-void launch_guess(const Geom&, T* bx, T* by, const T* bx1, const T* by1, const T* bx2,
-                  const T* by2, DevCounters*, hipStream_t);
 void launch_slice_end(DevCounters*, int32_t* iters_out, int32_t* iters_own, double* resid_out,
+                      double* resid_own,
                       double tol, int max_iter, int budgeted, const double* pc_partial, int pc_nblk,
                       hipStream_t);
 
