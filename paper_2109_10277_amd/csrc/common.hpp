@@ -129,8 +129,8 @@ __host__ __device__ constexpr int dense_out(int n, int t, int c) {
 }
 
 // Per-axis transform tables (device pointers): for the matrix core tw holds
-// real values, entry (t 64 + l) dense_lane + s the operand s of lane l for
-// tile t (dense_angle), and pre is unused; for the wave core tw[k1 * 64 + l] = e^{-2 pi i l k1 / 2n} (2n entries) and pre holds
+// 2n doubles sin(pi a / n) (exactly 0 for multiples of n; see dense_angle) and
+// pre is unused; for the wave core tw[k1 * 64 + l] = e^{-2 pi i l k1 / 2n} (2n entries) and pre holds
 // the complex table W_64^{la c1} at [la * 9 + c1] (la < 8, c1 < 8, entry 8 of
 // a row 0); for the symmetric core tw as in sym_table_* and pre unused.
 template <typename T>
@@ -160,22 +160,13 @@ __host__ __device__ inline double sym_table_angle(int n, int m) {
   return static_cast<double>(((2 * (q % 8) + 1) * (q / 8)) % 32) / 16.0;
 }
 
-// Matrix core: number of table values, and whole-number angle a of entry m
-// (the value is sin(pi a / n), exactly 0 for multiples of n): output o times
-// the operand index, which for the folded pair 0 means row entry n / 2 (and
-// nothing for the even outputs, o n / 2 being a multiple of n).
-__host__ __device__ constexpr int dense_table_size(int n) { return n / 16 * 64 * dense_lane(n); }
-__host__ __device__ inline int dense_angle(int n, int m) {
-  const int s = m % dense_lane(n), l = m / dense_lane(n) % 64, t = m / dense_lane(n) / 64;
+// Matrix core: entry of its table (sines of pi a / n for a = 0 .. 2n - 1, in
+// FP64 for both precisions) that is lane l's operand s for tile t: output o
+// times the operand index, which for the folded pair 0 means row entry n / 2
+// (nothing for the even outputs: the sine of a multiple of pi).
+__host__ __device__ constexpr int dense_angle(int n, int t, int l, int s) {
   const int o = dense_out(n, t, l % 16), k = dense_lane(n) * (l / 16) + s;
-  return o * (dense_fold(n) && k == 0 ? n / 2 : k) % (2 * n);
-}
-// Cplx<T> entries of AxisTables::tw
-__host__ __device__ constexpr bool dense_core(int elem_size, int n) {
-  return !sym_core(elem_size, n) && !wave_core(elem_size, n);
-}
-__host__ __device__ constexpr int axis_tw_size(int elem_size, int n) {
-  return dense_core(elem_size, n) ? dense_table_size(n) / 2 : 2 * n;
+  return (o * (dense_fold(n) && k == 0 ? n / 2 : k)) & (2 * n - 1);
 }
 
 // Grids whose solves run in one workgroup per field (small.hip): batches on

@@ -532,8 +532,10 @@ __device__ __forceinline__ void sym_dst(T* buf, const SymTw<T, LOGN>& w, const C
 
 // ---------------------------------------------------------------------------
 // Matrix core (n = 16 to 64, in FP32 128): the transform of 16 rows as a product with the
-// sine matrix on the matrix cores (16x16x4 in the field's own precision, FP32
-// or FP64).  Such rows are bound by the length of the chain, not by
+// sine matrix on the matrix cores, 16x16x4 in FP64 for both precisions: FP32
+// products of independently rounded sums put white round-off on the solution,
+// which the differences taken of it (Ex - By) amplify (1.5-2.5 times the error
+// of a half-length FFT at 64^2 and 128^2).  Such rows are bound by the length of the chain, not by
 // operations: one LDS read of the operand, at most 8 dependent matrix
 // instructions (two chains of 16 at 128 points) and one LDS write take the place of a half-length FFT with its
 // three exchanges and a prefix sum (64^2 in FP32: column pass 8.8 us, row
@@ -548,11 +550,7 @@ __device__ __forceinline__ void sym_dst(T* buf, const SymTw<T, LOGN>& w, const C
 // of padding after each row, which puts a quarter wave's 16-byte reads on
 // distinct banks.
 // ---------------------------------------------------------------------------
-typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef double f64x4 __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ f32x4 mfma4(float a, float b, f32x4 c) {
-  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
-}
 __device__ __forceinline__ f64x4 mfma4(double a, double b, f64x4 c) {
   return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
 }
@@ -568,7 +566,7 @@ struct Dense {
   static constexpr int TW = NT > 4 ? NT / 4 : 1;   // tiles per wave (both parities from two up)
   static constexpr int NW = NT / TW;           // busy waves
   static constexpr int pitch = n + 16 / static_cast<int>(sizeof(T));
-  using V4 = std::conditional_t<sizeof(T) == 4, f32x4, f64x4>;
+  using V4 = f64x4;
   __host__ __device__ static constexpr int ridx(int i) {
     return fold && i >= n / 2 ? n / 2 + ((n - i) & (n / 2 - 1)) : i;
   }
@@ -576,24 +574,27 @@ struct Dense {
   __host__ __device__ static constexpr int rpos(int, int, int r, int i) { return r * pitch + ridx(i); }
   // row of the 16x16 result that register r of a lane holds (column l % 16)
   __device__ static __forceinline__ int row_of(int lane, int r) {
-    return sizeof(T) == 4 ? 4 * (lane >> 4) + r : (lane >> 4) + 4 * r;
+    return (lane >> 4) + 4 * r;
   }
-  // the lane's matrix operands: the wave's tiles of an axis' table
+  // the lane's matrix operands: of one tile, of the wave's tiles
+  static __device__ __forceinline__ void load_tile(const Cplx<T>* tw, int tile, double (&a)[KL]) {
+    const int lane = static_cast<int>(threadIdx.x) & 63;
+#pragma unroll
+    for (int s = 0; s < KL; ++s)
+      a[s] = load_at(reinterpret_cast<const double*>(tw), dense_angle(n, tile, lane, s));
+  }
   struct Tab {
-    T a[TW][KL];
+    double a[TW][KL];
   };
   static __device__ __forceinline__ Tab load(const Cplx<T>* tw) {
     Tab t;
-    const int wave = static_cast<int>(threadIdx.x) >> 6, lane = static_cast<int>(threadIdx.x) & 63;
-    const T* p = reinterpret_cast<const T*>(tw) + ((wave < NW ? wave * TW : 0) * 64 + lane) * KL;
+    const int wave = static_cast<int>(threadIdx.x) >> 6;
 #pragma unroll
-    for (int q = 0; q < TW; ++q)
-#pragma unroll
-      for (int s = 0; s < KL; ++s) t.a[q][s] = p[q * 64 * KL + s];
+    for (int q = 0; q < TW; ++q) load_tile(tw, wave < NW ? wave * TW + q : q, t.a[q]);
     return t;
   }
   // 16 outputs (of one parity with folded rows) of the 16 rows at f
-  static __device__ __forceinline__ V4 product(const T* f, const T (&a)[KL], bool odd) {
+  static __device__ __forceinline__ V4 product(const T* f, const double (&a)[KL], bool odd) {
     T v[KL], w[KL];
     fetch(f, v, w);
     return chain(v, w, a, odd);
@@ -613,10 +614,13 @@ struct Dense {
 #pragma unroll
     for (int s = 0; s < KL; ++s) w[s] = fold ? p[n / 2 + s] : T(0);
   }
-  static __device__ __forceinline__ V4 chain(const T (&v)[KL], const T (&w)[KL], const T (&a)[KL], bool odd) {
-    V4 acc = {T(0), T(0), T(0), T(0)};
+  static __device__ __forceinline__ V4 chain(const T (&v)[KL], const T (&w)[KL], const double (&a)[KL], bool odd) {
+    V4 acc = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-    for (int s = 0; s < KL; ++s) acc = mfma4(!fold ? v[s] : odd ? v[s] + w[s] : v[s] - w[s], a[s], acc);
+    for (int s = 0; s < KL; ++s) {
+      const double x = static_cast<double>(v[s]), y = static_cast<double>(w[s]);
+      acc = mfma4(!fold ? x : odd ? x + y : x - y, a[s], acc);
+    }
     return acc;
   }
 };
@@ -638,7 +642,7 @@ __device__ __forceinline__ void dense_dst(T* buf, const typename Dense<T, LOGN>:
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const int row = D::row_of(lane, r);
-        out[row * D::pitch] = epi(4 * q + r, row, o, v[q][r]);
+        out[row * D::pitch] = epi(4 * q + r, row, o, static_cast<T>(v[q][r]));
       }
     }
   }

@@ -79,9 +79,8 @@ __global__ void k_axis_tables(AxisJob<T> x, AxisJob<T> y) {
       w[m] = c1 < 8 ? qsp::Cplx<T>{static_cast<T>(c), static_cast<T>(s)}
                     : qsp::Cplx<T>{T(0), T(0)};
     }
-  } else if (m < qsp::dense_table_size(n)) {
-    const int q_a = qsp::dense_angle(n, m);
-    reinterpret_cast<T*>(tw)[m] = q_a % n ? static_cast<T>(sinpi(static_cast<double>(q_a) / n)) : T(0);
+  } else if (m < 2 * n) {
+    reinterpret_cast<double*>(tw)[m] = m % n ? sinpi(static_cast<double>(m) / n) : 0.0;
   }
   if (m < n) {
     const double sm = sinpi(0.5 * m / n);
@@ -91,14 +90,14 @@ __global__ void k_axis_tables(AxisJob<T> x, AxisJob<T> y) {
 
 template <typename T>
 size_t axis_table_bytes(int n) {
-  return static_cast<size_t>(qsp::axis_tw_size(sizeof(T), n)) * sizeof(qsp::Cplx<T>) +
+  return static_cast<size_t>(2 * n) * sizeof(qsp::Cplx<T>) +
          static_cast<size_t>(n) * (sizeof(T) + sizeof(double));
 }
 
 template <typename T>
 qsp::AxisTables<T> axis_at(unsigned char* base, int n) {
   auto* tw = reinterpret_cast<qsp::Cplx<T>*>(base);
-  auto* pre = reinterpret_cast<T*>(tw + qsp::axis_tw_size(sizeof(T), n));
+  auto* pre = reinterpret_cast<T*>(tw + 2 * n);
   auto* lam = reinterpret_cast<double*>(pre + n);
   return {tw, pre, lam};
 }
@@ -128,9 +127,8 @@ void solve(const qsp_config& c, unsigned char* ptr, int nb, const T* src, T* dst
                       const_cast<double*>(tx.lam)};
   const AxisJob<T> jy{c.ny, g.hy, const_cast<Cplx<T>*>(ty.tw), const_cast<T*>(ty.pre),
                       const_cast<double*>(ty.lam)};
-  auto entries = [](int n) { return dense_core(sizeof(T), n) ? dense_table_size(n) : 2 * n; };   // one thread each
-  const int mx = entries(c.nx), my = entries(c.ny);
-  hipLaunchKernelGGL(k_axis_tables<T>, dim3(((mx > my ? mx : my) + 255) / 256, 2), dim3(256), 0, st, jx, jy);
+  const int nmax = c.nx > c.ny ? c.nx : c.ny;
+  hipLaunchKernelGGL(k_axis_tables<T>, dim3((2 * nmax + 255) / 256, 2), dim3(256), 0, st, jx, jy);
   QSP_LAUNCH_CHECK();
   if (small_solve(c.nx, c.ny)) {
     launch_small_nodes<T>(g, src, dst, nb, shift, tx, ty, st);

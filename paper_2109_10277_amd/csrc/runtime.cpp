@@ -1418,10 +1418,10 @@ class Box final : public BoxBase {
     p_.hist = alloc<T>(20 * np);
     p_.pab = alloc<T>(5 * np);
     // transform tables (pre: wave core only), one set for two axes of one length
-    twx_ = twy_ = alloc<Cplx<T>>(axis_tw_size(sizeof(T), cfg_.nx));
+    twx_ = twy_ = alloc<Cplx<T>>(2 * cfg_.nx);
     if (wave_core(sizeof(T), cfg_.nx)) prex_ = prey_ = alloc<T>(cfg_.nx);
     if (cfg_.ny != cfg_.nx) {
-      twy_ = alloc<Cplx<T>>(axis_tw_size(sizeof(T), cfg_.ny));
+      twy_ = alloc<Cplx<T>>(2 * cfg_.ny);
       prey_ = wave_core(sizeof(T), cfg_.ny) ? alloc<T>(cfg_.ny) : nullptr;
     }
     lamx_ = alloc<double>(cfg_.nx);
@@ -1451,10 +1451,10 @@ class Box final : public BoxBase {
     if (cfg_.mem_cap_bytes > 0 && bytes_ > cfg_.mem_cap_bytes) throw std::bad_alloc();
   }
 
-  // Per-axis tables of the sine transform (tw holds axis_tw_size entries, pre,
+  // Per-axis tables of the sine transform (tw holds 2n entries, pre,
   // if not null, n, laid out as AxisTables says) and the Laplacian eigenvalues.
   void axis_tables(int n, double h, Cplx<T>* tw, T* pre, double* lam) {
-    std::vector<Cplx<T>> htw(axis_tw_size(sizeof(T), n));
+    std::vector<Cplx<T>> htw(2 * n);
     std::vector<T> hpre(n);
     std::vector<double> hlam(n);
     const double pi = 3.14159265358979323846;
@@ -1478,11 +1478,8 @@ class Box final : public BoxBase {
       for (int la = 0; la < 8; ++la)
         for (int c1 = 0; c1 < 8; ++c1) w[la * 9 + c1] = unit(la * c1, 64);
     } else {
-      std::vector<T> sn(2 * n, T(0));   // sin(pi q / n)
-      for (int q = 1; q < 2 * n; ++q)
-        if (q != n) sn[q] = static_cast<T>(std::sin(pi * q / n));
-      T* d = reinterpret_cast<T*>(htw.data());
-      for (int m = 0; m < dense_table_size(n); ++m) d[m] = sn[dense_angle(n, m)];
+      double* d = reinterpret_cast<double*>(htw.data());
+      for (int q = 0; q < 2 * n; ++q) d[q] = q % n ? std::sin(pi * q / n) : 0.0;
     }
     for (int m = 0; m < n; ++m) {
       const double s = std::sin(pi * m / (2.0 * n));

@@ -34,18 +34,14 @@ struct Small {
   // the lane's operands of both axes and its eigenvalues, fetched behind the
   // source
   struct Op {
-    T x[X::KL], y[Y::KL];
+    double x[X::KL], y[Y::KL];
     double lx[4], ly;
   };
   static __device__ __forceinline__ Op load(const AxisTables<T>& tx, const AxisTables<T>& ty) {
     Op q;
     const int wave = static_cast<int>(threadIdx.x) >> 6, lane = static_cast<int>(threadIdx.x) & 63;
-    const T* px = reinterpret_cast<const T*>(tx.tw) + (wave % NTX * 64 + lane) * X::KL;
-    const T* py = reinterpret_cast<const T*>(ty.tw) + (wave % NTY * 64 + lane) * Y::KL;
-#pragma unroll
-    for (int s = 0; s < X::KL; ++s) q.x[s] = px[s];
-#pragma unroll
-    for (int s = 0; s < Y::KL; ++s) q.y[s] = py[s];
+    X::load_tile(tx.tw, wave % NTX, q.x);
+    Y::load_tile(ty.tw, wave % NTY, q.y);
 #pragma unroll
     for (int r = 0; r < 4; ++r) q.lx[r] = tx.lam[16 * (wave / NTY) + X::row_of(lane, r)];
     q.ly = ty.lam[dense_out(ny, wave % NTY, lane & 15)];
@@ -71,23 +67,23 @@ struct Small {
     __syncthreads();
     const auto f1 = X::product(a + 16 * rx * PX, q.x, ox & 1);
 #pragma unroll
-    for (int r = 0; r < 4; ++r) b[kx * PY + Y::ridx(16 * rx + X::row_of(lane, r))] = f1[r];
+    for (int r = 0; r < 4; ++r) b[kx * PY + Y::ridx(16 * rx + X::row_of(lane, r))] = static_cast<T>(f1[r]);
     __syncthreads();
     const auto f2 = Y::product(b + 16 * ry * PY, q.y, oy & 1);
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const int col = 16 * ry + X::row_of(lane, r);
-      const T z = f2[r] / den[r];
+      const T z = static_cast<T>(f2[r]) / den[r];
       a[col * PY + Y::ridx(ky)] = col > 0 && ky > 0 ? z : T(0);
     }
     __syncthreads();
     const auto f3 = Y::product(a + 16 * ry * PY, q.y, oy & 1);
 #pragma unroll
-    for (int r = 0; r < 4; ++r) b[ky * PX + X::ridx(16 * ry + X::row_of(lane, r))] = f3[r];
+    for (int r = 0; r < 4; ++r) b[ky * PX + X::ridx(16 * ry + X::row_of(lane, r))] = static_cast<T>(f3[r]);
     __syncthreads();
     const auto f4 = X::product(b + 16 * rx * PX, q.x, ox & 1);
 #pragma unroll
-    for (int r = 0; r < 4; ++r) a[at(kx, 16 * rx + X::row_of(lane, r))] = f4[r];
+    for (int r = 0; r < 4; ++r) a[at(kx, 16 * rx + X::row_of(lane, r))] = static_cast<T>(f4[r]);
     __syncthreads();
   }
 };
