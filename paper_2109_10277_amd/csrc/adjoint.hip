@@ -656,7 +656,7 @@ k_adj_src(Geom g, AdjSrcArgs<T> a, AxisTables<T> tx) {
       });
   xf.commit();
   __syncthreads();
-  block_dst<T, LOGN>(buf, ppitch, xf);
+  block_dst<T, LOGN, true>(buf, ppitch, xf);
   rows_to_plane<T, R, LOGN>(g, j0, buf, ppitch, a.out + static_cast<size_t>(fld) * g.nx * g.ny);
 }
 

@@ -72,7 +72,7 @@ k_src_fwd_pez(Geom g, SrcPEZ<T> a, AxisTables<T> tx) {
   }
   xf.commit();
   __syncthreads();
-  block_dst<T, LOGN>(buf, ppitch, xf);
+  block_dst<T, LOGN, true>(buf, ppitch, xf);
   rows_to_plane<T, R, LOGN>(g, j0, buf, ppitch, a.out + static_cast<size_t>(fld) * g.nx * g.ny);
 }
 
@@ -141,7 +141,7 @@ k_row_inv(Geom g, RowInvArgs<T> a, AxisTables<T> tx) {
     }
   }
   __syncthreads();
-  block_dst<T, LOGN>(buf, ppitch, xf);
+  block_dst<T, LOGN, false>(buf, ppitch, xf);
   T* out = a.out[fld];
   T* out_dx = a.out_dx[fld];
   if (a.out_strip) {   // an intermediate plane (no -d_x)
@@ -208,7 +208,7 @@ k_row_nodes(Geom g, NodeRowArgs<T> a, AxisTables<T> tx) {
   }
   xf.commit();
   __syncthreads();
-  block_dst<T, LOGN>(buf, ppitch, xf);
+  block_dst<T, LOGN, !OUT>(buf, ppitch, xf);
   if constexpr (!OUT) {
     rows_to_plane<T, R, LOGN>(g, j0, buf, ppitch, a.plane + b * plane);
   } else {

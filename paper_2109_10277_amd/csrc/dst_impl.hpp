@@ -532,10 +532,11 @@ __device__ __forceinline__ void sym_dst(T* buf, const SymTw<T, LOGN>& w, const C
 
 // ---------------------------------------------------------------------------
 // Matrix core (n = 16 to 64, in FP32 128): the transform of 16 rows as a product with the
-// sine matrix on the matrix cores, 16x16x4 in FP64 for both precisions: FP32
-// products of independently rounded sums put white round-off on the solution,
-// which the differences taken of it (Ex - By) amplify (1.5-2.5 times the error
-// of a half-length FFT at 64^2 and 128^2).  Such rows are bound by the length of the chain, not by
+// sine matrix on the matrix cores (16x16x4).  The inverse transforms sum in FP64
+// in both precisions: independently rounded FP32 sums put white round-off on
+// the solution, which the differences taken of it (Ex - By) amplify (1.5-2.5
+// times the error of a half-length FFT at 64^2 and 128^2); in front of the
+// eigenvalue division, which damps it, FP32 sums do.  Such rows are bound by the length of the chain, not by
 // operations: one LDS read of the operand, at most 8 dependent matrix
 // instructions (two chains of 16 at 128 points) and one LDS write take the place of a half-length FFT with its
 // three exchanges and a prefix sum (64^2 in FP32: column pass 8.8 us, row
@@ -550,7 +551,11 @@ __device__ __forceinline__ void sym_dst(T* buf, const SymTw<T, LOGN>& w, const C
 // of padding after each row, which puts a quarter wave's 16-byte reads on
 // distinct banks.
 // ---------------------------------------------------------------------------
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef double f64x4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ f32x4 mfma4(float a, float b, f32x4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
 __device__ __forceinline__ f64x4 mfma4(double a, double b, f64x4 c) {
   return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
 }
@@ -566,15 +571,21 @@ struct Dense {
   static constexpr int TW = NT > 4 ? NT / 4 : 1;   // tiles per wave (both parities from two up)
   static constexpr int NW = NT / TW;           // busy waves
   static constexpr int pitch = n + 16 / static_cast<int>(sizeof(T));
-  using V4 = f64x4;
+  // sums of a transform: FP64, or with FWD (in front of the eigenvalue
+  // division) the field's own precision
+  template <bool FWD>
+  using Sum = std::conditional_t<FWD, T, double>;
+  template <bool FWD>
+  using V4 = std::conditional_t<std::is_same_v<Sum<FWD>, float>, f32x4, f64x4>;
   __host__ __device__ static constexpr int ridx(int i) {
     return fold && i >= n / 2 ? n / 2 + ((n - i) & (n / 2 - 1)) : i;
   }
   __host__ __device__ static constexpr int rlen(int) { return pitch; }
   __host__ __device__ static constexpr int rpos(int, int, int r, int i) { return r * pitch + ridx(i); }
   // row of the 16x16 result that register r of a lane holds (column l % 16)
+  template <bool FWD>
   __device__ static __forceinline__ int row_of(int lane, int r) {
-    return (lane >> 4) + 4 * r;
+    return std::is_same_v<Sum<FWD>, float> ? 4 * (lane >> 4) + r : (lane >> 4) + 4 * r;
   }
   // the lane's matrix operands: of one tile, of the wave's tiles
   static __device__ __forceinline__ void load_tile(const Cplx<T>* tw, int tile, double (&a)[KL]) {
@@ -594,17 +605,19 @@ struct Dense {
     return t;
   }
   // 16 outputs (of one parity with folded rows) of the 16 rows at f
-  static __device__ __forceinline__ V4 product(const T* f, const double (&a)[KL], bool odd) {
+  template <bool FWD>
+  static __device__ __forceinline__ V4<FWD> product(const T* f, const double (&a)[KL], bool odd) {
     T v[KL], w[KL];
     fetch(f, v, w);
-    return chain(v, w, a, odd);
+    return chain<FWD>(v, w, a, odd);
   }
   // the outputs of the wave's tiles of the rows at f
-  static __device__ __forceinline__ void tiles_of(const T* f, const Tab& t, int wave, V4 (&acc)[TW]) {
+  template <bool FWD>
+  static __device__ __forceinline__ void tiles_of(const T* f, const Tab& t, int wave, V4<FWD> (&acc)[TW]) {
     T v[KL], w[KL];
     fetch(f, v, w);
 #pragma unroll
-    for (int q = 0; q < TW; ++q) acc[q] = chain(v, w, t.a[q], TW > 1 ? q & 1 : wave & 1);
+    for (int q = 0; q < TW; ++q) acc[q] = chain<FWD>(v, w, t.a[q], TW > 1 ? q & 1 : wave & 1);
   }
   static __device__ __forceinline__ void fetch(const T* f, T (&v)[KL], T (&w)[KL]) {
     const int lane = static_cast<int>(threadIdx.x) & 63;
@@ -614,12 +627,15 @@ struct Dense {
 #pragma unroll
     for (int s = 0; s < KL; ++s) w[s] = fold ? p[n / 2 + s] : T(0);
   }
-  static __device__ __forceinline__ V4 chain(const T (&v)[KL], const T (&w)[KL], const double (&a)[KL], bool odd) {
-    V4 acc = {0.0, 0.0, 0.0, 0.0};
+  template <bool FWD>
+  static __device__ __forceinline__ V4<FWD> chain(const T (&v)[KL], const T (&w)[KL], const double (&a)[KL],
+                                                  bool odd) {
+    using S = Sum<FWD>;
+    V4<FWD> acc = {S(0), S(0), S(0), S(0)};
 #pragma unroll
     for (int s = 0; s < KL; ++s) {
-      const double x = static_cast<double>(v[s]), y = static_cast<double>(w[s]);
-      acc = mfma4(!fold ? x : odd ? x + y : x - y, a[s], acc);
+      const S x = static_cast<S>(v[s]), y = static_cast<S>(w[s]);
+      acc = mfma4(!fold ? x : odd ? x + y : x - y, static_cast<S>(a[s]), acc);
     }
     return acc;
   }
@@ -627,12 +643,12 @@ struct Dense {
 
 // One transform of the kDenseRows rows at buf; epi(slot, row, output, value)
 // gives what is stored, slot = 0 .. 4 TW - 1 in order.  Ends without a barrier.
-template <typename T, int LOGN, typename Epi>
+template <bool FWD, typename T, int LOGN, typename Epi>
 __device__ __forceinline__ void dense_dst(T* buf, const typename Dense<T, LOGN>::Tab& t, Epi&& epi) {
   using D = Dense<T, LOGN>;
   const int wave = static_cast<int>(threadIdx.x) >> 6, lane = static_cast<int>(threadIdx.x) & 63;
-  typename D::V4 v[D::TW];
-  if (wave < D::NW) D::tiles_of(buf, t, wave, v);
+  typename D::template V4<FWD> v[D::TW];
+  if (wave < D::NW) D::template tiles_of<FWD>(buf, t, wave, v);
   __syncthreads();   // the rows are read
   if (wave < D::NW) {
 #pragma unroll
@@ -641,7 +657,7 @@ __device__ __forceinline__ void dense_dst(T* buf, const typename Dense<T, LOGN>:
       T* out = buf + D::ridx(o);
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const int row = D::row_of(lane, r);
+        const int row = D::template row_of<FWD>(lane, r);
         out[row * D::pitch] = epi(4 * q + r, row, o, static_cast<T>(v[q][r]));
       }
     }
@@ -715,7 +731,7 @@ struct Xform {
 // pair_pitch(n)).  Entry 0 of every input row must be 0; on output entry p
 // holds S_p (entry 0 = 0).  The wave core takes one pair per wave, the matrix
 // core kDenseRows rows.  Ends with a workgroup barrier.
-template <typename T, int LOGN, int NP>
+template <typename T, int LOGN, bool FWD, int NP>
 __device__ __forceinline__ void block_dst(T* buf, int ppitch, const Xform<T, LOGN, NP>& x) {
   constexpr int n = 1 << LOGN;
   if constexpr (sym_core(sizeof(T), n)) {
@@ -725,7 +741,7 @@ __device__ __forceinline__ void block_dst(T* buf, int ppitch, const Xform<T, LOG
     if (wave < NP) wave_dst_core<n / 32>(buf + static_cast<size_t>(wave) * ppitch, x.w.a, x.tw());
   } else {
     static_assert(2 * NP == kDenseRows, "rows of the matrix core");
-    dense_dst<T, LOGN>(buf, x.w, [](int, int, int, T v) { return v; });
+    dense_dst<FWD, T, LOGN>(buf, x.w, [](int, int, int, T v) { return v; });
   }
   __syncthreads();
 }
@@ -1109,7 +1125,7 @@ __device__ __forceinline__ void src_bxby_block(const Geom& g, const SrcBxBy<T>& 
     src_bxby_rows<T, LOGN, false>(g, a, j0, buf, ppitch);
   xf.commit();
   __syncthreads();
-  block_dst<T, LOGN>(buf, ppitch, xf);
+  block_dst<T, LOGN, true>(buf, ppitch, xf);
   rows_to_plane<T, R, LOGN>(g, j0, buf, ppitch, a.out + static_cast<size_t>(fld) * g.nx * g.ny);
 }
 
@@ -1329,7 +1345,7 @@ __device__ __forceinline__ void col_block_dense(const Geom& g, const ColArgs<T>&
   for (int u = 0; u < N; ++u) v[u] = load_at(in, (j0 + u * JS) * nx + p0 + c);
   double lx[4];
 #pragma unroll
-  for (int r = 0; r < 4; ++r) lx[r] = lamx[p0 + D::row_of(lane, r)];
+  for (int r = 0; r < 4; ++r) lx[r] = lamx[p0 + D::template row_of<true>(lane, r)];
   double ly[D::TW];
 #pragma unroll
   for (int q = 0; q < D::TW; ++q) ly[q] = ty.lam[wave < D::NW ? dense_out(n, wave * D::TW + q, lane & 15) : 0];
@@ -1346,12 +1362,12 @@ __device__ __forceinline__ void col_block_dense(const Geom& g, const ColArgs<T>&
   for (int q = 0; q < D::TW; ++q)
 #pragma unroll
     for (int r = 0; r < 4; ++r) den[4 * q + r] = static_cast<T>((lx[r] + (ly[q] - shift)) * inorm);
-  dense_dst<T, LOGN>(buf, xf.w, [&](int q, int row, int o, T s) {
+  dense_dst<true, T, LOGN>(buf, xf.w, [&](int q, int row, int o, T s) {
     const T z = s / den[q];
     return p0 + row > 0 && o > 0 ? z : T(0);
   });
   __syncthreads();
-  dense_dst<T, LOGN>(buf, xf.w, [](int, int, int, T s) { return s; });
+  dense_dst<false, T, LOGN>(buf, xf.w, [](int, int, int, T s) { return s; });
   __syncthreads();
   T* out = a.out + fld * plane;
   const T* row = buf + c * D::pitch;
@@ -1415,7 +1431,7 @@ __device__ __forceinline__ void row_inv_pc_block(const Geom& g, const PCArgs<T>&
   for (int u = 0; u < NOLD; ++u) pin(old_b[u]);
   xf.commit();
   __syncthreads();
-  block_dst<T, LOGN>(buf, ppitch, xf);
+  block_dst<T, LOGN, false>(buf, ppitch, xf);
   double dsum = 0.0, nsum = 0.0;
   auto update = [&](int e, T prev, auto taped) {
     const int r = e >> LOGN, i = e & (n - 1);

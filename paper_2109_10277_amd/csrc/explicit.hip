@@ -149,7 +149,7 @@ k_expl_setup(Geom g, ExplicitArgs<T> a, AxisTables<T> tx, DevCounters* ctr) {
       });
   xf.commit();
   __syncthreads();
-  block_dst<T, LOGN>(buf, ppitch, xf);
+  block_dst<T, LOGN, true>(buf, ppitch, xf);
   rows_to_plane<T, R, LOGN>(g, j0, buf, ppitch, a.fwd + fld * plane);
   double v[2] = {bn, rn};
   partials::store<2>(v, a.part_s, fld * (ny / R) + blockIdx.x);
@@ -201,7 +201,7 @@ k_expl_rowinv(Geom g, ExplicitArgs<T> a, AxisTables<T> tx, DevCounters* ctr) {
   rows.put(g, buf, ppitch);
   xf.commit();
   __syncthreads();
-  block_dst<T, LOGN>(buf, ppitch, xf);
+  block_dst<T, LOGN, false>(buf, ppitch, xf);
   // (r and q fetched in front of the transform, under the plane load, took
   // 10.0 us against 9.3 at 512^2 in FP32)
   double zr = 0.0, zq = 0.0;
@@ -385,7 +385,7 @@ k_expl_update(Geom g, ExplicitArgs<T> a, AxisTables<T> tx, DevCounters* ctr) {
       });
   xf.commit();
   __syncthreads();
-  block_dst<T, LOGN>(buf, ppitch, xf);
+  block_dst<T, LOGN, true>(buf, ppitch, xf);
   rows_to_plane<T, R, LOGN>(g, j0, buf, ppitch, a.fwd + fld * plane);
   double v[1] = {rn};
   partials::store<1>(v, a.part_u, fld * (ny / R) + blockIdx.x);

@@ -43,7 +43,7 @@ struct Small {
     X::load_tile(tx.tw, wave % NTX, q.x);
     Y::load_tile(ty.tw, wave % NTY, q.y);
 #pragma unroll
-    for (int r = 0; r < 4; ++r) q.lx[r] = tx.lam[16 * (wave / NTY) + X::row_of(lane, r)];
+    for (int r = 0; r < 4; ++r) q.lx[r] = tx.lam[16 * (wave / NTY) + X::template row_of<true>(lane, r)];
     q.ly = ty.lam[dense_out(ny, wave % NTY, lane & 15)];
     return q;
   }
@@ -65,25 +65,25 @@ struct Small {
 #pragma unroll
     for (int r = 0; r < 4; ++r) den[r] = static_cast<T>((q.lx[r] + (q.ly - shift)) * inorm);
     __syncthreads();
-    const auto f1 = X::product(a + 16 * rx * PX, q.x, ox & 1);
+    const auto f1 = X::template product<true>(a + 16 * rx * PX, q.x, ox & 1);
 #pragma unroll
-    for (int r = 0; r < 4; ++r) b[kx * PY + Y::ridx(16 * rx + X::row_of(lane, r))] = static_cast<T>(f1[r]);
+    for (int r = 0; r < 4; ++r) b[kx * PY + Y::ridx(16 * rx + X::template row_of<true>(lane, r))] = static_cast<T>(f1[r]);
     __syncthreads();
-    const auto f2 = Y::product(b + 16 * ry * PY, q.y, oy & 1);
+    const auto f2 = Y::template product<true>(b + 16 * ry * PY, q.y, oy & 1);
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      const int col = 16 * ry + X::row_of(lane, r);
+      const int col = 16 * ry + X::template row_of<true>(lane, r);
       const T z = static_cast<T>(f2[r]) / den[r];
       a[col * PY + Y::ridx(ky)] = col > 0 && ky > 0 ? z : T(0);
     }
     __syncthreads();
-    const auto f3 = Y::product(a + 16 * ry * PY, q.y, oy & 1);
+    const auto f3 = Y::template product<false>(a + 16 * ry * PY, q.y, oy & 1);
 #pragma unroll
-    for (int r = 0; r < 4; ++r) b[ky * PX + X::ridx(16 * ry + X::row_of(lane, r))] = static_cast<T>(f3[r]);
+    for (int r = 0; r < 4; ++r) b[ky * PX + X::ridx(16 * ry + X::template row_of<false>(lane, r))] = static_cast<T>(f3[r]);
     __syncthreads();
-    const auto f4 = X::product(b + 16 * rx * PX, q.x, ox & 1);
+    const auto f4 = X::template product<false>(b + 16 * rx * PX, q.x, ox & 1);
 #pragma unroll
-    for (int r = 0; r < 4; ++r) a[at(kx, 16 * rx + X::row_of(lane, r))] = static_cast<T>(f4[r]);
+    for (int r = 0; r < 4; ++r) a[at(kx, 16 * rx + X::template row_of<false>(lane, r))] = static_cast<T>(f4[r]);
     __syncthreads();
   }
 };
