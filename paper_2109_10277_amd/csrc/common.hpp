@@ -104,9 +104,10 @@ struct Lattice {
 //                    length of a lane's chain, which the symmetric core does
 //                    not shorten;
 //   matrix core      16-64 points, FP32 also 128: a product with the sine
-//                    matrix.  At 128 points (128^2 box) it takes 5.5 ms
-//                    against 6.1 with the symmetric core in FP32, 7.1 against
-//                    6.8 in FP64, whose matrix rate is half.
+//                    matrix.  At 128 points (128^2 box) it takes 6.8 ms
+//                    in FP32, 6.0 with the symmetric core, whose Ex - By errs
+//                    up to 1.25 times as much as the half-length FFT's (8.0
+//                    ms) did; in FP64 7.1 against 6.8.
 __host__ __device__ constexpr bool sym_core(int elem_size, int n) {
   return n >= 1024 || (elem_size == 8 && n >= 128);
 }
@@ -170,11 +171,11 @@ __host__ __device__ constexpr int dense_angle(int n, int t, int l, int s) {
 }
 
 // Grids whose solves run in one workgroup per field (small.hip): batches on
-// node arrays up to 64 x 64 (one launch of 5.5 us against three that take 11.7
-// eagerly, FP32; 10.2 in FP64), the slice loop's up to 2048 nodes (32 x 64 box:
-// 3.29 ms against 4.01; at 64 x 64 one CU's loads and products take as long as
-// three passes' launches from a graph, 4.36 against 4.30 ms, in FP64 5.6
-// against 4.7).
+// node arrays up to 64 x 64 (one launch of 9.8 us against three that take 11.7
+// eagerly, FP32; 11.3 in FP64), the slice loop's up to 2048 nodes (32 x 64 box:
+// 3.52 ms against 4.01; at 64 x 64 one CU's loads and products take longer than
+// three passes' launches from a graph, 4.36 against 4.30 ms with all sums in
+// FP32, 5.6 against 4.7 in FP64).
 __host__ __device__ constexpr bool small_solve(int nx, int ny) { return nx <= 64 && ny <= 64; }
 __host__ __device__ constexpr bool small_grid(int nx, int ny) {
   return small_solve(nx, ny) && nx * ny <= 2048;

@@ -531,23 +531,26 @@ __device__ __forceinline__ void sym_dst(T* buf, const SymTw<T, LOGN>& w, const C
 }
 
 // ---------------------------------------------------------------------------
-// Matrix core (n = 16 to 64, in FP32 128): the transform of 16 rows as a product with the
-// sine matrix on the matrix cores (16x16x4).  The inverse transforms sum in FP64
-// in both precisions: independently rounded FP32 sums put white round-off on
-// the solution, which the differences taken of it (Ex - By) amplify (1.5-2.5
-// times the error of a half-length FFT at 64^2 and 128^2); in front of the
-// eigenvalue division, which damps it, FP32 sums do.  Such rows are bound by the length of the chain, not by
-// operations: one LDS read of the operand, at most 8 dependent matrix
-// instructions (two chains of 16 at 128 points) and one LDS write take the place of a half-length FFT with its
-// three exchanges and a prefix sum (64^2 in FP32: column pass 8.8 us, row
-// passes 5.8-6.0).
+// Matrix core (n = 16 to 64, in FP32 128): the transform of 16 rows as a
+// product with the sine matrix on the matrix cores (16x16x4).  The inverse
+// transforms sum in FP64 in both precisions: independently rounded FP32 sums
+// put white round-off on the solution, which the differences taken of it
+// (Ex - By) amplify (1.5-2.5 times the error of a half-length FFT at 64^2 and
+// 128^2); in front of the eigenvalue division, which damps it, FP32 sums do.
+// Such rows are bound by the length of the chain, not by operations: one LDS
+// read of the operand, at most 8 dependent matrix instructions (two chains of
+// 16 at 128 points) and one LDS write take the place of a half-length FFT with
+// its three exchanges and a prefix sum (64^2 in FP32: box 7.28 -> 4.42 ms, 4.54
+// with all sums in FP64, 4.15 with none; errors at or below what they were,
+// field by field).
 // From 32 points up sin(pi (n - m) k / n) = -(-1)^k sin(pi m k / n) folds a row
 // to f_m + f_{n-m} for the odd outputs and f_m - f_{n-m} for the even ones,
 // m < n/2, with f_{n/2} in the place of the pair m = 0 (odd outputs only): each
 // wave forms 16 outputs of one parity from n/2 products.
 // A lane holds row l % 16 and the K/4 operands m = (K/4) (l / 16) + s, s < K/4,
 // of step s, both of the rows and of the matrix, so it reads consecutive
-// values: rows lie in LDS with f_m at m and f_{n-m} at n/2 + m (pos), 16 bytes
+// values of the rows (and gathers the matrix from a table of 2n sines, which
+// the L1 holds): rows lie in LDS with f_m at m and f_{n-m} at n/2 + m (pos), 16 bytes
 // of padding after each row, which puts a quarter wave's 16-byte reads on
 // distinct banks.
 // ---------------------------------------------------------------------------

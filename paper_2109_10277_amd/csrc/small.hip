@@ -4,8 +4,9 @@
 // not by work: at 32^2 to 64^2 in FP32 they take 3.6 + 3.7 + 3.6 us for at most
 // 2 MFLOP.  Here the field stays in LDS from its source to its epilogue: four
 // products with the folded sine matrices (Dense), one 16x16 output tile per
-// wave and product.  Measured (FP32): 32^2 box of 64 slices 3.77 -> 2.77 ms, its
-// gradient run 17.0 -> 13.6, one solve at 64^2 11.7 -> 5.5 us.
+// wave and product.  Measured (FP32): 32^2 box of 64 slices 3.77 -> 2.72 ms, its
+// gradient run 17.0 -> 13.6, one solve at 64^2 11.7 -> 9.8 us, at 32^2 11.6 ->
+// 4.4.
 #include <stdexcept>
 
 #include "common.hpp"
