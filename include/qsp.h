@@ -292,6 +292,8 @@ qsp_status qsp_set_slice_state(qsp_ctx ctx, const qsp_slice_state* src);
  * interior nodes, u_b = 0 on the boundary, lap_h the 5-point Laplacian.
  * src, dst: device arrays [nbatch][ny+1][nx+1] in the context's precision
  * (boundary entries of src are ignored); 1 <= nbatch <= 4; shift >= 0.
+ * dst may be src or overlap it in any way (every source is read before the
+ * first solution is written).
  * Asynchronous on the context's stream; uses the context's scratch, so it
  * must not overlap other calls on the same context. */
 qsp_status qsp_solve_poisson(qsp_ctx ctx, int32_t nbatch, const void* src, void* dst,
@@ -304,8 +306,8 @@ qsp_status qsp_solve_poisson(qsp_ctx ctx, int32_t nbatch, const void* src, void*
  * precision.  Solves (lap_h - shift) u_b = src_b for b < nbatch on
  * `device`, enqueued on `hip_stream` (a hipStream_t; NULL = the null
  * stream); src, dst: device arrays [nbatch][ny+1][nx+1] in the given
- * precision (boundary entries of src ignored, of dst written as 0);
- * 1 <= nbatch <= 4; shift >= 0.  Intermediate planes and transform tables
+ * precision (boundary entries of src ignored, of dst written as 0; dst may
+ * overlap src in any way); 1 <= nbatch <= 4; shift >= 0.  Intermediate planes and transform tables
  * live in one static device array per GPU of 16 MiB + 256 KiB (held from
  * the library's first use on that GPU until the process ends):
  * nbatch * nx * ny values above 16 MiB -> QSP_ERR_INVALID_ARG.  Every call

@@ -129,6 +129,17 @@ void launch_small_pez(const Geom&, const SrcPEZ<T>&, const RowInvArgs<T>&, const
 template <typename T>
 void launch_small_nodes(const Geom&, const T* src, T* dst, int nbatch, double shift,
                         const AxisTables<T>& tx, const AxisTables<T>& ty, hipStream_t);
+// Whether a batch on node arrays takes launch_small_nodes.  Its workgroups read
+// and write one field each and do not wait for each other, so the solutions
+// may not reach into another field's sources: one field, in place, or apart.
+// (The passes read every source before the first solution is written.)
+template <typename T>
+inline bool small_batch(const Geom& g, const T* src, const T* dst, int nbatch) {
+  if (!small_solve(g.nx, g.ny)) return false;
+  const uintptr_t s = reinterpret_cast<uintptr_t>(src), d = reinterpret_cast<uintptr_t>(dst);
+  const uintptr_t bytes = static_cast<uintptr_t>(nbatch) * (g.nx + 1) * (g.ny + 1) * sizeof(T);
+  return nbatch == 1 || s == d || s + bytes <= d || d + bytes <= s;
+}
 int pc_partial_count(const Geom&);
 // column-strip width of a column pass over nfield planes
 template <typename T>

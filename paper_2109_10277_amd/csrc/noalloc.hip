@@ -130,7 +130,7 @@ void solve(const qsp_config& c, unsigned char* ptr, int nb, const T* src, T* dst
   const int nmax = c.nx > c.ny ? c.nx : c.ny;
   hipLaunchKernelGGL(k_axis_tables<T>, dim3((2 * nmax + 255) / 256, 2), dim3(256), 0, st, jx, jy);
   QSP_LAUNCH_CHECK();
-  if (small_solve(c.nx, c.ny)) {
+  if (small_batch(g, src, dst, nb)) {
     launch_small_nodes<T>(g, src, dst, nb, shift, tx, ty, st);
     return;
   }

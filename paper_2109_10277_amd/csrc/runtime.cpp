@@ -534,12 +534,14 @@ class Box final : public BoxBase {
 
   void solve_poisson(int nb, const void* src, void* dst, double shift) override {
     QSP_HIP(hipSetDevice(device_));
-    if (small_solve(cfg_.nx, cfg_.ny)) {
-      launch_small_nodes<T>(geom_, static_cast<const T*>(src), static_cast<T*>(dst), nb, shift, tx(), ty(), st_);
+    const T* s = static_cast<const T*>(src);
+    T* d = static_cast<T*>(dst);
+    if (small_batch(geom_, s, d, nb)) {
+      launch_small_nodes<T>(geom_, s, d, nb, shift, tx(), ty(), st_);
       return;
     }
     // rows of the sources, columns, rows of the solutions: all in t2_
-    NodeRowArgs<T> r{static_cast<const T*>(src), static_cast<T*>(dst), t2_};
+    NodeRowArgs<T> r{s, d, t2_};
     launch_row_nodes<T>(geom_, r, false, nb, tx(), st_);
     ColArgs<T> c{};
     c.in = t2_;

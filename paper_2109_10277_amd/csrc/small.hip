@@ -300,8 +300,8 @@ k_small_pez(Geom g, SrcPEZ<T> s, RowInvArgs<T> r, ZeroJob z, AxisTables<T> tx, A
   }
 }
 
-// A batch of solves on node arrays, one workgroup per solve (in place or not:
-// a workgroup reads its sources before it writes).
+// A batch of solves on node arrays, one workgroup per solve (a workgroup reads
+// its sources before it writes; see small_batch for several).
 template <typename T, int LX, int LY>
 __global__ void __launch_bounds__((Small<T, LX, LY>::BS))
 k_small_nodes(const T* src, T* dst, double shift, AxisTables<T> tx, AxisTables<T> ty) {
