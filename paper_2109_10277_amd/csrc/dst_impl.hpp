@@ -663,7 +663,9 @@ struct Dense {
 };
 
 // One transform of the kDenseRows rows at buf; epi(slot, row, output, value)
-// gives what is stored, slot = 0 .. 4 TW - 1 in order.  Ends without a barrier.
+// gives what is stored, slot = 0 .. 4 TW - 1 in order.  Output 0 is a product
+// with zeros, which is not zero for an infinity or a NaN in the row, so epi
+// stores its zero.  Ends without a barrier.
 template <bool FWD, typename T, int LOGN, typename Epi>
 __device__ __forceinline__ void dense_dst(T* buf, const typename Dense<T, LOGN>::Tab& t, Epi&& epi) {
   using D = Dense<T, LOGN>;
@@ -765,7 +767,7 @@ __device__ __forceinline__ void block_dst(T* buf, int ppitch, const Xform<T, LOG
     if (wave < NP) wave_dst_core<n / 32>(buf + static_cast<size_t>(wave) * ppitch, x.w.a, x.tw());
   } else {
     static_assert(2 * NP == kDenseRows, "rows of the matrix core");
-    dense_dst<FWD, T, LOGN>(buf, x.w, [](int, int, int, T v) { return v; });
+    dense_dst<FWD, T, LOGN>(buf, x.w, [](int, int, int o, T v) { return o > 0 ? v : T(0); });
   }
   __syncthreads();
 }
@@ -1391,7 +1393,7 @@ __device__ __forceinline__ void col_block_dense(const Geom& g, const ColArgs<T>&
     return p0 + row > 0 && o > 0 ? z : T(0);
   });
   __syncthreads();
-  dense_dst<false, T, LOGN>(buf, xf.w, [](int, int, int, T s) { return s; });
+  dense_dst<false, T, LOGN>(buf, xf.w, [](int, int, int o, T s) { return o > 0 ? s : T(0); });
   __syncthreads();
   T* out = a.out + fld * plane;
   const T* row = buf + c * D::pitch;

@@ -53,7 +53,8 @@ struct Small {
   static __device__ __forceinline__ int at(int i, int j) { return j * PX + X::ridx(i); }
 
   // (Dxx + Dyy - shift) u = f: f by rows in `a`, whose row 0 and column 0 are
-  // zero, is replaced by u; `b` is scratch.  Starts and ends with a barrier.
+  // zero, is replaced by u, whose row 0 and column 0 are zero whatever f holds;
+  // `b` is scratch.  Starts and ends with a barrier.
   static __device__ __forceinline__ void solve(T* a, T* b, const Op& q, double shift) {
     const int wave = static_cast<int>(threadIdx.x) >> 6, lane = static_cast<int>(threadIdx.x) & 63;
     const int rx = wave / NTX, ox = wave % NTX;   // rows j, outputs along x
@@ -80,11 +81,13 @@ struct Small {
     __syncthreads();
     const auto f3 = Y::template product<false>(a + 16 * ry * PY, q.y, oy & 1);
 #pragma unroll
-    for (int r = 0; r < 4; ++r) b[ky * PX + X::ridx(16 * ry + X::template row_of<false>(lane, r))] = static_cast<T>(f3[r]);
+    for (int r = 0; r < 4; ++r)
+      b[ky * PX + X::ridx(16 * ry + X::template row_of<false>(lane, r))] = ky > 0 ? static_cast<T>(f3[r]) : T(0);
     __syncthreads();
     const auto f4 = X::template product<false>(b + 16 * rx * PX, q.x, ox & 1);
 #pragma unroll
-    for (int r = 0; r < 4; ++r) a[at(kx, 16 * rx + X::template row_of<false>(lane, r))] = static_cast<T>(f4[r]);
+    for (int r = 0; r < 4; ++r)
+      a[at(kx, 16 * rx + X::template row_of<false>(lane, r))] = kx > 0 ? static_cast<T>(f4[r]) : T(0);
     __syncthreads();
   }
 };
