@@ -197,7 +197,7 @@ struct NoScale {
 };
 
 // 1 / d: the hardware estimate in FP32 (1 ulp), refined by two Newton steps
-// in FP64
+// in FP64, which need a finite d
 __device__ __forceinline__ float recip(float d) { return __builtin_amdgcn_rcpf(d); }
 __device__ __forceinline__ double recip(double d) {
   double y = __builtin_amdgcn_rcp(d);
@@ -210,13 +210,18 @@ __device__ __forceinline__ double recip(double d) {
 // eigenvalue of the shifted Laplacian times the two transforms'
 // normalisation; column p = 0 (a boundary node line) is zero.  ry holds
 // (lambda_y(k) - shift) nx ny / 4 for the lane's NK output slots k (see
-// core_out_k, sym_out_k), xa / xb lambda_x(p) nx ny / 4.
+// core_out_k, sym_out_k), xa / xb lambda_x(p) nx ny / 4, in FP64 held to a
+// quarter of the range so that their sum is finite (eigen_term).
 // In FP32 columns of 2048 points the sum is formed in FP64, rounded once and
 // divided by (ONCE): terms rounded before the sum and the reciprocal err up to
 // 6 units of 2^-24 there instead of 3.  Shorter FP32 columns add FP32 terms,
 // and FP64 columns multiply by the reciprocal: with a division solves of
 // 1024 x 512 points err no less (4.6e-16 against 4.5e-16) and take 41.1 us
 // instead of 40.1, the 512^2 FP64 box 30.4 ms instead of 29.8.
+template <typename R>
+__device__ __forceinline__ R eigen_term(double v) {
+  return static_cast<R>(sizeof(R) == 8 ? fmax(v, -0x1p1022) : v);
+}
 template <typename T, int N>
 constexpr bool eigen_once = sizeof(T) == 4 && N > 1024;
 template <typename T, int NK, bool ONCE>
@@ -1290,9 +1295,9 @@ __device__ __forceinline__ void col_block_core(const Geom& g, const ColArgs<T>& 
     Scale sc;
     if (busy) {
 #pragma unroll
-      for (int q = 0; q < NK; ++q) sc.ry[q] = static_cast<typename Scale::R>((ly[q] - shift) * inorm);
-      sc.xa = static_cast<typename Scale::R>(lxa * inorm);
-      sc.xb = static_cast<typename Scale::R>(lxb * inorm);
+      for (int q = 0; q < NK; ++q) sc.ry[q] = eigen_term<typename Scale::R>((ly[q] - shift) * inorm);
+      sc.xa = eigen_term<typename Scale::R>(lxa * inorm);
+      sc.xb = eigen_term<typename Scale::R>(lxb * inorm);
       sc.za = p0 + 2 * pr == 0;
     }
     if constexpr (sym) {
