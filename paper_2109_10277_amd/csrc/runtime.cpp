@@ -647,8 +647,14 @@ class Box final : public BoxBase {
     replay_graph(graph_);
     if (pc && fresh) {
       learn_budgets(fell_short);
-      // capture the speculative box now, from this box's start, so that the
-      // next box only replays it
+      // The explicit solver's speculative box is captured when a second box of
+      // the same drive comes: a caller with a new drive for every box never
+      // replays it (512^2 box of 128 slices, a new drive each: 30 ms, with the
+      // second capture 35, without budgets 33; the second box of a drive 25 ms
+      // with its capture, the same without budgets, from the third on 19.4).
+      if (explicit_) return;
+      // the predictor-corrector's now, from this box's start, so that the next
+      // box only replays it
       const HostState end = save_host();
       restore_host(graph_.start);
       set_budget_launch();
