@@ -199,4 +199,11 @@ struct DevCounters {
   unsigned int reserved0;
 };
 
+// What the library keeps of a slice's iterations: their count (at most 1000),
+// and whether the last residual lies within a factor of ten of the tolerance.
+constexpr int32_t kNearTol = 1 << 16;
+__device__ inline int32_t own_iters(unsigned int iters, double resid, double tol) {
+  return static_cast<int32_t>(iters) | (resid > 0.1 * tol ? kNearTol : 0);
+}
+
 }  // namespace qsp

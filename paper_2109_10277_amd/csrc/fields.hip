@@ -36,15 +36,13 @@ __global__ void k_add_current(size_t n, const double* src, double* jz, double* r
 }
 
 __global__ void k_slice_end(DevCounters* ctr, int32_t* iters_out, int32_t* iters_own,
-                            double* resid_out, double* resid_own, double tol, int max_iter,
-                            int budgeted, const double* pc_partial, int pc_nblk) {
+                            double* resid_out, double tol, int max_iter, int budgeted, const double* pc_partial, int pc_nblk) {
   if (pc_partial && !ctr->pc_done) partials::pc_consume(pc_partial, pc_nblk, tol, ctr, true);
   if (threadIdx.x != 0) return;
   const double r = ctr->pc_resid;
   if (iters_out) *iters_out = static_cast<int32_t>(ctr->pc_iters);
-  if (iters_own) *iters_own = static_cast<int32_t>(ctr->pc_iters);
+  if (iters_own) *iters_own = own_iters(ctr->pc_iters, r, tol);
   if (resid_out) *resid_out = r;
-  if (resid_own) *resid_own = r;
   if (r > ctr->max_resid || r != r) ctr->max_resid = r;
   if (tol > 0.0 && !ctr->pc_done) {
     if (static_cast<int>(ctr->pc_iters) >= max_iter) ctr->pc_not_converged += 1ull;
@@ -102,10 +100,10 @@ void launch_add_current(size_t n, const double* src, double* jz, double* rho, hi
 }
 
 void launch_slice_end(DevCounters* ctr, int32_t* iters_out, int32_t* iters_own, double* resid_out,
-                      double* resid_own, double tol, int max_iter, int budgeted, const double* pc_partial, int pc_nblk,
+                      double tol, int max_iter, int budgeted, const double* pc_partial, int pc_nblk,
                       hipStream_t st) {
   hipLaunchKernelGGL(k_slice_end, dim3(1), dim3(kBlock), 0, st, ctr, iters_out, iters_own,
-                     resid_out, resid_own, tol, max_iter, budgeted, pc_partial, pc_nblk);
+                     resid_out, tol, max_iter, budgeted, pc_partial, pc_nblk);
   QSP_LAUNCH_CHECK();
 }
 

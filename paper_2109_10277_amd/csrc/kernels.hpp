@@ -222,13 +222,12 @@ struct PushArgs {
   int tile_halo;            // cells of LDS histogram around the tile's own cells
   // end-of-slice bookkeeping of the predictor-corrector (real push only):
   // the slice's iteration count to iters_out (caller) and iters_own
-  // (library), the residual to resid_out; pc_budgeted: fewer iterations
+  // (library, see own_iters), the residual to resid_out; pc_budgeted: fewer iterations
   // than pc_max_iter were launched for the slice (a slice left unconverged
   // by them is counted in DevCounters::budget_short)
   int32_t* iters_out;
   int32_t* iters_own;
   double* resid_out;
-  double* resid_own;        // (library; may be null)
   int pc_budgeted;
   double pc_tol;
   int pc_max_iter;
@@ -320,7 +319,6 @@ void launch_zero(double* p, size_t n, hipStream_t);
 template <typename T>
 void launch_zero_t(T* p, size_t n, hipStream_t);
 void launch_slice_end(DevCounters*, int32_t* iters_out, int32_t* iters_own, double* resid_out,
-                      double* resid_own,
                       double tol, int max_iter, int budgeted, const double* pc_partial, int pc_nblk,
                       hipStream_t);
 

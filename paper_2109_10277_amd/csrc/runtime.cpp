@@ -698,14 +698,9 @@ class Box final : public BoxBase {
     // short in two runs of three): slices that end within a factor of ten get
     // a margin from the start (512^2 box 19.7 ms; 18.9 without margins, 20.2
     // with one everywhere, 23.8 with every iteration launched).
-    std::vector<double> res;
-    if (resid_own_) {
-      res.resize(cfg_.nzeta);
-      QSP_HIP(hipMemcpy(res.data(), resid_own_, res.size() * sizeof(double), hipMemcpyDeviceToHost));
-    }
     for (int k = 0; k < cfg_.nzeta; ++k) {
-      if (resid_own_ && spec_mode_ > 0 && res[k] > 0.1 * cfg_.pc_tol) margin_[k] = 1;
-      const int v = std::max(1, std::min(static_cast<int>(it[k]), cfg_.pc_max_iter));
+      if (explicit_ && spec_mode_ > 0 && (it[k] & kNearTol)) margin_[k] = 1;
+      const int v = std::max(1, std::min(static_cast<int>(it[k] & (kNearTol - 1)), cfg_.pc_max_iter));
       if (after_shortfall && spec_mode_ > 0 && v > budget_launch_[k]) margin_[k] = 1;
       budget_[k] = std::max(budget_[k], v);
     }
@@ -1453,7 +1448,6 @@ class Box final : public BoxBase {
       iony_ = alloc<double>(cfg_.ny + 1);
     }
     iters_own_ = alloc<int32_t>(cfg_.nzeta);
-    if (explicit_) resid_own_ = alloc<double>(cfg_.nzeta);
     ctr_ = alloc<DevCounters>(1);
     partial_ = alloc<double>(2 * static_cast<size_t>(pc_partial_count(geom_)) + 2);
     if (cfg_.mem_cap_bytes > 0 && bytes_ > cfg_.mem_cap_bytes) throw std::bad_alloc();
@@ -1735,7 +1729,6 @@ class Box final : public BoxBase {
       a.iters_out = iters_out;
       a.iters_own = iters_own_ + k;
       a.resid_out = resid_out;
-      a.resid_own = resid_own_ ? resid_own_ + k : nullptr;
       a.pc_budgeted = budgeted;
       if (beam_n_ > 0) {
         // the launch also pushes slice k's beam particles and deposits
@@ -1764,8 +1757,7 @@ class Box final : public BoxBase {
       pushes_ += lat_.np;
     } else {
       timed(QSP_K_OTHER, [&] {
-        launch_slice_end(ctr_, iters_out, iters_own_ + k, resid_out,
-                         resid_own_ ? resid_own_ + k : nullptr, cfg_.pc_tol, cfg_.pc_max_iter,
+        launch_slice_end(ctr_, iters_out, iters_own_ + k, resid_out, cfg_.pc_tol, cfg_.pc_max_iter,
                          budgeted,
                          explicit_ ? nullptr : partial_, pc_partial_count(geom_), st_);
       });
@@ -1943,8 +1935,7 @@ class Box final : public BoxBase {
   hipStream_t cap_st_ = nullptr;  // capture stream
   uint64_t launch_version_ = 0;
   // speculative P-C launch budgets (run_box_graphs)
-  int32_t* iters_own_ = nullptr;   // per-slice iteration counts of the last box
-  double* resid_own_ = nullptr;    // explicit solver: each slice's last residual (learn_budgets)
+  int32_t* iters_own_ = nullptr;   // per-slice iterations of the last box (own_iters)
   std::vector<int> budget_;          // learned: iterations the slices needed so far
   std::vector<int> budget_launch_;   // launched in the speculative box
   std::vector<int> margin_;          // 1: the slice's count has risen before, or may
