@@ -162,7 +162,8 @@ typedef struct {
   int64_t n_clamped;          /* real pushes in which 1 + Psi was floored      */
   int64_t n_absorbed;         /* plasma particles absorbed at the box edge     */
   int64_t n_deposit_global;   /* particle deposits outside their LDS tile      */
-  int64_t dst_solves;         /* scalar 2D Dirichlet solves                    */
+  int64_t dst_solves;         /* scalar 2D Dirichlet solves: three a slice and */
+                              /* two an iteration (of either Bx/By solver)     */
   double max_pc_residual;     /* largest final residual of a slice             */
   double elapsed_ms;          /* device time of the last qsp_run_box           */
   int64_t device_bytes;       /* device memory held by the context             */

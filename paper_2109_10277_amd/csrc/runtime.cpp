@@ -422,6 +422,7 @@ class Box final : public BoxBase {
     s->n_clamped = static_cast<int64_t>(c.n_clamped);
     s->n_absorbed = static_cast<int64_t>(c.n_absorbed);
     s->n_deposit_global = static_cast<int64_t>(c.n_dep_global);
+    // Bx and By of every iteration that ran: corrector or preconditioner solves
     s->dst_solves = dst_solves_ + 2 * static_cast<int64_t>(c.pc_iterations);
     s->max_pc_residual = c.max_resid;
     s->elapsed_ms = last_ms_;
@@ -1832,7 +1833,6 @@ class Box final : public BoxBase {
     }
     a.it = launch;
     timed(QSP_K_OTHER, [&] { launch_explicit<T>(geom_, a, kExplClose, tx(), ctr_, st_); });
-    dst_solves_ += 2 * (cfg_.pc_max_iter);
   }
 
   PushArgs<T> push_args(const SliceFields<T>& f, double* const* ch, int k, int nch = 4,
