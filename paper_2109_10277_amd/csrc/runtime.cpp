@@ -1744,16 +1744,17 @@ class Box final : public BoxBase {
         if (beam_push_here) beam_dirty_ = true;
         beam_ahead_ = true;
       }
-      const auto job = [this, a, out = out_rides && oc.count ? &oc : nullptr] {
-        launch_push<T>(geom_, lat_, a, kPushReal, ctr_, st_, out);
-      };
       if (capturing_ && timer_.active(cursor_)) {
-        // the sampled launch runs between graph segments, under its events
+        // the sampled launch runs between graph segments, under its events; it
+        // outlives this call, so it holds its arguments by value and carries no
+        // outputs (out_rides)
         end_segment();
-        cap_graph_->items.push_back({nullptr, std::function<void()>(job), QSP_K_PUSH});
+        cap_graph_->items.push_back(
+            {nullptr, [this, a] { launch_push<T>(geom_, lat_, a, kPushReal, ctr_, st_); }, QSP_K_PUSH});
         begin_segment();
       } else {
-        timed(QSP_K_PUSH, job);
+        const OutCopy* out = out_rides && oc.count ? &oc : nullptr;
+        timed(QSP_K_PUSH, [&] { launch_push<T>(geom_, lat_, a, kPushReal, ctr_, st_, out); });
       }
       pushes_ += lat_.np;
     } else {
