@@ -811,7 +811,7 @@ void with_logn(int n, F&& f) {
 // Bytes of the per-axis tables a transform pass stages in LDS: the W_64 table
 // (72 complex) of the wave core, the stage-B table of the symmetric core.
 template <typename T>
-__host__ __device__ inline size_t table_bytes(int n) {
+__host__ __device__ constexpr size_t table_bytes(int n) {
   if (sym_core(sizeof(T), n))
     return static_cast<size_t>(sym_g(n) > 1 ? 17 * sym_g(n) : 0) * sizeof(Cplx<T>);
   return wave_core(sizeof(T), n) ? size_t(72) * sizeof(Cplx<T>) : 0;
@@ -856,7 +856,7 @@ __device__ __forceinline__ auto stage_row_tables(const AxisTables<T>& t, unsigne
 }
 // LDS bytes of a pass over r rows (columns) of n values.
 template <typename T>
-inline size_t pass_lds(int r, int n) {
+constexpr size_t pass_lds(int r, int n) {
   return static_cast<size_t>(r / 2) * pair_pitch<T>(n) * sizeof(T) + table_bytes<T>(n);
 }
 
@@ -937,14 +937,25 @@ __device__ inline int xcd_strip(int b, int nstrip) {
 // their twiddles, and FP32 rows of 128 points, whose lanes keep 32 matrix operands;
 // four (<= 128 VGPRs) else, except the wave core's column pass, which keeps
 // its eigenvalue divisors and a strip load in flight beside the core's
-// registers.
+// registers.  The LDS of a CU (160 KiB) holds that many, but for FP64 rows of
+// 1024 points (83,840 bytes a workgroup): one.
+constexpr size_t kLdsPerCu = size_t(160) << 10;
+constexpr int lds_blocks(int want, size_t lds) { return want * lds <= kLdsPerCu ? want : 1; }
+constexpr size_t pass_lds_of(int logn, int tsize, bool rows) {
+  const int n = 1 << logn;
+  return tsize == 8 ? pass_lds<double>(rows ? pass_rows<double>(n) : pass_cols<double>(n), n)
+                    : pass_lds<float>(rows ? pass_rows<float>(n) : pass_cols<float>(n), n);
+}
 constexpr int dst_blocks_per_cu(int logn, int tsize) {
-  return sym_core(tsize, 1 << logn) || logn == 7 ? 2 : 4;
+  return lds_blocks(sym_core(tsize, 1 << logn) || logn == 7 ? 2 : 4, pass_lds_of(logn, tsize, true));
 }
 
 constexpr int col_blocks_per_cu(int logn, int tsize) {
-  return (1 << logn) >= 128 ? 2 : 4;
+  return lds_blocks(logn >= 7 ? 2 : 4, pass_lds_of(logn, tsize, false));
 }
+static_assert(dst_blocks_per_cu(9, 8) == 2 && dst_blocks_per_cu(10, 8) == 1 && dst_blocks_per_cu(11, 8) == 2 &&
+                  dst_blocks_per_cu(10, 4) == 2 && col_blocks_per_cu(10, 8) == 1 && col_blocks_per_cu(11, 8) == 2,
+              "workgroups of long rows per CU");
 
 // Calls f(e) for e = t + u kBlock, u = 0 .. TOTAL / kBlock - 1 (TOTAL a
 // multiple of kBlock known at compile time), fully unrolled: with the row
