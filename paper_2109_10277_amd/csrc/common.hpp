@@ -85,11 +85,6 @@ __device__ __forceinline__ void store_at(T* base, unsigned int i, T v) {
   *reinterpret_cast<T*>(reinterpret_cast<char*>(base) + i * static_cast<unsigned int>(sizeof(T))) = v;
 }
 
-// Offset of element (j, i) of a strip-ordered intermediate plane.
-__host__ __device__ inline size_t strip_at(int j, int i, int ny) {
-  return (static_cast<size_t>(i >> 2) * ny + j) * 4 + (i & 3);
-}
-
 // Plasma lattice: (nx*ppc_x) x (ny*ppc_y) sites, particle p = I + J*nX.
 struct Lattice {
   int nX, nY, ppc_x, ppc_y;

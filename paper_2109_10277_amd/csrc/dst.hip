@@ -116,17 +116,15 @@ k_row_inv(Geom g, RowInvArgs<T> a, AxisTables<T> tx) {
   const auto xf = stage_row_tables<T, LOGN>(tx, smem_raw);
   const int j0 = xcd_strip(blockIdx.x, gridDim.x) * R;   // neighbours on one XCD
   const int fld = blockIdx.y;
-  Geom gi = g;
-  gi.strip = a.in_strip;
   const size_t plane = static_cast<size_t>(g.nx) * g.ny;
   const size_t gstride = static_cast<size_t>(gridDim.x) * gridDim.y * kBlock;
   const size_t gi0 = (static_cast<size_t>(blockIdx.y) * gridDim.x + blockIdx.x) * kBlock + threadIdx.x;
   GuessRegs<T> gr;
   RowFetch<T, R, LOGN> rows;
-  rows.load(gi, j0, a.in[fld]);
+  rows.load(g, j0, a.in[fld]);
   if (a.guess.ctr) guess_load(a.guess, plane, gi0, gstride, gr);
   __builtin_amdgcn_sched_barrier(0);
-  rows.put(gi, buf, ppitch);
+  rows.put(g, buf, ppitch);
   xf.commit();
   if (a.guess.ctr) {   // its stores drain under the transform
     if (gi0 == 0) {
@@ -144,12 +142,6 @@ k_row_inv(Geom g, RowInvArgs<T> a, AxisTables<T> tx) {
   block_dst<T, LOGN, false>(buf, ppitch, xf);
   T* out = a.out[fld];
   T* out_dx = a.out_dx[fld];
-  if (a.out_strip) {   // an intermediate plane (no -d_x)
-    Geom go = g;
-    go.strip = 1;
-    rows_to_plane<T, R, LOGN>(go, j0, buf, ppitch, out);
-    return;
-  }
   const T mihx = static_cast<T>(-0.5 / g.hx);
   // tested once: per element the loop stays rolled (21.7 against 20.2 us at
   // 1024^2 in FP32)
@@ -342,17 +334,17 @@ int pc_partial_count(const Geom& g) {
 }
 
 template <typename T>
-int col_width(const Geom& g, int) {
+int col_width(const Geom& g) {
   return pass_cols<T>(g.ny);
 }
-template int col_width<float>(const Geom&, int);
-template int col_width<double>(const Geom&, int);
+template int col_width<float>(const Geom&);
+template int col_width<double>(const Geom&);
 template <typename T>
-int row_rows(int nx, int) {
+int row_rows(int nx) {
   return pass_rows<T>(nx);
 }
-template int row_rows<float>(int, int);
-template int row_rows<double>(int, int);
+template int row_rows<float>(int);
+template int row_rows<double>(int);
 
 #define QSP_INST(T)                                                                       \
   template void launch_src_fwd_pez<T>(const Geom&, const SrcPEZ<T>&, const AxisTables<T>&, \

@@ -153,7 +153,7 @@ __device__ __forceinline__ Cplx<T> w32(int k) {
   return {static_cast<T>(sg * c), static_cast<T>(-sg * s)};
 }
 
-// In-register forward DFT of length P = R1 * 8 (R1 = 1, 2, 4), in place with
+// In-register forward DFT of length P = R1 * 8 (R1 = 1, 2), in place with
 // j = j0 + 8 j1 and k = k0 + R1 k1: DFT_R1 over j1, twiddles W_P^{j0 k0},
 // DFT_8 over j0.  X_k ends at position dft_pos<P>(k) = 8 k0 + k1.
 template <int P>
@@ -164,6 +164,7 @@ __host__ __device__ constexpr int dft_pos(int k) {
 template <int P, typename T>
 __device__ __forceinline__ void dft_reg(Cplx<T>* v) {
   constexpr int R1 = P / 8;
+  static_assert(R1 == 1 || R1 == 2, "8 or 16 points");
   if constexpr (R1 == 2) {
 #pragma unroll
     for (int j0 = 0; j0 < 8; ++j0) {
@@ -171,9 +172,6 @@ __device__ __forceinline__ void dft_reg(Cplx<T>* v) {
       v[j0] = cadd(a, b);
       v[j0 + 8] = csub(a, b);
     }
-  } else if constexpr (R1 == 4) {
-#pragma unroll
-    for (int j0 = 0; j0 < 8; ++j0) dft4(v[j0], v[j0 + 8], v[j0 + 16], v[j0 + 24]);
   }
   if constexpr (R1 > 1) {
 #pragma unroll
@@ -1196,7 +1194,7 @@ __device__ __forceinline__ void for_iters(F&& f) {
   }
 }
 
-// Column pass with one of the FFT cores (W = 2, 4 or 8 columns): strip load,
+// Column pass with one of the FFT cores (W = 2 or 4 columns): strip load,
 // forward core whose output stage divides by the eigenvalues, inverse core,
 // store.  Strip-ordered planes (W = 4): the strip is one contiguous block, 4
 // consecutive values per row and thread.  Row-major planes: thread t handles
@@ -1212,11 +1210,12 @@ __device__ __forceinline__ void col_block_core(const Geom& g, const ColArgs<T>& 
   constexpr int n = 1 << LOGN;
   constexpr bool sym = sym_core(sizeof(T), n);
   constexpr int NK = sym ? 16 : n / 64;       // output slots per lane
-  constexpr int LW = W == 2 ? 1 : (W == 4 ? 2 : 3);
+  constexpr int LW = W == 2 ? 1 : 2;
   constexpr int JS = kBlock / W;              // row step of a thread
-  constexpr int NIT = n >= JS ? n / JS : 1;   // rows per thread
+  constexpr int NIT = n / JS;                 // rows per thread
   constexpr int LS = Pd::ridx(JS);            // LDS step of ridx
   constexpr int rl = Pd::rlen(n);
+  static_assert((W == 2 || W == 4) && n >= JS, "whole steps of rows");
   static_assert(JS % (1 << Pd::S) == 0, "row step must keep the LDS padding affine");
   T* buf = reinterpret_cast<T*>(smem_raw);
   const int nx = g.nx;
@@ -1276,7 +1275,7 @@ __device__ __forceinline__ void col_block_core(const Geom& g, const ColArgs<T>& 
         d[ppitch] = v[u].v[2];
         d[ppitch + rl] = v[u].v[3];
       }
-  } else if (n >= JS || j0 < n) {
+  } else {
     const T* in = a.in + fld * plane + p0 + c + static_cast<size_t>(j0) * nx;
     T* d = buf + lcol;
     for_iters<NIT>([&](int it) { d[it * LS] = in[static_cast<size_t>(it) * JS * nx]; });
@@ -1355,7 +1354,6 @@ __device__ __forceinline__ void col_block_core(const Geom& g, const ColArgs<T>& 
     }
     return;
   }
-  if (n < JS && j0 >= n) return;
   T* out = a.out + fld * plane + p0 + c + static_cast<size_t>(j0) * nx;
   const T* r = buf + lcol;
   if (with_dy) {

@@ -78,11 +78,6 @@ __global__ void k_to_nodes(Geom g, const T* src, double* dst) {
 
 }  // namespace
 
-void launch_zero_int(int* p, size_t n, hipStream_t st) {
-  hipLaunchKernelGGL(k_zero<int>, grid_for(n), dim3(kBlock), 0, st, p, n);
-  QSP_LAUNCH_CHECK();
-}
-
 void launch_zero(double* p, size_t n, hipStream_t st) {
   hipLaunchKernelGGL(k_zero<double>, grid_for(n), dim3(kBlock), 0, st, p, n);
   QSP_LAUNCH_CHECK();

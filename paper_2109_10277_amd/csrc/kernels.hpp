@@ -78,7 +78,6 @@ struct RowInvArgs {
   T* out[4];
   T* out_dx[4];             // optional -d_x of the result
   GuessJob<T> guess;
-  int in_strip, out_strip;  // in / out planes in the strip order of Geom::strip
 };
 
 // The ends of a batched solve on node arrays [nbatch][ny+1][nx+1].
@@ -141,12 +140,12 @@ inline bool small_batch(const Geom& g, const T* src, const T* dst, int nbatch) {
   return nbatch == 1 || s == d || s + bytes <= d || d + bytes <= s;
 }
 int pc_partial_count(const Geom&);
-// column-strip width of a column pass over nfield planes
+// column-strip width of a column pass
 template <typename T>
-int col_width(const Geom&, int nfield);
+int col_width(const Geom&);
 // rows per workgroup of the transform row passes (Geom::rr)
 template <typename T>
-int row_rows(int nx, int ny);
+int row_rows(int nx);
 
 // ---------------------------------------------------------------- particles
 template <typename T>
@@ -377,7 +376,6 @@ void launch_beam_deposit(const Geom&, const float* soa, int64_t n, const int64_t
 template <typename T>
 void launch_beam_push(const Geom&, float* soa, int64_t n, const int64_t* off, int k,
                       int64_t grid_count, const SliceFields<T>& f, double dt, hipStream_t);
-void launch_zero_int(int* p, size_t n, hipStream_t);
 
 // ---------------------------------------------------------------- adjoint
 template <typename T>

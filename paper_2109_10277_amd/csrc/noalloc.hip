@@ -115,7 +115,7 @@ void solve(const qsp_config& c, unsigned char* ptr, int nb, const T* src, T* dst
   g.y_lo = c.y_lo;
   g.hx = (c.x_hi - c.x_lo) / c.nx;
   g.hy = (c.y_hi - c.y_lo) / c.ny;
-  g.rr = row_rows<T>(c.nx, c.ny);
+  g.rr = row_rows<T>(c.nx);
   g.order = 1;
   g.strip = 0;   // the passes run in place: the planes stay row-major
   T* planes = reinterpret_cast<T*>(ptr);
@@ -142,7 +142,7 @@ void solve(const qsp_config& c, unsigned char* ptr, int nb, const T* src, T* dst
   col.in = planes;
   col.out = planes;
   for (int b = 0; b < 4; ++b) col.shift[b] = shift;
-  col.w = col_width<T>(g, nb);
+  col.w = col_width<T>(g);
   launch_col_solve<T>(g, col, nb, ty, tx.lam, nullptr, st);
   launch_row_nodes<T>(g, r, true, nb, tx, st);
 }

@@ -195,10 +195,10 @@ class Box final : public BoxBase {
     geom_.y_lo = cfg.y_lo;
     geom_.hx = (cfg.x_hi - cfg.x_lo) / cfg.nx;
     geom_.hy = (cfg.y_hi - cfg.y_lo) / cfg.ny;
-    geom_.rr = row_rows<T>(cfg.nx, cfg.ny);
+    geom_.rr = row_rows<T>(cfg.nx);
     geom_.order = cfg.shape_order;
     // column strips of 4 columns: strip-ordered intermediate planes
-    geom_.strip = col_width<T>(geom_, 2) == 4 &&
+    geom_.strip = col_width<T>(geom_) == 4 &&
                   (sym_core(sizeof(T), cfg.ny) || wave_core(sizeof(T), cfg.ny));
     lat_.ppc_x = cfg.ppc_x;
     lat_.ppc_y = cfg.ppc_y;
@@ -548,7 +548,7 @@ class Box final : public BoxBase {
     c.in = t2_;
     c.out = t2_;
     for (int b = 0; b < 4; ++b) c.shift[b] = shift;
-    c.w = col_width<T>(geom_, nb);
+    c.w = col_width<T>(geom_);
     launch_col_solve<T>(geom_, c, nb, ty(), lamx_, ctr_, st_);
     launch_row_nodes<T>(geom_, r, true, nb, tx(), st_);
   }
@@ -1147,14 +1147,13 @@ class Box final : public BoxBase {
     c.out = t2_;
     for (int b = 0; b < 4; ++b) c.shift[b] = shift;
     c.honor_done = 0;
-    c.w = col_width<T>(geom_, nb);
+    c.w = col_width<T>(geom_);
     launch_col_solve<T>(geom_, c, nb, ty(), lamx_, ctr_, st_);
     RowInvArgs<T> r{};
     for (int b = 0; b < nb; ++b) {
       r.in[b] = t2_ + b * pl;
       r.out[b] = out[b];
     }
-    r.in_strip = geom_.strip;
     launch_row_inv<T>(geom_, r, nb, tx(), st_);
   }
 
@@ -1603,7 +1602,7 @@ class Box final : public BoxBase {
       c.out_dy = t2_ + 3 * pl;
       c.shift[0] = c.shift[1] = c.shift[2] = 0.0;
       c.honor_done = 0;
-      c.w = col_width<T>(geom_, 3);
+      c.w = col_width<T>(geom_);
       // the deposit planes of slice k+1 are free: clear them for the real push
       for (int q = 0; q < 4; ++q) c.zero.p[q] = dn[q];
       c.zero.count = 4;
@@ -1620,8 +1619,7 @@ class Box final : public BoxBase {
       r.out[2] = ez_;
       r.in[3] = t2_ + 2 * pl;
       r.out[3] = bz_;
-      r.in_strip = geom_.strip;
-      // Bx/By initial guess of the predictor-corrector rides along
+        // Bx/By initial guess of the predictor-corrector rides along
       r.guess = {bxk, byk, b_[i1_][0], b_[i1_][1], b_[i2_][0], b_[i2_][1], ctr_,
                  tape_slot_ ? tape_b(*tape_slot_, 0, 0) : nullptr,
                  tape_slot_ ? tape_b(*tape_slot_, 0, 1) : nullptr};
@@ -1672,7 +1670,7 @@ class Box final : public BoxBase {
         c.out_dy = nullptr;
         c.shift[0] = c.shift[1] = shift_;
         c.honor_done = 1;
-        c.w = col_width<T>(geom_, 2);
+        c.w = col_width<T>(geom_);
         // the trial currents have been read: clear what the next trial adds
         // into (the shared planes; with no tiles the owner planes)
         c.zero.p[0] = tiled_ ? trial_sh_[0] : trial_[0];
@@ -1817,7 +1815,7 @@ class Box final : public BoxBase {
     c.out_dy = nullptr;
     c.shift[0] = c.shift[1] = shift_;
     c.honor_done = 1;
-    c.w = col_width<T>(geom_, 2);
+    c.w = col_width<T>(geom_);
     auto precondition = [&](int it) {
       a.it = it;
       timed(QSP_K_COL, [&] { launch_col_solve<T>(geom_, c, 2, ty(), lamx_, ctr_, st_); });
