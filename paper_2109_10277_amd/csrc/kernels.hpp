@@ -219,11 +219,6 @@ struct PushArgs {
   int tiled;                // 1: LDS tile histograms, 0: direct global atomics
   int tile_rows;            // lattice rows per workgroup tile
   int tile_halo;            // cells of LDS histogram around the tile's own cells
-  // kPushTrialTape: copy of the slice-k particle state the push reads, 6
-  // planes of np in the order xi_x, xi_y, ux, uy, psi, w (its place keeps what
-  // the trial pushes read from here on in the argument lines it was measured
-  // in: 8 bytes earlier the 512^2 FP64 box takes 29.76 instead of 29.62 ms)
-  T* tape;
   // end-of-slice bookkeeping of the predictor-corrector (real push only):
   // the slice's iteration count to iters_out (caller) and iters_own
   // (library, see own_iters), the residual to resid_out; pc_budgeted: fewer iterations
@@ -232,6 +227,10 @@ struct PushArgs {
   int32_t* iters_out;
   int32_t* iters_own;
   double* resid_out;
+  // unused: with it the counters' pointer and the grid size that follow these
+  // arguments share one 64-byte line, which every trial push waits for first
+  // (512^2 FP64: later trials 12.0 us, 12.27 without; first 16.15, 16.33)
+  int64_t reserved0;
   int pc_budgeted;
   double pc_tol;
   int pc_max_iter;
@@ -245,6 +244,9 @@ struct PushArgs {
   // on taped slices only, Psi at k+1.  The first trial push of a slice writes
   // it (if non-null), later ones read it.
   T* rec;
+  // kPushTrialTape: copy of the slice-k particle state the push reads, 6
+  // planes of np in the order xi_x, xi_y, ux, uy, psi, w
+  T* tape;
   BeamRide beam;            // kPushReal only
 };
 
