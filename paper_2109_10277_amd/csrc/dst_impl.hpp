@@ -209,16 +209,19 @@ __device__ __forceinline__ double recip(double d) {
 // normalisation; column p = 0 (a boundary node line) is zero.  ry holds
 // (lambda_y(k) - shift) nx ny / 4 for the lane's NK output slots k (see
 // core_out_k, sym_out_k), xa / xb lambda_x(p) nx ny / 4, in FP64 held to a
-// quarter of the range so that their sum is finite (eigen_term).
+// quarter of the range where their sum might not be finite (eigen_range).
 // In FP32 columns of 2048 points the sum is formed in FP64, rounded once and
 // divided by (ONCE): terms rounded before the sum and the reciprocal err up to
 // 6 units of 2^-24 there instead of 3.  Shorter FP32 columns add FP32 terms,
 // and FP64 columns multiply by the reciprocal: with a division solves of
 // 1024 x 512 points err no less (4.6e-16 against 4.5e-16) and take 41.1 us
 // instead of 40.1, the 512^2 FP64 box 30.4 ms instead of 29.8.
-template <typename R>
-__device__ __forceinline__ R eigen_term(double v) {
-  return static_cast<R>(sizeof(R) == 8 ? fmax(v, -0x1p1022) : v);
+// Whether the terms may reach 2^1022 (spacings or a shift at the end of the
+// range); tested once, under the strip load: holding the terms always took the
+// 512^2 FP64 column pass from 12.55 to 12.65 us.
+__device__ __forceinline__ bool eigen_range(const Geom& g, double shift, double inorm) {
+  const double hx2 = g.hx * g.hx, hy2 = g.hy * g.hy;
+  return !(4.0 * inorm < 0x1p1000 * hx2 && 4.0 * inorm < 0x1p1000 * hy2 && shift * inorm < 0x1p1000);
 }
 template <typename T, int N>
 constexpr bool eigen_once = sizeof(T) == 4 && N > 1024;
@@ -1252,6 +1255,9 @@ __device__ __forceinline__ void col_block_core(const Geom& g, const ColArgs<T>& 
   }
   lxa = lamx[p0 + (busy ? 2 * pr : 0)];
   lxb = lamx[p0 + (busy ? 2 * pr + 1 : 1)];
+  const double shift = a.shift[fld];
+  const double inorm = 0.25 * static_cast<double>(nx) * n;
+  const bool hold = sizeof(T) == 8 && eigen_range(g, shift, inorm);
   const size_t plane = static_cast<size_t>(nx) * n;
   const int c = tid & (W - 1), j0 = tid >> LW;
   const int lcol = (c >> 1) * ppitch + (c & 1) * rl + Pd::ridx(j0);
@@ -1299,15 +1305,21 @@ __device__ __forceinline__ void col_block_core(const Geom& g, const ColArgs<T>& 
         }
       }
     }
-    const double shift = a.shift[fld];
-    const double inorm = 0.25 * static_cast<double>(nx) * n;
     using Scale = EigenScale<T, NK, eigen_once<T, n>>;
     Scale sc;
     if (busy) {
 #pragma unroll
-      for (int q = 0; q < NK; ++q) sc.ry[q] = eigen_term<typename Scale::R>((ly[q] - shift) * inorm);
-      sc.xa = eigen_term<typename Scale::R>(lxa * inorm);
-      sc.xb = eigen_term<typename Scale::R>(lxb * inorm);
+      for (int q = 0; q < NK; ++q) sc.ry[q] = static_cast<typename Scale::R>((ly[q] - shift) * inorm);
+      sc.xa = static_cast<typename Scale::R>(lxa * inorm);
+      sc.xb = static_cast<typename Scale::R>(lxb * inorm);
+      if constexpr (sizeof(T) == 8) {
+        if (hold) {
+#pragma unroll
+          for (int q = 0; q < NK; ++q) sc.ry[q] = fmax(sc.ry[q], -0x1p1022);
+          sc.xa = fmax(sc.xa, -0x1p1022);
+          sc.xb = fmax(sc.xb, -0x1p1022);
+        }
+      }
       sc.za = p0 + 2 * pr == 0;
     }
     if constexpr (sym) {
