@@ -634,7 +634,7 @@ class Box final : public BoxBase {
       }
       budget_on_ = false;
       unsigned int shortfall = 0;
-      QSP_HIP(hipMemcpy(&shortfall, &ctr_->budget_short, sizeof(shortfall), hipMemcpyDeviceToHost));
+      read_back(&shortfall, &ctr_->budget_short, 1);
       if (shortfall == 0) return;
       fell_short = true;
       ++box_reruns_;
@@ -672,6 +672,13 @@ class Box final : public BoxBase {
     }
   }
 
+  // on the box's own stream: the null stream would wait for the caller's others
+  template <typename U>
+  void read_back(U* dst, const U* src, size_t n) {
+    QSP_HIP(hipMemcpyAsync(dst, src, n * sizeof(U), hipMemcpyDeviceToHost, st_));
+    QSP_HIP(hipStreamSynchronize(st_));
+  }
+
   // the iterations a speculative box launches per slice
   void set_budget_launch() {
     budget_launch_.resize(cfg_.nzeta);
@@ -687,7 +694,7 @@ class Box final : public BoxBase {
   // slices that needed more than they were given get a margin from now on
   void learn_budgets(bool after_shortfall) {
     std::vector<int32_t> it(cfg_.nzeta);
-    QSP_HIP(hipMemcpy(it.data(), iters_own_, it.size() * sizeof(int32_t), hipMemcpyDeviceToHost));
+    read_back(it.data(), iters_own_, it.size());
     if (!budget_ready_ || budget_version_ != launch_version_) {
       budget_.assign(cfg_.nzeta, 1);
       margin_.assign(cfg_.nzeta, 0);
