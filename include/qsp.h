@@ -206,7 +206,7 @@ qsp_status qsp_validate_config(const qsp_config* cfg, char* msg, size_t msg_len)
 
 /* Creates a context on HIP device `device`; all later work of the context is
  * enqueued on `hip_stream` (a hipStream_t; NULL = the null stream).  Allocates
- * every device buffer the box needs (the size does not depend on nzeta).
+ * every device buffer the box needs (nzeta adds four bytes a slice).
  * On success *out holds the new context; on failure *out is NULL. */
 qsp_status qsp_create(const qsp_config* cfg, int device, void* hip_stream,
                       qsp_ctx* out);

@@ -166,7 +166,7 @@ __host__ __device__ constexpr int dense_angle(int n, int t, int l, int s) {
 }
 
 // Grids whose solves run in one workgroup per field (small.hip): batches on
-// node arrays up to 64 x 64 (one launch of 9.8 us against three that take 11.7
+// node arrays up to 64 x 64 (one launch of 9.7 us against three that take 11.7
 // eagerly, FP32; 11.3 in FP64), the slice loop's up to 2048 nodes (32 x 64 box:
 // 3.52 ms against 4.01; at 64 x 64 one CU's loads and products take longer than
 // three passes' launches from a graph, 4.36 against 4.30 ms with all sums in

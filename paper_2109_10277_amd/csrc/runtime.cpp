@@ -601,7 +601,7 @@ class Box final : public BoxBase {
   // pc_max_iter (the launches after convergence would read the device's
   // converged flag and return: 4 launches an iteration, 2 us each even then;
   // the explicit 512^2 box, which needs 1.8 iterations of 5 on average, took
-  // 23.8 ms with all of them launched, 20.4 with exact budgets).  A budget
+  // 23.8 ms with all of them launched, 18.9 with exact budgets).  A budget
   // is the most iterations the slice needed in the boxes run so far, plus one
   // where the slice's count has risen before (or may, see learn_budgets).  A
   // slice that ends its budget unconverged below

@@ -5,7 +5,7 @@
 // 2 MFLOP.  Here the field stays in LDS from its source to its epilogue: four
 // products with the folded sine matrices (Dense), one 16x16 output tile per
 // wave and product.  Measured (FP32): 32^2 box of 64 slices 3.77 -> 2.72 ms, its
-// gradient run 17.0 -> 13.6, one solve at 64^2 11.7 -> 9.8 us, at 32^2 11.6 ->
+// gradient run 17.0 -> 13.6, one solve at 64^2 11.7 -> 9.7 us, at 32^2 11.6 ->
 // 4.4.
 #include <stdexcept>
 
