@@ -40,18 +40,17 @@ KCLASSES = ("push", "trial", "row_fwd", "col", "row_inv", "other")
 
 # HBM bytes per real-push launch from the FETCH_SIZE / WRITE_SIZE counter
 # runs (each scaled by what the counter reads for a plain 256 MiB copy),
-# valid while the push kernel's sources (and the runtime, which picks its
-# tiles) hash to the recorded value
-PUSH_SOURCES = ["paper_2109_10277_amd/csrc/particles.hip",
-                "paper_2109_10277_amd/csrc/push_tile.hpp",
-                "paper_2109_10277_amd/csrc/shape.hpp",
-                "paper_2109_10277_amd/csrc/runtime.cpp"]
+# valid while the files the push kernel is compiled from (and the runtime, which
+# picks its tiles) hash to the recorded value
+PUSH_SOURCES = ["paper_2109_10277_amd/csrc/" + f for f in (
+    "particles.hip", "push_tile.hpp", "beam_body.hpp", "out_body.hpp", "partials.hpp", "shape.hpp",
+    "kernels.hpp", "common.hpp", "runtime.cpp")]
 PUSH_TRAFFIC = {
-    "c2": {"sha256_prefix": "92fde147c4a76b1b", "bytes": 72.62e6,
+    "c2": {"sha256_prefix": "98bea9be54f16f57", "bytes": 72.62e6,
            "summary": "profiles/kernel_stats_c2_blowout_512x512x1024_fp32.md"},
-    "c5": {"sha256_prefix": "92fde147c4a76b1b", "bytes": 824.09e6,
+    "c5": {"sha256_prefix": "98bea9be54f16f57", "bytes": 823.78e6,
            "summary": "profiles/kernel_stats_c5_forward_1024x1024_4ppc_fp32.md"},
-    "c3": {"sha256_prefix": "92fde147c4a76b1b", "bytes": 268.16e6,
+    "c3": {"sha256_prefix": "98bea9be54f16f57", "bytes": 268.18e6,
            "summary": "profiles/hbm_traffic_c3_paper_step_1024x1024x1024_fp32.md"},
 }
 
