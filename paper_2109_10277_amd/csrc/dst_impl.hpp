@@ -212,7 +212,11 @@ __device__ __forceinline__ double recip(double d) {
 // quarter of the range where their sum might not be finite (eigen_range).
 // In FP32 columns of 2048 points the sum is formed in FP64, rounded once and
 // divided by (ONCE): terms rounded before the sum and the reciprocal err up to
-// 6 units of 2^-24 there instead of 3.  Shorter FP32 columns add FP32 terms,
+// 6 units of 2^-24 there instead of 3.  The FP64 terms take registers (191
+// against 164, two waves a SIMD instead of three): 2048^2 nodes 67 us for one
+// field and 153 for three, 64 and 130 with the reciprocal; holding the kernel
+// to 168 registers (20 spilled) or correcting the reciprocal's product instead
+// of dividing gives 154 and 151.  Shorter FP32 columns add FP32 terms,
 // and FP64 columns multiply by the reciprocal: with a division solves of
 // 1024 x 512 points err no less (4.6e-16 against 4.5e-16) and take 41.1 us
 // instead of 40.1, the 512^2 FP64 box 30.4 ms instead of 29.8.
