@@ -210,16 +210,10 @@ __device__ __forceinline__ double recip(double d) {
 // (lambda_y(k) - shift) nx ny / 4 for the lane's NK output slots k (see
 // core_out_k, sym_out_k), xa / xb lambda_x(p) nx ny / 4, in FP64 held to a
 // quarter of the range where their sum might not be finite (eigen_range).
-// In FP32 columns of 2048 points the sum is formed in FP64, rounded once and
-// divided by (ONCE): terms rounded before the sum and the reciprocal err up to
-// 6 units of 2^-24 there instead of 3.  The FP64 terms take registers (191
-// against 164, two waves a SIMD instead of three): 2048^2 nodes 67 us for one
-// field and 153 for three, 64 and 130 with the reciprocal; holding the kernel
-// to 168 registers (20 spilled) or correcting the reciprocal's product instead
-// of dividing gives 154 and 151.  Shorter FP32 columns add FP32 terms,
-// and FP64 columns multiply by the reciprocal: with a division solves of
-// 1024 x 512 points err no less (4.6e-16 against 4.5e-16) and take 41.1 us
-// instead of 40.1, the 512^2 FP64 box 30.4 ms instead of 29.8.
+// Shorter FP32 columns add FP32 terms, and FP64 columns multiply by the
+// reciprocal: with a division solves of 1024 x 512 points err no less (4.6e-16
+// against 4.5e-16) and take 41.1 us instead of 40.1, the 512^2 FP64 box 30.4 ms
+// instead of 29.8.
 // Whether the terms may reach 2^1022 (spacings or a shift at the end of the
 // range); tested once, under the strip load: holding the terms always took the
 // 512^2 FP64 column pass from 12.55 to 12.65 us.
@@ -227,24 +221,38 @@ __device__ __forceinline__ bool eigen_range(const Geom& g, double shift, double 
   const double hx2 = g.hx * g.hx, hy2 = g.hy * g.hy;
   return !(4.0 * inorm < 0x1p1000 * hx2 && 4.0 * inorm < 0x1p1000 * hy2 && shift * inorm < 0x1p1000);
 }
-template <typename T, int N>
-constexpr bool eigen_once = sizeof(T) == 4 && N > 1024;
-template <typename T, int NK, bool ONCE>
+template <typename T, int NK>
 struct EigenScale {
-  using R = std::conditional_t<ONCE, double, T>;
-  R ry[NK];
-  R xa, xb;
+  T ry[NK];
+  T xa, xb;
   bool za;
   __device__ void operator()(int q, T& oa, T& ob) const {
-    if constexpr (ONCE) {
-      oa = za ? T(0) : oa / static_cast<T>(xa + ry[q]);
-      ob /= static_cast<T>(xb + ry[q]);
-    } else {
-      const T ra = recip(xa + ry[q]);
-      const T rb = recip(xb + ry[q]);
-      oa = za ? T(0) : oa * ra;
-      ob *= rb;
-    }
+    const T ra = recip(xa + ry[q]);
+    const T rb = recip(xb + ry[q]);
+    oa = za ? T(0) : oa * ra;
+    ob *= rb;
+  }
+};
+
+// The same for FP32 columns of 2048 points, the sum formed in FP64, rounded
+// once and divided by: terms rounded before the sum and the reciprocal err up
+// to 6 units of 2^-24 there instead of 3.  The outputs of a lane are k0 + 256 q
+// (or 4096 less that), so lambda_y = -2 / h^2 + c cos(pi q / 8) + s sin(pi q / 8)
+// with c = lambda_y(k0) + 2 / h^2 and s = lambda_y(k0 + 1024) + 2 / h^2: four
+// doubles instead of sixteen, exact to 1e-10 of the smallest eigenvalue.  2048^2
+// nodes, three fields: 126 us; 153 with sixteen doubles a lane (191 registers
+// against 165, two waves a SIMD instead of three), 130 with rounded terms.
+template <typename T, int N>
+constexpr bool eigen_once = sizeof(T) == 4 && N > 1024;
+struct EigenOnce {
+  double c, s;     // times nx ny / 4
+  double xa, xb;   // (lambda_x(p) - shift - 2 / h^2) nx ny / 4
+  bool za;
+  __device__ void operator()(int q, float& oa, float& ob) const {
+    const Cplx<double> w = w32<double>(2 * q);   // cos, -sin (pi q / 8)
+    const double y = c * w.re - s * w.im;
+    oa = za ? 0.f : oa / static_cast<float>(xa + y);
+    ob /= static_cast<float>(xb + y);
   }
 };
 
@@ -1216,6 +1224,7 @@ __device__ __forceinline__ void col_block_core(const Geom& g, const ColArgs<T>& 
   using Pd = CoreLay<T>;
   constexpr int n = 1 << LOGN;
   constexpr bool sym = sym_core(sizeof(T), n);
+  constexpr bool once = eigen_once<T, n>;     // the eigenvalue of each slot from two of them
   constexpr int NK = sym ? 16 : n / 64;       // output slots per lane
   constexpr int LW = W == 2 ? 1 : 2;
   constexpr int JS = kBlock / W;              // row step of a thread
@@ -1245,10 +1254,18 @@ __device__ __forceinline__ void col_block_core(const Geom& g, const ColArgs<T>& 
     const SymLane<LOGN, W / 2> t;
     pr = t.pair_b;
     busy = t.row;
-    lam_s = reinterpret_cast<double*>(buf + Sym<LOGN>::template soff<T>());
-    static_assert(sizeof(double) * n <= sizeof(Cplx<T>) * 9 * Sym<LOGN>::RP, "eigenvalues fit the exchange region");
+    if constexpr (once) {
+      // k0 of slot 0 (EigenOnce)
+      static_assert(Sym<LOGN>::G == 16 && n == 2048, "outputs k0 + 256 q");
+      const int k0 = t.k1 + 16 * t.g;
+      lam_v[0] = ty.lam[k0];
+      lam_v[1] = ty.lam[k0 + n / 2];
+    } else {
+      lam_s = reinterpret_cast<double*>(buf + Sym<LOGN>::template soff<T>());
+      static_assert(sizeof(double) * n <= sizeof(Cplx<T>) * 9 * Sym<LOGN>::RP, "eigenvalues fit the exchange region");
 #pragma unroll
-    for (int u = 0; u < NLAM; ++u) lam_v[u] = ty.lam[n >= kBlock ? tid + u * kBlock : tid & (n - 1)];
+      for (int u = 0; u < NLAM; ++u) lam_v[u] = ty.lam[n >= kBlock ? tid + u * kBlock : tid & (n - 1)];
+    }
   } else {
     pr = tid >> 6;
     busy = pr < W / 2;
@@ -1291,14 +1308,14 @@ __device__ __forceinline__ void col_block_core(const Geom& g, const ColArgs<T>& 
     for_iters<NIT>([&](int it) { d[it * LS] = in[static_cast<size_t>(it) * JS * nx]; });
   }
   xf.commit();
-  if constexpr (sym) {
+  if constexpr (sym && !once) {
 #pragma unroll
     for (int u = 0; u < NLAM; ++u)
       if (n >= kBlock || tid < n) lam_s[tid + u * kBlock] = lam_v[u];
   }
   __syncthreads();
   {
-    if constexpr (sym) {
+    if constexpr (sym && !once) {
       const SymLane<LOGN, W / 2> t;
       if (busy) {
 #pragma unroll
@@ -1309,13 +1326,20 @@ __device__ __forceinline__ void col_block_core(const Geom& g, const ColArgs<T>& 
         }
       }
     }
-    using Scale = EigenScale<T, NK, eigen_once<T, n>>;
-    Scale sc;
+    std::conditional_t<once, EigenOnce, EigenScale<T, NK>> sc;
     if (busy) {
+      if constexpr (once) {
+        const double two = 2.0 / (g.hy * g.hy);
+        sc.c = (lam_v[0] + two) * inorm;
+        sc.s = (lam_v[1] + two) * inorm;
+        sc.xa = (lxa - shift - two) * inorm;
+        sc.xb = (lxb - shift - two) * inorm;
+      } else {
 #pragma unroll
-      for (int q = 0; q < NK; ++q) sc.ry[q] = static_cast<typename Scale::R>((ly[q] - shift) * inorm);
-      sc.xa = static_cast<typename Scale::R>(lxa * inorm);
-      sc.xb = static_cast<typename Scale::R>(lxb * inorm);
+        for (int q = 0; q < NK; ++q) sc.ry[q] = static_cast<T>((ly[q] - shift) * inorm);
+        sc.xa = static_cast<T>(lxa * inorm);
+        sc.xb = static_cast<T>(lxb * inorm);
+      }
       if constexpr (sizeof(T) == 8) {
         if (hold) {
 #pragma unroll
@@ -1331,7 +1355,7 @@ __device__ __forceinline__ void col_block_core(const Geom& g, const ColArgs<T>& 
       // global loads here: a wait on a load also waits on earlier stores)
       zero_job(a.zero, static_cast<size_t>(blockIdx.y) * gridDim.x + blockIdx.x,
                static_cast<size_t>(gridDim.x) * gridDim.y);
-      __syncthreads();   // the eigenvalues have left the exchange region
+      if constexpr (!once) __syncthreads();   // the eigenvalues have left the exchange region
       sym_dst<T, double, double, LOGN, W / 2>(buf, xf.w, xf.tw(), sc);
       __syncthreads();   // the rows are the next transform's input
       sym_dst<T, T, T, LOGN, W / 2>(buf, xf.w, xf.tw());
