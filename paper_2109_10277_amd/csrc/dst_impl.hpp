@@ -696,8 +696,8 @@ struct Dense {
 
 // One transform of the kDenseRows rows at buf; epi(slot, row, output, value)
 // gives what is stored, slot = 0 .. 4 TW - 1 in order.  Output 0 is a product
-// with zeros, which is not zero for an infinity or a NaN in the row, so epi
-// stores its zero.  Ends without a barrier.
+// with zeros, which is not zero for an infinity or a NaN in the row, so the
+// inverse transforms' epi stores its zero.  Ends without a barrier.
 template <bool FWD, typename T, int LOGN, typename Epi>
 __device__ __forceinline__ void dense_dst(T* buf, const typename Dense<T, LOGN>::Tab& t, Epi&& epi) {
   using D = Dense<T, LOGN>;
@@ -799,7 +799,7 @@ __device__ __forceinline__ void block_dst(T* buf, int ppitch, const Xform<T, LOG
     if (wave < NP) wave_dst_core<n / 32>(buf + static_cast<size_t>(wave) * ppitch, x.w.a, x.tw());
   } else {
     static_assert(2 * NP == kDenseRows, "rows of the matrix core");
-    dense_dst<FWD, T, LOGN>(buf, x.w, [](int, int, int o, T v) { return o > 0 ? v : T(0); });
+    dense_dst<FWD, T, LOGN>(buf, x.w, [](int, int, int o, T v) { return FWD || o > 0 ? v : T(0); });
   }
   __syncthreads();
 }
@@ -1276,9 +1276,8 @@ __device__ __forceinline__ void col_block_core(const Geom& g, const ColArgs<T>& 
   }
   lxa = lamx[p0 + (busy ? 2 * pr : 0)];
   lxb = lamx[p0 + (busy ? 2 * pr + 1 : 1)];
-  const double shift = a.shift[fld];
-  const double inorm = 0.25 * static_cast<double>(nx) * n;
-  const bool hold = sizeof(T) == 8 && eigen_range(g, shift, inorm);
+  bool hold = false;
+  if constexpr (sizeof(T) == 8) hold = eigen_range(g, a.shift[fld], 0.25 * static_cast<double>(nx) * n);
   const size_t plane = static_cast<size_t>(nx) * n;
   const int c = tid & (W - 1), j0 = tid >> LW;
   const int lcol = (c >> 1) * ppitch + (c & 1) * rl + Pd::ridx(j0);
@@ -1326,6 +1325,8 @@ __device__ __forceinline__ void col_block_core(const Geom& g, const ColArgs<T>& 
         }
       }
     }
+    const double shift = a.shift[fld];
+    const double inorm = 0.25 * static_cast<double>(nx) * n;
     std::conditional_t<once, EigenOnce, EigenScale<T, NK>> sc;
     if (busy) {
       if constexpr (once) {
